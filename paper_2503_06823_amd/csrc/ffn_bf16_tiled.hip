@@ -6,9 +6,14 @@
 //   pass 2: y_perm[r, n] = h[r,:] . W2_s[n,:]                                         K = d_ff
 //
 // Tile: a workgroup of NW = 4 wavefronts (2 x 2, one per SIMD) owns 256 tokens x 256 weight rows;
-// each wavefront accumulates 128 x 128 as 4 x 4 blocks of v_mfma_f32_32x32x16_bf16 in fp32 (256
-// accumulator registers).  Eight wavefronts (128 x 64 each) measured slower: more LDS reads per
-// MFMA.  In the SwiGLU pass the 256 weight rows are 128 rows of W1 and the SAME 128 rows of
+// each wavefront accumulates 128 x 128 as 8 x 8 blocks of v_mfma_f32_16x16x32_bf16 in fp32 (256
+// accumulator registers).  The kernel runs at the chip's power limit, and this shape does the most
+// matrix work per joule: an instruction reads and writes its accumulators once per 32 K elements where
+// the 32 x 32 x 16 shape does so per 16.  A loop of nothing but matrix instructions on N(0,1) operands
+// runs at 2.08 PFLOP/s with it, at 1.83 with 32 x 32 x 16; with it the Mixtral prefill layer (4096
+// tokens, 4 slots) takes 2.15 ms instead of 2.30, a fine-grained layer (d 2048, f 1408, 24 slots of
+// 2048 rows) 0.79 instead of 0.83.  Eight wavefronts (128 x 64 each) measured slower: more LDS reads
+// per MFMA.  In the SwiGLU pass the 256 weight rows are 128 rows of W1 and the SAME 128 rows of
 // W3, arranged so that a lane holds the gate and the up value of the same output element and the
 // activation is applied in registers.  The weight rows go on the MFMA's row operand: a lane then
 // owns four consecutive output columns of one token and stores them as one 8-byte write.
@@ -22,14 +27,14 @@
 // weight rows in slot 2t+1 mod 5 - so one and a half K tiles are in flight while one is multiplied.
 // Each load instruction fills 1 KiB of LDS contiguously (8 rows x 128 bytes); the 16-byte chunk c
 // of row r is stored at chunk position c ^ ((r >> 1) & 7), chosen by which global chunk a lane
-// fetches, which makes the MFMA fragment reads (32 rows x one chunk per ds_read_b128) bank-conflict
+// fetches, which makes the MFMA fragment reads (16 rows x four chunks per ds_read_b128) bank-conflict
 // free without padding.  Buffer addressing gives a uniform (scalar) K offset plus a per-lane row
 // offset, so the loop has no address arithmetic; in the K tail, chunks past K are fetched out of
 // range and arrive as zeros.
 //
-// Schedule per K tile (four MFMA steps of 16 each): fragment reads for the next step and the loads
+// Schedule per K tile (two MFMA K-steps of 32 each): fragment reads for the next step and the loads
 // of tile t+2 are slotted one by one between the MFMAs, so no memory instruction waits in a full
-// queue while the matrix pipe idles.  One barrier per tile, before its last step.
+// queue while the matrix pipe idles.  One barrier per tile, between its steps.
 //
 // Epilogue: results go through LDS so that they leave as whole 256- or 512-byte row segments (see
 // epilogue()); accumulators are read from their AGPRs one block at a time.
@@ -56,7 +61,6 @@ namespace emoe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
@@ -68,15 +72,17 @@ constexpr int ROW_BYTES = BK * 2;           // 128: a tile row is one whole cach
 constexpr int TILE_BYTES = BM * ROW_BYTES;  // 32 KiB per operand
 constexpr int SLOTS = 5;                    // LDS ring of operand tiles: x(t), w(t), x(t+1), w(t+1), x(t+2), ...
 constexpr size_t LDS_BYTES = SLOTS * TILE_BYTES;  // 160 KiB, all of a CU's LDS
-static_assert(BK / 16 == 4, "the K loop is written out for four MFMA K-steps per tile");
+constexpr int KSTEP = 32;                   // K elements of one matrix instruction (16 x 16 x 32)
+static_assert(BK / KSTEP == 2, "the K loop is written out for two MFMA K-steps per tile");
 constexpr int kMaxSplits = 8;           // K pieces per leftover tile, at most
 constexpr int kFixupGroups = (kMaxGroups - 1) * 16;  // workgroups of the fix-up launch: the most units there can be
 constexpr int kPlanFloats = kTiledPlanBytes / 4;  // the plan sits ahead of the partial sums
 constexpr unsigned kRotation = 21;  // K-tile rotation per slot
 constexpr int NW = 4;            // wavefronts per workgroup, arranged 2 (tokens) x NW/2 (weight rows)
 constexpr int WN = NW / 2;
-constexpr int TB = 4;            // 32-token blocks per wavefront (128 tokens)
-constexpr int WB = BR / WN / 32; // 32-row weight blocks per wavefront
+constexpr int TB = 4;            // 32-token blocks per wavefront (128 tokens): the grain in which blocks without rows are skipped
+constexpr int TS = 2 * TB;       // 16-token blocks per wavefront
+constexpr int WB = BR / WN / 16; // 16-row weight blocks per wavefront
 constexpr int RPI = 1024 / ROW_BYTES;      // tile rows filled by one load instruction (8)
 constexpr int LPW = BM / RPI / NW;         // load instructions per wavefront, per tile and operand (8)
 
@@ -171,36 +177,37 @@ __device__ __forceinline__ int rows_per_tile(int rows, int tiles) {
 // the two wavefront rows, so that both finish together whatever the number of blocks that hold rows.
 // -> tile block of block i of wavefront row wm, and the number of its blocks that hold rows.
 __device__ __forceinline__ int tile_block(int wm, int i) { return 2 * i + wm; }
+// first tile row of 16-token block j (0 .. TS-1) of wavefront row wm
+__device__ __forceinline__ int token_row(int wm, int j) { return tile_block(wm, j >> 1) * 32 + (j & 1) * 16; }
 __device__ __forceinline__ int blocks_of_wavefront(int row0, int row_end, int wm) {
     return ((row_end - row0 + 31) / 32 - wm + 1) / 2;
 }
 
-// One 32 x 32 output block of a wavefront: token block mi, output-column block ni.  `gate` holds the
-// accumulators (for SwiGLU the gate rows), `up` the matching up rows (unused otherwise).
-// A lane holds token lane%32 and weight rows 8g + 4*(lane/32) + 0..3.
+// Four 16 x 16 output blocks of a wavefront side by side: 16-token block ts, weight blocks 4 wg .. 4 wg + 3.  `gate`
+// holds the accumulators (for SwiGLU the gate rows), `up` the matching up rows (unused otherwise).
+// A lane holds token lane%16 and weight rows 4*(lane/16) + 0..3 of each block.
 template <int EPI>
-__device__ __forceinline__ void epilogue_block(const floatx16& gate, const floatx16& up, bf16_t* __restrict__ c,
-                                               const int32_t* __restrict__ out_perm, int row0, int row_end, int n0, int N,
-                                               int wm, int wn, int mi, int ni, int lane) {
+__device__ __forceinline__ void epilogue_blocks(const floatx4 (&gate)[4], const floatx4 (&up)[4], bf16_t* __restrict__ c,
+                                                const int32_t* __restrict__ out_perm, int row0, int row_end, int n0, int N,
+                                                int wm, int wn, int ts, int wg, int lane) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
-    const int r = row0 + tile_block(wm, mi) * 32 + (lane & 31);
+    const int r = row0 + token_row(wm, ts) + (lane & 15);
     if (r >= row_end) return;
     bf16_t* crow = c + (size_t)((EPI == kPlain && out_perm != nullptr) ? out_perm[r] : r) * N;
-    const int col0 = n0 + wn * (BNO / WN) + ni * 32 + (lane >> 5) * 4;
+    const int col0 = n0 + wn * (BNO / WN) + wg * 64 + (lane >> 4) * 4;
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int n = col0 + 8 * g;
+    for (int b = 0; b < 4; ++b) {
+        const int n = col0 + 16 * b;
         if (n >= N) continue;
         floatx4 v;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            float t = gate[4 * g + q];
-            if (EPI == kSwiglu) t = t / (1.0f + __expf(-t)) * up[4 * g + q];
+            float t = gate[b][q];
+            if (EPI == kSwiglu) t = t / (1.0f + __expf(-t)) * up[b][q];
             if (EPI == kRelu) t = fmaxf(t, 0.0f);
             v[q] = t;
         }
-        bf16x4 o = __builtin_convertvector(v, bf16x4);
-        *reinterpret_cast<bf16x4*>(crow + n) = o;
+        *reinterpret_cast<bf16x4*>(crow + n) = __builtin_convertvector(v, bf16x4);
     }
 }
 
@@ -257,6 +264,16 @@ __device__ __forceinline__ float acc_read(float a) {
     return v;
 }
 
+// The matrix instruction, written out with its accumulator tied to AGPRs: with 64 accumulators of four registers filling
+// all 256 AGPRs the compiler's own allocation moves them between AGPRs and VGPRs inside the loop (500 moves per K tile).
+// The compiler does not see a matrix instruction in it, so mfma_settle() has to stand between the last one and the first
+// read of an accumulator: more wait states than the longest that the ISA asks for there.
+__device__ __forceinline__ void mfma_16x16x32(floatx4& acc, const bf16x8& w, const bf16x8& x) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+
+__device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
+
 // Epilogue of a whole tile.  The MFMA layout gives a lane 4 consecutive columns of 32 different
 // token rows, so storing straight from registers writes 16-byte scraps into 32 rows per
 // instruction.  Instead the wavefronts put their (activated, rounded) results into LDS as a
@@ -266,7 +283,7 @@ __device__ __forceinline__ float acc_read(float a) {
 // 16-byte reads (nearly) free of bank conflicts.  All DMA loads have landed and all fragment reads
 // are done when this runs; the barrier at the end keeps the next tile's loads off the image.
 template <int EPI>
-__device__ __forceinline__ void epilogue(floatx16 (&acc)[WB][TB], bf16_t* __restrict__ c,
+__device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], bf16_t* __restrict__ c,
                                          const int32_t* __restrict__ out_perm, char* lds, int row0,
                                          int row_end, int n0, int N, int wm, int wn, int wave, int lane) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
@@ -274,28 +291,25 @@ __device__ __forceinline__ void epilogue(floatx16 (&acc)[WB][TB], bf16_t* __rest
     constexpr int ROWB = BNO * 2;      // bytes per image row
     constexpr int CPR = ROWB / 16;     // 16-byte chunks per image row
 #pragma unroll
-    for (int mi = 0; mi < TB; ++mi) {
-        const int r = tile_block(wm, mi) * 32 + (lane & 31);  // token row of the tile
+    for (int ts = 0; ts < TS; ++ts) {
+        const int r = token_row(wm, ts) + (lane & 15);  // token row of the tile
 #pragma unroll
         for (int ni = 0; ni < NB; ++ni) {
-            const floatx16& gate = acc[ni][mi];
-            const floatx16& up = acc[EPI == kSwiglu ? ni + NB : ni][mi];
+            const floatx4& gate = acc[ni][ts];
+            const floatx4& up = acc[EPI == kSwiglu ? ni + NB : ni][ts];
+            floatx4 v;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                floatx4 v;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    float t = acc_read(gate[4 * g + q]);
-                    if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * acc_read(up[4 * g + q]);
-                    if (EPI == kRelu) t = fmaxf(t, 0.0f);
-                    v[q] = t;
-                }
-                // columns wn*(BNO/2) + ni*32 + 8g + 4*(lane/32) .. +3: chunk j, its lower or upper half
-                const int j = wn * (BNO / WN / 8) + ni * 4 + g;
-                *reinterpret_cast<bf16x4*>(lds + r * ROWB + ((j ^ (r & 15)) * 16) + (lane >> 5) * 8) =
-                    __builtin_convertvector(v, bf16x4);
+            for (int q = 0; q < 4; ++q) {
+                float t = acc_read(gate[q]);
+                if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * acc_read(up[q]);
+                if (EPI == kRelu) t = fmaxf(t, 0.0f);
+                v[q] = t;
             }
-            __builtin_amdgcn_sched_barrier(0);  // one block at a time: the accumulators stay where they are until used
+            // columns wn*(BNO/2) + ni*16 + 4*(lane/16) .. +3: chunk j, its lower or upper half
+            const int j = wn * (BNO / WN / 8) + ni * 2 + (lane >> 5);
+            *reinterpret_cast<bf16x4*>(lds + r * ROWB + ((j ^ (r & 15)) * 16) + ((lane >> 4) & 1) * 8) =
+                __builtin_convertvector(v, bf16x4);
+            if (ni % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // a few blocks at a time: the accumulators stay where they are until used
         }
     }
     __syncthreads();
@@ -346,19 +360,13 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     const uint32_t b_bytes = (uint32_t)N * (uint32_t)K * 2u;
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(a, a_bytes);
     const bf16_t* wsel = (EPI == kSwiglu && wave >= NW / 2) ? b1 : b0;  // upper wavefronts load the W3 half
-    const int f_row = lane & 31;
-    const int f_sw = (((lane >> 5) ^ ((f_row >> 1) & 7)) & 7) * 16;
-    const int x_off = (tile_block(wm, 0) * 32 + f_row) * ROW_BYTES + f_sw;  // token block 0 of this wavefront; block i: tile_block(wm, i)
-    int w_off[WB];  // SwiGLU: weight blocks 0..WB/2-1 are gate rows, WB/2..WB-1 the matching up rows
-#pragma unroll
-    for (int i = 0; i < WB; ++i) {
-        int rr;
-        if (EPI == kSwiglu)
-            rr = (i < WB / 2) ? wn * (BR / 2 / WN) + i * 32 : BR / 2 + wn * (BR / 2 / WN) + (i - WB / 2) * 32;
-        else
-            rr = wn * (BR / WN) + i * 32;
-        w_off[i] = (rr + f_row) * ROW_BYTES + f_sw;
-    }
+    // fragments: a lane holds row lane % 16 of a 16-row block and, in MFMA K-step kk, chunk 4 kk + lane / 16 of it.
+    // The blocks of an operand are whole multiples of 16 rows apart, so they share the swizzle of the row.
+    const int f_row = lane & 15;
+    const int f_sw = ((lane >> 4) ^ ((f_row >> 1) & 7)) * 16;
+    const int x_off = (tile_block(wm, 0) * 32 + f_row) * ROW_BYTES + f_sw;  // token block 0 of this wavefront
+    // SwiGLU: weight blocks 0..WB/2-1 are gate rows, WB/2..WB-1 the matching up rows
+    const int w_off = (wn * ((EPI == kSwiglu ? BR / 2 : BR) / WN) + f_row) * ROW_BYTES + f_sw;
 
     for (int item = 0; item <= plan.rounds; ++item) {
         // ---- what to do in this trip -------------------------------------------------------------
@@ -431,62 +439,53 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
             __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_void*)dst, 16, (int)voff, k0 * 2, 0, 2);
         };
 
-        floatx16 acc[WB][TB];  // [weight block][token block]
+        floatx4 acc[WB][TS];  // [weight block][token block]
 #pragma unroll
         for (int i = 0; i < WB; ++i)
 #pragma unroll
-            for (int j = 0; j < TB; ++j)
+            for (int j = 0; j < TS; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
 
-        bf16x8 xf[2][TB], wf[2][WB];
+        bf16x8 xf[2][TS], wf[2][WB];
         // Everything that touches the matrix cores is compiled for NB = 0 .. TB token blocks: the number
         // of this wavefront's 32-row blocks that hold rows of the tile (a ragged or evenly cut tile holds
         // fewer than 256 rows).  NB = TB is the full tile, NB = 0 a wavefront that only takes part in the
         // loads and barriers.
-        // fragments of MFMA K-step kk of the tile whose token rows sit in ring slot sx and weight rows in sw
-        auto load_frags = [&](auto nb_c, int buf, int sx, int sw, int kk) {
-            constexpr int NB = decltype(nb_c)::value;
-            if (NB == 0) return;
-            const char* xb = lds + sx * TILE_BYTES;
-            const char* wb = lds + sw * TILE_BYTES;
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-                xf[buf][i] = *reinterpret_cast<const bf16x8*>(xb + ((x_off + tile_block(0, i) * 32 * ROW_BYTES) ^ (kk * 32)));
-#pragma unroll
-            for (int i = 0; i < WB; ++i) wf[buf][i] = *reinterpret_cast<const bf16x8*>(wb + (w_off[i] ^ (kk * 32)));
+        // fragment f of MFMA K-step kk: token blocks 0 .. 2 NB - 1, then the weight blocks.  xb, wb: this lane's place in
+        // the operand tiles for that step
+        auto load_frag = [&](auto nb_c, int kk, int f, const char* xb, const char* wb) {
+            constexpr int NT = 2 * decltype(nb_c)::value;
+            if (f < NT) {
+                xf[kk][f] = *reinterpret_cast<const bf16x8*>(xb + token_row(0, f) * ROW_BYTES);
+            } else {
+                const int i = f - NT;
+                const int rr = (EPI == kSwiglu && i >= WB / 2) ? BR / 2 + (i - WB / 2) * 16 : i * 16;
+                wf[kk][i] = *reinterpret_cast<const bf16x8*>(wb + rr * ROW_BYTES);
+            }
         };
-        auto mfma_step = [&](auto nb_c, int buf) {
+        auto x_place = [&](int rs, int kk) { return lds + rs * TILE_BYTES + (x_off ^ (kk * 64)); };
+        auto w_place = [&](int rs, int kk) { return lds + rs * TILE_BYTES + (w_off ^ (kk * 64)); };
+        // One MFMA K-step: multiplies the fragments of step kk and, slotted in between so that no memory
+        // instruction waits in a full queue while the matrix pipe idles, reads the fragments of the step after it
+        // (from xb, wb; in the first three quarters of the step, so that they are there at its end) and issues
+        // LPW global->LDS loads.
+        auto step = [&](auto nb_c, int kk, const char* xb, const char* wb, auto issue) {
             constexpr int NB = decltype(nb_c)::value;
+            constexpr int NT = 2 * NB, MF = WB * NT, FR = WB + NT;
+            if constexpr (NB == 0) {
 #pragma unroll
-            for (int ni = 0; ni < WB; ++ni)
+                for (int i = 0; i < LPW; ++i) issue(i);
+            } else {
+                constexpr int FR_EVERY = MF * 3 / 4 / FR, LD_EVERY = MF / LPW;
+                static_assert(FR_EVERY >= 1 && FR_EVERY * FR <= MF && LD_EVERY * LPW <= MF, "everything finds its place");
 #pragma unroll
-                for (int m = 0; m < NB; ++m) {
-                    const int mi = (ni & 1) ? NB - 1 - m : m;  // back and forth: only one operand changes between two MFMAs
-                    acc[ni][mi] =
-                        __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][ni], xf[buf][mi], acc[ni][mi], 0, 0, 0);
-                }
-        };
-        // the step's MFMAs with its LDS reads and LOADS global->LDS loads slotted in between, so that no
-        // memory instruction waits in a full queue while the matrix pipe idles
-        auto interleave = [&](auto nb_c, auto loads_c) {
-            constexpr int NB = decltype(nb_c)::value;
-            constexpr int LOADS = decltype(loads_c)::value;
-            if constexpr (NB == TB) {
-#pragma unroll
-                for (int i = 0; i < TB * WB; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                           // one MFMA
-                    if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          // one DS read
-                    else if (i < TB + WB + LOADS) __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);  // one VMEM
-                }
-            } else if constexpr (NB > 0) {  // fewer MFMAs than memory instructions: several of those per MFMA
-                constexpr int MF = NB * WB;
-                constexpr int DS_PER = (NB + WB + MF - 1) / MF, VM_PER = (LOADS + MF - 1) / MF;
-#pragma unroll
-                for (int i = 0; i < MF; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x100, DS_PER, 0);
-                    if (VM_PER > 0) __builtin_amdgcn_sched_group_barrier(0x010, VM_PER, 0);
+                for (int m = 0; m < MF; ++m) {
+                    const int ni = m / NT;
+                    const int mi = (ni & 1) ? NT - 1 - m % NT : m % NT;  // back and forth: only one operand changes between two MFMAs
+                    mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
+                    if (m % FR_EVERY == FR_EVERY - 1 && m / FR_EVERY < FR) load_frag(nb_c, kk ^ 1, m / FR_EVERY, xb, wb);
+                    if (m % LD_EVERY == LD_EVERY / 2) issue(m / LD_EVERY);
                 }
             }
         };
@@ -512,16 +511,17 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         barrier_keep_loads<2 * LPW>();
 
         // ---- main loop -----------------------------------------------------------------------------
-        // Per K tile: four MFMA steps of 16.  Token rows of tile t+2 are requested during steps 0 and 1
-        // (into the slot that held the weight rows of tile t-1), weight rows of tile t+2 during step 3
-        // (into the slot of this tile's token rows, dead after the barrier).  One barrier per tile,
-        // before step 3: by then every wavefront has read its last fragments of tile t, and tile t+1
-        // has landed once only the 8 newest loads (token rows of t+2) are pending.
+        // Per K tile: two MFMA steps of 32.  Token rows of tile t+2 are requested during step 0 (into the slot
+        // that held the weight rows of tile t-1), weight rows of tile t+2 during step 1 (into the slot of this
+        // tile's token rows, dead after the barrier).  One barrier per tile, between the steps: by then every
+        // wavefront has read its last fragments of tile t, and tile t+1 has landed once only the LPW newest
+        // loads (token rows of t+2) are pending.
         // A wavefront skips the fragment reads and MFMAs of its token blocks without rows: the kernel
         // runs at the chip's power limit, so work not done is speed for the others.
         auto k_loop = [&](auto nb_c, auto once_c) {
-            constexpr bool IDLE = decltype(nb_c)::value == 0;
-            load_frags(nb_c, 0, 0, 1, 0);
+            constexpr int NB = decltype(nb_c)::value;
+#pragma unroll
+            for (int f = 0; NB > 0 && f < 2 * NB + WB; ++f) load_frag(nb_c, 0, f, x_place(0, 0), w_place(1, 0));
             __builtin_amdgcn_sched_barrier(0);
             int sx = 0;  // ring slot of tile t's token rows
             for (int t = 0; t < k_tiles; ++t) {
@@ -529,40 +529,14 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
                 const int sx1 = sx + 2 >= SLOTS ? sx + 2 - SLOTS : sx + 2;  // next tile's token rows
                 const int sw1 = sx + 3 >= SLOTS ? sx + 3 - SLOTS : sx + 3;  // next tile's weight rows
                 const int sx2 = sx + 4 >= SLOTS ? sx + 4 - SLOTS : sx + 4;  // token rows of t+2 (held weights of t-1)
-                load_frags(nb_c, 1, sx, sw, 1);
-#pragma unroll
-                for (int i = 0; i < LPW / 2; ++i) issue_load(true, i, sx2, t + 2);
-                if (!IDLE) {
-                    mfma_step(nb_c, 0);
-                    interleave(nb_c, std::integral_constant<int, LPW / 2>{});
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                load_frags(nb_c, 0, sx, sw, 2);
-#pragma unroll
-                for (int i = LPW / 2; i < LPW; ++i) issue_load(true, i, sx2, t + 2);
-                if (!IDLE) {
-                    mfma_step(nb_c, 1);
-                    interleave(nb_c, std::integral_constant<int, LPW / 2>{});
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                if (!IDLE) {
-                    load_frags(nb_c, 1, sx, sw, 3);
-                    mfma_step(nb_c, 0);
-                    interleave(nb_c, std::integral_constant<int, 0>{});
-                }
+                step(nb_c, 0, x_place(sx, 1), w_place(sw, 1), [&](int i) { issue_load(true, i, sx2, t + 2); });
                 __builtin_amdgcn_sched_barrier(0);
                 barrier_keep_loads<LPW>();
                 __builtin_amdgcn_sched_barrier(0);
-                load_frags(nb_c, 0, sx1, sw1, 0);
-#pragma unroll
-                for (int i = 0; i < LPW; ++i) {  // weight rows of t+2 over this tile's token rows
+                step(nb_c, 1, x_place(sx1, 0), w_place(sw1, 0), [&](int i) {  // weight rows of t+2 over this tile's token rows
                     if (decltype(once_c)::value) issue_weights_once(i, sx, t + 2);
                     else issue_load(false, i, sx, t + 2);
-                }
-                if (!IDLE) {
-                    mfma_step(nb_c, 1);
-                    interleave(nb_c, std::integral_constant<int, LPW>{});
-                }
+                });
                 __builtin_amdgcn_sched_barrier(0);
                 sx = sx1;
             }
@@ -594,6 +568,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         }
         // surplus loads must not land in the next trip's tiles (or outlive the workgroup's LDS)
         barrier_keep_loads<0>();
+        mfma_settle();
 
         if (piece < 0) {
             epilogue<EPI>(acc, c, gather.out_perm, lds, row0, row_end, n0, N, wm, wn, wave, lane);
@@ -602,17 +577,17 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
 #pragma unroll
             for (int i = 0; i < WB; ++i)
 #pragma unroll
-                for (int j = 0; j < TB; ++j) {
-                    if (row0 + tile_block(wm, j) * 32 >= row_end) continue;  // a block without rows: the fix-up skips it too
+                for (int j = 0; j < TS; ++j) {
+                    if (row0 + token_row(wm, j) >= row_end) continue;  // a block without rows: the fix-up skips it too
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) dst[((i * TB + j) * 16 + v) * (64 * NW)] = acc_read(acc[i][j][v]);
+                    for (int v = 0; v < 4; ++v) dst[((i * TS + j) * 4 + v) * (64 * NW)] = acc_read(acc[i][j][v]);
                 }
         }
     }
 }
 
 // Adds the K pieces of each leftover tile in piece order and applies the epilogue.  One unit of work
-// per (leftover tile, 32 x 32 block position of the wavefronts), so the sum itself is spread over
+// per (leftover tile, 16 x 64 block position of the wavefronts), so the sum itself is spread over
 // the chip.  The plan (how many leftover tiles, how many pieces)
 // is read from the head of the workspace, where the main kernel left it: when nothing was split,
 // which the host cannot know, every workgroup exits after one load.
@@ -624,8 +599,8 @@ __global__ __launch_bounds__(64 * NW * kFixupUnitsPerGroup) void splitk_fixup(co
                                                         const float* __restrict__ partials, int S, int N, int K,
                                                         int n_tiles, int G) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
-    constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
-    constexpr int UNITS = TB * NB;
+    constexpr int NG = (EPI == kSwiglu ? WB / 2 : WB) / 4;  // groups of four output blocks
+    constexpr int UNITS = TS * NG;
     Plan plan;  // uniform address: scalar loads
     plan.tiles = hdr[0]; plan.rounds = hdr[1]; plan.left = hdr[2]; plan.splits = hdr[3];
     if (plan.splits <= 1) return;
@@ -635,32 +610,33 @@ __global__ __launch_bounds__(64 * NW * kFixupUnitsPerGroup) void splitk_fixup(co
     const int u = blockIdx.x * kFixupUnitsPerGroup + threadIdx.x / (64 * NW);  // the launch covers the most units there can be
     if (u >= plan.left * UNITS) return;
     const int tile = u / UNITS, unit = u % UNITS;
-    const int mi = unit / NB, ni = unit % NB;
+    const int ts = unit / NG, wg = unit % NG;
     int slot, row0, row_end, nt, slot_tiles;
     // the slot table in registers, as in the main kernel: a walk over slot_offsets in memory is a chain of up to S
     // dependent loads, longer than everything else this kernel does
     const SlotTable table = make_slot_table(offsets, S, n_tiles, lane);
     decode_tile(table, S, n_tiles, lane, plan.rounds * G + tile, slot, row0, row_end, nt, slot_tiles);
-    if (row0 + tile_block(wave / WN, mi) * 32 >= row_end) return;  // this wavefront's block holds no rows: nothing was written
-    floatx16 gate, up;
+    if (row0 + token_row(wave / WN, ts) >= row_end) return;  // this wavefront's block holds no rows: nothing was written
+    floatx4 gate[4], up[4];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { gate[v] = 0.0f; up[v] = 0.0f; }
+    for (int v = 0; v < 16; ++v) { gate[v >> 2][v & 3] = 0.0f; up[v >> 2][v & 3] = 0.0f; }
     for (int sp = 0; sp < plan.splits; ++sp) {
         const float* src = partials + (size_t)(tile * plan.splits + sp) * (BM * BR) + tid;
         float g[16], w[16];  // all loads of a piece in flight together, then the adds
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            g[v] = src[((ni * TB + mi) * 16 + v) * (64 * NW)];
-            w[v] = EPI == kSwiglu ? src[(((ni + NB) * TB + mi) * 16 + v) * (64 * NW)] : 0.0f;
+            const int ni = wg * 4 + (v >> 2);
+            g[v] = src[((ni * TS + ts) * 4 + (v & 3)) * (64 * NW)];
+            w[v] = EPI == kSwiglu ? src[(((ni + WB / 2) * TS + ts) * 4 + (v & 3)) * (64 * NW)] : 0.0f;
         }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            gate[v] += g[v];
-            up[v] += w[v];
+            gate[v >> 2][v & 3] += g[v];
+            up[v >> 2][v & 3] += w[v];
         }
     }
-    epilogue_block<EPI>(gate, up, c, out_perm, row0, row_end, nt * BNO, N, wave / WN, wave % WN, mi, ni, lane);
+    epilogue_blocks<EPI>(gate, up, c, out_perm, row0, row_end, nt * BNO, N, wave / WN, wave % WN, ts, wg, lane);
 }
 
 template <int EPI, bool KTAIL>
