@@ -36,8 +36,12 @@
 // of tile t+2 are slotted one by one between the MFMAs, so no memory instruction waits in a full
 // queue while the matrix pipe idles.  One barrier per tile, between its steps.
 //
-// Epilogue: results go through LDS so that they leave as whole 256- or 512-byte row segments (see
-// epilogue()); accumulators are read from their AGPRs one block at a time.
+// The stream of operand tiles does not stop between output tiles: an output tile's last two K tiles
+// request the first two of the next one, and the epilogue stores from registers, without LDS and
+// without a barrier (see epilogue()), so that they arrive meanwhile.  A wavefront's tile boundary used
+// to cost 24 000 cycles (epilogue through LDS, then the first loads from nothing), a fifth of the
+// fine-grained layer's first product (32 K tiles of 2 048 cycles per output tile); fine-grained layer
+// 788 -> 763 us, Mixtral prefill layer 2153 -> 2095, two prompts at that shape 816 -> 802.
 //
 // Slots that do not fill their tiles: a slot's rows are spread evenly over its m-tiles in whole
 // 32-row MFMA blocks (257 rows: tiles of 160 and 97 rows, not 256 and 1), a tile's blocks alternate
@@ -63,7 +67,10 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
+// a pointer into global memory, said so: the loads are counted by vmcnt alone (a flat load has to be waited for with vmcnt(0))
+typedef const int32_t __attribute__((address_space(1)))* global_i32;
 
 constexpr int BM = 256;                     // tokens per tile
 constexpr int BR = 256;                     // weight rows per tile (SwiGLU: 128 of W1 + 128 of W3)
@@ -266,67 +273,77 @@ __device__ __forceinline__ float acc_read(float a) {
 
 // The matrix instruction, written out with its accumulator tied to AGPRs: with 64 accumulators of four registers filling
 // all 256 AGPRs the compiler's own allocation moves them between AGPRs and VGPRs inside the loop (500 moves per K tile).
-// The compiler does not see a matrix instruction in it, so mfma_settle() has to stand between the last one and the first
-// read of an accumulator: more wait states than the longest that the ISA asks for there.
+// The compiler does not see matrix instructions in these statements and adds none of the wait states they need, so
+//  - operands come from LDS reads (waited for by counter) and accumulators from other matrix instructions (mfma_zero);
+//  - mfma_settle(), more wait states than the longest the ISA asks for, stands between the last one and the first read
+//    of an accumulator, and between VALU writes of an operand and the first one.
 __device__ __forceinline__ void mfma_16x16x32(floatx4& acc, const bf16x8& w, const bf16x8& x) {
     asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
-
+__device__ __forceinline__ void mfma_zero(floatx4& acc, const bf16x8& zero) {  // 0 * 0 + 0
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %1, 0" : "=a"(acc) : "v"(zero));
+}
 __device__ __forceinline__ void mfma_settle() { asm volatile("s_nop 15\n\ts_nop 15" ::: "memory"); }
 
-// Epilogue of a whole tile.  The MFMA layout gives a lane 4 consecutive columns of 32 different
-// token rows, so storing straight from registers writes 16-byte scraps into 32 rows per
-// instruction.  Instead the wavefronts put their (activated, rounded) results into LDS as a
-// [256 token rows][BNO columns] bf16 image, and after a barrier every wavefront stores 64 of its
-// rows with 16 bytes per lane, 256 or 512 contiguous bytes per row.  In the image the 16-byte
-// chunk j of row r sits at chunk position j ^ (r & 15), which keeps both the 8-byte writes and the
-// 16-byte reads (nearly) free of bank conflicts.  All DMA loads have landed and all fragment reads
-// are done when this runs; the barrier at the end keeps the next tile's loads off the image.
+// The value, through a statement that the compiler cannot look into.
+__device__ __forceinline__ int opaque(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Epilogue of a whole tile, straight from the registers: no LDS, no barrier, so that the next tile's operands can be on
+// their way into the ring meanwhile.  The MFMA layout gives a lane four consecutive columns of one token in every block;
+// two exchanges between odd and even rows of 16 lanes turn those of two neighbouring blocks into eight consecutive columns
+// of one block, and a store instruction then writes 64 contiguous bytes of each of 16 token rows.
+// TBLOCKS: the wavefront's 32-row token blocks that hold rows.
+// Every wavefront issues kEpilogueStores<EPI> stores, whatever the tile holds (rows and columns that do not exist are
+// addressed out of range, which writes nothing): the K loop counts on it, see there.
 template <int EPI>
-__device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], bf16_t* __restrict__ c,
-                                         const int32_t* __restrict__ out_perm, char* lds, int row0,
-                                         int row_end, int n0, int N, int wm, int wn, int wave, int lane) {
+constexpr int kEpilogueStores = TS * (EPI == kSwiglu ? WB / 2 : WB) / 2;
+constexpr uint32_t kNoStore = 0xffffffffu;  // past the end of the output's buffer resource
+
+template <int EPI, int TBLOCKS>
+__device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], __amdgpu_buffer_rsrc_t c_rsrc, const int (&out_entry)[2],
+                                         bool scatter, int row0, int row_end, int n0, int N, int wm, int wn, int lane) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
-    constexpr int ROWB = BNO * 2;      // bytes per image row
-    constexpr int CPR = ROWB / 16;     // 16-byte chunks per image row
+    const int col0 = n0 + wn * (BNO / WN) + ((lane >> 4) & 1) * 16 + (lane >> 5) * 8;
 #pragma unroll
     for (int ts = 0; ts < TS; ++ts) {
-        const int r = token_row(wm, ts) + (lane & 15);  // token row of the tile
+        const bool row_ok = row0 + token_row(wm, ts) + (lane & 15) < row_end;
+        int r_out = row0 + token_row(wm, ts) + (lane & 15);
+        if (scatter) r_out = __shfl(out_entry[ts >> 2], (ts & 3) * 16 + (lane & 15));  // the token's row of the output
+        const uint32_t row_off = (uint32_t)r_out * (uint32_t)N * 2u;
 #pragma unroll
-        for (int ni = 0; ni < NB; ++ni) {
-            const floatx4& gate = acc[ni][ts];
-            const floatx4& up = acc[EPI == kSwiglu ? ni + NB : ni][ts];
-            floatx4 v;
+        for (int np = 0; np < NB; np += 2) {
+            uintx4 val = {0u, 0u, 0u, 0u};
+            if (ts < 2 * TBLOCKS) {
+                uint32_t two[2][2];  // block, its four columns as two packed pairs
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float t = acc_read(gate[q]);
-                if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * acc_read(up[q]);
-                if (EPI == kRelu) t = fmaxf(t, 0.0f);
-                v[q] = t;
+                for (int b = 0; b < 2; ++b) {
+                    const floatx4& gate = acc[np + b][ts];
+                    const floatx4& up = acc[EPI == kSwiglu ? np + b + NB : np + b][ts];
+                    floatx4 v;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        float t = acc_read(gate[q]);
+                        if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * acc_read(up[q]);
+                        if (EPI == kRelu) t = fmaxf(t, 0.0f);
+                        v[q] = t;
+                    }
+                    const bf16x4 o = __builtin_convertvector(v, bf16x4);
+                    __builtin_memcpy(two[b], &o, 8);
+                }
+                const auto lo = __builtin_amdgcn_permlane16_swap(two[0][0], two[1][0], false, false);
+                const auto hi = __builtin_amdgcn_permlane16_swap(two[0][1], two[1][1], false, false);
+                val = uintx4{lo[0], hi[0], lo[1], hi[1]};
             }
-            // columns wn*(BNO/2) + ni*16 + 4*(lane/16) .. +3: chunk j, its lower or upper half
-            const int j = wn * (BNO / WN / 8) + ni * 2 + (lane >> 5);
-            *reinterpret_cast<bf16x4*>(lds + r * ROWB + ((j ^ (r & 15)) * 16) + ((lane >> 4) & 1) * 8) =
-                __builtin_convertvector(v, bf16x4);
-            if (ni % 4 == 3) __builtin_amdgcn_sched_barrier(0);  // a few blocks at a time: the accumulators stay where they are until used
+            const int n = col0 + np * 16;
+            const uint32_t off = row_ok && n < N ? row_off + (uint32_t)n * 2u : kNoStore;
+            __builtin_amdgcn_raw_buffer_store_b128(val, c_rsrc, (int)off, 0, 0);
         }
+        __builtin_amdgcn_sched_barrier(0);  // a few blocks at a time: the accumulators stay where they are until used
     }
-    __syncthreads();
-    constexpr int RPS = 64 / CPR;  // image rows per store instruction (2 or 4)
-    const int jc = lane % CPR;
-    const int n = n0 + jc * 8;
-#pragma unroll 4
-    for (int it = 0; it < BM / NW / RPS; ++it) {
-        const int r = wave * (BM / NW) + it * RPS + lane / CPR;
-        const uint4 val = *reinterpret_cast<const uint4*>(lds + r * ROWB + ((jc ^ (r & 15)) * 16));
-        if (row0 + r < row_end && n < N) {
-            // combine folded in (second product, one expert per token): the row goes to its token's row of the output
-            const int dr = (EPI == kPlain && out_perm != nullptr) ? out_perm[row0 + r] : row0 + r;
-            *reinterpret_cast<uint4*>(c + (size_t)dr * N + n) = val;
-        }
-    }
-    __syncthreads();
 }
 
 template <int EPI, bool KTAIL>
@@ -343,7 +360,8 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WN, wn = wave % WN;
-    const int k_tiles_all = (K + BK - 1) / BK;
+    // at least two: an item's last two K tiles request the first two of the next one (a second one past K is all zeros)
+    const int k_tiles_all = K > BK ? (K + BK - 1) / BK : 2;
     const int G = gridDim.x;
     const SlotTable table = make_slot_table(offsets, S, n_tiles, lane);
     const Plan plan = make_plan(table.total, k_tiles_all, G);
@@ -353,192 +371,298 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     const int xcd = blockIdx.x % XCDS, cu = blockIdx.x / XCDS, per_xcd = G / XCDS;
     const int sk_item = xcd * per_xcd + cu;  // this workgroup's piece of the leftover tiles
 
-    // lane-constant parts of the addressing
+    // ---- the tiles of this workgroup ---------------------------------------------------------------
+    struct Item {
+        int slot, row0, row_end, nt, slot_tiles;
+        int kb, kt;  // its K tiles: kb .. kb + kt - 1
+        int piece;   // -1: a whole tile; else the number of the K piece of a leftover tile (always the last item)
+    };
+    auto item_at = [&](int idx, Item& it) {
+        int L;
+        it.kb = 0;
+        it.kt = k_tiles_all;
+        it.piece = -1;
+        if (idx < plan.rounds) {
+            L = idx * G + xcd * per_xcd + cu;
+        } else {
+            if (idx > plan.rounds || sk_item >= plan.left * plan.splits) return false;
+            L = plan.rounds * G + sk_item / plan.splits;
+            if (plan.splits > 1) {
+                const int sp = sk_item % plan.splits;
+                it.kb = (int)((long long)k_tiles_all * sp / plan.splits);
+                it.kt = (int)((long long)k_tiles_all * (sp + 1) / plan.splits) - it.kb;
+                it.piece = sk_item;
+            }
+        }
+        decode_tile(table, S, n_tiles, lane, L, it.slot, it.row0, it.row_end, it.nt, it.slot_tiles);
+        return true;
+    };
+
+    // ---- global -> LDS -----------------------------------------------------------------------------
+    // Wavefront w issues, per K tile and per operand, load instructions i = 0..LPW-1; instruction
+    // (w, i) fills tile rows (LPW*w + i)*8 .. +7, 128 bytes each.  Lane l lands in row l>>3, chunk
+    // position l&7 and therefore fetches global chunk (l&7) ^ ((row>>1)&7).
     const int l_row = lane >> 3;  // row within a load instruction's eight rows
     const int l_pos = lane & 7;   // chunk position within the row, in LDS
     const uint32_t a_bytes = (uint32_t)(gather.perm != nullptr ? gather.rows : rows_total) * (uint32_t)K * 2u;
     const uint32_t b_bytes = (uint32_t)N * (uint32_t)K * 2u;
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(a, a_bytes);
+    const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(c, kNoStore);
     const bf16_t* wsel = (EPI == kSwiglu && wave >= NW / 2) ? b1 : b0;  // upper wavefronts load the W3 half
+    // that chunk depends on i only through its parity
+    const int chunk2[2] = {l_pos ^ (l_row >> 1), l_pos ^ (4 + (l_row >> 1))};
+    static_assert(RPI == 8 && LPW == 8, "the swizzle of a row is a function of l_row and the parity of i");
+    // A wavefront loads 64 rows of a token tile: a lane looks up where row 64 wave + lane comes from (its perm entry,
+    // or the row of x_perm itself), and the lanes that load pieces of it get the row from that lane.
+    auto load_perm = [&](const Item& it) {
+        int r = it.row0 + LPW * RPI * wave + lane;
+        r = r >= it.row_end ? it.row_end - 1 : r;
+        return gather.perm != nullptr ? global_i32(gather.perm)[r] : r;
+    };
+    const int perm_div = gather.perm != nullptr ? gather.k : 1;
+    // (the lane number is made opaque where addresses are formed: the parts of them that are the same for every item would
+    // otherwise be computed ahead of the loop, and there are no registers to keep them in)
+    auto token_addr = [&](const Item& it, int perm_entry, uint32_t (&voff)[LPW]) {
+        const int l = opaque(lane);
+        const uint32_t x_row = (uint32_t)perm_entry / (uint32_t)perm_div;  // the token's row of x, not a copy of it
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int tr = (LPW * wave + i) * RPI + (l >> 3);
+            const uint32_t row = (uint32_t)__shfl((int)x_row, i * RPI + (l >> 3));
+            const int v = opaque((int)((row * (uint32_t)K + ((l & 7) ^ ((tr >> 1) & 7)) * 8) * 2u));  // (no branch around it)
+            // rows past the slot's end: out of range, zeros without memory traffic
+            voff[i] = it.row0 + tr >= it.row_end ? a_bytes : (uint32_t)v;
+        }
+    };
+    auto weight_addr = [&](const Item& it, uint32_t (&voff)[LPW]) {
+        const int l = opaque(lane);
+#pragma unroll
+        for (int i = 0; i < LPW; ++i) {
+            const int tr = (LPW * wave + i) * RPI + (l >> 3);  // row of the tile
+            int n = it.nt * BNO + (EPI == kSwiglu ? tr % (BR / 2) : tr);  // SwiGLU: second half = same rows of W3
+            n = n < N ? n : N - 1;
+            voff[i] = ((uint32_t)n * (uint32_t)K + ((l & 7) ^ ((tr >> 1) & 7)) * 8) * 2u;
+        }
+    };
+    // Where an item's loads stand in its K tiles, as a byte offset into a row.  The tiles of different slots start at
+    // different K tiles of their range and wrap around (all workgroups on the same 128-byte column of rows a power
+    // of two apart land on few memory channels); the tiles of a slot share the start and so stay in step.  The order
+    // is a fixed function of the tile.
+    struct Cursor {
+        int at, begin, end;
+    };
+    auto cursor_of = [&](const Item& it) {
+        Cursor u;
+        u.begin = it.kb * ROW_BYTES;
+        u.end = u.begin + it.kt * ROW_BYTES;
+        u.at = u.begin + __builtin_amdgcn_readfirstlane((int)(((unsigned)it.slot * kRotation) % (unsigned)it.kt)) * ROW_BYTES;
+        return u;
+    };
+    auto advance = [](Cursor& u) {
+        u.at += ROW_BYTES;
+        u.at = u.at == u.end ? u.begin : u.at;
+    };
+    // one load instruction of the token tile or the weight tile at row byte k, into the ring slot at LDS byte rs
+    const uint32_t k_bytes = (uint32_t)K * 2u;
+    auto issue_x = [&](const uint32_t (&voff)[LPW], int i, int rs, int k) {
+        uint32_t v = voff[i];
+        if (KTAIL && (uint32_t)(k + chunk2[i & 1] * 16) >= k_bytes) v = a_bytes;  // past K: zeros
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(lds + rs + (LPW * wave + i) * 1024), 16, (int)v, k, 0, 0);
+    };
+    auto issue_w = [&](const uint32_t (&voff)[LPW], const bf16_t* base, int i, int rs, int k, bool once) {
+        uint32_t v = voff[i];
+        if (KTAIL && (uint32_t)(k + chunk2[i & 1] * 16) >= k_bytes) v = b_bytes;
+        lds_void* dst = (lds_void*)(lds + rs + (LPW * wave + i) * 1024);
+        if (once) __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 2);  // non-temporal hint
+        else __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 0);
+    };
+    auto ring = [](int rs, int n) {  // the ring slot n places after the one at byte rs
+        rs += n * TILE_BYTES;
+        return rs >= SLOTS * TILE_BYTES ? rs - SLOTS * TILE_BYTES : rs;
+    };
+
     // fragments: a lane holds row lane % 16 of a 16-row block and, in MFMA K-step kk, chunk 4 kk + lane / 16 of it.
-    // The blocks of an operand are whole multiples of 16 rows apart, so they share the swizzle of the row.
+    // The blocks of an operand are whole multiples of 16 rows apart, so they share the swizzle of the row; the places
+    // of the two K-steps differ in bit 6 only.
     const int f_row = lane & 15;
     const int f_sw = ((lane >> 4) ^ ((f_row >> 1) & 7)) * 16;
     const int x_off = (tile_block(wm, 0) * 32 + f_row) * ROW_BYTES + f_sw;  // token block 0 of this wavefront
     // SwiGLU: weight blocks 0..WB/2-1 are gate rows, WB/2..WB-1 the matching up rows
     const int w_off = (wn * ((EPI == kSwiglu ? BR / 2 : BR) / WN) + f_row) * ROW_BYTES + f_sw;
 
-    for (int item = 0; item <= plan.rounds; ++item) {
-        // ---- what to do in this trip -------------------------------------------------------------
-        int L, kb = 0, ke = k_tiles_all, piece = -1;
-        if (item < plan.rounds) {
-            L = item * G + xcd * per_xcd + cu;
-        } else {
-            if (sk_item >= plan.left * plan.splits) break;
-            L = plan.rounds * G + sk_item / plan.splits;
-            if (plan.splits > 1) {
-                const int sp = sk_item % plan.splits;
-                kb = (int)((long long)k_tiles_all * sp / plan.splits);
-                ke = (int)((long long)k_tiles_all * (sp + 1) / plan.splits);
-                piece = sk_item;
+    // ---- prologue: K tiles 0 and 1 of the first item on their way, the first landed -------------------
+    // Ring slots: the operand tiles follow each other round the ring, x(0), w(0), x(1), w(1), x(2), ...
+    Item cur, nxt;
+    if (!item_at(0, cur)) return;
+    uint32_t a_voff[LPW], b_voff[LPW];
+    int perm_entry = load_perm(cur);
+    weight_addr(cur, b_voff);
+    const bf16_t* w_base = wsel + (size_t)cur.slot * N * K;
+    Cursor cursor = cursor_of(cur);
+    int sx = 0;  // ring slot (LDS byte) of the token rows of the K tile being multiplied
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, TILE_BYTES, cursor.at, false);
+    token_addr(cur, perm_entry, a_voff);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, 0, cursor.at);
+    advance(cursor);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, 2 * TILE_BYTES, cursor.at);
+#pragma unroll
+    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, 3 * TILE_BYTES, cursor.at, false);
+    advance(cursor);
+    barrier_keep_loads<2 * LPW>();
+    bf16x8 zero;
+    __builtin_memset(&zero, 0, sizeof(zero));
+    bool stores_pending = false;  // the item before this one ended with kEpilogueStores<EPI> stores
+
+    for (int idx = 0;; ++idx) {
+        // the perm entries of the next item, which have this whole item to arrive in, and (with the combine folded in) the
+        // output rows of this one: register h of a lane holds that of row 64 h + lane of this wavefront's 128
+        const bool have_nxt = item_at(idx + 1, nxt);
+        if (have_nxt) perm_entry = load_perm(nxt);
+        int out_entry[2] = {0, 0};
+        if (EPI == kPlain && gather.out_perm != nullptr) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int r = cur.row0 + token_row(wm, 4 * h + (lane >> 4)) + (lane & 15);
+                out_entry[h] = global_i32(gather.out_perm)[r < cur.row_end ? r : cur.row_end - 1];
             }
         }
-        int slot, row0, row_end, nt, slot_tiles;
-        decode_tile(table, S, n_tiles, lane, L, slot, row0, row_end, nt, slot_tiles);
-        const int n0 = nt * BNO;
 
-        // ---- global -> LDS -------------------------------------------------------------------------
-        // Wavefront w issues, per K tile and per operand, load instructions i = 0..LPW-1; instruction
-        // (w, i) fills tile rows (LPW*w + i)*8 .. +7, 128 bytes each.  Lane l lands in row l>>3, chunk
-        // position l&7 and therefore fetches global chunk (l&7) ^ ((row>>1)&7).
-        uint32_t a_voff[LPW], b_voff[LPW];
-        int chunk[LPW], a_row[LPW];
-        // the rows of x come through perm: those loads go out first, the first weight tile is requested
-        // while they are on their way (further down), and only then are the token addresses formed
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int tr = (LPW * wave + i) * RPI + l_row;  // row of the tile
-            chunk[i] = l_pos ^ ((tr >> 1) & 7);
-            int r = row0 + tr;
-            r = r >= row_end ? row_end - 1 : r;
-            a_row[i] = gather.perm != nullptr ? gather.perm[r] : r;  // the token's row of x (times k), not a copy of it
-            int n = n0 + (EPI == kSwiglu ? tr % (BR / 2) : tr);  // SwiGLU: second half = same rows of W3
-            n = n < N ? n : N - 1;
-            b_voff[i] = ((uint32_t)n * (uint32_t)K + chunk[i] * 8) * 2u;
-        }
-        const __amdgpu_buffer_rsrc_t b_rsrc = make_rsrc(wsel + (size_t)slot * N * K, b_bytes);
-        const int k_tiles = ke - kb;
-        const int k_first = kb * BK, k_last = (ke - 1) * BK;
-        // one load instruction i of the token (tok) or weight tile of K tile number tk, into ring slot rs.
-        // Near the end of K the loads go on (the loop body stays free of branches) but out of range:
-        // zeros land in a slot that nobody reads any more.
-        // The tiles of different slots start at different K tiles of their range (all workgroups on the
-        // same 128-byte column of rows a power of two apart land on few memory channels); the tiles of a
-        // slot share the start and so stay in step.  The order is a fixed function of the tile.
-        const int k_rot = (int)(((unsigned)slot * kRotation) % (unsigned)k_tiles);
-        auto k_of = [&](int tk) {
-            int kk = tk + k_rot;
-            kk = kk >= k_tiles ? kk - k_tiles : kk;
-            const int k0 = k_first + kk * BK;
-            return k0 < k_last ? k0 : k_last;
-        };
-        auto issue_load = [&](bool tok, int i, int rs, int tk) {
-            const int k0 = k_of(tk);
-            uint32_t voff = tok ? a_voff[i] : b_voff[i];
-            // out of range (zeros arrive, memory is not touched): chunks past K, and the loads past the last tile
-            if ((KTAIL && k0 + chunk[i] * 8 >= K) || tk >= k_tiles) voff = tok ? a_bytes : b_bytes;
-            char* dst = lds + rs * TILE_BYTES + (LPW * wave + i) * 1024;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(tok ? a_rsrc : b_rsrc, (lds_void*)dst, 16, (int)voff, k0 * 2, 0, 0);
-        };
-        // the same for a weight tile whose bytes no other tile reads (a slot of one m-tile): non-temporal hint
-        auto issue_weights_once = [&](int i, int rs, int tk) {
-            const int k0 = k_of(tk);
-            uint32_t voff = b_voff[i];
-            if ((KTAIL && k0 + chunk[i] * 8 >= K) || tk >= k_tiles) voff = b_bytes;
-            char* dst = lds + rs * TILE_BYTES + (LPW * wave + i) * 1024;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_void*)dst, 16, (int)voff, k0 * 2, 0, 2);
-        };
-
-        floatx4 acc[WB][TS];  // [weight block][token block]
-#pragma unroll
-        for (int i = 0; i < WB; ++i)
-#pragma unroll
-            for (int j = 0; j < TS; ++j)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.0f;
-
-        bf16x8 xf[2][TS], wf[2][WB];
         // Everything that touches the matrix cores is compiled for NB = 0 .. TB token blocks: the number
         // of this wavefront's 32-row blocks that hold rows of the tile (a ragged or evenly cut tile holds
         // fewer than 256 rows).  NB = TB is the full tile, NB = 0 a wavefront that only takes part in the
-        // loads and barriers.
-        // fragment f of MFMA K-step kk: token blocks 0 .. 2 NB - 1, then the weight blocks.  xb, wb: this lane's place in
-        // the operand tiles for that step
-        auto load_frag = [&](auto nb_c, int kk, int f, const char* xb, const char* wb) {
-            constexpr int NT = 2 * decltype(nb_c)::value;
-            if (f < NT) {
-                xf[kk][f] = *reinterpret_cast<const bf16x8*>(xb + token_row(0, f) * ROW_BYTES);
-            } else {
-                const int i = f - NT;
-                const int rr = (EPI == kSwiglu && i >= WB / 2) ? BR / 2 + (i - WB / 2) * 16 : i * 16;
-                wf[kk][i] = *reinterpret_cast<const bf16x8*>(wb + rr * ROW_BYTES);
-            }
-        };
-        auto x_place = [&](int rs, int kk) { return lds + rs * TILE_BYTES + (x_off ^ (kk * 64)); };
-        auto w_place = [&](int rs, int kk) { return lds + rs * TILE_BYTES + (w_off ^ (kk * 64)); };
-        // One MFMA K-step: multiplies the fragments of step kk and, slotted in between so that no memory
-        // instruction waits in a full queue while the matrix pipe idles, reads the fragments of the step after it
-        // (from xb, wb; in the first three quarters of the step, so that they are there at its end) and issues
-        // LPW global->LDS loads.
-        auto step = [&](auto nb_c, int kk, const char* xb, const char* wb, auto issue) {
+        // loads and barriers.  The accumulators live and die inside one instance: where instances met, the compiler
+        // would permute all 256 of them.
+        auto do_item = [&](auto nb_c, auto once_c) {
             constexpr int NB = decltype(nb_c)::value;
-            constexpr int NT = 2 * NB, MF = WB * NT, FR = WB + NT;
-            if constexpr (NB == 0) {
+            floatx4 acc[WB][TS];  // [weight block][token block]
+            mfma_settle();  // the last of the item before have been read, and the zero operand has been written
 #pragma unroll
-                for (int i = 0; i < LPW; ++i) issue(i);
-            } else {
-                constexpr int FR_EVERY = MF * 3 / 4 / FR, LD_EVERY = MF / LPW;
-                static_assert(FR_EVERY >= 1 && FR_EVERY * FR <= MF && LD_EVERY * LPW <= MF, "everything finds its place");
+            for (int i = 0; i < WB; ++i)
 #pragma unroll
-                for (int m = 0; m < MF; ++m) {
-                    const int ni = m / NT;
-                    const int mi = (ni & 1) ? NT - 1 - m % NT : m % NT;  // back and forth: only one operand changes between two MFMAs
-                    mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
-                    if (m % FR_EVERY == FR_EVERY - 1 && m / FR_EVERY < FR) load_frag(nb_c, kk ^ 1, m / FR_EVERY, xb, wb);
-                    if (m % LD_EVERY == LD_EVERY / 2) issue(m / LD_EVERY);
+                for (int j = 0; j < 2 * NB; ++j) mfma_zero(acc[i][j], zero);
+
+            bf16x8 xf[2][TS], wf[2][WB];
+            // fragment f of MFMA K-step kk: token blocks 0 .. 2 NB - 1, then the weight blocks.  xp, wp: this lane's place (LDS
+            // byte) in the operand tiles for that step
+            auto load_frag = [&](int kk, int f, int xp, int wp) {
+                constexpr int NT = 2 * NB;
+                if (f < NT) {
+                    xf[kk][f] = *reinterpret_cast<const bf16x8*>(lds + xp + token_row(0, f) * ROW_BYTES);
+                } else {
+                    const int i = f - NT;
+                    const int rr = (EPI == kSwiglu && i >= WB / 2) ? BR / 2 + (i - WB / 2) * 16 : i * 16;
+                    wf[kk][i] = *reinterpret_cast<const bf16x8*>(lds + wp + rr * ROW_BYTES);
                 }
-            }
-        };
+            };
+            // One MFMA K-step: multiplies the fragments of step kk and, slotted in between so that no memory
+            // instruction waits in a full queue while the matrix pipe idles, reads the fragments of the step after it
+            // (from xp, wp; in the first three quarters of the step, so that they are there at its end), issues LPW
+            // global->LDS loads and runs `scalar`, the next step's address arithmetic.
+            auto step = [&](int kk, int xp, int wp, auto issue, auto scalar) {
+                constexpr int NT = 2 * NB, MF = WB * NT, FR = WB + NT;
+                if constexpr (NB == 0) {
+    #pragma unroll
+                    for (int i = 0; i < LPW; ++i) issue(i);
+                    scalar();
+                } else {
+                    constexpr int FR_EVERY = MF * 3 / 4 / FR, LD_EVERY = MF / LPW;
+                    static_assert(FR_EVERY >= 1 && FR_EVERY * FR <= MF && LD_EVERY * LPW <= MF, "everything finds its place");
+    #pragma unroll
+                    for (int m = 0; m < MF; ++m) {
+                        const int ni = m / NT;
+                        const int mi = (ni & 1) ? NT - 1 - m % NT : m % NT;  // back and forth: only one operand changes between two MFMAs
+                        mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
+                        if (m % FR_EVERY == FR_EVERY - 1 && m / FR_EVERY < FR) load_frag(kk ^ 1, m / FR_EVERY, xp, wp);
+                        if (m % LD_EVERY == LD_EVERY / 2) issue(m / LD_EVERY);
+                        if (m == MF / 2) {
+                            __builtin_amdgcn_sched_barrier(0);
+                            scalar();
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+                }
+            };
 
-        // ---- prologue: K tiles 0 and 1 of this piece on their way, the first landed ----------------
-        // (every wavefront is past the last barrier of the previous trip, so nobody reads LDS any more)
-        // Ring slots: token rows of K tile t in slot 2t mod 5, weight rows in slot 2t+1 mod 5.
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) issue_load(false, i, 1, 0);
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) {
-            const int tr = (LPW * wave + i) * RPI + l_row;
-            const bool past = row0 + tr >= row_end;  // rows past the slot's end: out of range, zeros without memory traffic
-            const int r = gather.perm != nullptr ? a_row[i] / gather.k : a_row[i];
-            a_voff[i] = past ? a_bytes : ((uint32_t)r * (uint32_t)K + chunk[i] * 8) * 2u;
-        }
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) issue_load(true, i, 0, 0);
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) issue_load(true, i, 2, 1);
-#pragma unroll
-        for (int i = 0; i < LPW; ++i) issue_load(false, i, 3, 1);
-        barrier_keep_loads<2 * LPW>();
-
-        // ---- main loop -----------------------------------------------------------------------------
-        // Per K tile: two MFMA steps of 32.  Token rows of tile t+2 are requested during step 0 (into the slot
-        // that held the weight rows of tile t-1), weight rows of tile t+2 during step 1 (into the slot of this
-        // tile's token rows, dead after the barrier).  One barrier per tile, between the steps: by then every
-        // wavefront has read its last fragments of tile t, and tile t+1 has landed once only the LPW newest
-        // loads (token rows of t+2) are pending.
-        // A wavefront skips the fragment reads and MFMAs of its token blocks without rows: the kernel
-        // runs at the chip's power limit, so work not done is speed for the others.
-        auto k_loop = [&](auto nb_c, auto once_c) {
-            constexpr int NB = decltype(nb_c)::value;
-#pragma unroll
-            for (int f = 0; NB > 0 && f < 2 * NB + WB; ++f) load_frag(nb_c, 0, f, x_place(0, 0), w_place(1, 0));
+            // ---- main loop -----------------------------------------------------------------------------
+            // Per K tile: two MFMA steps of 32.  Token rows of tile t+2 are requested during step 0 (into the slot
+            // that held the weight rows of tile t-1), weight rows of tile t+2 during step 1 (into the slot of this
+            // tile's token rows, dead after the barrier).  One barrier per tile, between the steps: by then every
+            // wavefront has read its last fragments of tile t, and tile t+1 has landed once only the LPW newest
+            // loads (token rows of t+2) are pending - and, in an item's first K tile, the stores of the item before,
+            // which are newer than the loads of this item's first two K tiles.
+            // The stream of operand tiles does not end with the item: its last two K tiles request the first two of
+            // the next one, which have the epilogue's time to arrive in.
+            // A wavefront skips the fragment reads and MFMAs of its token blocks without rows: the kernel
+            // runs at the chip's power limit, so work not done is speed for the others.
+            int xp0 = sx + x_off, wp0 = ring(sx, 1) + w_off;
+    #pragma unroll
+            for (int f = 0; NB > 0 && f < 2 * NB + WB; ++f) load_frag(0, f, xp0, wp0);
+            int xp1 = xp0 ^ 64, wp1 = wp0 ^ 64;
             __builtin_amdgcn_sched_barrier(0);
-            int sx = 0;  // ring slot of tile t's token rows
-            for (int t = 0; t < k_tiles; ++t) {
-                const int sw = sx + 1 >= SLOTS ? sx + 1 - SLOTS : sx + 1;   // this tile's weight rows
-                const int sx1 = sx + 2 >= SLOTS ? sx + 2 - SLOTS : sx + 2;  // next tile's token rows
-                const int sw1 = sx + 3 >= SLOTS ? sx + 3 - SLOTS : sx + 3;  // next tile's weight rows
-                const int sx2 = sx + 4 >= SLOTS ? sx + 4 - SLOTS : sx + 4;  // token rows of t+2 (held weights of t-1)
-                step(nb_c, 0, x_place(sx, 1), w_place(sw, 1), [&](int i) { issue_load(true, i, sx2, t + 2); });
+            auto k_tile = [&] {
+                const int k = __builtin_amdgcn_readfirstlane(cursor.at);  // (uniform, which the compiler does not see)
+                const int sx2 = ring(sx, 4);
+                int sx1 = 0;
+                step(0, xp1, wp1, [&](int i) { issue_x(a_voff, i, sx2, k); },
+                     [&] {
+                         sx1 = ring(sx, 2);
+                         xp0 = sx1 + x_off;
+                         wp0 = ring(sx, 3) + w_off;
+                     });
                 __builtin_amdgcn_sched_barrier(0);
-                barrier_keep_loads<LPW>();
+                if (stores_pending) {
+                    barrier_keep_loads<LPW + kEpilogueStores<EPI>>();
+                    stores_pending = false;
+                } else {
+                    barrier_keep_loads<LPW>();
+                }
                 __builtin_amdgcn_sched_barrier(0);
-                step(nb_c, 1, x_place(sx1, 0), w_place(sw1, 0), [&](int i) {  // weight rows of t+2 over this tile's token rows
-                    if (decltype(once_c)::value) issue_weights_once(i, sx, t + 2);
-                    else issue_load(false, i, sx, t + 2);
-                });
+                step(1, xp0, wp0, [&](int i) { issue_w(b_voff, w_base, i, sx, k, decltype(once_c)::value); },
+                     [&] {
+                         xp1 = xp0 ^ 64;
+                         wp1 = wp0 ^ 64;
+                     });
                 __builtin_amdgcn_sched_barrier(0);
+                advance(cursor);
                 sx = sx1;
+            };
+            int t = cur.kt - 2;
+            if (t > 0) {
+                do k_tile();
+                while (--t > 0);
+            } else {  // nothing has waited for the next item's perm entries yet
+                __builtin_amdgcn_s_waitcnt(wait_imm(0));
+            }
+            // from here on the loads are the next item's
+            cursor = Cursor{0, 0, 2 * ROW_BYTES};
+            if (have_nxt) {
+                token_addr(nxt, perm_entry, a_voff);
+                weight_addr(nxt, b_voff);
+                w_base = wsel + (size_t)nxt.slot * N * K;
+                cursor = cursor_of(nxt);
+            } else {  // none: they go on, out of range: zeros land in ring slots that nobody reads any more
+    #pragma unroll
+                for (int i = 0; i < LPW; ++i) { a_voff[i] = a_bytes; b_voff[i] = b_bytes; }
+            }
+            __builtin_amdgcn_sched_barrier(0);
+    #pragma unroll 1
+            for (int t = 0; t < 2; ++t) k_tile();
+            mfma_settle();
+
+            if (cur.piece < 0) {
+                epilogue<EPI, NB>(acc, c_rsrc, out_entry, EPI == kPlain && gather.out_perm != nullptr, cur.row0, cur.row_end, cur.nt * BNO, N, wm, wn, lane);
+            } else {  // a K piece of a leftover tile: raw accumulators to the workspace, [register][thread]
+                float* dst = partials + kPlanFloats + (size_t)cur.piece * (BM * BR) + tid;
+    #pragma unroll
+                for (int i = 0; i < WB; ++i)
+    #pragma unroll
+                    for (int j = 0; j < 2 * NB; ++j) {  // (the fix-up skips blocks without rows)
+    #pragma unroll
+                        for (int v = 0; v < 4; ++v) dst[((i * TS + j) * 4 + v) * (64 * NW)] = acc_read(acc[i][j][v]);
+                    }
             }
         };
         // Blocks without rows are skipped in slots of up to kBlockM tiles (one block of tile_in_slot), where a
@@ -549,41 +673,29 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         // shape: 10.5 instead of 6.6 GB) and gains nothing: with the three policies (limit 4, 8, none) run
         // in turns inside one process, layer times differ by less than 1 % on every workload (prefill
         // 2.298 / 2.288 / 2.307 ms, fine-grained layer 0.845 / 0.842 / 0.836 ms).
-        const int my_blocks = slot_tiles > kSkipBlocksUpToTiles ? TB : blocks_of_wavefront(row0, row_end, wm);
+        const int my_blocks = cur.slot_tiles > kSkipBlocksUpToTiles ? TB : blocks_of_wavefront(cur.row0, cur.row_end, wm);
         static_assert(TB == 4, "written out for four token blocks per wavefront");
         // A slot of one m-tile: nobody else reads its weight panel, which is then loaded with the
         // non-temporal hint, so that the stream does not push the token rows out of the caches.
-        if (slot_tiles == 1) {
-            if (my_blocks >= 4) k_loop(std::integral_constant<int, 4>{}, std::true_type{});
-            else if (my_blocks == 3) k_loop(std::integral_constant<int, 3>{}, std::true_type{});
-            else if (my_blocks == 2) k_loop(std::integral_constant<int, 2>{}, std::true_type{});
-            else if (my_blocks == 1) k_loop(std::integral_constant<int, 1>{}, std::true_type{});
-            else k_loop(std::integral_constant<int, 0>{}, std::true_type{});
+        if (cur.slot_tiles == 1) {
+            if (my_blocks >= 4) do_item(std::integral_constant<int, 4>{}, std::true_type{});
+            else if (my_blocks == 3) do_item(std::integral_constant<int, 3>{}, std::true_type{});
+            else if (my_blocks == 2) do_item(std::integral_constant<int, 2>{}, std::true_type{});
+            else if (my_blocks == 1) do_item(std::integral_constant<int, 1>{}, std::true_type{});
+            else do_item(std::integral_constant<int, 0>{}, std::true_type{});
         } else {
-            if (my_blocks >= 4) k_loop(std::integral_constant<int, 4>{}, std::false_type{});
-            else if (my_blocks == 3) k_loop(std::integral_constant<int, 3>{}, std::false_type{});
-            else if (my_blocks == 2) k_loop(std::integral_constant<int, 2>{}, std::false_type{});
-            else if (my_blocks == 1) k_loop(std::integral_constant<int, 1>{}, std::false_type{});
-            else k_loop(std::integral_constant<int, 0>{}, std::false_type{});
+            if (my_blocks >= 4) do_item(std::integral_constant<int, 4>{}, std::false_type{});
+            else if (my_blocks == 3) do_item(std::integral_constant<int, 3>{}, std::false_type{});
+            else if (my_blocks == 2) do_item(std::integral_constant<int, 2>{}, std::false_type{});
+            else if (my_blocks == 1) do_item(std::integral_constant<int, 1>{}, std::false_type{});
+            else do_item(std::integral_constant<int, 0>{}, std::false_type{});
         }
-        // surplus loads must not land in the next trip's tiles (or outlive the workgroup's LDS)
-        barrier_keep_loads<0>();
-        mfma_settle();
-
-        if (piece < 0) {
-            epilogue<EPI>(acc, c, gather.out_perm, lds, row0, row_end, n0, N, wm, wn, wave, lane);
-        } else {  // a K piece of a leftover tile: raw accumulators to the workspace, [register][thread]
-            float* dst = partials + kPlanFloats + (size_t)piece * (BM * BR) + tid;
-#pragma unroll
-            for (int i = 0; i < WB; ++i)
-#pragma unroll
-                for (int j = 0; j < TS; ++j) {
-                    if (row0 + token_row(wm, j) >= row_end) continue;  // a block without rows: the fix-up skips it too
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) dst[((i * TS + j) * 4 + v) * (64 * NW)] = acc_read(acc[i][j][v]);
-                }
-        }
+        if (!have_nxt) break;
+        stores_pending = true;  // (a K piece is always the last item)
+        cur = nxt;
     }
+    // the surplus loads must not outlive the workgroup's LDS
+    barrier_keep_loads<0>();
 }
 
 // Adds the K pieces of each leftover tile in piece order and applies the epilogue.  One unit of work
@@ -665,7 +777,7 @@ hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets,
                       float* partials, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     const int n_tiles = (N + BNO - 1) / BNO;
-    if (K % BK == 0) return launch_cfg<EPI, false>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, st);
+    if (K % BK == 0 && K > BK) return launch_cfg<EPI, false>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, st);
     return launch_cfg<EPI, true>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, st);
 }
 
