@@ -71,6 +71,9 @@ int validate_desc(const emoe_layer_desc* d);
 hipError_t launch_route_bf16(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
                              const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
                              unsigned long long* expert_tokens, hipStream_t st);
+hipError_t launch_route_f32(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
+                            const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
+                            unsigned long long* expert_tokens, hipStream_t st);
 // expert_tokens: nullptr, or [E] counters that receive each token's k experts under ordinary routing
 hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
                         const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,

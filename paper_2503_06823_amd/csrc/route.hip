@@ -1,7 +1,7 @@
 // Gate logits and resident-restricted top-k (eMoE Section 1: the gate; Section 3.2.2, last
 // paragraph: a token whose expert is not on the GPU goes to its next-best expert that is):
-// fp32 inputs, and bf16 inputs when there are few tokens, few experts and long rows (a decode step
-// of a Mixtral-shaped layer).  Other bf16 batches take the matrix-core kernel of route_mfma.hip,
+// fp32 inputs with few tokens or few experts, and bf16 inputs when there are few tokens, few experts and
+// long rows (a decode step of a Mixtral-shaped layer).  Other fp32 batches take route_f32.hip.  Other bf16 batches take the matrix-core kernel of route_mfma.hip,
 // which puts 32 tokens on a workgroup: with 64 tokens it runs on two CUs, bound by the latency of
 // their walk along d_model.
 //
@@ -13,6 +13,8 @@
 // are then read into scalar registers and top-k is k rounds of compares that every lane performs
 // on the same values (lower index wins a tie); softmax over the k winners.
 // The summation order is fixed by the code, so results are reproducible run to run.
+#include <type_traits>
+
 #include "common.h"
 
 namespace emoe {
@@ -219,9 +221,9 @@ hipError_t launch_t(const emoe_layer_desc& d, const void* x, const void* w_gate,
     if (d.E <= 2) return launch_ep<T, 2>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 4) return launch_ep<T, 4>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 8) return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
-    if (d.E <= 16) return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
-    if (d.E <= 32) return launch_ep<T, 32>(d, x, w_gate, bias, soe, te, tw, et, st);
-    return launch_ep<T, 64>(d, x, w_gate, bias, soe, te, tw, et, st);
+    if constexpr (std::is_same<T, float>::value)
+        if (d.E > 16) return launch_ep<T, 64>(d, x, w_gate, bias, soe, te, tw, et, st);
+    return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
 }
 
 }  // namespace
@@ -229,8 +231,18 @@ hipError_t launch_t(const emoe_layer_desc& d, const void* x, const void* w_gate,
 hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
                         const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
                         unsigned long long* expert_tokens, hipStream_t st) {
-    if (d.dtype == EMOE_F32)
+    if (d.dtype == EMOE_F32) {
+        // The matrix kernel reads the gate matrix once per 16 tokens, the wavefront kernel once per token, which is
+        // the better one with few experts or so few tokens that each has a CU to itself.  Wavefront / matrix, us:
+        // 1024 tokens, d 768: 8 experts level, 16: 12 / 8, 64: 46 / 13; 8192 tokens, d 768, 8 experts 12 / 8, d 2048, 4
+        // experts 13 / 15; 512 tokens, d 2048: 16 experts 9.6 / 10.5, 64: 38 / 25; 1 to 256 tokens, d 2048: 40 experts
+        // 20 / 16, 64: 21 to 23 / 23 to 26.  (A launch of 2^26 tokens would not fit a grid.)
+        const bool matrix = d.E > 16 ? !(d.T <= 256 && d.E > 48 && d.d_model >= 1536)
+                                     : d.E > 8 ? d.T >= 1024 : d.E > 4 && d.T >= 4096;
+        if (matrix && d.T < (1 << 26))
+            return launch_route_f32(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
         return launch_t<float>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+    }
     // bf16: the matrix-core kernel runs T / 32 workgroups, each bound by the latency of its walk along
     // d_model (11 us at d_model = 4096 however few the tokens); one workgroup per token takes 6-8 us
     // with up to 16 experts (19 us with 64, where the matrix-core kernel stays the better one)
