@@ -172,6 +172,12 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;  // output columns per tile
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;   // output column blocks per wavefront
     static_assert((STAGES - 1) * LPT <= 63, "vmcnt counts 63 loads");
+    constexpr auto part_of = [](int i) { return i * 4 / LPT; };  // the quarter of a tile's loads that load i belongs to
+    constexpr auto part_size = [](int part) {
+        int n = 0;
+        for (int i = 0; i < LPT; ++i) n += i * 4 / LPT == part;
+        return n;
+    };
     static_assert(BM * BNO * 2 <= STAGES * STAGE_BYTES, "the output image reuses the stages");
     extern __shared__ __align__(16) char lds[];
 
@@ -282,25 +288,28 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         // to 15 % once the slot's token rows no longer stay in L2 beside the weight stream.
         const int k_rot = (int)(((unsigned)slot * kRotation) % (unsigned)cnt);
         // once: the weight panel of a slot of one m-tile is read by nobody else, and is loaded with the non-temporal hint
-        auto issue_tile = [&](int st, int tk, auto once_tag) {
-            constexpr int kWeightAux = decltype(once_tag)::value ? 2 : 0;
+        // A tile's loads go out in four parts (part 0 .. 3, or ALL of them at once): see the main loop.
+        constexpr int ALL = 4;
+        auto issue_part = [&](int st, int tk, int part, auto once_tag) {
+            constexpr int kWeightAux = decltype(once_tag)::value && !KTAIL ? 2 : 0;  // (see below)
             int kk = tk + k_rot;
             kk = kk >= cnt ? kk - cnt : kk;
             int k0 = k_first + kk * BK;
             k0 = k0 < k_last ? k0 : k_last;
+            // the chunk of load i depends on the parity of i only
+            const bool out[2] = {tk >= cnt || (KTAIL && k0 + x_chunk[0] * 8 >= K), tk >= cnt || (KTAIL && k0 + x_chunk[1] * 8 >= K)};
 #pragma unroll
-            for (int i = 0; i < LX; ++i) {
-                uint32_t v = x_voff[i];
-                if ((KTAIL && k0 + x_chunk[i] * 8 >= K) || tk >= cnt) v = a_bytes;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(lds + st * STAGE_BYTES + (LX * wave + i) * 1024),
-                                                         16, (int)v, k0 * 2, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < LW; ++i) {
-                uint32_t v = w_voff[i];
-                if ((KTAIL && k0 + w_chunk[i] * 8 >= K) || tk >= cnt) v = b_bytes;
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                    b_rsrc, (lds_void*)(lds + st * STAGE_BYTES + X_TILE + (LW * wave + i) * 1024), 16, (int)v, k0 * 2, 0, kWeightAux);
+            for (int i = 0; i < LPT; ++i) {
+                if (part != ALL && part_of(i) != part) continue;
+                if (i < LX) {
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(lds + st * STAGE_BYTES + (LX * wave + i) * 1024),
+                                                             16, (int)(out[i & 1] ? a_bytes : x_voff[i < LX ? i : 0]), k0 * 2, 0, 0);
+                } else {
+                    const int j = i - LX;
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                        b_rsrc, (lds_void*)(lds + st * STAGE_BYTES + X_TILE + (LW * wave + j) * 1024), 16,
+                        (int)(out[j & 1] ? b_bytes : w_voff[j >= 0 ? j : 0]), k0 * 2, 0, kWeightAux);
+                }
             }
         };
 
@@ -328,15 +337,15 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
                 for (int mi = 0; mi < TB; ++mi)
                     acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[buf][ni], xf[buf][mi], acc[ni][mi], 0, 0, 0);
         };
-        // a step's MFMAs with its fragment reads and (in the step after the barrier) the tile's
-        // global->LDS loads slotted between them, so that no memory instruction queues up behind another
-        auto interleave = [&](auto with_loads) {
-            constexpr bool LOADS = decltype(with_loads)::value;
+        // a step's MFMAs with its fragment reads and its part of the global->LDS loads slotted between them, so that no
+        // memory instruction queues up behind another
+        auto interleave = [&](auto part) {
+            constexpr int LOADS = part_size(decltype(part)::value), PER = (LOADS + TB * WB - 1) / (TB * WB);
 #pragma unroll
             for (int i = 0; i < TB * WB; ++i) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                           // one MFMA
                 if (i < TB + WB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);          // one LDS read
-                if (LOADS) __builtin_amdgcn_sched_group_barrier(0x010, (LPT + TB * WB - 1) / (TB * WB), 0);  // VMEM
+                if (i * PER < LOADS) __builtin_amdgcn_sched_group_barrier(0x010, PER, 0);    // VMEM
             }
         };
 
@@ -345,47 +354,46 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         // holds its last fragments of tile t in registers, so the stage of tile t is free for the data of
         // tile t+STAGES, and tile t+1 has landed once only the loads of tiles t+2 .. t+STAGES-1 are pending.
         // The last step's MFMAs then cover the first fragment reads of tile t+1.
+        // The loads of tile t+STAGES go out in quarters, one per step: the last step of tile t and the first
+        // three of tile t+1.  A CU takes 16 cycles per load instruction, and a wavefront that has to wait with one
+        // issues no MFMA meanwhile.
         // A wavefront whose 64 token rows all lie past the slot's end takes part in loads and barriers only.
         auto k_loop = [&](auto idle_tag, auto once_tag) {
             constexpr bool IDLE = decltype(idle_tag)::value;
             // prologue: the trip's K tiles 0 .. STAGES-1 on their way, tile 0 landed (every wavefront is past
             // the last barrier of the previous trip: nobody reads LDS any more)
 #pragma unroll
-            for (int p = 0; p < STAGES; ++p) issue_tile(p, p, once_tag);
-            barrier_keep_loads<(STAGES - 1) * LPT>();
+            for (int p = 0; p < STAGES - 1; ++p) issue_part(p, p, ALL, once_tag);
+            issue_part(STAGES - 1, STAGES - 1, 0, once_tag);
+            barrier_keep_loads<(STAGES - 2) * LPT + part_size(0)>();
             if (!IDLE) load_frags(0, 0, 0);
             __builtin_amdgcn_sched_barrier(0);
-            int st = 0;
+            int st = 0, st_prev = STAGES - 1;
+            auto step = [&](int frag_stage, int kk, int load_stage, int tk, auto part) {
+                if (!IDLE) load_frags(kk & 1, frag_stage, kk);
+                issue_part(load_stage, tk, decltype(part)::value, once_tag);
+                if (!IDLE) {
+                    mfma_step((kk & 1) ^ 1);
+                    interleave(part);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
             for (int t = 0; t < cnt; ++t) {
                 const int st1 = st + 1 == STAGES ? 0 : st + 1;
-                if (!IDLE) {
-                    load_frags(1, st, 1);
-                    mfma_step(0);
-                    interleave(std::false_type{});
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_frags(0, st, 2);
-                    mfma_step(1);
-                    interleave(std::false_type{});
-                    __builtin_amdgcn_sched_barrier(0);
-                    load_frags(1, st, 3);
-                    mfma_step(0);
-                    interleave(std::false_type{});
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                step(st, 1, st_prev, t + STAGES - 1, std::integral_constant<int, 1>{});
+                step(st, 2, st_prev, t + STAGES - 1, std::integral_constant<int, 2>{});
+                step(st, 3, st_prev, t + STAGES - 1, std::integral_constant<int, 3>{});
                 barrier_keep_loads<(STAGES - 2) * LPT>();
                 __builtin_amdgcn_sched_barrier(0);
-                if (!IDLE) load_frags(0, st1, 0);
-                issue_tile(st, t + STAGES, once_tag);
-                if (!IDLE) {
-                    mfma_step(1);
-                    interleave(std::true_type{});
-                }
-                __builtin_amdgcn_sched_barrier(0);
+                step(st1, 0, st, t + STAGES, std::integral_constant<int, 0>{});
+                st_prev = st;
                 st = st1;
             }
         };
         // The weight panel of a slot of one m-tile is read by nobody else: non-temporal hint, so that the stream
-        // does not push the token rows out of the caches (-5 to -12 % per product at 22-110 rows per slot).
+        // does not push the token rows out of the caches (-5 to -12 % per product at 22-110 rows per slot).  Not where rows
+        // are not whole 128-byte lines: two K tiles then share the lines between them, and the second would fetch
+        // them from HBM again (d 1032, f 2808, 16 slots of 48 rows: 68 + 39 us with the hint, 57 + 37 without).
         const bool once = slot_mtiles == 1;
         const bool idle = row0 + wm * 64 >= row_end;  // never with one row of wavefronts
         if (once) {

@@ -43,8 +43,12 @@ constexpr int CPR = ROW_BYTES / 16;         // 16-byte chunks per tile row
 constexpr int RPI = 1024 / ROW_BYTES;       // tile rows filled by one load instruction
 constexpr int SPW = BK / 16 / 4;            // MFMA steps per wavefront and tile
 constexpr int LX = X_BYTES / 1024 / 4;      // token load instructions per wavefront and tile
-// cache policy of the weight loads: every weight byte is read once per launch (non-temporal: bit 1 of the aux operand)
+// Cache policy of the weight loads: every weight byte is read once per launch (non-temporal: bit 1 of the aux operand).
+// Where rows are not whole 128-byte lines, two K tiles share the lines between them, and the second would fetch them from
+// HBM again: no hint (d 1032, f 2808, 16 slots of 48 rows: 86 + 53 -> 67 + 45 us; with whole lines the hint stays the
+// better one, d 1088, f 2880, slots of 4 rows: 34 + 22 us, without 38 + 23).
 constexpr int kStreamOnce = 2;
+enum Tail { kNoTail = 0, kTailWholeLines = 1, kTailSplitLines = 2 };  // K a multiple of the tile; of a line; neither
 constexpr unsigned kRotation = 21;           // K-tile rotation per workgroup (measured best of 1..29)
 constexpr int RED_BYTES = 3 * 32 * 64 * 4;  // partial sums of wavefronts 1..3
 static_assert(RED_BYTES <= kMinStages * (32 * ROW_BYTES + X_BYTES), "the reduction reuses the tile stages");
@@ -64,12 +68,13 @@ __device__ __forceinline__ void barrier_keep_loads() {
 }
 
 // grid.x = S * ceil(N / BNO) workgroups, BNO = output columns per workgroup (32 SwiGLU, else 64).
-template <int EPI, int WR, bool KTAIL>
+template <int EPI, int WR, int TAIL>
 __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restrict__ a, RowGather gather,
                                                            const int32_t* __restrict__ offsets,
                                                            const bf16_t* __restrict__ b0,
                                                            const bf16_t* __restrict__ b1, bf16_t* __restrict__ c,
                                                            int S, int N, int K, int n_units) {
+    constexpr bool KTAIL = TAIL != kNoTail;
     constexpr int BNO = EPI == kSwiglu ? WR / 2 : WR;
     constexpr int W_BYTES = WR * ROW_BYTES;          // 16 KiB at WR = 64
     constexpr int STAGE_BYTES = W_BYTES + X_BYTES;
@@ -142,7 +147,7 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
                 uint32_t v = w_voff[i];
                 if (KTAIL && k0 + w_chunk[i] * 8 >= K) v = b_bytes;  // out of range: zeros
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_void*)(base + (LW * wave + i) * 1024), 16, (int)v,
-                                                         k0 * 2, 0, kStreamOnce);
+                                                         k0 * 2, 0, TAIL == kTailSplitLines ? 0 : kStreamOnce);
             }
 #pragma unroll
             for (int i = 0; i < LX; ++i) {
@@ -239,9 +244,11 @@ hipError_t launch_wr(const bf16_t* a, RowGather gather, const int32_t* offsets, 
     const int n_units = (N + BNO - 1) / BNO;
     const unsigned blocks = (unsigned)(S * n_units);
     if (K % BK == 0)
-        stream_gemm_bf16<EPI, WR, false><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
+        stream_gemm_bf16<EPI, WR, kNoTail><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
+    else if (K % 64 == 0)
+        stream_gemm_bf16<EPI, WR, kTailWholeLines><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
     else
-        stream_gemm_bf16<EPI, WR, true><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
+        stream_gemm_bf16<EPI, WR, kTailSplitLines><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
     return hipGetLastError();
 }
 
