@@ -93,23 +93,21 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
 // 723 against 563 us).
 constexpr long long kStreamRowsPerSlot = 22;
 constexpr long long kMidRowsPerSlot = 100;
-// A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
-// fill the chip, not by the weight stream, and around 256 rows per slot the 128-row tiles fill it
-// better: half the slots then need a second 256-row tile for a few rows.  Measured (FFN, us, 256-row
-// against 128-row tiles): d = 768, f = 3072, 16 slots of 214-291 rows 120 / 86; 32 slots of 195-315
-// rows 177 / 145; d = 2048, f = 1408, 8 slots of 182-206 rows 100 / 72; d = 2048, f = 8192, 2 slots
-// of 256 rows 134 / 102, 3 slots of 238-266 rows 172 / 148.  Below about 170 rows per slot the
-// 256-row tiles win or are level there too (16 slots of 99-148 rows: 104 / 123), and so they do at
-// any number of rows once the weights are large (Mixtral shape, 8 slots of 232-278 rows: 863 / 998).
-constexpr long long kSmallLayerWeightBytes = 320ll << 20;
-constexpr long long kSmallLayerMidFrom = 170, kSmallLayerMidTo = 300;  // rows per slot
+// A small layer (all slots' weights stream in some 20 us) is bound by how well its tiles fill the chip, not by the
+// weight stream, and up to about 300 rows per slot the 128-row tiles fill it better.  Measured with weights that come from
+// HBM (FFN, us, 256-row against 128-row tiles): d = 2048, f = 1408, 4 slots of 128 rows 62 / 37, of 256 72 / 47; d = 768,
+// f = 3072, 4 slots of 160 57 / 44, 8 slots (113 MB) of 128 58 / 61, of 200 65 / 61; d = 1536, 8 slots of 160 72 / 52;
+// d = 4104, f = 2056, 2 slots (101 MB) of 128 76 / 89, of 200 85 / 80.  Of larger layers more lose than win: d = 1032,
+// f = 2808, 8 slots (139 MB) of 200 82 / 104; d = 2048, f = 1408, 12 slots (208 MB) of 200 96 / 101; d = 4104, 4 slots of
+// 200 111 / 150; Mixtral shape, 8 slots of 232-278 rows 799 / 998.
+constexpr long long kSmallLayerWeightBytes = 112ll << 20;
+constexpr long long kSmallLayerMidTo = 300;  // rows per slot
 FfnPath ffn_bf16_path(const emoe_layer_desc& d) {
     const long long A = (long long)d.T * d.k;
     if (A <= kStreamRowsPerSlot * d.S) return kFfnStream;
     if (A <= kMidRowsPerSlot * d.S) return kFfnMid;
     const long long weight_bytes = (long long)d.S * (d.act == EMOE_ACT_SWIGLU ? 3 : 2) * d.d_model * d.d_ff * 2;
-    if (weight_bytes <= kSmallLayerWeightBytes && A >= kSmallLayerMidFrom * d.S && A <= kSmallLayerMidTo * d.S)
-        return kFfnMid;
+    if (weight_bytes <= kSmallLayerWeightBytes && A <= kSmallLayerMidTo * d.S) return kFfnMid;
     return kFfnTiled;
 }
 
