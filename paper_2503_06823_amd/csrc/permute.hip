@@ -1,7 +1,7 @@
 // Stable counting sort of the A = T*k assignments by slot id and the row gather into slot-contiguous
 // order.  The per-slot row counts are the per-expert "workload" of eMoE Section 3.2.2.
 //
-// Four launches (three up to 65 536 assignments: scan and place fused; two when all assignments fit
+// Four launches (three up to 65 536 assignments: scan and place fused; two up to 4096, which fit
 // one workgroup: count, scan and place fused), no atomics on global memory, so the result is the
 // unique stable permutation:
 //   1. count    : each workgroup histograms its chunk of kPermuteChunk assignments (LDS counters)
@@ -163,36 +163,58 @@ __global__ __launch_bounds__(kThreads) void place_kernel(const int32_t* __restri
     }
 }
 
-// count + scan + place in one workgroup, for A <= kPermuteChunk (a decode step, a short prompt): two
-// launches fewer.  One thread per assignment (16 wavefronts), one pass: every wavefront ranks its 64
-// assignments per slot with ballots, wavefront 0 turns the 16 x S counts into the slots' offsets, and
-// each assignment's row is its slot's offset + the counts of the wavefronts before its own + its rank.
+// The assignments of this wavefront with the same key as this lane's: the lanes that hold them.  One ballot per bit of the
+// key, not one per slot.
+static_assert(kMaxExperts == 64, "six bits of key");
+__device__ __forceinline__ unsigned long long same_key(int key) {
+    unsigned long long m = __ballot(key >= 0);
+#pragma unroll
+    for (int b = 0; b < 6; ++b) {
+        const bool bit = (key >> b) & 1;
+        const unsigned long long set = __ballot(bit);
+        m &= bit ? set : ~set;
+    }
+    return m;
+}
+
+// count + scan + place in one workgroup of 16 wavefronts, for A <= PASSES * 1024 assignments (a decode step, a few prompts):
+// one launch instead of two.  Every wavefront ranks 64 consecutive assignments per pass, wavefront 0 turns the
+// counts [pass and wavefront][slot] into the first row of every such share, and each assignment's row is its share's first
+// row + its rank.
 constexpr int kSmallThreads = kPermuteChunk;
 constexpr int kSmallWaves = kSmallThreads / 64;
+template <int PASSES>
 __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const int32_t* __restrict__ topk_expert,
                                                                    const int32_t* __restrict__ slot_of_expert,
                                                                    int32_t* __restrict__ slot_counts,
                                                                    int32_t* __restrict__ slot_offsets,
                                                                    int32_t* __restrict__ perm,
                                                                    int32_t* __restrict__ inv_perm, int A, int E, int S) {
-    __shared__ int wave_cnt[kSmallWaves][kMaxExperts];  // [wavefront][slot]: count, then the first row of that wavefront's share
+    constexpr int SHARES = PASSES * kSmallWaves;
+    __shared__ int cnt[SHARES][kMaxExperts];  // [share][slot]: count, then the first row of that share
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int a = threadIdx.x;
-    const int key = key_of(topk_expert, slot_of_expert, a, A, E, S);
     const unsigned long long below = (1ull << lane) - 1ull;
-    int rank = 0, mine = 0;  // lane s ends up with this wavefront's count for slot s
-    for (int s = 0; s < S; ++s) {
-        const unsigned long long m = __ballot(key == s);
-        if (key == s) rank = __popcll(m & below);
-        if (lane == s) mine = __popcll(m);
-    }
-    wave_cnt[wave][lane] = mine;
-    __syncthreads();
-    if (wave == 0) {  // lane = slot: total, exclusive prefix over the slots, then the start of every wavefront's share
-        int c = 0;
+    int key[PASSES], rank[PASSES];
 #pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) c += wave_cnt[w][lane];
+    for (int p = 0; p < PASSES; ++p) {
+        key[p] = key_of(topk_expert, slot_of_expert, p * kSmallThreads + (int)threadIdx.x, A, E, S);
+        cnt[p * kSmallWaves + wave][lane] = 0;  // this wavefront's own row
+    }
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const unsigned long long m = same_key(key[p]);
+        rank[p] = __popcll(m & below);
+        if (key[p] >= 0 && rank[p] == 0) cnt[p * kSmallWaves + wave][key[p]] = __popcll(m);
+    }
+    __syncthreads();
+    if (wave == 0) {  // lane = slot: total, exclusive prefix over the slots, then the start of every share
+        int n[SHARES], c = 0;
+#pragma unroll
+        for (int w = 0; w < SHARES; ++w) {
+            n[w] = cnt[w][lane];
+            c += n[w];
+        }
         int incl = c;
 #pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
@@ -206,19 +228,22 @@ __global__ __launch_bounds__(kSmallThreads) void sort_small_kernel(const int32_t
         if (lane == S - 1) slot_offsets[S] = incl;
         int run = incl - c;
 #pragma unroll
-        for (int w = 0; w < kSmallWaves; ++w) {
-            const int n = wave_cnt[w][lane];
-            wave_cnt[w][lane] = run;
-            run += n;
+        for (int w = 0; w < SHARES; ++w) {
+            cnt[w][lane] = run;
+            run += n[w];
         }
     }
     __syncthreads();
-    if (key >= 0) {
-        const int r = wave_cnt[wave][key] + rank;
-        perm[r] = a;
-        inv_perm[a] = r;
-    } else if (a < A) {
-        inv_perm[a] = -1;
+#pragma unroll
+    for (int p = 0; p < PASSES; ++p) {
+        const int a = p * kSmallThreads + (int)threadIdx.x;
+        if (key[p] >= 0) {
+            const int r = cnt[p * kSmallWaves + wave][key[p]] + rank[p];
+            perm[r] = a;
+            inv_perm[a] = r;
+        } else if (a < A) {
+            inv_perm[a] = -1;
+        }
     }
 }
 
@@ -325,9 +350,11 @@ hipError_t launch_permute(const emoe_layer_desc& d, const void* x, const int32_t
     const int A = d.T * d.k;
     const int n_blocks = (A + kPermuteChunk - 1) / kPermuteChunk;
     int32_t* block_counts = reinterpret_cast<int32_t*>(static_cast<uint8_t*>(ws) + permute_ws_layout(d).block_counts);
-    if (n_blocks == 1) {
-        sort_small_kernel<<<1, kSmallThreads, 0, st>>>(topk_expert, slot_of_expert, counts, offsets, perm, inv_perm, A, d.E,
-                                                  d.S);
+    // One workgroup up to 4096 assignments: a launch less is more than it takes longer (one against two launches, 20 slots,
+    // 1071 assignments 4.9 / 9.3 us; 8 slots, 2048: 5.1 / 9.9; 16 slots, 4096: 7.3 / 9.9; with eight passes it would be level).
+    if (n_blocks <= 4) {
+        auto kern = n_blocks == 1 ? sort_small_kernel<1> : n_blocks == 2 ? sort_small_kernel<2> : sort_small_kernel<4>;
+        kern<<<1, kSmallThreads, 0, st>>>(topk_expert, slot_of_expert, counts, offsets, perm, inv_perm, A, d.E, d.S);
     } else if (n_blocks <= kScanPlaceBlocks) {
         count_kernel<<<n_blocks, kThreads, 0, st>>>(topk_expert, slot_of_expert, block_counts, A, d.E, d.S);
         scan_place_kernel<<<n_blocks, kSmallThreads, 0, st>>>(topk_expert, slot_of_expert, block_counts, n_blocks, counts,
