@@ -75,8 +75,12 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
     w.h = 0;
     w.partials = align256((A > 0 ? A : 1) * d.d_ff * elem_bytes(d));
     w.total = w.partials;
-    if (d.dtype == EMOE_BF16 && ffn_bf16_path(d) == kFfnTiled) w.total += kTiledPartialBytes;
-    if (d.dtype == EMOE_BF16 && ffn_bf16_path(d) == kFfnMid) w.total += kMidPartialBytes;
+    if (d.dtype != EMOE_BF16 || ffn_bf16_path(d) == kFfnStream) return w;
+    // Small layers of 100 to 170 rows per slot run on the 128-row tiles, whose pieces fit the larger workspace that a layer
+    // of so many rows is told to bring: the size does not follow that choice.
+    static_assert(kMidPartialBytes <= kTiledPartialBytes, "either kernel's pieces fit");
+    const bool larger = ffn_bf16_path(d) == kFfnTiled || ((long long)A > 100ll * d.S && (long long)A < 170ll * d.S);
+    w.total += larger ? kTiledPartialBytes : kMidPartialBytes;
     return w;
 }
 
