@@ -297,13 +297,14 @@ __device__ __forceinline__ int opaque(int v) {
 // of one block, and a store instruction then writes 64 contiguous bytes of each of 16 token rows.
 // TBLOCKS: the wavefront's 32-row token blocks that hold rows.
 // Every wavefront issues kEpilogueStores<EPI> stores, whatever the tile holds (rows and columns that do not exist are
-// addressed out of range, which writes nothing): the K loop counts on it, see there.
+// addressed out of range, which writes nothing): the K loop counts on it, see there.  "Out of range" is the first byte
+// past the output, c_bytes: all 16 bytes of such a store then lie past it (the host checks leave room for a row
+// between the largest output and 2^32), and nothing depends on what becomes of an address that wraps.
 template <int EPI>
 constexpr int kEpilogueStores = TS * (EPI == kSwiglu ? WB / 2 : WB) / 2;
-constexpr uint32_t kNoStore = 0xffffffffu;  // past the end of the output's buffer resource
 
 template <int EPI, int TBLOCKS>
-__device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], __amdgpu_buffer_rsrc_t c_rsrc, const int (&out_entry)[2],
+__device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], __amdgpu_buffer_rsrc_t c_rsrc, uint32_t c_bytes, const int (&out_entry)[2],
                                          bool scatter, int row0, int row_end, int n0, int N, int wm, int wn, int lane) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
@@ -339,7 +340,7 @@ __device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], __amdgpu_buffer
                 val = uintx4{lo[0], hi[0], lo[1], hi[1]};
             }
             const int n = col0 + np * 16;
-            const uint32_t off = row_ok && n < N ? row_off + (uint32_t)n * 2u : kNoStore;
+            const uint32_t off = row_ok && n < N ? row_off + (uint32_t)n * 2u : c_bytes;
             __builtin_amdgcn_raw_buffer_store_b128(val, c_rsrc, (int)off, 0, 0);
         }
         __builtin_amdgcn_sched_barrier(0);  // a few blocks at a time: the accumulators stay where they are until used
@@ -351,7 +352,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
                                                          const int32_t* __restrict__ offsets,
                                                          const bf16_t* __restrict__ b0,
                                                          const bf16_t* __restrict__ b1, bf16_t* __restrict__ c,
-                                                         float* __restrict__ partials, int S, int N, int K,
+                                                         float* __restrict__ partials, int c_rows, int S, int N, int K,
                                                          int n_tiles, int XCDS) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;  // output columns per tile
     extern __shared__ __align__(16) char lds[];
@@ -407,7 +408,8 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     const uint32_t a_bytes = (uint32_t)(gather.perm != nullptr ? gather.rows : rows_total) * (uint32_t)K * 2u;
     const uint32_t b_bytes = (uint32_t)N * (uint32_t)K * 2u;
     const __amdgpu_buffer_rsrc_t a_rsrc = make_rsrc(a, a_bytes);
-    const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(c, kNoStore);
+    const uint32_t c_bytes = (uint32_t)c_rows * (uint32_t)N * 2u;
+    const __amdgpu_buffer_rsrc_t c_rsrc = make_rsrc(c, c_bytes);
     const bf16_t* wsel = (EPI == kSwiglu && wave >= NW / 2) ? b1 : b0;  // upper wavefronts load the W3 half
     // that chunk depends on i only through its parity
     const int chunk2[2] = {l_pos ^ (l_row >> 1), l_pos ^ (4 + (l_row >> 1))};
@@ -653,7 +655,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
             mfma_settle();
 
             if (cur.piece < 0) {
-                epilogue<EPI, NB>(acc, c_rsrc, out_entry, EPI == kPlain && gather.out_perm != nullptr, cur.row0, cur.row_end, cur.nt * BNO, N, wm, wn, lane);
+                epilogue<EPI, NB>(acc, c_rsrc, c_bytes, out_entry, EPI == kPlain && gather.out_perm != nullptr, cur.row0, cur.row_end, cur.nt * BNO, N, wm, wn, lane);
             } else {  // a K piece of a leftover tile: raw accumulators to the workspace, [register][thread]
                 float* dst = partials + kPlanFloats + (size_t)cur.piece * (BM * BR) + tid;
     #pragma unroll
@@ -754,7 +756,7 @@ __global__ __launch_bounds__(64 * NW * kFixupUnitsPerGroup) void splitk_fixup(co
 
 template <int EPI, bool KTAIL>
 hipError_t launch_cfg(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
-                      float* partials, int S, int N, int K, int n_tiles, hipStream_t st) {
+                      float* partials, int c_rows, int S, int N, int K, int n_tiles, hipStream_t st) {
     auto kern = grouped_gemm_bf16<EPI, KTAIL>;
     static std::atomic<bool> attr_set{false};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set.load(std::memory_order_acquire)) {
@@ -767,7 +769,7 @@ hipError_t launch_cfg(const bf16_t* a, RowGather gather, const int32_t* offsets,
     hipError_t es = device_shape(&shape);
     if (es != hipSuccess) return es;
     // persistent: one workgroup per CU (the partial sums of the tiles cut along K are sized for kMaxGroups)
-    kern<<<shape.groups, 64 * NW, LDS_BYTES, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, shape.xcds);
+    kern<<<shape.groups, 64 * NW, LDS_BYTES, st>>>(a, gather, offsets, b0, b1, c, partials, c_rows, S, N, K, n_tiles, shape.xcds);
     splitk_fixup<EPI><<<kFixupGroups / kFixupUnitsPerGroup, 64 * NW * kFixupUnitsPerGroup, 0, st>>>(offsets, c, gather.out_perm, reinterpret_cast<const int*>(partials),
                                                         partials + kPlanFloats, S, N, K, n_tiles, shape.groups);
     return hipGetLastError();
@@ -775,11 +777,11 @@ hipError_t launch_cfg(const bf16_t* a, RowGather gather, const int32_t* offsets,
 
 template <int EPI>
 hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
-                      float* partials, int S, int N, int K, hipStream_t st) {
+                      float* partials, int c_rows, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     const int n_tiles = (N + BNO - 1) / BNO;
-    if (K % BK == 0 && K > BK) return launch_cfg<EPI, false>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, st);
-    return launch_cfg<EPI, true>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, st);
+    if (K % BK == 0 && K > BK) return launch_cfg<EPI, false>(a, gather, offsets, b0, b1, c, partials, c_rows, S, N, K, n_tiles, st);
+    return launch_cfg<EPI, true>(a, gather, offsets, b0, b1, c, partials, c_rows, S, N, K, n_tiles, st);
 }
 
 }  // namespace
@@ -792,17 +794,18 @@ hipError_t launch_ffn_bf16_tiled(const emoe_layer_desc& d, const void* x_perm, R
     bf16_t* h = reinterpret_cast<bf16_t*>(static_cast<uint8_t*>(ws) + lay.h);
     float* partials = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + lay.partials);
     const bf16_t* xp = static_cast<const bf16_t*>(x_perm);
+    const int A = d.T * d.k;  // rows of h and of y_perm; with the combine folded in (k = 1) of the layer's output
     hipError_t e = hipSuccess;
     if (!(passes & 1)) {
     } else if (d.act == EMOE_ACT_SWIGLU)
         e = launch_one<kSwiglu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), static_cast<const bf16_t*>(w3), h,
-                                partials, d.S, d.d_ff, d.d_model, st);
+                                partials, A, d.S, d.d_ff, d.d_model, st);
     else
-        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), nullptr, h, partials, d.S, d.d_ff, d.d_model,
+        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), nullptr, h, partials, A, d.S, d.d_ff, d.d_model,
                               st);
     if (e != hipSuccess || !(passes & 2)) return e;
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const bf16_t*>(w2), nullptr, static_cast<bf16_t*>(y_perm),
-                              partials, d.S, d.d_model, d.d_ff, st);
+                              partials, A, d.S, d.d_model, d.d_ff, st);
 }
 
 }  // namespace emoe
