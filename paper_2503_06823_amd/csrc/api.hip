@@ -69,21 +69,6 @@ PermuteWs permute_ws_layout(const emoe_layer_desc& d) {
     return w;
 }
 
-FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
-    FfnWs w;
-    const size_t A = (size_t)d.T * d.k;
-    w.h = 0;
-    w.partials = align256((A > 0 ? A : 1) * d.d_ff * elem_bytes(d));
-    w.total = w.partials;
-    if (d.dtype != EMOE_BF16 || ffn_bf16_path(d) == kFfnStream) return w;
-    // Small layers of 100 to 170 rows per slot run on the 128-row tiles, whose pieces fit the larger workspace that a layer
-    // of so many rows is told to bring: the size does not follow that choice.
-    static_assert(kMidPartialBytes <= kTiledPartialBytes, "either kernel's pieces fit");
-    const bool larger = ffn_bf16_path(d) == kFfnTiled || ((long long)A > 100ll * d.S && (long long)A < 170ll * d.S);
-    w.total += larger ? kTiledPartialBytes : kMidPartialBytes;
-    return w;
-}
-
 // Row counts live on the device, so the choice goes by the average number of rows per slot.
 // Few rows per slot: reading the weights dominates, use the streaming kernels.  They take 32 rows
 // of a slot per pass over its weights, so they win only while every slot fits one pass, and lose
@@ -95,24 +80,53 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
 // (Mixtral shape, 8 slots, whole FFN: 493 us against the large tiles' 538 us at 64 rows per slot,
 // 527 against 552 us at 96), but they lose once many slots need a second tile (128 rows per slot:
 // 723 against 563 us).
+namespace {
 constexpr long long kStreamRowsPerSlot = 22;
 constexpr long long kMidRowsPerSlot = 100;
-// A small layer (all slots' weights stream in some 20 us) is bound by how well its tiles fill the chip, not by the
-// weight stream, and up to about 300 rows per slot the 128-row tiles fill it better.  Measured with weights that come from
-// HBM (FFN, us, 256-row against 128-row tiles): d = 2048, f = 1408, 4 slots of 128 rows 62 / 37, of 256 72 / 47; d = 768,
-// f = 3072, 4 slots of 160 57 / 44, 8 slots (113 MB) of 128 58 / 61, of 200 65 / 61; d = 1536, 8 slots of 160 72 / 52;
-// d = 4104, f = 2056, 2 slots (101 MB) of 128 76 / 89, of 200 85 / 80.  Of larger layers more lose than win: d = 1032,
-// f = 2808, 8 slots (139 MB) of 200 82 / 104; d = 2048, f = 1408, 12 slots (208 MB) of 200 96 / 101; d = 4104, 4 slots of
-// 200 111 / 150; Mixtral shape, 8 slots of 232-278 rows 799 / 998.
-constexpr long long kSmallLayerWeightBytes = 112ll << 20;
-constexpr long long kSmallLayerMidTo = 300;  // rows per slot
+// A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
+// fill the chip, not by the weight stream, and around 256 rows per slot the 128-row tiles fill it
+// better: half the slots then need a second 256-row tile for a few rows.  Measured with weights that come from HBM
+// (FFN, us, 256-row against 128-row tiles): d = 2048, f = 1408, 8 slots (132 MiB) of 200 rows 87 / 65, of 256 90 / 73;
+// d = 768, f = 3072, ReLU, 16 slots (144 MiB) of 200 97 / 72; d = 2048, f = 8192, 2 slots (192 MiB) of 200 100 / 81.  It
+// is not better everywhere: the larger the layer, the more it hangs on how the rows fall (above 112 MiB the 128-row
+// tiles take between 0.74 and 1.43 of the other's time, 1.04 in the mean; d = 4104, f = 2056, 4 slots (193 MiB) of 200 113 / 150,
+// d = 1040, f = 1048, 32 slots (200 MiB) of 200 111 / 136), which the host does not know; and the workspace of these
+// layers holds the 128-row tiles' pieces only.
+constexpr long long kSmallLayerWeightBytes = 320ll << 20;
+constexpr long long kSmallLayerMidFrom = 170, kSmallLayerMidTo = 300;  // rows per slot
+long long weight_bytes(const emoe_layer_desc& d) {
+    return (long long)d.S * (d.act == EMOE_ACT_SWIGLU ? 3 : 2) * d.d_model * d.d_ff * 2;
+}
+bool back_on_mid(const emoe_layer_desc& d) {
+    const long long A = (long long)d.T * d.k;
+    return weight_bytes(d) <= kSmallLayerWeightBytes && A >= kSmallLayerMidFrom * d.S && A <= kSmallLayerMidTo * d.S;
+}
+// Below that a layer of weights that stream in some 20 us stays on the 128-row tiles too (same measurement: d = 2048,
+// f = 1408, 4 slots of 128 rows 62 / 37; d = 768, f = 3072, 4 slots of 160 57 / 44; d = 1536, 8 slots of 160 72 / 52).
+constexpr long long kTinyLayerWeightBytes = 112ll << 20;
+}  // namespace
+
 FfnPath ffn_bf16_path(const emoe_layer_desc& d) {
     const long long A = (long long)d.T * d.k;
     if (A <= kStreamRowsPerSlot * d.S) return kFfnStream;
-    if (A <= kMidRowsPerSlot * d.S) return kFfnMid;
-    const long long weight_bytes = (long long)d.S * (d.act == EMOE_ACT_SWIGLU ? 3 : 2) * d.d_model * d.d_ff * 2;
-    if (weight_bytes <= kSmallLayerWeightBytes && A <= kSmallLayerMidTo * d.S) return kFfnMid;
+    if (A <= kMidRowsPerSlot * d.S || back_on_mid(d)) return kFfnMid;
+    if (A < kSmallLayerMidFrom * d.S && weight_bytes(d) <= kTinyLayerWeightBytes) return kFfnMid;
     return kFfnTiled;
+}
+
+// The size goes by the rows per slot and the weights, not by the kernel that ffn_bf16_path() picks among those that fit
+// it: callers keep it.
+FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
+    FfnWs w;
+    const size_t A = (size_t)d.T * d.k;
+    w.h = 0;
+    w.partials = align256((A > 0 ? A : 1) * d.d_ff * elem_bytes(d));
+    w.total = w.partials;
+    if (d.dtype != EMOE_BF16 || (long long)A <= kStreamRowsPerSlot * d.S) return w;
+    static_assert(kMidPartialBytes <= kTiledPartialBytes, "either kernel's pieces fit");
+    const bool mid_only = (long long)A <= kMidRowsPerSlot * d.S || back_on_mid(d);
+    w.total += mid_only ? kMidPartialBytes : kTiledPartialBytes;
+    return w;
 }
 
 }  // namespace emoe
