@@ -101,16 +101,35 @@ bool back_on_mid(const emoe_layer_desc& d) {
     const long long A = (long long)d.T * d.k;
     return weight_bytes(d) <= kSmallLayerWeightBytes && A >= kSmallLayerMidFrom * d.S && A <= kSmallLayerMidTo * d.S;
 }
-// Below that a layer of weights that stream in some 20 us stays on the 128-row tiles too (same measurement: d = 2048,
-// f = 1408, 4 slots of 128 rows 62 / 37; d = 768, f = 3072, 4 slots of 160 57 / 44; d = 1536, 8 slots of 160 72 / 52).
+// Below that a layer of weights that stream in some 20 us stays on the 128-row tiles too, if a CU has few K tiles of 64
+// to walk on them, and that in both products alike.  Measured at 907 such layers of 100 to 169 rows per slot (d_model and
+// d_ff 200 to 8200, whole lines and not, SwiGLU and ReLU, weights from HBM): 726 are given to the 128-row tiles, which take
+// 0.39 to 1.16 of the 256-row tiles' time there, 12 of them above 1.07; over all 907 the mean is 0.81.  (us, 256-row against
+// 128-row: d = 2048, f = 1408, 4 slots of 128 rows 62 / 37; d = 768, f = 3072, 4 slots of 160 57 / 44; d = 1040, f = 1048,
+// ReLU, 16 slots of 128 69 / 44.)  Beyond 32 K tiles per CU the larger tiles have fewer rounds.  A layer that is long and
+// narrow has one product of few tiles with a long K, which the 256-row kernel cuts in more pieces (d = 520, f = 4104, ReLU,
+// 12 slots of 128 66 / 102; d = 640, f = 5120, ReLU, 8 slots of 140 64 / 76).  Where rows are not whole lines a long K walk
+// of the 128-row tiles takes about twice as long and is counted twice (d = 2056, f = 4104, 2 slots of 166 79 / 103).
 constexpr long long kTinyLayerWeightBytes = 112ll << 20;
+constexpr long long kTinyLayerWalk = 32 * 256;      // K tiles of 64 of all 128-row tiles: per CU, of 256
+constexpr long long kTinyLayerNarrow = 140 * 256;   // the same times the ratio of d_model and d_ff
+constexpr int kLongK = 4096;
+bool tiny_on_mid(const emoe_layer_desc& d) {
+    const long long A = (long long)d.T * d.k;
+    if (A >= kSmallLayerMidFrom * d.S || weight_bytes(d) > kTinyLayerWeightBytes) return false;
+    auto k_tiles = [](long long K) { return (K + 63) / 64 * (K % 64 != 0 && K >= kLongK ? 2 : 1); };
+    const long long columns = d.act == EMOE_ACT_SWIGLU ? 128 : 256;  // of a tile's output, first product
+    const long long walk = (A / 128 + d.S) * ((d.d_ff + columns - 1) / columns * k_tiles(d.d_model) +
+                                              (d.d_model + 255) / 256 * k_tiles(d.d_ff));
+    const long long wide = d.d_model < d.d_ff ? d.d_ff : d.d_model, narrow = d.d_model < d.d_ff ? d.d_model : d.d_ff;
+    return walk <= kTinyLayerWalk && walk * wide <= kTinyLayerNarrow * narrow;
+}
 }  // namespace
 
 FfnPath ffn_bf16_path(const emoe_layer_desc& d) {
     const long long A = (long long)d.T * d.k;
     if (A <= kStreamRowsPerSlot * d.S) return kFfnStream;
-    if (A <= kMidRowsPerSlot * d.S || back_on_mid(d)) return kFfnMid;
-    if (A < kSmallLayerMidFrom * d.S && weight_bytes(d) <= kTinyLayerWeightBytes) return kFfnMid;
+    if (A <= kMidRowsPerSlot * d.S || back_on_mid(d) || tiny_on_mid(d)) return kFfnMid;
     return kFfnTiled;
 }
 

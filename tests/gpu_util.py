@@ -2,6 +2,8 @@
 C-ABI binding, bring results back as numpy, and compare with the oracle."""
 from __future__ import annotations
 
+import ctypes
+
 import numpy as np
 import torch
 
@@ -41,6 +43,15 @@ def raw_bits(t: torch.Tensor) -> np.ndarray:
 
 def desc_of(cfg: gen.LayerConfig):
     return P.make_desc(cfg.T, cfg.d_model, cfg.d_ff, cfg.E, cfg.k, cfg.slots, cfg.dtype, cfg.act)
+
+
+STREAM, MID, TILED = 0, 1, 2
+
+
+def ffn_path(desc) -> int:
+    """Which kernels a bf16 FFN takes (decided on the host): STREAM, MID (tiles of 128 token rows or fewer) or TILED
+    (256).  An internal symbol of the library: no result tells."""
+    return getattr(P.lib(), "_ZN4emoe13ffn_bf16_pathERK15emoe_layer_desc")(ctypes.byref(desc))
 
 
 class DeviceLayer:

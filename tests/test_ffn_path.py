@@ -1,0 +1,42 @@
+"""Which kernels the bf16 FFN of a layer takes, at layers where the times of the two tile sizes were measured to be apart
+and on both sides of the rows per slot at which the choice may change."""
+import pytest
+
+import paper_2503_06823_amd as P
+from gpu_util import MID, STREAM, TILED, ffn_path
+
+
+@pytest.mark.parametrize("rows,small,large", [(1, STREAM, STREAM), (22, STREAM, STREAM), (23, MID, MID), (100, MID, MID),
+                                              (101, MID, TILED), (169, MID, TILED), (170, MID, TILED), (300, MID, TILED),
+                                              (301, TILED, TILED), (4000, TILED, TILED)])
+def test_rows_per_slot(rows, small, large):
+    for S in (1, 4, 8):
+        assert ffn_path(P.make_desc(rows * S, 256, 512, S, 1, S, "bf16", "swiglu")) == small
+        assert ffn_path(P.make_desc(rows * S, 4096, 14336, S, 1, S, "bf16", "swiglu")) == large
+    assert ffn_path(P.make_desc(rows * 4, 256, 512, 8, 2, 8, "bf16", "relu")) == small  # A = T * k
+
+
+# d_model, d_ff, slots, rows per slot, activation: where tiles of 128 (MID) or of 256 rows were the faster ones, by 10 % or more
+FASTER = [
+    # 100 to 169 rows per slot
+    (2048, 1408, 4, 128, "swiglu", MID), (768, 3072, 4, 160, "swiglu", MID), (1536, 1536, 8, 160, "swiglu", MID),
+    (1040, 1048, 8, 160, "swiglu", MID), (1032, 2808, 4, 128, "relu", MID), (1024, 2816, 8, 160, "relu", MID),
+    (2048, 1408, 8, 160, "relu", MID), (512, 1408, 32, 128, "relu", MID), (4104, 2056, 1, 160, "swiglu", MID),
+    (1536, 1536, 12, 128, "relu", MID), (6144, 2048, 2, 128, "relu", MID), (2048, 8192, 1, 160, "swiglu", MID),
+    (520, 4104, 12, 128, "relu", TILED), (520, 4104, 8, 160, "relu", TILED), (520, 4104, 8, 160, "swiglu", TILED),
+    (4104, 2056, 2, 128, "swiglu", TILED), (2056, 4104, 2, 140, "swiglu", TILED), (2056, 4104, 2, 166, "swiglu", TILED),
+    (520, 6152, 8, 140, "relu", TILED), (6152, 520, 8, 140, "relu", TILED), (512, 4096, 8, 118, "swiglu", TILED),
+    (640, 5120, 4, 140, "swiglu", TILED), (640, 5120, 8, 140, "relu", TILED), (520, 6152, 4, 140, "swiglu", TILED),
+    (4096, 4096, 2, 128, "relu", TILED), (4104, 2056, 4, 128, "relu", TILED),
+    # 170 to 300
+    (2048, 1408, 8, 200, "swiglu", MID), (2048, 1408, 8, 256, "swiglu", MID), (768, 3072, 16, 200, "relu", MID),
+    (2048, 8192, 2, 200, "relu", MID), (1536, 1536, 16, 256, "relu", MID), (6144, 2048, 2, 200, "swiglu", MID),
+    (1024, 2816, 8, 200, "swiglu", MID), (512, 1408, 32, 200, "swiglu", MID), (1536, 4096, 8, 200, "relu", MID),
+    # weights above the limits
+    (4096, 14336, 8, 256, "swiglu", TILED), (4096, 14336, 4, 128, "swiglu", TILED), (4104, 4096, 4, 128, "swiglu", TILED),
+]
+
+
+@pytest.mark.parametrize("d,f,S,rows,act,path", FASTER)
+def test_faster_tiles_are_chosen(d, f, S, rows, act, path):
+    assert ffn_path(P.make_desc(rows * S, d, f, S, 1, S, "bf16", act)) == path
