@@ -43,12 +43,16 @@ constexpr int CPR = ROW_BYTES / 16;         // 16-byte chunks per tile row
 constexpr int RPI = 1024 / ROW_BYTES;       // tile rows filled by one load instruction
 constexpr int SPW = BK / 16 / 4;            // MFMA steps per wavefront and tile
 constexpr int LX = X_BYTES / 1024 / 4;      // token load instructions per wavefront and tile
-// Cache policy of the weight loads: every weight byte is read once per launch (non-temporal: bit 1 of the aux operand).
-// Where rows are not whole 128-byte lines, two K tiles share the lines between them, and the second would fetch them from
-// HBM again: no hint (d 1032, f 2808, 16 slots of 48 rows: 86 + 53 -> 67 + 45 us; with whole lines the hint stays the
-// better one, d 1088, f 2880, slots of 4 rows: 34 + 22 us, without 38 + 23).
+// Cache policy of the weight loads: a slot of up to 32 rows reads its weights once, so they carry the non-temporal hint
+// (bit 1 of the aux operand).  Where rows are not whole 128-byte lines, two K tiles share the lines between them, and
+// with the hint the second fetches them from HBM again: no hint.  Measured at 1 to 20 rows per slot, weights from HBM (time
+// without over time with the hint): second product 0.96 in the mean of 392 layers, 0.69 to 1.10; first product 0.97
+// from 128 MiB of weights on (208 layers, 0.77 to 1.06), but 1.00 below (184 layers, 0.87 to 1.16), where it keeps the
+// hint.  (d 1032, f 2808, 64 slots of 8 rows: 95 % of the layer's time; d 4104, f 2056, 16 slots: 93 %.)  With whole lines
+// and a K tail the hint stays the better one (d 1088, f 2880, slots of 4 rows: 34 + 22 us, without 38 + 23).
 constexpr int kStreamOnce = 2;
-enum Tail { kNoTail = 0, kTailWholeLines = 1, kTailSplitLines = 2 };  // K a multiple of the tile; of a line; neither
+enum Tail { kNoTail = 0, kTailOnce = 1, kTailCached = 2 };  // K a multiple of the tile; not, weights with and without the hint
+constexpr long long kCachedFrom = 128ll << 20;              // bytes of weights of a first product
 constexpr unsigned kRotation = 21;           // K-tile rotation per workgroup (measured best of 1..29)
 constexpr int RED_BYTES = 3 * 32 * 64 * 4;  // partial sums of wavefronts 1..3
 static_assert(RED_BYTES <= kMinStages * (32 * ROW_BYTES + X_BYTES), "the reduction reuses the tile stages");
@@ -147,7 +151,7 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
                 uint32_t v = w_voff[i];
                 if (KTAIL && k0 + w_chunk[i] * 8 >= K) v = b_bytes;  // out of range: zeros
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(b_rsrc, (lds_void*)(base + (LW * wave + i) * 1024), 16, (int)v,
-                                                         k0 * 2, 0, TAIL == kTailSplitLines ? 0 : kStreamOnce);
+                                                         k0 * 2, 0, TAIL == kTailCached ? 0 : kStreamOnce);
             }
 #pragma unroll
             for (int i = 0; i < LX; ++i) {
@@ -243,12 +247,13 @@ hipError_t launch_wr(const bf16_t* a, RowGather gather, const int32_t* offsets, 
     constexpr int BNO = EPI == kSwiglu ? WR / 2 : WR;
     const int n_units = (N + BNO - 1) / BNO;
     const unsigned blocks = (unsigned)(S * n_units);
+    const long long weight_bytes = (long long)S * N * K * (EPI == kSwiglu ? 4 : 2);
     if (K % BK == 0)
         stream_gemm_bf16<EPI, WR, kNoTail><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
-    else if (K % 64 == 0)
-        stream_gemm_bf16<EPI, WR, kTailWholeLines><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
+    else if (K % 64 == 0 || (EPI != kPlain && weight_bytes < kCachedFrom))
+        stream_gemm_bf16<EPI, WR, kTailOnce><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
     else
-        stream_gemm_bf16<EPI, WR, kTailSplitLines><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
+        stream_gemm_bf16<EPI, WR, kTailCached><<<blocks, 256, 0, st>>>(a, gather, offsets, b0, b1, c, S, N, K, n_units);
     return hipGetLastError();
 }
 
