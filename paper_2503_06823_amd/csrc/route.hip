@@ -45,13 +45,12 @@ template <> struct Vec<float> {
 
 // Adds this lane's products of PIECES pieces of the token row (x, x + step) with the gate rows to acc.
 // Rows past the last expert repeat that expert's row (their sums are never looked at): without a branch around them
-// the loads of all rows are independent.  All loads - 16 experts at a time - go out before any is used: left to itself
+// the loads of all rows are independent.  The loads of GROUP experts go out before any is used: left to itself
 // the compiler waits for one expert's pieces after the other, a memory round trip each (gate in HBM, d_model 4096:
 // 8 experts 11 -> 6 us, 16 experts 22 -> 10 us).
-template <typename T, int EP, int PIECES>
+template <typename T, int EP, int PIECES, int GROUP>
 __device__ __forceinline__ void add_pieces(const T* __restrict__ x, const T* __restrict__ w, int step, int d, int E, float (&acc)[EP]) {
     typedef typename Vec<T>::Raw Raw;
-    constexpr int GROUP = EP < 16 ? EP : 16;
     Raw x_raw[PIECES];
 #pragma unroll
     for (int h = 0; h < PIECES; ++h) x_raw[h] = *reinterpret_cast<const Raw*>(x + h * step);
@@ -83,8 +82,9 @@ __device__ __forceinline__ void add_pieces(const T* __restrict__ x, const T* __r
 // SPLIT = wavefronts that share one token (1 or 4).  With few tokens (a decode step) one wavefront
 // per token would leave most of the chip idle and make each wavefront walk the whole row alone, so
 // four wavefronts split the row and add their partial logits through LDS in wavefront order.
-template <typename T, int EP, int SPLIT>
-__global__ __launch_bounds__(256) void route_kernel(const T* __restrict__ x, const T* __restrict__ w_gate,
+// GROUP, PER_CU: experts whose loads go out together, and workgroups that have to fit a CU side by side.
+template <typename T, int EP, int SPLIT, int GROUP, int PER_CU>
+__global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict__ x, const T* __restrict__ w_gate,
                                                     const float* __restrict__ bias,
                                                     const int32_t* __restrict__ slot_of_expert,
                                                     int32_t* __restrict__ topk_expert,
@@ -112,8 +112,8 @@ __global__ __launch_bounds__(256) void route_kernel(const T* __restrict__ x, con
             const T* xr = x + (size_t)t * d;
             int c = (part * 64 + lane) * VN;
             const int step = SPLIT * 64 * VN;
-            for (; c + step < d; c += 2 * step) add_pieces<T, EP, 2>(xr + c, w_gate + c, step, d, E, acc);
-            if (c < d) add_pieces<T, EP, 1>(xr + c, w_gate + c, step, d, E, acc);
+            for (; c + step < d; c += 2 * step) add_pieces<T, EP, 2, GROUP>(xr + c, w_gate + c, step, d, E, acc);
+            if (c < d) add_pieces<T, EP, 1, GROUP>(xr + c, w_gate + c, step, d, E, acc);
         }
         // butterfly reduce-scatter over the lanes
         int n = EP;
@@ -211,12 +211,21 @@ hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate
     const T* wg = static_cast<const T*>(w_gate);
     if (d.T <= 2048) {  // fewer than two wavefronts per SIMD otherwise: share each token among four
         int blocks = d.T < 256 * 16 ? d.T : 256 * 16;
-        route_kernel<T, EP, 4><<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
+        // All experts (16) at a time takes up to 220 registers, which leaves a CU two workgroups.  With more tokens than
+        // CUs fp32 rows take four at a time in 128 registers (9 to 16 experts, d_model 2048, 513 to 1023 tokens: 10.6 to 12.8 us
+        // against 13.6 to 16.3; d_model 4096, 512 tokens 10.8 against 11.3; 8 experts, d_model 6144, 600 tokens 9.0 against
+        // 9.4), and so do 32 experts, whose sums alone are many (64 tokens, d_model 6144: 23.5 us, 16 at a time 26.1; 300
+        // tokens: 30, against 35).
+        constexpr int kAll = EP < 16 ? EP : 16;
+        auto kern = route_kernel<T, EP, 4, EP == 32 ? 4 : kAll, EP == 32 ? 2 : 1>;
+        if constexpr ((EP == 8 || EP == 16) && std::is_same<T, float>::value)
+            if (d.T > 256) kern = route_kernel<T, EP, 4, 4, 4>;
+        kern<<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
                                                        expert_tokens, d.T, d.d_model, d.E, d.k);
     } else {
         int blocks = (d.T + 3) / 4;
         if (blocks > 256 * 16) blocks = 256 * 16;
-        route_kernel<T, EP, 1><<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
+        route_kernel<T, EP, 1, EP < 16 ? EP : 16, 1><<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
                                                        expert_tokens, d.T, d.d_model, d.E, d.k);
     }
     return hipGetLastError();
@@ -229,8 +238,10 @@ hipError_t launch_t(const emoe_layer_desc& d, const void* x, const void* w_gate,
     if (d.E <= 2) return launch_ep<T, 2>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 4) return launch_ep<T, 4>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 8) return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
-    if constexpr (std::is_same<T, float>::value)
+    if constexpr (std::is_same<T, float>::value) {
+        if (d.E > 16 && d.E <= 32 && d.T <= 2048) return launch_ep<T, 32>(d, x, w_gate, bias, soe, te, tw, et, st);
         if (d.E > 16) return launch_ep<T, 64>(d, x, w_gate, bias, soe, te, tw, et, st);
+    }
     return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
 }
 
@@ -241,12 +252,17 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
                         unsigned long long* expert_tokens, hipStream_t st) {
     if (d.dtype == EMOE_F32) {
         // The matrix kernel reads the gate matrix once per 16 tokens, the wavefront kernel once per token, which is
-        // the better one with few experts or so few tokens that each has a CU to itself.  Wavefront / matrix, us:
-        // 1024 tokens, d 768: 8 experts level, 16: 12 / 8, 64: 46 / 13; 8192 tokens, d 768, 8 experts 12 / 8, d 2048, 4
-        // experts 13 / 15; 512 tokens, d 2048: 16 experts 9.6 / 10.5, 64: 38 / 25; 1 to 256 tokens, d 2048: 40 experts
-        // 20 / 16, 64: 21 to 23 / 23 to 26.  (A launch of 2^26 tokens would not fit a grid.)
-        const bool matrix = d.E > 16 ? !(d.T <= 256 && d.E > 48 && d.d_model >= 1536)
-                                     : d.E > 8 ? d.T >= 1024 : d.E > 4 && d.T >= 4096;
+        // the better one with few experts, or with so few tokens that each has a CU to itself and rows so long that
+        // splitting them over more wavefronts counts.  Wavefront / matrix, us: 1024 tokens, d 768: 8 experts level, 16: 12 /
+        // 8, 64: 46 / 13; 8192 tokens, d 768, 8 experts 12 / 8, d 2048, 4 experts 13 / 15; 512 tokens, d 2048, 64 experts
+        // 38 / 25.  64 tokens: 64 experts, d 768 14 / 12, d 1536 16.6 / 18.6; 48 experts, d 1536 16 / 15, d 2048 17 / 18.7,
+        // d 6144 25 / 46; 32 experts, d 3072 21 / 20, d 4096 21.6 / 24.7, d 6144 23.5 / 35.  300 tokens: 48 experts,
+        // d 8192 54 / 60 but d 4096 37 / 32.5; 32 experts, d 4096 25.7 / 24.8, d 6144 29.7 / 35.
+        // (A launch of 2^26 tokens would not fit a grid.)
+        const int blocks = (d.E + 15) / 16;
+        bool matrix = d.E > 8 ? d.T >= 1024 : d.E > 4 && d.T >= 4096;
+        if (blocks == 2) matrix = !(d.T <= 512 && d.d_model >= (d.T <= 256 ? 4096 : 5120));
+        if (blocks > 2) matrix = !(d.T <= 256 && (long long)d.d_model * blocks >= 6144);
         if (matrix && d.T < (1 << 26))
             return launch_route_f32(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
         return launch_t<float>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
