@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         // A tile's loads go out in four parts (part 0 .. 3, or ALL of them at once): see the main loop.
         constexpr int ALL = 4;
         auto issue_part = [&](int st, int tk, int part, auto once_tag) {
-            constexpr int kWeightAux = decltype(once_tag)::value && !KTAIL ? 2 : 0;  // (see below)
+            constexpr int kWeightAux = decltype(once_tag)::value ? 2 : 0;
             int kk = tk + k_rot;
             kk = kk >= cnt ? kk - cnt : kk;
             int k0 = k_first + kk * BK;
@@ -393,8 +393,9 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         // The weight panel of a slot of one m-tile is read by nobody else: non-temporal hint, so that the stream
         // does not push the token rows out of the caches (-5 to -12 % per product at 22-110 rows per slot).  Not where rows
         // are not whole 128-byte lines: two K tiles then share the lines between them, and the second would fetch
-        // them from HBM again (d 1032, f 2808, 16 slots of 48 rows: 68 + 39 us with the hint, 57 + 37 without).
-        const bool once = slot_mtiles == 1;
+        // them from HBM again (d 1032, f 2808, 16 slots of 48 rows: 68 + 39 us with the hint, 57 + 37 without; 0.92 of the
+        // time in the mean of 83 layers of 30 to 96 rows per slot).
+        const bool once = !KTAIL && slot_mtiles == 1;
         const bool idle = row0 + wm * 64 >= row_end;  // never with one row of wavefronts
         if (once) {
             if (BM == 128 && idle) k_loop(std::true_type{}, std::true_type{});

@@ -477,7 +477,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         uint32_t v = voff[i];
         if (KTAIL && (uint32_t)(k + chunk2[i & 1] * 16) >= k_bytes) v = b_bytes;
         lds_void* dst = (lds_void*)(lds + rs + (LPW * wave + i) * 1024);
-        if (once && !KTAIL) __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 2);  // non-temporal hint
+        if (once) __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 2);  // non-temporal hint
         else __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 0);
     };
     auto ring = [](int rs, int n) {  // the ring slot n places after the one at byte rs
@@ -680,9 +680,9 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         const int my_blocks = cur.slot_tiles > kSkipBlocksUpToTiles ? TB : blocks_of_wavefront(cur.row0, cur.row_end, wm);
         static_assert(TB == 4, "written out for four token blocks per wavefront");
         // A slot of one m-tile: nobody else reads its weight panel, which is then loaded with the
-        // non-temporal hint, so that the stream does not push the token rows out of the caches (but where rows
-        // are not whole lines: a line between two K tiles would come from HBM twice).
-        if (cur.slot_tiles == 1) {
+        // non-temporal hint, so that the stream does not push the token rows out of the caches (but not with a K tail: rows are
+        // not whole lines then, and a line between two K tiles would come from HBM twice).
+        if (!KTAIL && cur.slot_tiles == 1) {
             if (my_blocks >= 4) do_item(std::integral_constant<int, 4>{}, std::true_type{});
             else if (my_blocks == 3) do_item(std::integral_constant<int, 3>{}, std::true_type{});
             else if (my_blocks == 2) do_item(std::integral_constant<int, 2>{}, std::true_type{});
