@@ -98,14 +98,13 @@ def test_workspace_sizes_scale_with_the_layer():
 
 
 def test_ffn_workspace_holds_the_partial_sums_of_the_tile_paths():
-    """The bf16 FFN takes one of three paths by the average rows per slot (A / S): up to 22 the
-    streaming kernels (h only), up to 100 the 128-row tiles (h + 32 MiB of K pieces), above that
-    the 256-row tiles (h + a 256-byte plan + 64 MiB); fp32 needs h only.  A layer whose weights are
-    small is an exception to the last step."""
+    """What a bf16 layer is told to bring by the average rows per slot (A / S): up to 22 h only (weight
+    streaming), up to 100 h + 32 MiB of K pieces (128-row tiles), above that h + a 256-byte plan + 64 MiB
+    (256-row tiles; small layers may take the 128-row tiles and use less of it); fp32 needs h only.  A layer
+    of up to 320 MiB of weights takes the 128-row tiles, with their size, from 170 to 300 rows per slot."""
     def h_bytes(T, k, f, elem):
         return (T * k * f * elem + 255) // 256 * 256
     S, k, f = 4, 2, 256
-    # a small layer takes the 128-row tiles again from 170 to 300 rows per slot
     for T, extra in ((44, 0), (45, 32 << 20), (200, 32 << 20), (201, 256 + (64 << 20)), (339, 256 + (64 << 20)),
                      (340, 32 << 20), (600, 32 << 20), (601, 256 + (64 << 20)), (4096, 256 + (64 << 20))):
         assert P.emoe_workspace_bytes(good(T=T, S=S, k=k, d_ff=f))[1] == h_bytes(T, k, f, 2) + extra, T

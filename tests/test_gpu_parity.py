@@ -218,7 +218,7 @@ def test_random_small_layers(gpu_device, c):
 def _random_long_k_cases(n, seed):
     """Seeded random layers with one long and one short product (K >= 64 tiles of 64 in one of them)
     and 29-200 rows per slot: the persistent launch of the 128-row tiles, which cuts tiles along K
-    when they are few, takes whole tiles otherwise, and the 256-row tiles' K pieces beyond that."""
+    when they are few and takes whole tiles otherwise."""
     rng = np.random.default_rng(seed)
     cases = []
     for i in range(n):
@@ -251,7 +251,7 @@ def test_random_layers_with_a_long_k(gpu_device, c):
 # one expert per token on every FFN path: fp32, streaming, tiles of 64 / 128 / 256 token rows, whole and cut along K
 TOP1_CASES = [c for c in SMALL_CASES if c.k == 1] + [
     cfg("tiled_top1_splitk", T=1600, d_model=1032, d_ff=1160, E=8, k=1, R=4, index=80),
-    cfg("tiled_top1_swiglu_ragged", T=900, d_model=328, d_ff=456, E=8, k=1, R=3, S=4, index=81),
+    cfg("tiled_top1_swiglu_ragged", T=1300, d_model=328, d_ff=456, E=8, k=1, R=3, S=4, index=81),
     cfg("mid_top1_swiglu", T=200, d_model=256, d_ff=384, E=8, k=1, R=4, index=82),
 ]
 

@@ -7,7 +7,8 @@ import torch
 
 import emoe_inputs as gen
 import oracle
-from gpu_util import DeviceLayer, check_ffn_rows, check_outputs, check_routing_and_permutation
+from gpu_util import (MID, STREAM, TILED, DeviceLayer, check_ffn_rows, check_outputs, check_routing_and_permutation, desc_of,
+                      ffn_path)
 
 pytestmark = pytest.mark.gpu
 
@@ -33,12 +34,17 @@ CASES = [
     cfg("stream_split_lines", 352, T=60, d_model=200, d_ff=392, E=4, k=1, R=4, zipf_s=1.1),
     cfg("stream_whole_lines_tail", 353, T=40, d_model=192, d_ff=320, E=4, k=2, R=4),
     cfg("mid_split_lines", 354, T=1200, d_model=520, d_ff=2056, E=16, k=1, R=16),
-    cfg("tiled_split_lines", 355, T=1800, d_model=1032, d_ff=2056, E=8, k=1, R=8),
+    cfg("tiled_split_lines", 355, T=2600, d_model=1032, d_ff=2056, E=8, k=1, R=8),
 ]
+
+PATHS = {"k_8": MID, "k_64_128": MID, "k_192_200": MID, "k_256_264": MID, "k_320_384": MID, "small_101_rows": MID,
+         "small_300_rows": MID, "small_301_rows": TILED, "stream_split_lines": STREAM, "stream_whole_lines_tail": STREAM,
+         "mid_split_lines": MID, "tiled_split_lines": TILED}
 
 
 @pytest.mark.parametrize("c", CASES, ids=lambda c: c.name)
 def test_layer_matches_oracle(gpu_device, c):
+    assert ffn_path(desc_of(c)) == PATHS[c.name]
     inp = gen.make_layer_inputs(c, shuffle_slots=c.slots > 1)
     ref = oracle.layer_forward(inp)
     dl = DeviceLayer(inp)
