@@ -412,10 +412,10 @@ int emoe_generation_tick(emoe_request *request, int32_t completed, double reset_
  * emoe_measure_mfma_loop: `workgroups` workgroups of four wavefronts each copy a 256 x 64 tile
  * of a and of b (dev, bf16, a_elems / b_elems elements, at least 16384 each; pass the workload's
  * own token rows and weights so that the operand values are the GEMM's) into LDS once and then
- * issue `iters` rounds of 4 x 16 matrix instructions (v_mfma_f32_32x32x16_bf16, 4 x 4 blocks per
+ * issue `iters` rounds of 2 x 64 matrix instructions (v_mfma_f32_16x16x32_bf16, 8 x 8 blocks per
  * wavefront as in the tiled FFN kernel) with no global memory traffic; lds_reads != 0 adds the
- * GEMM's LDS fragment reads (8 per 16 matrix instructions).  sink: dev, workgroups * 256 floats
- * (out, meaningless sums).  *flop (host, may be NULL) = workgroups * 4 * iters * 64 * 32768.
+ * GEMM's LDS fragment reads (16 per 64 matrix instructions).  sink: dev, workgroups * 256 floats
+ * (out, meaningless sums).  *flop (host, may be NULL) = workgroups * 4 * iters * 128 * 16384.
  *
  * emoe_measure_read_stream: grid-stride read of src (dev, `bytes` a multiple of 32768) with
  * 16-byte loads, eight in flight per lane, nothing written.  sink: dev, 16 bytes.

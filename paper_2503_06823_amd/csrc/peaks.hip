@@ -5,22 +5,21 @@
 //   matrix loop : every workgroup copies a 256 x 64 tile of each of two caller-supplied bf16 operand
 //                 buffers (the workload's own token rows and weights, so the matrix cores switch the
 //                 same bit patterns as in the GEMM) into LDS once and then issues
-//                 v_mfma_f32_32x32x16_bf16 back to back, four wavefronts of 4 x 4 blocks like the
+//                 v_mfma_f32_16x16x32_bf16 back to back, four wavefronts of 8 x 8 blocks like the
 //                 tiled FFN kernel, with (lds_reads = 1) or without the GEMM's LDS fragment reads and
 //                 with no global memory traffic at all.  Flop per launch = workgroups * 4 wavefronts *
-//                 iters * 4 K-steps * 16 MFMAs * 32768.
+//                 iters * 2 K-steps * 64 MFMAs * 16384.
 //   read stream : a grid-stride read of a buffer with 16-byte loads, eight in flight per lane,
 //                 nothing written: the rate at which HBM delivers a stream that is read once.
 //   copy stream : a plain copy, the kernel of known traffic for scaling hardware-counter readings.
 //   scatter combine : the gate-weighted combine by atomic adds into an fp32 image, what folding the
 //                 combine into the second product costs when a token has several experts.
 #include "common.h"
+#include "mfma_agpr.h"
 
 namespace emoe {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
 constexpr int kRowElems = 72;                      // 64 K elements + 8 of padding: conflict-free fragment reads
@@ -42,48 +41,48 @@ __global__ __launch_bounds__(256) void mfma_loop_kernel(const bf16_t* __restrict
         tile[(kTileRows + i / 64) * kRowElems + i % 64] = bsrc[i];
     }
     __syncthreads();
-    floatx16 acc[4][4];
+    constexpr int NB = 8;  // 16-row blocks per wavefront and operand
+    bf16x8 zero;
+    __builtin_memset(&zero, 0, sizeof(zero));
+    floatx4 acc[NB][NB];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    int xr[4], wr[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        xr[i] = ((wave & 1) * 128 + i * 32 + (lane & 31)) * kRowElems + (lane >> 5) * 8;
-        wr[i] = (kTileRows + (wave >> 1) * 128 + i * 32 + (lane & 31)) * kRowElems + (lane >> 5) * 8;
-    }
-    bf16x8 xf[2][4], wf[2][4];
-    auto load_frags = [&](int buf, int kk) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) xf[buf][i] = *reinterpret_cast<const bf16x8*>(tile + xr[i] + kk * 16);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) wf[buf][i] = *reinterpret_cast<const bf16x8*>(tile + wr[i] + kk * 16);
+        for (int j = 0; j < NB; ++j) mfma_zero(acc[i][j], zero);
+    // a lane holds row lane % 16 of a block and, in K-step kk, elements 32 kk + 8 (lane / 16) .. +7
+    const bf16_t* xp = tile + ((wave & 1) * 128 + (lane & 15)) * kRowElems + (lane >> 4) * 8;
+    const bf16_t* wp = tile + (kTileRows + (wave >> 1) * 128 + (lane & 15)) * kRowElems + (lane >> 4) * 8;
+    bf16x8 xf[2][NB], wf[2][NB];
+    auto load_frag = [&](int kk, int i) {
+        if (i < NB) xf[kk][i] = *reinterpret_cast<const bf16x8*>(xp + i * 16 * kRowElems + kk * 32);
+        else wf[kk][i - NB] = *reinterpret_cast<const bf16x8*>(wp + (i - NB) * 16 * kRowElems + kk * 32);
     };
-    load_frags(0, 0);
-    load_frags(1, 1);
+#pragma unroll
+    for (int i = 0; i < 4 * NB; ++i) load_frag(i / (2 * NB), i % (2 * NB));
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) {
-            if (LDS_READS) load_frags((kk + 1) & 1, (kk + 1) & 3);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int kk = 0; kk < 2; ++kk) {
 #pragma unroll
-            for (int ni = 0; ni < 4; ++ni)
+            for (int ni = 0; ni < NB; ++ni)
 #pragma unroll
-                for (int mi = 0; mi < 4; ++mi)
-                    acc[ni][mi] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[kk & 1][ni], xf[kk & 1][mi], acc[ni][mi], 0, 0, 0);
+                for (int m = 0; m < NB; ++m) {
+                    const int mi = (ni & 1) ? NB - 1 - m : m;  // back and forth, as in the GEMM
+                    mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
+                    // the next step's fragments, one read per three instructions
+                    const int at = ni * NB + m;
+                    if (LDS_READS && at % 3 == 2 && at / 3 < 2 * NB) load_frag(kk ^ 1, at / 3);
+                }
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    mfma_settle();
     float s = 0.0f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < NB; ++i)
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
+        for (int j = 0; j < NB; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) s += acc[i][j][v];
+            for (int v = 0; v < 4; ++v) s += acc_read(acc[i][j][v]);
     sink[(size_t)blockIdx.x * 256 + threadIdx.x] = s;
 }
 
@@ -167,7 +166,7 @@ int emoe_measure_mfma_loop(const void* a, size_t a_elems, const void* b, size_t 
         mfma_loop_kernel<false><<<workgroups, 256, kLoopLds, st>>>(static_cast<const bf16_t*>(a), a_elems,
                                                                    static_cast<const bf16_t*>(b), b_elems, iters, sink);
     }
-    if (flop) *flop = (double)workgroups * 4.0 * iters * 4.0 * 16.0 * 32768.0;
+    if (flop) *flop = (double)workgroups * 4.0 * iters * 2.0 * 64.0 * 16384.0;
     return hipGetLastError() == hipSuccess ? EMOE_OK : EMOE_ERR_DEVICE;
 }
 
