@@ -22,7 +22,9 @@ namespace {
 
 typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowElems = 72;                      // 64 K elements + 8 of padding: conflict-free fragment reads
+// 64 K elements per row; the 16-byte chunk c of row r sits at chunk position c ^ ((r >> 1) & 7), as in the GEMM: conflict-free
+// fragment reads
+constexpr int kRowElems = 64;
 constexpr int kTileRows = 256;
 constexpr int kLoopLds = 2 * kTileRows * kRowElems * 2;  // both operand tiles, bytes
 
@@ -37,8 +39,9 @@ __global__ __launch_bounds__(256) void mfma_loop_kernel(const bf16_t* __restrict
     const bf16_t* asrc = a + (size_t)(blockIdx.x % a_tiles) * (kTileRows * 64);
     const bf16_t* bsrc = b + (size_t)((blockIdx.x * 7u + 3u) % b_tiles) * (kTileRows * 64);
     for (int i = threadIdx.x; i < kTileRows * 64; i += 256) {
-        tile[(i / 64) * kRowElems + i % 64] = asrc[i];
-        tile[(kTileRows + i / 64) * kRowElems + i % 64] = bsrc[i];
+        const int row = i / 64, at = (((i % 64) / 8) ^ ((row >> 1) & 7)) * 8 + i % 8;
+        tile[row * kRowElems + at] = asrc[i];
+        tile[(kTileRows + row) * kRowElems + at] = bsrc[i];
     }
     __syncthreads();
     constexpr int NB = 8;  // 16-row blocks per wavefront and operand
@@ -50,12 +53,13 @@ __global__ __launch_bounds__(256) void mfma_loop_kernel(const bf16_t* __restrict
 #pragma unroll
         for (int j = 0; j < NB; ++j) mfma_zero(acc[i][j], zero);
     // a lane holds row lane % 16 of a block and, in K-step kk, elements 32 kk + 8 (lane / 16) .. +7
-    const bf16_t* xp = tile + ((wave & 1) * 128 + (lane & 15)) * kRowElems + (lane >> 4) * 8;
-    const bf16_t* wp = tile + (kTileRows + (wave >> 1) * 128 + (lane & 15)) * kRowElems + (lane >> 4) * 8;
+    const int f_at = ((lane >> 4) ^ (((lane & 15) >> 1) & 7)) * 8;  // K-step 1: bit 5 flipped
+    const int x_at = ((wave & 1) * 128 + (lane & 15)) * kRowElems + f_at;
+    const int w_at = (kTileRows + (wave >> 1) * 128 + (lane & 15)) * kRowElems + f_at;
     bf16x8 xf[2][NB], wf[2][NB];
     auto load_frag = [&](int kk, int i) {
-        if (i < NB) xf[kk][i] = *reinterpret_cast<const bf16x8*>(xp + i * 16 * kRowElems + kk * 32);
-        else wf[kk][i - NB] = *reinterpret_cast<const bf16x8*>(wp + (i - NB) * 16 * kRowElems + kk * 32);
+        if (i < NB) xf[kk][i] = *reinterpret_cast<const bf16x8*>(tile + (x_at ^ kk * 32) + i * 16 * kRowElems);
+        else wf[kk][i - NB] = *reinterpret_cast<const bf16x8*>(tile + (w_at ^ kk * 32) + (i - NB) * 16 * kRowElems);
     };
 #pragma unroll
     for (int i = 0; i < 4 * NB; ++i) load_frag(i / (2 * NB), i % (2 * NB));

@@ -5,6 +5,8 @@
     python -m paper_2503_06823_amd.profile_tools traffic <fetch_dir> <write_dir> --command "<cmd>" --out profiles/x.md
     python -m paper_2503_06823_amd.profile_tools counters <dir> [<dir> ...] --command "<cmd>" --out profiles/x.md
             [--kernels substring,substring]
+    rocprofv3 --kernel-trace --output-format csv -d <dir> -- python3 -m paper_2503_06823_amd.profile_tools run-layers
+    python -m paper_2503_06823_amd.profile_tools layers <dir> --command "<cmd>" --out profiles/x.md
 
 <dir> is what `rocprofv3 -d <dir>` wrote (searched recursively for *_kernel_stats.csv or
 *_counter_collection.csv).  `traffic` expects the profiled command to have run bench.py with
@@ -176,6 +178,54 @@ def cmd_counters(a):
     print(a.out)
 
 
+LAYER_PASSES = 20
+
+
+def cmd_run_layers(a):
+    """Runs every listed layer of perf/cases.py LAYER_PASSES times between two marker kernels, each pass on another of several
+    states, so that weights come from HBM."""
+    import torch
+    sys.path.insert(0, os.getcwd())
+    from perf import cases
+    marker = torch.zeros(1, dtype=torch.float64, device="cuda:0")
+    for c in cases.listed():
+        weights = c["S"] * (3 if c["act"] == "swiglu" else 2) * c["d"] * c["f"] * (4 if c["dtype"] == "f32" else 2)
+        states = [cases.prepare(c, 7 + i) for i in range(max(2, min(LAYER_PASSES, (600 << 20) // weights + 1)))]
+        for s in states:
+            cases.run(s)
+        torch.cuda.synchronize()
+        marker.sin_()
+        for i in range(LAYER_PASSES):
+            cases.run(states[i % len(states)])
+        marker.sin_()
+        torch.cuda.synchronize()
+        print("layer", c["name"], flush=True)
+        del states, s
+        torch.cuda.empty_cache()
+
+
+def cmd_layers(a):
+    from perf import cases
+    rows = sorted(csv.DictReader(open(_find(a.dir, "kernel_trace.csv"), newline="")), key=lambda r: int(r["Start_Timestamp"]))
+    marks = [i for i, r in enumerate(rows) if "sin_kernel" in r["Kernel_Name"]]
+    names = [c["name"] for c in cases.listed()]
+    if len(marks) != 2 * len(names):
+        raise SystemExit(f"{len(marks)} marker kernels, expected {2 * len(names)}")
+    with open(a.out, "w") as f:
+        f.write(f"# {a.title}\n\nCommand (run on the MI355X box from the repository root):\n\n```\n{a.command.strip()}\n```\n\n")
+        f.write(f"Each layer {LAYER_PASSES} times, each time on another of several states (weights from HBM):\n\n")
+        f.write("| layer | kernel | median us | min us |\n|---|---|---|---|\n")
+        for n, name in enumerate(names):
+            part = rows[marks[2 * n] + 1:marks[2 * n + 1]]
+            per = len(part) // LAYER_PASSES
+            for i in range(per):
+                us = sorted((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3 for r in part[i::per])
+                f.write(f"| {name if i == 0 else ''} | `{short_name(part[i]['Kernel_Name'])}` | {us[len(us) // 2]:.1f} | {us[0]:.1f} |\n")
+        if a.note:
+            f.write("\n" + a.note + "\n")
+    print(a.out)
+
+
 def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__, formatter_class=argparse.RawDescriptionHelpFormatter)
     sub = ap.add_subparsers(dest="what", required=True)
@@ -193,6 +243,8 @@ def main(argv=None):
     p = sub.add_parser("counters"); p.add_argument("dirs", nargs="+"); common(p); p.add_argument("--kernels", default="")
     p.add_argument("--cus", type=int, default=256, help="compute units the per-chip cycle counters are divided by")
     p.set_defaults(fn=cmd_counters)
+    p = sub.add_parser("run-layers"); p.set_defaults(fn=cmd_run_layers)
+    p = sub.add_parser("layers"); p.add_argument("dir"); common(p); p.set_defaults(fn=cmd_layers)
     a = ap.parse_args(argv)
     a.fn(a)
 
