@@ -16,7 +16,8 @@
 // per MFMA.  In the SwiGLU pass the 256 weight rows are 128 rows of W1 and the SAME 128 rows of
 // W3, arranged so that a lane holds the gate and the up value of the same output element and the
 // activation is applied in registers.  The weight rows go on the MFMA's row operand: a lane then
-// owns four consecutive output columns of one token and stores them as one 8-byte write.
+// owns four consecutive output columns of one token in every block, which two exchanges between lanes
+// turn into stores of eight (see epilogue()).
 //
 // Data movement: both operands are K-contiguous in memory.  K is walked in tiles of 64, so that a
 // tile row is one whole 128-byte cache line (with 64-byte rows every line is requested twice, by

@@ -1,7 +1,8 @@
 // Gate logits and resident-restricted top-k (eMoE Section 1: the gate; Section 3.2.2, last
 // paragraph: a token whose expert is not on the GPU goes to its next-best expert that is):
-// fp32 inputs with few tokens or few experts, and bf16 inputs when there are few tokens, few experts and
-// long rows (a decode step of a Mixtral-shaped layer).  Other fp32 batches take route_f32.hip.  Other bf16 batches take the matrix-core kernel of route_mfma.hip,
+// fp32 inputs with few experts, or with few tokens and long rows, and bf16 inputs when there are few tokens, few
+// experts and long rows (a decode step of a Mixtral-shaped layer).  Other fp32 batches take route_f32.hip, other bf16
+// batches the matrix-core kernel of route_mfma.hip,
 // which puts 32 tokens on a workgroup: with 64 tokens it runs on two CUs, bound by the latency of
 // their walk along d_model.
 //
