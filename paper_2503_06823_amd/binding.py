@@ -62,6 +62,7 @@ def lib() -> ctypes.CDLL:
         L.emoe_status_string.argtypes = [ctypes.c_int]
         L.emoe_workspace_bytes.argtypes = [dp, ctypes.POINTER(sz), ctypes.POINTER(sz)]
         L.emoe_route.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp]
+        L.emoe_route_observe.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.emoe_permute.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.emoe_measure_mfma_loop.argtypes = [vp, sz, vp, sz, i32, i32, i32, vp, vp, vp]
         L.emoe_measure_read_stream.argtypes = [vp, sz, i32, vp, vp]
@@ -70,6 +71,8 @@ def lib() -> ctypes.CDLL:
         L.emoe_permute_static.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, vp]
         L.emoe_expert_ffn.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.emoe_expert_ffn_pass.argtypes = [dp, i32, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.emoe_expert_ffn_gather.argtypes = [dp, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
+        L.emoe_expert_ffn_gather_pass.argtypes = [dp, i32, vp, vp, vp, vp, vp, vp, vp, vp, sz, vp]
         L.emoe_combine.argtypes = [dp, vp, vp, vp, vp, vp]
         L.emoe_expert_ffn_gather_combine.argtypes = [dp] + [vp] * 11 + [sz, vp]
         L.emoe_layer_forward.argtypes = [dp] + [vp] * 15 + [vp, sz, vp, sz, vp]
@@ -110,6 +113,27 @@ def _stream(stream) -> ctypes.c_void_p:
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+# The forward path's calls.  Their argument types are declared, so that a plain int is passed as the pointer it is: making a
+# c_void_p of each of a layer's 17 addresses, and a Stream object of the current stream, took the host longer than the GPU needs
+# for a layer of a few tokens (the call 19.4 -> 9.6 us without the launches; 64 tokens, d 128, f 256, fp32: 26.0 -> 21.6 us a
+# layer; 2 tokens, d 224, f 416 with the four steps called one by one: 36.2 -> 24.4).
+def _addr(t) -> Optional[int]:
+    """_ptr() without the wrapping: the address as an int, None for a NULL pointer."""
+    try:
+        return t.data_ptr()
+    except AttributeError:
+        return _ptr(t).value
+
+
+def _stream_addr(stream) -> Optional[int]:
+    """_stream() without the wrapping."""
+    if stream is None:
+        import torch
+        if torch.cuda.is_initialized():  # as torch.cuda.current_stream(), without making a Stream object of it
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return _stream(stream).value
+
+
 def _event(ev) -> ctypes.c_void_p:
     if ev is None:
         return ctypes.c_void_p(0)
@@ -146,32 +170,32 @@ def emoe_workspace_bytes(desc: EmoeLayerDesc, check: bool = True) -> Tuple[int, 
 
 
 def emoe_route(desc, x, w_gate, gate_bias, slot_of_expert, topk_expert, topk_weight, stream=None, check=True) -> int:
-    rc = lib().emoe_route(ctypes.byref(desc), _ptr(x), _ptr(w_gate), _ptr(gate_bias), _ptr(slot_of_expert),
-                          _ptr(topk_expert), _ptr(topk_weight), _stream(stream))
+    rc = lib().emoe_route(ctypes.byref(desc), _addr(x), _addr(w_gate), _addr(gate_bias), _addr(slot_of_expert),
+                          _addr(topk_expert), _addr(topk_weight), _stream_addr(stream))
     return _check(rc, "emoe_route", check)
 
 
 def emoe_route_observe(desc, x, w_gate, gate_bias, slot_of_expert, topk_expert, topk_weight, expert_tokens,
                        stream=None, check=True) -> int:
     """`expert_tokens`: int64 device tensor [E], accumulated."""
-    rc = lib().emoe_route_observe(ctypes.byref(desc), _ptr(x), _ptr(w_gate), _ptr(gate_bias), _ptr(slot_of_expert),
-                                  _ptr(topk_expert), _ptr(topk_weight), _ptr(expert_tokens), _stream(stream))
+    rc = lib().emoe_route_observe(ctypes.byref(desc), _addr(x), _addr(w_gate), _addr(gate_bias), _addr(slot_of_expert),
+                                  _addr(topk_expert), _addr(topk_weight), _addr(expert_tokens), _stream_addr(stream))
     return _check(rc, "emoe_route_observe", check)
 
 
 def emoe_permute(desc, x, topk_expert, slot_of_expert, slot_counts, slot_offsets, perm, inv_perm, x_perm, ws,
                  ws_bytes, stream=None, check=True) -> int:
-    rc = lib().emoe_permute(ctypes.byref(desc), _ptr(x), _ptr(topk_expert), _ptr(slot_of_expert), _ptr(slot_counts),
-                            _ptr(slot_offsets), _ptr(perm), _ptr(inv_perm), _ptr(x_perm), _ptr(ws), int(ws_bytes),
-                            _stream(stream))
+    rc = lib().emoe_permute(ctypes.byref(desc), _addr(x), _addr(topk_expert), _addr(slot_of_expert), _addr(slot_counts),
+                            _addr(slot_offsets), _addr(perm), _addr(inv_perm), _addr(x_perm), _addr(ws), int(ws_bytes),
+                            _stream_addr(stream))
     return _check(rc, "emoe_permute", check)
 
 
 def emoe_permute_static(desc, x, topk_expert, slot_of_expert, slot_counts, slot_offsets, perm, inv_perm, x_perm,
                         stream=None, check=True) -> int:
-    rc = lib().emoe_permute_static(ctypes.byref(desc), _ptr(x), _ptr(topk_expert), _ptr(slot_of_expert),
-                                   _ptr(slot_counts), _ptr(slot_offsets), _ptr(perm), _ptr(inv_perm), _ptr(x_perm),
-                                   _stream(stream))
+    rc = lib().emoe_permute_static(ctypes.byref(desc), _addr(x), _addr(topk_expert), _addr(slot_of_expert),
+                                   _addr(slot_counts), _addr(slot_offsets), _addr(perm), _addr(inv_perm), _addr(x_perm),
+                                   _stream_addr(stream))
     return _check(rc, "emoe_permute_static", check)
 
 
@@ -205,57 +229,57 @@ def emoe_measure_copy_stream(src, dst, nbytes: int, workgroups: int, stream=None
 
 def emoe_expert_ffn(desc, x_perm, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, ws_bytes, stream=None,
                     check=True) -> int:
-    rc = lib().emoe_expert_ffn(ctypes.byref(desc), _ptr(x_perm), _ptr(slot_offsets), _ptr(w1_slots), _ptr(w3_slots),
-                               _ptr(w2_slots), _ptr(y_perm), _ptr(ws), int(ws_bytes), _stream(stream))
+    rc = lib().emoe_expert_ffn(ctypes.byref(desc), _addr(x_perm), _addr(slot_offsets), _addr(w1_slots), _addr(w3_slots),
+                               _addr(w2_slots), _addr(y_perm), _addr(ws), int(ws_bytes), _stream_addr(stream))
     return _check(rc, "emoe_expert_ffn", check)
 
 
 def emoe_expert_ffn_pass(desc, which, x_perm, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, ws_bytes,
                          stream=None, check=True) -> int:
-    rc = lib().emoe_expert_ffn_pass(ctypes.byref(desc), int(which), _ptr(x_perm), _ptr(slot_offsets), _ptr(w1_slots),
-                                    _ptr(w3_slots), _ptr(w2_slots), _ptr(y_perm), _ptr(ws), int(ws_bytes),
-                                    _stream(stream))
+    rc = lib().emoe_expert_ffn_pass(ctypes.byref(desc), int(which), _addr(x_perm), _addr(slot_offsets), _addr(w1_slots),
+                                    _addr(w3_slots), _addr(w2_slots), _addr(y_perm), _addr(ws), int(ws_bytes),
+                                    _stream_addr(stream))
     return _check(rc, "emoe_expert_ffn_pass", check)
 
 
 def emoe_expert_ffn_gather(desc, x, perm, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, ws_bytes, stream=None,
                            check=True) -> int:
-    rc = lib().emoe_expert_ffn_gather(ctypes.byref(desc), _ptr(x), _ptr(perm), _ptr(slot_offsets), _ptr(w1_slots),
-                                      _ptr(w3_slots), _ptr(w2_slots), _ptr(y_perm), _ptr(ws),
-                                      ctypes.c_size_t(int(ws_bytes)), _stream(stream))
+    rc = lib().emoe_expert_ffn_gather(ctypes.byref(desc), _addr(x), _addr(perm), _addr(slot_offsets), _addr(w1_slots),
+                                      _addr(w3_slots), _addr(w2_slots), _addr(y_perm), _addr(ws),
+                                      int(ws_bytes), _stream_addr(stream))
     return _check(rc, "emoe_expert_ffn_gather", check)
 
 
 def emoe_expert_ffn_gather_pass(desc, which, x, perm, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, ws_bytes,
                                 stream=None, check=True) -> int:
-    rc = lib().emoe_expert_ffn_gather_pass(ctypes.byref(desc), int(which), _ptr(x), _ptr(perm), _ptr(slot_offsets),
-                                           _ptr(w1_slots), _ptr(w3_slots), _ptr(w2_slots), _ptr(y_perm), _ptr(ws),
-                                           ctypes.c_size_t(int(ws_bytes)), _stream(stream))
+    rc = lib().emoe_expert_ffn_gather_pass(ctypes.byref(desc), int(which), _addr(x), _addr(perm), _addr(slot_offsets),
+                                           _addr(w1_slots), _addr(w3_slots), _addr(w2_slots), _addr(y_perm), _addr(ws),
+                                           int(ws_bytes), _stream_addr(stream))
     return _check(rc, "emoe_expert_ffn_gather_pass", check)
 
 
 def emoe_expert_ffn_gather_combine(desc, x, perm, inv_perm, slot_offsets, w1_slots, w3_slots, w2_slots, topk_weight,
                                    y_perm, out, ws, ws_bytes, stream=None, check=True) -> int:
-    rc = lib().emoe_expert_ffn_gather_combine(ctypes.byref(desc), _ptr(x), _ptr(perm), _ptr(inv_perm), _ptr(slot_offsets),
-                                              _ptr(w1_slots), _ptr(w3_slots), _ptr(w2_slots), _ptr(topk_weight),
-                                              _ptr(y_perm), _ptr(out), _ptr(ws), int(ws_bytes), _stream(stream))
+    rc = lib().emoe_expert_ffn_gather_combine(ctypes.byref(desc), _addr(x), _addr(perm), _addr(inv_perm), _addr(slot_offsets),
+                                              _addr(w1_slots), _addr(w3_slots), _addr(w2_slots), _addr(topk_weight),
+                                              _addr(y_perm), _addr(out), _addr(ws), int(ws_bytes), _stream_addr(stream))
     return _check(rc, "emoe_expert_ffn_gather_combine", check)
 
 
 def emoe_combine(desc, y_perm, inv_perm, topk_weight, out, stream=None, check=True) -> int:
-    rc = lib().emoe_combine(ctypes.byref(desc), _ptr(y_perm), _ptr(inv_perm), _ptr(topk_weight), _ptr(out),
-                            _stream(stream))
+    rc = lib().emoe_combine(ctypes.byref(desc), _addr(y_perm), _addr(inv_perm), _addr(topk_weight), _addr(out),
+                            _stream_addr(stream))
     return _check(rc, "emoe_combine", check)
 
 
 def emoe_layer_forward(desc, x, w_gate, gate_bias, slot_of_expert, w1_slots, w3_slots, w2_slots, topk_expert, topk_weight,
                        slot_counts, slot_offsets, perm, inv_perm, y_perm, out, permute_ws, permute_ws_bytes, ffn_ws,
                        ffn_ws_bytes, stream=None, check=True) -> int:
-    rc = lib().emoe_layer_forward(ctypes.byref(desc), _ptr(x), _ptr(w_gate), _ptr(gate_bias), _ptr(slot_of_expert),
-                                  _ptr(w1_slots), _ptr(w3_slots), _ptr(w2_slots), _ptr(topk_expert), _ptr(topk_weight),
-                                  _ptr(slot_counts), _ptr(slot_offsets), _ptr(perm), _ptr(inv_perm), _ptr(y_perm),
-                                  _ptr(out), _ptr(permute_ws), int(permute_ws_bytes), _ptr(ffn_ws), int(ffn_ws_bytes),
-                                  _stream(stream))
+    rc = lib().emoe_layer_forward(ctypes.byref(desc), _addr(x), _addr(w_gate), _addr(gate_bias), _addr(slot_of_expert),
+                                  _addr(w1_slots), _addr(w3_slots), _addr(w2_slots), _addr(topk_expert), _addr(topk_weight),
+                                  _addr(slot_counts), _addr(slot_offsets), _addr(perm), _addr(inv_perm), _addr(y_perm),
+                                  _addr(out), _addr(permute_ws), int(permute_ws_bytes), _addr(ffn_ws), int(ffn_ws_bytes),
+                                  _stream_addr(stream))
     return _check(rc, "emoe_layer_forward", check)
 
 
