@@ -3,7 +3,7 @@
 // fp32 inputs with few experts, or with few tokens and long rows, and bf16 inputs when there are few tokens, few
 // experts and long rows (a decode step of a Mixtral-shaped layer).  Other fp32 batches take route_f32.hip, other bf16
 // batches the matrix-core kernel of route_mfma.hip,
-// which puts 32 tokens on a workgroup: with 64 tokens it runs on two CUs, bound by the latency of
+// which puts 16 tokens on a workgroup: with 64 tokens it runs on four CUs, bound by the latency of
 // their walk along d_model.
 //
 // One wavefront (or, when there are few tokens, four) owns one token at a time.  Its 64 lanes
@@ -268,10 +268,11 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
             return launch_route_f32(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
         return launch_t<float>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     }
-    // bf16: the matrix-core kernel runs T / 32 workgroups, each bound by the latency of its walk along
-    // d_model (11 us at d_model = 4096 however few the tokens); one workgroup per token takes 6-8 us
-    // with up to 16 experts (19 us with 64, where the matrix-core kernel stays the better one)
-    if (d.T <= kWaveRouteTokens && d.E <= 16 && d.d_model >= 2048)
+    // bf16: with few tokens and experts a workgroup per token spreads the walk along d_model over more CUs and is
+    // level or better (us, wavefront / matrix: 8 experts, d_model 4096, 1 token 4.4 / 4.8, 128 tokens 4.9 / 5.3, 256 tokens
+    // 5.1 / 5.7; d_model 8192, 64 tokens 5.8 / 7.3); with 16 experts it is not (d_model 2048, 1 token 7.3 / 3.9; d_model
+    // 4096, 64 tokens 8.8 / 5.3)
+    if (d.T <= kWaveRouteTokens && d.E <= 8 && d.d_model >= 2048)
         return launch_t<bf16_t>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     return launch_route_bf16(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
 }

@@ -1,27 +1,31 @@
 // Gate logits and resident-restricted top-k for bf16 inputs (eMoE Section 1: the gate; Section
 // 3.2.2, last paragraph: a token whose expert is not on the GPU goes to its next-best expert that
-// is), with the logits of 32 tokens computed together on the matrix cores.
+// is), with the logits of 16 or 32 tokens computed together on the matrix cores.
 //
-// A workgroup of four wavefronts owns 32 tokens.  logit[t, e] = sum_i x[t, i] * Wg[e, i] is a
-// 32-token x (16, 32 or 64)-expert product with K = d_model: the gate rows go on the row operand
-// of v_mfma_f32_32x32x16_bf16 and the token rows on the column operand, so every gate row fetched
-// is used for 32 tokens (a wavefront per token re-reads the whole gate matrix per token, which at
-// 64 experts costs several times the read of x).
-// K is walked in tiles of 128 elements.  A tile (32 token row pieces and the gate row pieces, 256
-// bytes each) goes from global memory straight into LDS with buffer_load_dwordx4 ... lds, 1 KiB
-// of whole row pieces per instruction, so memory is read in full cache lines; a lane-per-row
-// register load would touch 32 rows per instruction and is bound by the L1's tag rate instead.
-// In LDS the 16-byte chunk c of row r sits at chunk position c ^ (r & 15), which makes the MFMA
-// fragment reads (32 rows x one chunk) bank-conflict free.  The kernel is bound by the latency of
-// the x stream, so as many tile stages as fit in LDS are kept in flight.
-// The four wavefronts split the eight MFMA steps of a tile; their partial logits meet in LDS and
-// are added in wavefront order: fp32 accumulation, summation order fixed by the code.
+// A wavefront per token re-reads the whole gate matrix per token; here a workgroup owns 16 tokens (32
+// when 16 would give more workgroups than the chip has CUs), and every gate row fetched is used for
+// all of them: v_mfma_f32_16x16x32_bf16 with gate rows on the row and token rows on the column
+// operand.  What bounds it is the latency of the walk along d_model and the rate at which a CU moves gate rows into LDS.
+// Up to eight wavefronts share the walk in pieces of 64 elements.  A piece (128 bytes, one line, of every token and gate
+// row) goes from global memory straight into LDS with buffer_load_dwordx4 ... lds, 1 KiB of whole lines per
+// instruction (a register load in the operand's layout puts 16 rows side by side in its lanes and is bound by the L1's
+// tag rate: 100 tokens, d_model 4096, 64 experts 23 us, 13 with LDS), into a ring of the wavefront's own: a
+// wavefront waits for nobody, there is no barrier in the walk.  All of LDS is ring.
+// In LDS the 16-byte chunk c of row r sits at chunk position c ^ ((r >> 1) & 7), which makes the fragment reads (16 rows
+// x one chunk) bank-conflict free.
+// Measured (us a launch, x from HBM; before, with 32 tokens, four wavefronts and a barrier per tile): 1024 tokens, d_model
+// 4096, 8 experts 11.8 -> 5.9; 4096 of them 15.1 -> 10.1 (3.4 TB/s of x); 512 tokens, d_model 2048, 64 experts, k = 6 16.5 ->
+// 7.6; 8192 of them 21.2 -> 15.5; 64 tokens, d_model 768, 64 experts 7.0 -> 4.2; one token 13.4 -> 4.8 (d_model 1024).
 //
-// Wavefront 0 then holds, per lane, token lane%32 and 16 (or 32) of its logits, the other half
-// being in lane^32.  Top-k is k rounds of: best available logit of this lane (ascending expert
-// order, strict comparison, so the lower index wins a tie), one exchange with the partner lane,
-// winner marked taken.  Weights are the softmax over the k winners.
+// The partial sums of a logit meet in LDS and are added as a tree: fp32 accumulation, summation
+// order fixed by the code.
+//
+// Top-k: a wavefront per token, lane = expert: k rounds of a maximum over the lanes (DPP), the lowest lane
+// that holds it wins.  The logits are compared as integers of the same order, so that every round has
+// one winner whatever they are; a NaN comes after all numbers.  (With 64 experts and k = 6 the scan of 32 logits per lane
+// that this replaces took some 9 us of a launch.)  Weights are the softmax over the k winners.
 #include <atomic>
+#include <type_traits>
 
 #include "common.h"
 
@@ -29,256 +33,231 @@ namespace emoe {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int TOK = 32;                   // tokens per workgroup
-constexpr int BK = 128;                   // K elements per tile
-constexpr int ROW_BYTES = BK * 2;         // 256
-constexpr int X_BYTES = TOK * ROW_BYTES;  // 8 KiB
-constexpr int CPR = ROW_BYTES / 16;       // 16-byte chunks per tile row
-constexpr int RPI = 1024 / ROW_BYTES;     // tile rows filled by one load instruction
-constexpr int SPW = BK / 16 / 4;          // MFMA steps per wavefront and tile
-constexpr int LX = X_BYTES / 1024 / 4;    // token load instructions per wavefront and tile
-constexpr unsigned kRotation = 21;        // K-tile rotation per workgroup
+constexpr int NW = 16;                    // wavefronts: all of them for the top-k, the first NL for the walk along d_model
+constexpr int PIECE = 64;                 // elements of a row per wavefront and step
+constexpr int ROW_BYTES = PIECE * 2;      // 128
+constexpr int kLdsBytes = 160 * 1024;     // of one CU
+constexpr unsigned kRotation = 21;        // rotation of the walk per workgroup
 
 // s_waitcnt immediate: vmcnt <= n and all LDS traffic done (vmcnt[3:0] | [15:14], expcnt [6:4], lgkmcnt [11:8])
 constexpr int wait_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0x0 << 8); }
-
-// Workgroup barrier that leaves up to N global->LDS loads of this wavefront pending
-// (__syncthreads() would drain them all).
 template <int N>
-__device__ __forceinline__ void barrier_keep_loads() {
+__device__ __forceinline__ void wait_loads() {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(wait_imm(N));
-    __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 }
 
-// WR = gate rows in a tile (16, 32 or 64 >= E; rows past E repeat row E-1 and are masked out).
-template <int WR, int STAGES, bool KTAIL>
-__global__ __launch_bounds__(256) void route_mfma_kernel(const bf16_t* __restrict__ x,
-                                                         const bf16_t* __restrict__ w_gate,
-                                                         const float* __restrict__ bias,
-                                                         const int32_t* __restrict__ slot_of_expert,
-                                                         int32_t* __restrict__ topk_expert,
-                                                         float* __restrict__ topk_weight,
-                                                         unsigned long long* __restrict__ expert_tokens, int T_,
-                                                         int K, int E, int k) {
-    constexpr int NB = WR == 64 ? 2 : 1;             // MFMA row blocks
-    constexpr int W_BYTES = WR * ROW_BYTES;
-    constexpr int STAGE_BYTES = W_BYTES + X_BYTES;
-    constexpr int LW = W_BYTES / 1024 / 4;           // gate load instructions per wavefront and tile
-    constexpr int LOADS = LW + LX;
-    static_assert(LW >= 1 && (STAGES - 1) * LOADS < 64, "vmcnt counts at most 63 loads");
-    static_assert(3 * NB * 16 * 64 * 4 <= STAGES * STAGE_BYTES, "the reduction reuses the tile stages");
+// What follows from the blocks of 16 experts and 16 tokens: the wavefronts that walk, the pieces in flight in each.
+template <int EB, int TB>
+struct Shape {
+    static constexpr int EX = 16 * EB, TOK = 16 * TB;
+    static constexpr int PIECE_BYTES = (EX + TOK) * ROW_BYTES;
+    static constexpr int LOADS = PIECE_BYTES / 1024;                              // load instructions per piece
+    static constexpr int NL = 8 * 2 * PIECE_BYTES <= kLdsBytes ? 8 : 4;
+    static constexpr int FIT = kLdsBytes / (NL * PIECE_BYTES), DEPTH = FIT < 4 ? FIT : 4;
+    static constexpr int LDE = EX + 4;  // a token's logits, padded: 16-byte stores of 16 tokens spread over the banks
+    static constexpr int SUM_BYTES = NL * TOK * LDE * (int)sizeof(float);         // reuses the rings, and so does
+    static constexpr int LDS = NL * DEPTH * PIECE_BYTES;                          // the histogram behind it
+    static_assert(SUM_BYTES + kMaxExperts * (int)sizeof(int) <= LDS && LDS <= kLdsBytes, "LDS of one CU");
+    static_assert((DEPTH - 1) * LOADS < 64, "vmcnt counts at most 63 loads");
+};
+
+// The largest of the values that lanes 0 .. EX-1 hold, in all lanes; 0 where a lane takes no part.
+template <int EX>
+__device__ __forceinline__ uint32_t max_over_experts(uint32_t v) {
+    auto with = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
+        v = v > o ? v : o;
+    };
+    with(std::integral_constant<int, 0x111>{});  // row_shr:1, 2, 4, 8: lane 15 of every 16 holds their largest
+    with(std::integral_constant<int, 0x112>{});
+    with(std::integral_constant<int, 0x114>{});
+    with(std::integral_constant<int, 0x118>{});
+    if (EX > 16) with(std::integral_constant<int, 0x142>{});  // row_bcast:15
+    if (EX > 32) with(std::integral_constant<int, 0x143>{});  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, EX > 32 ? 63 : EX - 1);
+}
+
+// EB: blocks of 16 experts.  TB: blocks of 16 tokens.
+template <int EB, int TB>
+__global__ __launch_bounds__(64 * NW) void route_mfma_kernel(const bf16_t* __restrict__ x,
+                                                             const bf16_t* __restrict__ w_gate,
+                                                             const float* __restrict__ bias,
+                                                             const int32_t* __restrict__ slot_of_expert,
+                                                             int32_t* __restrict__ topk_expert,
+                                                             float* __restrict__ topk_weight,
+                                                             unsigned long long* __restrict__ expert_tokens, int T_,
+                                                             int K, int E, int k) {
+    typedef Shape<EB, TB> Sh;
+    constexpr int EX = Sh::EX, TOK = Sh::TOK, NL = Sh::NL, LOADS = Sh::LOADS, DEPTH = Sh::DEPTH, LDE = Sh::LDE;
     extern __shared__ __align__(16) char lds[];
-    float* s_bias = reinterpret_cast<float*>(lds + STAGES * STAGE_BYTES);
-    int* s_resident = reinterpret_cast<int*>(s_bias + kMaxExperts);
-    int* s_hist = s_resident + kMaxExperts;  // this workgroup's tokens per expert under ordinary routing
+    float* part = reinterpret_cast<float*>(lds);                   // [wavefront][token][LDE], once the rings are read
+    int* s_hist = reinterpret_cast<int*>(lds + Sh::SUM_BYTES);     // this workgroup's tokens per expert under ordinary routing
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    if (threadIdx.x < kMaxExperts) {
-        const int e = threadIdx.x;
-        s_bias[e] = (bias != nullptr && e < E) ? bias[e] : 0.0f;
-        s_resident[e] = (e < E && slot_of_expert[e] >= 0) ? 1 : 0;
-        s_hist[e] = 0;
-    }
     const int t0 = blockIdx.x * TOK;
+    // lane = expert, for the second half
+    const float lane_bias = (bias != nullptr && lane < E) ? bias[lane] : 0.0f;
+    const bool resident = lane < E && slot_of_expert[lane] >= 0;
 
-    // ---- global -> LDS: instruction (w, i) fills RPI tile rows; lane l lands in row l/CPR, chunk
-    //      position l%CPR and fetches global chunk (l%CPR) ^ (row&15) ------------------------------
-    const int l_rin = lane / CPR, l_pos = lane % CPR;
-    const uint32_t x_bytes = (uint32_t)T_ * (uint32_t)K * 2u;
-    const uint32_t w_bytes = (uint32_t)E * (uint32_t)K * 2u;
-    uint32_t w_voff[LW], x_voff[LX];
-    int w_chunk[LW], x_chunk[LX];
+    // with up to 16 experts the halves of a piece have sums of their own: chains of roundings half as long
+    constexpr int HALVES = EB == 1 ? 2 : 1;
+    floatx4 acc[HALVES][EB][TB];
 #pragma unroll
-    for (int i = 0; i < LW; ++i) {
-        const int tr = (LW * wave + i) * RPI + l_rin;  // row of the gate tile
-        w_chunk[i] = l_pos ^ (tr & 15);
-        const int e = tr < E ? tr : E - 1;
-        w_voff[i] = ((uint32_t)e * (uint32_t)K + w_chunk[i] * 8) * 2u;
-    }
+    for (int h = 0; h < HALVES; ++h)
 #pragma unroll
-    for (int i = 0; i < LX; ++i) {
-        const int tr = (LX * wave + i) * RPI + l_rin;  // row of the token tile
-        x_chunk[i] = l_pos ^ (tr & 15);
-        int t = t0 + tr;
-        t = t < T_ ? t : T_ - 1;  // repeats of the last token, never written out
-        x_voff[i] = ((uint32_t)t * (uint32_t)K + x_chunk[i] * 8) * 2u;
-    }
-    const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(x), 0, (int)x_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w_gate), 0, (int)w_bytes, 0x00020000);
-    auto issue_tile = [&](int stage, int k0) {
-        char* base = lds + stage * STAGE_BYTES;
+        for (int b = 0; b < EB; ++b)
 #pragma unroll
-        for (int i = 0; i < LW; ++i) {
-            uint32_t v = w_voff[i];
-            if (KTAIL && k0 + w_chunk[i] * 8 >= K) v = w_bytes;  // out of range: zeros
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(w_rsrc, (lds_void*)(base + (LW * wave + i) * 1024), 16, (int)v,
-                                                     k0 * 2, 0, 0);
+            for (int j = 0; j < TB; ++j) acc[h][b][j] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (wave < NL) {
+        // Load instruction i fills rows 8 i .. 8 i + 7 of a piece, gate rows first; lane l lands in row l / 8 of those, chunk
+        // position l % 8.  Rows past the last token or expert and chunks past K are addressed out of range: zeros.
+        const int l_row = lane >> 3, l_pos = lane & 7;
+        const uint32_t x_bytes = (uint32_t)T_ * (uint32_t)K * 2u, w_bytes = (uint32_t)E * (uint32_t)K * 2u;
+        const __amdgpu_buffer_rsrc_t x_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(x), 0, (int)x_bytes, 0x00020000);
+        const __amdgpu_buffer_rsrc_t w_rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(w_gate), 0, (int)w_bytes, 0x00020000);
+        uint32_t voff[LOADS];
+        int chunk[2];  // of load i: by its parity
+#pragma unroll
+        for (int i = 0; i < 2; ++i) chunk[i] = l_pos ^ (((8 * i + l_row) >> 1) & 7);
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) {
+            const int r = 8 * i + l_row;
+            if (8 * i < EX) voff[i] = r < E ? ((uint32_t)r * (uint32_t)K + chunk[i & 1] * 8) * 2u : w_bytes;
+            else voff[i] = t0 + r - EX < T_ ? ((uint32_t)(t0 + r - EX) * (uint32_t)K + chunk[i & 1] * 8) * 2u : x_bytes;
         }
+        const int pieces = (K + PIECE - 1) / PIECE;
+        // Workgroups start at different pieces of K: token rows are a power-of-two-ish stride apart, so workgroups that
+        // march through K in step would all pull from the same few HBM channels.  The order is fixed per workgroup.
+        const int rot = (int)((blockIdx.x * kRotation) % (unsigned)pieces);
+        char* ring = lds + wave * DEPTH * Sh::PIECE_BYTES;
+        auto issue = [&](int slot, int p) {  // past the last piece: out of range too, so that every wait counts the same
+            int pp = p + rot;
+            pp = pp >= pieces ? pp - pieces : pp;
+            const int k0 = p < pieces ? pp * PIECE : K;
+            const bool out[2] = {k0 + chunk[0] * 8 >= K, k0 + chunk[1] * 8 >= K};
 #pragma unroll
-        for (int i = 0; i < LX; ++i) {
-            uint32_t v = x_voff[i];
-            if (KTAIL && k0 + x_chunk[i] * 8 >= K) v = x_bytes;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(x_rsrc, (lds_void*)(base + W_BYTES + (LX * wave + i) * 1024), 16,
-                                                     (int)v, k0 * 2, 0, 0);
-        }
-    };
-
-    // ---- fragment addresses: lane holds row lane%32 and, for MFMA step s, chunk 2s + lane/32 ------
-    const int c = lane & 31;
-    const int h = lane >> 5;
-    const int w_row = WR == 16 ? (c & 15) : c;
-    floatx16 acc[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
-
-    const int k_tiles = (K + BK - 1) / BK;
-    // Workgroups walk K from different starting tiles: token rows are a power-of-two-ish stride
-    // apart, so workgroups marching through K in step would all pull from the same few HBM channels
-    // at once.  The order is fixed per workgroup, so results stay reproducible.
-    const int k_rot = (int)((blockIdx.x * kRotation) % (unsigned)k_tiles);
-    auto k_of = [&](int t) {
-        int tt = t + k_rot;
-        return (tt >= k_tiles ? tt - k_tiles : tt) * BK;
-    };
-#pragma unroll
-    for (int t = 0; t < STAGES - 1; ++t)
-        if (t < k_tiles) issue_tile(t, k_of(t));
-    // loads are counted per wavefront and retire in order: with `pending` tiles issued after tile t,
-    // tile t has landed once at most pending * LOADS loads are outstanding
-    int stage = 0;
-    for (int t = 0; t < k_tiles; ++t) {
-        if (t + STAGES - 2 < k_tiles) barrier_keep_loads<(STAGES - 2) * LOADS>();
-        else barrier_keep_loads<0>();
-        // everyone has finished tile t-1: its stage can take tile t+STAGES-1
-        if (t + STAGES - 1 < k_tiles) issue_tile(stage == 0 ? STAGES - 1 : stage - 1, k_of(t + STAGES - 1));
-        const char* wt = lds + stage * STAGE_BYTES;
-        const char* xt = wt + W_BYTES;
-#pragma unroll
-        for (int s2 = 0; s2 < SPW; ++s2) {
-            const int ch = 2 * (SPW * wave + s2) + h;  // this wavefront's MFMA steps of the tile
-            const bf16x8 xf = *reinterpret_cast<const bf16x8*>(xt + c * ROW_BYTES + ((ch ^ (c & 15)) * 16));
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const bf16x8 wf = *reinterpret_cast<const bf16x8*>(wt + (32 * b + w_row) * ROW_BYTES +
-                                                                   ((ch ^ (w_row & 15)) * 16));
-                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf, xf, acc[b], 0, 0, 0);
+            for (int i = 0; i < LOADS; ++i) {
+                const bool gate = 8 * i < EX;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(gate ? w_rsrc : x_rsrc,
+                                                         (lds_void*)(ring + slot * Sh::PIECE_BYTES + i * 1024), 16,
+                                                         (int)(out[i & 1] ? (gate ? w_bytes : x_bytes) : voff[i]),
+                                                         p < pieces ? k0 * 2 : 0, 0, 0);
             }
+        };
+        // fragments: lane holds row lane % 16 and, of half h of the piece, chunk 4 h + lane / 16
+        const int row = lane & 15, sw = (row >> 1) & 7;
+        const int f_off = row * ROW_BYTES;
+#pragma unroll
+        for (int s = 0; s < DEPTH - 1; ++s) issue(s, wave + s * NL);
+        int slot = 0;
+        for (int p = wave; p < pieces; p += NL) {
+            const int ahead = slot == 0 ? DEPTH - 1 : slot - 1;  // read in the last trip: its LDS reads are done (below)
+            issue(ahead, p + (DEPTH - 1) * NL);
+            wait_loads<(DEPTH - 1) * LOADS>();
+            const char* at = ring + slot * Sh::PIECE_BYTES + f_off;
+            bf16x8 wf[2][EB], xf[2][TB];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = ((4 * h + (lane >> 4)) ^ sw) * 16;
+#pragma unroll
+                for (int b = 0; b < EB; ++b) wf[h][b] = *reinterpret_cast<const bf16x8*>(at + b * 16 * ROW_BYTES + c);
+#pragma unroll
+                for (int j = 0; j < TB; ++j) xf[h][j] = *reinterpret_cast<const bf16x8*>(at + (EX + j * 16) * ROW_BYTES + c);
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < EB; ++b)
+#pragma unroll
+                    for (int j = 0; j < TB; ++j)
+                        acc[h % HALVES][b][j] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[h][b], xf[h][j], acc[h % HALVES][b][j], 0, 0, 0);
+            wait_loads<63>();  // the fragments are in registers: the next trip's loads may overwrite this piece
+            slot = slot + 1 == DEPTH ? 0 : slot + 1;
         }
-        stage = stage + 1 == STAGES ? 0 : stage + 1;
+        wait_loads<0>();  // surplus loads have landed too
     }
-
-    // the wavefronts' shares of K meet in LDS (the tile stages, all consumed), added in wavefront order
-    barrier_keep_loads<0>();
-    float* red = reinterpret_cast<float*>(lds);  // [wavefront - 1][NB * 16][64]
-    if (wave > 0) {
+    __syncthreads();  // the rings are read: the partial sums may overwrite them
+    if (wave < NL) {
+        // a lane holds token lane % 16 and experts 16 b + 4 (lane / 16) .. +3
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
+        for (int j = 0; j < TB; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) red[((wave - 1) * NB * 16 + b * 16 + v) * 64 + lane] = acc[b][v];
+            for (int b = 0; b < EB; ++b)
+                *reinterpret_cast<floatx4*>(part + (size_t)(wave * TOK + 16 * j + (lane & 15)) * LDE + 16 * b + (lane >> 4) * 4) =
+                    HALVES == 2 ? acc[0][b][j] + acc[HALVES - 1][b][j] : acc[0][b][j];
+    } else if (wave == NL) {
+        s_hist[lane] = 0;
     }
     __syncthreads();
-    if (wave > 0) return;
 
-    // Register i = 16 b + 4 g + r of this lane is the logit of expert 32 b + 8 g + 4 h + r.
-    float logit[NB * 16];
-#pragma unroll
-    for (int i = 0; i < NB * 16; ++i) logit[i] = acc[i >> 4][i & 15];
 #pragma unroll 1
-    for (int w = 0; w < 3; ++w) {
+    for (int tt = wave; tt < TOK && t0 + tt < T_; tt += NW) {
+        float s[NL];
+        const int e = lane < EX ? lane : EX - 1;
 #pragma unroll
-        for (int i = 0; i < NB * 16; ++i) logit[i] += red[(w * NB * 16 + i) * 64 + lane];
-    }
-    const int t = t0 + c;
-    const bool live = t < T_;
-    uint32_t avail = 0, exists = 0;
+        for (int w = 0; w < NL; ++w) s[w] = part[(size_t)(w * TOK + tt) * LDE + e];
 #pragma unroll
-    for (int i = 0; i < NB * 16; ++i) {
-        const int e = 32 * (i >> 4) + 8 * ((i >> 2) & 3) + 4 * h + (i & 3);
-        logit[i] += s_bias[e];
-        if (s_resident[e]) avail |= 1u << i;
-        if (e < E) exists |= 1u << i;
-    }
-
-    constexpr int kNone = 0x7fffffff;
-    float top_v = 0.0f, sum = 0.0f;
-    const size_t out0 = (size_t)t * k;
-    for (int j = 0; j < k; ++j) {
-        float bv = 0.0f;
-        int bi = -1;
+        for (int n = NL / 2; n > 0; n /= 2)
 #pragma unroll
-        for (int i = 0; i < NB * 16; ++i) {  // ascending expert order within the lane
-            const bool ok = (avail >> i) & 1u;
-            if (ok && (bi < 0 || logit[i] > bv)) { bv = logit[i]; bi = i; }
+            for (int w = 0; w < n; ++w) s[w] += s[w + n];
+        const float logit = s[0] + lane_bias;
+        // the logit as an integer of the same order, 1 for a NaN; -0 and +0 are equal
+        const int bits = __float_as_int(logit + 0.0f);
+        const uint32_t order = logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
+        const int t = t0 + tt;
+        uint32_t left = resident ? order : 0u;
+        int top_v = 0, sel_v = 0, sel_e = 0;  // lane j: the j-th winner
+        for (int j = 0; j < k; ++j) {
+            const uint32_t best = max_over_experts<EX>(left);
+            // fewer than k resident experts: precondition broken, stay defined
+            const int je = best ? __builtin_ctzll(__ballot(left == best)) : 0;
+            const int jv = best ? __builtin_amdgcn_readlane(__float_as_int(logit), je) : 0;
+            left = lane == je ? 0u : left;
+            if (j == 0) top_v = jv;
+            if (lane == j) { sel_v = jv; sel_e = je; }
         }
-        const int be = bi < 0 ? kNone : 32 * (bi >> 4) + 8 * ((bi >> 2) & 3) + 4 * h + (bi & 3);
-        const float ov = __shfl_xor(bv, 32);
-        const int oe = __shfl_xor(be, 32);
-        const bool mine = be != kNone && (oe == kNone || bv > ov || (bv == ov && be < oe));
-        float win_v = mine ? bv : ov;
-        int win_e = mine ? be : oe;
-        if (win_e == kNone) {  // fewer than k resident experts: precondition broken, stay defined
-            win_e = 0;
-            win_v = 0.0f;
+        const float prob = expf(__int_as_float(sel_v) - __int_as_float(top_v));
+        float sum = 0.0f;
+        for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(prob), j));
+        if (lane < k) {
+            topk_expert[(size_t)t * k + lane] = sel_e;
+            topk_weight[(size_t)t * k + lane] = prob / sum;
         }
-        if (mine) avail &= ~(1u << bi);
-        if (j == 0) top_v = win_v;
-        const float p = expf(win_v - top_v);
-        sum += p;
-        if (live && h == 0) {
-            topk_expert[out0 + j] = win_e;
-            topk_weight[out0 + j] = p;  // divided by the sum below
+        // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all E
+        // experts, resident or not; integer counts, so the accumulated result does not depend on order.
+        if (expert_tokens != nullptr) {
+            left = lane < E ? order : 0u;
+            bool mine = false;
+            for (int j = 0; j < k; ++j) {
+                const uint32_t best = max_over_experts<EX>(left);
+                const bool wins = lane == __builtin_ctzll(__ballot(left == best));  // k <= E: best > 0
+                left = wins ? 0u : left;
+                mine |= wins;
+            }
+            if (mine) atomicAdd(&s_hist[lane], 1);
         }
     }
-    if (live && h == 0) {
-        for (int j = 0; j < k; ++j) topk_weight[out0 + j] = topk_weight[out0 + j] / sum;
-    }
-
-    // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all
-    // E experts, resident or not; integer counts, so the accumulated result does not depend on order.
     if (expert_tokens == nullptr) return;
-    for (int j = 0; j < k; ++j) {
-        float bv = 0.0f;
-        int bi = -1;
-#pragma unroll
-        for (int i = 0; i < NB * 16; ++i) {
-            const bool ok = (exists >> i) & 1u;
-            if (ok && (bi < 0 || logit[i] > bv)) { bv = logit[i]; bi = i; }
-        }
-        const int be = bi < 0 ? kNone : 32 * (bi >> 4) + 8 * ((bi >> 2) & 3) + 4 * h + (bi & 3);
-        const float ov = __shfl_xor(bv, 32);
-        const int oe = __shfl_xor(be, 32);
-        const bool mine = be != kNone && (oe == kNone || bv > ov || (bv == ov && be < oe));
-        const int win_e = mine ? be : oe;
-        if (mine) exists &= ~(1u << bi);
-        if (live && h == 0 && win_e != kNone) atomicAdd(&s_hist[win_e], 1);
-    }
-    // one wavefront: its LDS operations complete in program order
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    if (lane < E) {
-        const int n = s_hist[lane];
-        if (n > 0) atomicAdd(&expert_tokens[lane], (unsigned long long)n);
+    __syncthreads();
+    if ((int)threadIdx.x < E) {
+        const int n = s_hist[threadIdx.x];
+        if (n > 0) atomicAdd(&expert_tokens[threadIdx.x], (unsigned long long)n);
     }
 }
 
-}  // namespace
-
-namespace {
-
-template <int WR, int STAGES, bool KTAIL>
-hipError_t launch_cfg(const emoe_layer_desc& d, const bf16_t* x, const bf16_t* wg, const float* bias,
-                      const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
-                      unsigned long long* expert_tokens, hipStream_t st) {
-    constexpr int kLds = STAGES * (WR * ROW_BYTES + X_BYTES) + kMaxExperts * 12;
-    static_assert(kLds <= 160 * 1024, "LDS of one CU");
-    auto kern = route_mfma_kernel<WR, STAGES, KTAIL>;
+template <int EB, int TB>
+hipError_t launch_tb(const emoe_layer_desc& d, const bf16_t* x, const bf16_t* wg, const float* bias,
+                     const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
+                     unsigned long long* expert_tokens, hipStream_t st) {
+    constexpr int kLds = Shape<EB, TB>::LDS, TOK = Shape<EB, TB>::TOK;
+    auto kern = route_mfma_kernel<EB, TB>;
     static std::atomic<bool> attr_set{false};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -286,18 +265,24 @@ hipError_t launch_cfg(const emoe_layer_desc& d, const bf16_t* x, const bf16_t* w
         if (e != hipSuccess) return e;
         attr_set.store(true, std::memory_order_release);
     }
-    kern<<<(d.T + TOK - 1) / TOK, 256, kLds, st>>>(x, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, d.T,
-                                                  d.d_model, d.E, d.k);
+    kern<<<(unsigned)(((long long)d.T + TOK - 1) / TOK), 64 * NW, kLds, st>>>(x, wg, bias, slot_of_expert, topk_expert, topk_weight,
+                                                                             expert_tokens, d.T, d.d_model, d.E, d.k);
     return hipGetLastError();
 }
 
-template <int WR, int STAGES>
-hipError_t launch_wr(const emoe_layer_desc& d, const bf16_t* x, const bf16_t* wg, const float* bias,
+template <int EB>
+hipError_t launch_eb(const emoe_layer_desc& d, const bf16_t* x, const bf16_t* wg, const float* bias,
                      const int32_t* slot_of_expert, int32_t* topk_expert, float* topk_weight,
-                      unsigned long long* expert_tokens, hipStream_t st) {
-    if (d.d_model % BK == 0)
-        return launch_cfg<WR, STAGES, false>(d, x, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
-    return launch_cfg<WR, STAGES, true>(d, x, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+                     unsigned long long* expert_tokens, hipStream_t st) {
+    DeviceShape shape;
+    hipError_t e = device_shape(&shape);
+    if (e != hipSuccess) return e;
+    // 32 tokens per workgroup fetch the gate rows half as often; 16 fill the chip with fewer tokens and have
+    // half the top-k to do (16 against 32: 4200 tokens, d_model 2048, 64 experts 14.4 / 10.7 us, 8192 of d_model 1024, 16
+    // experts 8.4 / 6.8; at 4096 tokens 32 would leave half the CUs idle).
+    if (d.T <= 16 * shape.cus)
+        return launch_tb<EB, 1>(d, x, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+    return launch_tb<EB, 2>(d, x, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
 }
 
 }  // namespace
@@ -307,10 +292,12 @@ hipError_t launch_route_bf16(const emoe_layer_desc& d, const void* x, const void
                              unsigned long long* expert_tokens, hipStream_t st) {
     const bf16_t* xp = static_cast<const bf16_t*>(x);
     const bf16_t* wg = static_cast<const bf16_t*>(w_gate);
-    // as many stages as LDS holds (12 / 16 / 24 KiB each), within the 63 loads vmcnt can count
-    if (d.E <= 16) return launch_wr<16, 13>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
-    if (d.E <= 32) return launch_wr<32, 9>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
-    return launch_wr<64, 6>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+    switch ((d.E + 15) / 16) {
+        case 1: return launch_eb<1>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+        case 2: return launch_eb<2>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+        case 3: return launch_eb<3>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+        default: return launch_eb<4>(d, xp, wg, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
+    }
 }
 
 }  // namespace emoe
