@@ -6,7 +6,7 @@
 // when 16 would give more workgroups than the chip has CUs), and every gate row fetched is used for
 // all of them: v_mfma_f32_16x16x32_bf16 with gate rows on the row and token rows on the column
 // operand.  What bounds it is the latency of the walk along d_model and the rate at which a CU moves gate rows into LDS.
-// Up to eight wavefronts share the walk in pieces of 64 elements.  A piece (128 bytes, one line, of every token and gate
+// Four to sixteen wavefronts share the walk in pieces of 64 elements.  A piece (128 bytes, one line, of every token and gate
 // row) goes from global memory straight into LDS with buffer_load_dwordx4 ... lds, 1 KiB of whole lines per
 // instruction (a register load in the operand's layout puts 16 rows side by side in its lanes and is bound by the L1's
 // tag rate: 100 tokens, d_model 4096, 64 experts 23 us, 13 with LDS), into a ring of the wavefront's own: a
@@ -58,7 +58,7 @@ struct Shape {
     static constexpr int EX = 16 * EB, TOK = 16 * TB;
     static constexpr int PIECE_BYTES = (EX + TOK) * ROW_BYTES;
     static constexpr int LOADS = PIECE_BYTES / 1024;                              // load instructions per piece
-    static constexpr int NL = 8 * 2 * PIECE_BYTES <= kLdsBytes ? 8 : 4;
+    static constexpr int NL = 16 * 2 * PIECE_BYTES <= kLdsBytes ? 16 : 8 * 2 * PIECE_BYTES <= kLdsBytes ? 8 : 4;
     static constexpr int FIT = kLdsBytes / (NL * PIECE_BYTES), DEPTH = FIT < 4 ? FIT : 4;
     static constexpr int LDE = EX + 4;  // a token's logits, padded: 16-byte stores of 16 tokens spread over the banks
     static constexpr int SUM_BYTES = NL * TOK * LDE * (int)sizeof(float);         // reuses the rings, and so does
@@ -192,9 +192,8 @@ __global__ __launch_bounds__(64 * NW) void route_mfma_kernel(const bf16_t* __res
             for (int b = 0; b < EB; ++b)
                 *reinterpret_cast<floatx4*>(part + (size_t)(wave * TOK + 16 * j + (lane & 15)) * LDE + 16 * b + (lane >> 4) * 4) =
                     HALVES == 2 ? acc[0][b][j] + acc[HALVES - 1][b][j] : acc[0][b][j];
-    } else if (wave == NL) {
-        s_hist[lane] = 0;
     }
+    if (wave == NW - 1) s_hist[lane] = 0;
     __syncthreads();
 
 #pragma unroll 1
