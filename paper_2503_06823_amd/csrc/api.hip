@@ -82,6 +82,7 @@ PermuteWs permute_ws_layout(const emoe_layer_desc& d) {
 // 723 against 563 us).
 namespace {
 constexpr long long kStreamRowsPerSlot = 22;
+constexpr int kFewTokens = 16;  // one tile of tokens of the few-token kernel; such a layer has at most 16 rows per slot
 constexpr long long kMidRowsPerSlot = 100;
 // A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
 // fill the chip, not by the weight stream, and around 256 rows per slot the 128-row tiles fill it
@@ -233,6 +234,8 @@ static int expert_ffn_passes(const emoe_layer_desc* desc, int passes, const void
     hipError_t e;
     if (desc->dtype == EMOE_F32)
         e = launch_ffn_f32(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
+    else if (desc->T <= kFewTokens)
+        e = launch_ffn_bf16_few(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
     else if (ffn_bf16_path(*desc) == kFfnStream)
         e = launch_ffn_bf16_stream(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
     else if (ffn_bf16_path(*desc) == kFfnMid)

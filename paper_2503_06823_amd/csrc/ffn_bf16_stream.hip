@@ -1,4 +1,5 @@
-// Expert FFN for bf16 layers with few rows per slot (a decode step): the cost is reading each
+// Expert FFN for bf16 layers with few rows per slot and more than 16 tokens (a decode step; up to 16 tokens:
+// ffn_bf16_few.hip): the cost is reading each
 // resident, non-empty slot's weights from HBM exactly once (eMoE Section 5.1: fewer experts
 // means fewer global-memory reads), so the kernels are shaped for streaming, not for MFMA rate.
 //
