@@ -82,6 +82,7 @@ PermuteWs permute_ws_layout(const emoe_layer_desc& d) {
 // 723 against 563 us).
 namespace {
 constexpr long long kStreamRowsPerSlot = 22;
+constexpr int kSortRounds = 4;  // see first_product_sorts()
 constexpr int kFewTokens = 16;  // one tile of tokens of the few-token kernel; such a layer has at most 16 rows per slot
 constexpr long long kMidRowsPerSlot = 100;
 // A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
@@ -221,7 +222,8 @@ int emoe_permute(const emoe_layer_desc* desc, const void* x, const int32_t* topk
 
 static int expert_ffn_passes(const emoe_layer_desc* desc, int passes, const void* x_perm, const int32_t* perm,
                              const int32_t* out_perm, const int32_t* slot_offsets, const void* w1_slots, const void* w3_slots,
-                             const void* w2_slots, void* y_perm, void* ws, size_t ws_bytes, void* stream) {
+                             const void* w2_slots, void* y_perm, void* ws, size_t ws_bytes, void* stream,
+                             const SortTables& sort = {}) {
     int rc = validate_desc(desc);
     if (rc != EMOE_OK) return rc;
     if (!x_perm || !slot_offsets || !w1_slots || !w2_slots || !y_perm) return EMOE_ERR_NULL;
@@ -230,7 +232,7 @@ static int expert_ffn_passes(const emoe_layer_desc* desc, int passes, const void
     if (!ws || ws_bytes < ffn_ws_layout(*desc).total) return EMOE_ERR_WORKSPACE;
     if (desc->T == 0) return EMOE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const RowGather gather{perm, desc->k, desc->T, out_perm};  // perm == nullptr: x_perm holds the grouped rows themselves
+    const SortingGather gather{{perm, desc->k, desc->T, out_perm}, sort};  // perm == nullptr: x_perm holds the grouped rows themselves
     hipError_t e;
     if (desc->dtype == EMOE_F32)
         e = launch_ffn_f32(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
@@ -277,20 +279,29 @@ int emoe_expert_ffn_gather_pass(const emoe_layer_desc* desc, int32_t pass, const
                              ws_bytes, stream);
 }
 
-int emoe_expert_ffn_gather_combine(const emoe_layer_desc* desc, const void* x, const int32_t* perm,
-                                   const int32_t* inv_perm, const int32_t* slot_offsets, const void* w1_slots,
-                                   const void* w3_slots, const void* w2_slots, const float* topk_weight, void* y_perm,
-                                   void* out, void* ws, size_t ws_bytes, void* stream) {
+static int ffn_and_combine(const emoe_layer_desc* desc, const void* x, const int32_t* perm, const int32_t* inv_perm,
+                           const int32_t* slot_offsets, const void* w1_slots, const void* w3_slots, const void* w2_slots,
+                           const float* topk_weight, void* y_perm, void* out, void* ws, size_t ws_bytes, void* stream,
+                           const SortTables& sort = {}) {
     if (!perm || !inv_perm || !topk_weight || !out) return EMOE_ERR_NULL;
     if (desc != nullptr && desc->k == 1)
         // one expert per token: its gate weight is exactly 1 and the combine is the inverse of the row
         // permutation, so the second product stores row r as out[perm[r]] and the fifth launch disappears
-        return expert_ffn_passes(desc, 3, x, perm, perm, slot_offsets, w1_slots, w3_slots, w2_slots, out, ws, ws_bytes, stream);
+        return expert_ffn_passes(desc, 3, x, perm, perm, slot_offsets, w1_slots, w3_slots, w2_slots, out, ws, ws_bytes, stream,
+                                 sort);
     if (!y_perm) return EMOE_ERR_NULL;
     int rc = expert_ffn_passes(desc, 3, x, perm, nullptr, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, ws_bytes,
-                               stream);
+                               stream, sort);
     if (rc != EMOE_OK) return rc;
     return emoe_combine(desc, y_perm, inv_perm, topk_weight, out, stream);
+}
+
+int emoe_expert_ffn_gather_combine(const emoe_layer_desc* desc, const void* x, const int32_t* perm,
+                                   const int32_t* inv_perm, const int32_t* slot_offsets, const void* w1_slots,
+                                   const void* w3_slots, const void* w2_slots, const float* topk_weight, void* y_perm,
+                                   void* out, void* ws, size_t ws_bytes, void* stream) {
+    return ffn_and_combine(desc, x, perm, inv_perm, slot_offsets, w1_slots, w3_slots, w2_slots, topk_weight, y_perm, out, ws,
+                           ws_bytes, stream);
 }
 
 int emoe_combine(const emoe_layer_desc* desc, const void* y_perm, const int32_t* inv_perm, const float* topk_weight,
@@ -301,6 +312,41 @@ int emoe_combine(const emoe_layer_desc* desc, const void* y_perm, const int32_t*
     if (desc->T == 0) return EMOE_OK;
     hipError_t e = launch_combine(*desc, y_perm, inv_perm, topk_weight, out, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? EMOE_OK : EMOE_ERR_DEVICE;
+}
+
+// Whether a layer called as a whole leaves the sort to its first product (block_sort.h), which spares a launch and costs
+// every workgroup about 1 us per 256 assignments: with as many workgroups as the chip holds at once that is less than the
+// launch, with many times as many it is not.  Counted here: the workgroups that the kernel launches (few: in units of 32 rows), the
+// surplus ones included, by how many the chip holds.  Layer, us, sort launch / sort in the product, passes x rounds in
+// brackets: 64 tokens, d 128, f 256, fp32 21.3 / 18.8 (1), 1 token, d 4096, f 14336 116.6 / 115.6 (3.5), 300 tokens, k 3, d 1024, f 1024
+// 37.4 / 36.3 (1.9); but 30 tokens, k 6, 64 slots, f 1408 181 / 183 (5.5), 256 tokens, d 4096, f 14336 427 / 429 (8.8), 120 tokens,
+// k 8, 64 slots, f 3072 125 / 133 (24).
+static bool first_product_sorts(const emoe_layer_desc& d) {
+    const long long A = (long long)d.T * d.k;
+    if (A <= 0 || A > kBlockSortMax) return false;
+    DeviceShape shape;
+    if (device_shape(&shape) != hipSuccess) return false;
+    const bool swiglu = d.act == EMOE_ACT_SWIGLU;
+    const long long slots = A < d.S ? A : d.S;
+    auto column_tiles = [&](int rows) { return (d.d_ff + (swiglu ? rows / 2 : rows) - 1) / (swiglu ? rows / 2 : rows); };
+    long long workgroups, at_once;
+    if (d.dtype == EMOE_F32) {
+        workgroups = (A / 32 + slots) * column_tiles(64);
+        at_once = 4 * shape.cus;
+    } else if (d.T <= kFewTokens) {
+        workgroups = slots * column_tiles(32);
+        at_once = 2 * shape.cus;
+    } else if (ffn_bf16_path(d) == kFfnStream) {
+        workgroups = d.S * (long long)column_tiles(64);
+        at_once = 2 * shape.cus;
+    } else if (ffn_bf16_path(d) == kFfnMid) {
+        workgroups = (A / 128 + slots) * column_tiles(256);
+        at_once = shape.cus;
+    } else {
+        return false;
+    }
+    const long long passes = (A + 255) / 256;
+    return passes * workgroups <= kSortRounds * at_once;
 }
 
 int emoe_layer_forward(const emoe_layer_desc* desc, const void* x, const void* w_gate, const float* gate_bias,
@@ -320,6 +366,11 @@ int emoe_layer_forward(const emoe_layer_desc* desc, const void* x, const void* w
     if (!ffn_ws || ffn_ws_bytes < ffn_ws_layout(*desc).total) return EMOE_ERR_WORKSPACE;
     rc = emoe_route(desc, x, w_gate, gate_bias, slot_of_expert, topk_expert, topk_weight, stream);
     if (rc != EMOE_OK) return rc;
+    if (first_product_sorts(*desc)) {
+        const SortTables sort{topk_expert, slot_of_expert, slot_counts, slot_offsets, perm, inv_perm, desc->T * desc->k, desc->E};
+        return ffn_and_combine(desc, x, perm, inv_perm, slot_offsets, w1_slots, w3_slots, w2_slots, topk_weight, y_perm, out,
+                               ffn_ws, ffn_ws_bytes, stream, sort);
+    }
     rc = emoe_permute(desc, x, topk_expert, slot_of_expert, slot_counts, slot_offsets, perm, inv_perm, nullptr, permute_ws,
                       permute_ws_bytes, stream);
     if (rc != EMOE_OK) return rc;

@@ -89,24 +89,42 @@ hipError_t launch_combine(const emoe_layer_desc& d, const void* y_perm, const in
 // with one expert per token, the permutation by which result row r is stored as row out_perm[r] of
 // the output (the token it belongs to) instead of row r.
 struct RowGather {
+    static constexpr bool kSorts = false;
     const int32_t* perm;
     int k;
     int rows;
     const int32_t* out_perm;
 };
+// A first product whose permutation has not been made yet (sort.A > 0): every workgroup sorts the assignments for itself
+// (block_sort.h), and the launch writes the permutation and the slots' offsets that slot_offsets, perm and the combine expect.
+// A type of its own, so that other launches do not carry the tables (48 bytes of arguments: 0.3 us).
+struct SortTables {
+    const int32_t* topk_expert;
+    const int32_t* slot_of_expert;
+    int32_t* slot_counts;
+    int32_t* slot_offsets;
+    int32_t* perm;
+    int32_t* inv_perm;
+    int A, E;
+};
+constexpr int kBlockSortMax = 1024;  // assignments
+struct SortingGather : RowGather {
+    static constexpr bool kSorts = true;
+    SortTables sort;
+};
 
-hipError_t launch_ffn_f32(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets, const void* w1,
+hipError_t launch_ffn_f32(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets, const void* w1,
                           const void* w3, const void* w2, void* y_perm, void* ws, int passes, hipStream_t st);
 hipError_t launch_ffn_bf16_tiled(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
                                  const void* w1, const void* w3, const void* w2, void* y_perm, void* ws,
                                  int passes, hipStream_t st);
-hipError_t launch_ffn_bf16_mid(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
+hipError_t launch_ffn_bf16_mid(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st);
-hipError_t launch_ffn_bf16_stream(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
+hipError_t launch_ffn_bf16_stream(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                   const void* w1, const void* w3, const void* w2, void* y_perm, void* ws,
                                   int passes, hipStream_t st);
-hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
+hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st);
 hipError_t launch_fill_i32(int32_t* p, int n, int32_t value, hipStream_t st);

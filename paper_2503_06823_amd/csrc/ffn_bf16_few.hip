@@ -19,7 +19,7 @@
 // The launch covers as many slots as can hold rows, at most one per assignment; a workgroup finds its slot as the n-th that does.
 #include <atomic>
 
-#include "common.h"
+#include "block_sort.h"
 
 namespace emoe {
 namespace {
@@ -58,8 +58,9 @@ struct Shape {
     static_assert(WAVES * (WR / 16) * 64 * 16 <= LDS, "the sums reuse the rings");
 };
 
-template <int EPI, int WR, int WAVES, bool ONCE>
-__global__ __launch_bounds__(64 * WAVES) void few_gemm_bf16(const bf16_t* __restrict__ a, RowGather gather,
+// Gather: SortingGather if the launch makes the permutation, else RowGather.
+template <int EPI, int WR, int WAVES, bool ONCE, class Gather>
+__global__ __launch_bounds__(64 * WAVES) void few_gemm_bf16(const bf16_t* __restrict__ a, Gather gather,
                                                            const int32_t* __restrict__ offsets,
                                                            const bf16_t* __restrict__ b0, const bf16_t* __restrict__ b1,
                                                            bf16_t* __restrict__ c, int S, int N, int K, int n_units) {
@@ -71,7 +72,14 @@ __global__ __launch_bounds__(64 * WAVES) void few_gemm_bf16(const bf16_t* __rest
     extern __shared__ __align__(16) char lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int s_begin = lane < S ? offsets[lane] : 0, s_end = lane < S ? offsets[lane + 1] : 0;
+    BlockSort<WAVES> sorted;
+    constexpr bool sorts = Gather::kSorts;
+    if constexpr (sorts) {
+        sorted.run(gather.sort, S, reinterpret_cast<int*>(lds));
+        if (blockIdx.x == 0) sorted.store_slots(gather.sort, S);
+    }
+    const int s_begin = sorts ? sorted.begin : lane < S ? offsets[lane] : 0;
+    const int s_end = sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0;
     unsigned long long used = __ballot(s_end > s_begin);
     int nth = blockIdx.x / n_units;
     if (nth >= __popcll(used)) return;
@@ -109,14 +117,22 @@ __global__ __launch_bounds__(64 * WAVES) void few_gemm_bf16(const bf16_t* __rest
     const int f_off = (lane & 15) * ROW_BYTES, f_sw = ((lane & 15) >> 1) & 7;
 
     for (int tok0 = row0; tok0 < row_end; tok0 += TOK) {
+        int* list = reinterpret_cast<int*>(lds + kSortLdsBytes);
+        if constexpr (sorts) {
+            sorted.list_rows(slot, tok0, TOK, list);
+            if (n0 == 0) sorted.store_rows(gather.sort, slot, tok0, TOK);
+            __syncthreads();
+        }
 #pragma unroll
         for (int i = WR / 8; i < LOADS; ++i) {
             int r = tok0 + 8 * (i - WR / 8) + l_row;
             const bool past = r >= row_end;
             r = past ? row_end - 1 : r;
-            if (gather.perm != nullptr) r = gather.perm[r] / gather.k;  // the token's row of x, not a copy of it
+            // the token's row of x, not a copy of it
+            if (gather.perm != nullptr) r = (sorts ? list[r - tok0] : gather.perm[r]) / gather.k;
             voff[i] = past ? a_bytes : ((uint32_t)r * (uint32_t)K + chunk[i & 1] * 8) * 2u;
         }
+        if (sorts) __syncthreads();  // the list is read: the rings may be filled
         auto issue = [&](int at, int p) {  // past the last piece: out of range too, so that every wait counts the same
             int pp = p + rot;
             pp = pp >= pieces ? pp - pieces : pp;
@@ -191,15 +207,15 @@ __global__ __launch_bounds__(64 * WAVES) void few_gemm_bf16(const bf16_t* __rest
     }
 }
 
-template <int EPI, int WR, int WAVES>
-hipError_t launch_shape(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
+template <int EPI, int WR, int WAVES, class Gather>
+hipError_t launch_shape(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
                         int slots, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? WR / 2 : WR;
     constexpr int kLds = Shape<WR, WAVES>::LDS;
     // Where rows are not whole 128-byte lines two pieces share the lines between them: no non-temporal hint there, but for a
     // small first product (the rule of the streaming kernels).
     const bool once = K % 64 == 0 || (EPI != kPlain && (long long)S * N * K * (EPI == kSwiglu ? 4 : 2) < kCachedFrom);
-    auto kern = once ? few_gemm_bf16<EPI, WR, WAVES, true> : few_gemm_bf16<EPI, WR, WAVES, false>;
+    auto kern = once ? few_gemm_bf16<EPI, WR, WAVES, true, Gather> : few_gemm_bf16<EPI, WR, WAVES, false, Gather>;
     static std::atomic<bool> attr_set[2] = {};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set[once].load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
@@ -211,8 +227,8 @@ hipError_t launch_shape(const bf16_t* a, RowGather gather, const int32_t* offset
     return hipGetLastError();
 }
 
-template <int EPI>
-hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
+template <int EPI, class Gather>
+hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c,
                       int slots, int S, int N, int K, hipStream_t st) {
     DeviceShape shape;
     hipError_t e = device_shape(&shape);
@@ -234,19 +250,20 @@ hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets,
 
 }  // namespace
 
-hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
+hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st) {
     bf16_t* h = reinterpret_cast<bf16_t*>(static_cast<uint8_t*>(ws) + ffn_ws_layout(d).h);
     const bf16_t* xp = static_cast<const bf16_t*>(x_perm);
     const int A = d.T * d.k, slots = A < d.S ? A : d.S;
     hipError_t e = hipSuccess;
-    if (!(passes & 1)) {
-    } else if (d.act == EMOE_ACT_SWIGLU)
-        e = launch_one<kSwiglu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), static_cast<const bf16_t*>(w3), h, slots, d.S,
-                                d.d_ff, d.d_model, st);
-    else
-        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), nullptr, h, slots, d.S, d.d_ff, d.d_model, st);
+    auto first = [&](auto rows) {
+        const bf16_t* w1p = static_cast<const bf16_t*>(w1);
+        if (d.act == EMOE_ACT_SWIGLU)
+            return launch_one<kSwiglu>(xp, rows, offsets, w1p, static_cast<const bf16_t*>(w3), h, slots, d.S, d.d_ff, d.d_model, st);
+        return launch_one<kRelu>(xp, rows, offsets, w1p, nullptr, h, slots, d.S, d.d_ff, d.d_model, st);
+    };
+    if (passes & 1) e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
     if (e != hipSuccess || !(passes & 2)) return e;
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const bf16_t*>(w2), nullptr,
                               static_cast<bf16_t*>(y_perm), slots, d.S, d.d_model, d.d_ff, st);

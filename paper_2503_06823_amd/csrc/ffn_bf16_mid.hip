@@ -51,7 +51,7 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
+#include "block_sort.h"
 
 namespace emoe {
 namespace {
@@ -99,11 +99,10 @@ struct Work {
     long long units;                      // tiles * kt: the sequence that is cut into shares
     int sharers;                          // > 0: tiles are cut, that many workgroups take equal shares; 0: whole tiles
 };
-__device__ __forceinline__ Work make_work(const int32_t* __restrict__ offsets, int S, int n_tiles, int K, int lane, int G,
-                                          int bm) {
+__device__ __forceinline__ Work make_work(int s_begin, int s_end, int n_tiles, int K, int lane, int G, int bm) {
     Work w;
-    w.s_begin = lane < S ? offsets[lane] : 0;
-    w.s_end = lane < S ? offsets[lane + 1] : 0;
+    w.s_begin = s_begin;
+    w.s_end = s_end;
     w.s_mtiles = (w.s_end - w.s_begin + bm - 1) / bm;
     const int span = w.s_mtiles * n_tiles;
     int incl = span;
@@ -153,8 +152,9 @@ __device__ __forceinline__ int piece_slot(int g, bool starts_inside) { return 2 
 // STAGES: LDS stages of one K tile each (token rows + weight rows), STAGES - 1 of them in flight.
 // PERSIST: one workgroup per CU that takes whole tiles or, when they are few, an equal share of all
 // tiles' K tiles; otherwise one workgroup per tile and surplus workgroups exit.
-template <int EPI, int BM, int BR, int STAGES, bool KTAIL, bool PERSIST>
-__global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restrict__ a, RowGather gather,
+// Gather: SortingGather if the launch makes the permutation, else RowGather.
+template <int EPI, int BM, int BR, int STAGES, bool KTAIL, bool PERSIST, class Gather>
+__global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restrict__ a, Gather gather,
                                                      const int32_t* __restrict__ offsets,
                                                      const bf16_t* __restrict__ b0, const bf16_t* __restrict__ b1,
                                                      bf16_t* __restrict__ c, float* __restrict__ partials, int S, int N,
@@ -187,7 +187,14 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     const int wm = wave / WN, wn = wave % WN;
 
     const int G = gridDim.x;
-    const Work work = make_work(offsets, S, n_tiles, K, lane, G, BM);
+    BlockSort<NW> sorted;
+    constexpr bool sorts = Gather::kSorts;
+    if constexpr (sorts) {
+        sorted.run(gather.sort, S, reinterpret_cast<int*>(lds));
+        if (blockIdx.x == 0) sorted.store_slots(gather.sort, S);
+    }
+    const Work work = make_work(sorts ? sorted.begin : lane < S ? offsets[lane] : 0,
+                                sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0, n_tiles, K, lane, G, BM);
     // workgroup ids go round-robin over the XCDs: g numbers them XCD by XCD
     const int xcd = blockIdx.x % XCDS, idx = blockIdx.x / XCDS;
     const int g = xcd * (G / XCDS) + idx;
@@ -210,7 +217,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         u = share_begin(work, g);
         u_end = share_begin(work, g + 1);
     }
-    const int rows_total = offsets[S];
+    const int rows_total = sorts ? __builtin_amdgcn_readlane(work.s_end, S - 1) : offsets[S];
 
     // ---- lane-constant parts of the addressing -------------------------------------------------------
     // Load instruction (w, i) of an operand fills tile rows (L? * w + i) * 8 .. +7; lane l lands in row
@@ -260,15 +267,23 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         const int n0 = nt * BNO;
 
         uint32_t x_voff[LX], w_voff[LW];
+        int* list = reinterpret_cast<int*>(lds + kSortLdsBytes);
+        if constexpr (sorts) {
+            sorted.list_rows(slot, row0, BM, list);
+            if (nt == 0) sorted.store_rows(gather.sort, slot, row0, BM);
+            __syncthreads();
+        }
 #pragma unroll
         for (int i = 0; i < LX; ++i) {
             const int tr = (LX * wave + i) * 8 + l_row;
             int r = row0 + tr;
             const bool past = r >= row_end;
             r = past ? row_end - 1 : r;
-            if (gather.perm != nullptr) r = gather.perm[r] / gather.k;  // the token's row of x, not a copy of it
+            // the token's row of x, not a copy of it
+            if (gather.perm != nullptr) r = (sorts ? list[r - row0] : gather.perm[r]) / gather.k;
             x_voff[i] = past ? a_bytes : ((uint32_t)r * (uint32_t)K + x_chunk[i] * 8) * 2u;
         }
+        if (sorts) __syncthreads();  // the list is read: the stages may be filled
 #pragma unroll
         for (int i = 0; i < LW; ++i) {
             const int tr = (LW * wave + i) * 8 + l_row;
@@ -490,7 +505,7 @@ __global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int b = blockIdx.x + 1;
-    const Work work = make_work(offsets, S, n_tiles, K, lane, G, BM);
+    const Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, n_tiles, K, lane, G, BM);
     if (b >= work.sharers) return;              // nothing was cut, or no share starts here
     const long long ub = share_begin(work, b);  // first unit of share b
     if (ub % work.kt == 0) return;              // the boundary falls between two tiles
@@ -544,15 +559,15 @@ __global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__
     }
 }
 
-template <int EPI, int BM, int BR, int STAGES, bool KTAIL, bool PERSIST>
-hipError_t launch_cfg(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
+template <int EPI, int BM, int BR, int STAGES, bool KTAIL, bool PERSIST, class Gather>
+hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
                       bf16_t* c, float* partials, long long m_tiles, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int kLds = STAGES * (BM * ROW_BYTES + BR * ROW_BYTES);
     static_assert(kLds <= 160 * 1024, "LDS of one CU");
     static_assert(!PERSIST || (size_t)2 * kGroups * BM * BR * sizeof(float) <= kMidPartialBytes,
                   "two pieces per workgroup fit the workspace");
-    auto kern = mid_gemm_bf16<EPI, BM, BR, STAGES, KTAIL, PERSIST>;
+    auto kern = mid_gemm_bf16<EPI, BM, BR, STAGES, KTAIL, PERSIST, Gather>;
     static std::atomic<bool> attr_set{false};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -577,16 +592,16 @@ hipError_t launch_cfg(const bf16_t* a, RowGather gather, const int32_t* offsets,
     return hipGetLastError();
 }
 
-template <int EPI, int BM, int BR, int STAGES, bool PERSIST>
-hipError_t launch_ktail(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
+template <int EPI, int BM, int BR, int STAGES, bool PERSIST, class Gather>
+hipError_t launch_ktail(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
                         bf16_t* c, float* partials, long long m_tiles, int S, int N, int K, hipStream_t st) {
     if (K % BK == 0)
         return launch_cfg<EPI, BM, BR, STAGES, false, PERSIST>(a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
     return launch_cfg<EPI, BM, BR, STAGES, true, PERSIST>(a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
 }
 
-template <int EPI>
-hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
+template <int EPI, class Gather>
+hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1,
                       bf16_t* c, float* partials, long long A, int S, int N, int K, hipStream_t st) {
     DeviceShape shape;
     hipError_t es = device_shape(&shape);
@@ -627,7 +642,7 @@ hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets,
 
 }  // namespace
 
-hipError_t launch_ffn_bf16_mid(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets,
+hipError_t launch_ffn_bf16_mid(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st) {
     const FfnWs lay = ffn_ws_layout(d);
@@ -636,13 +651,13 @@ hipError_t launch_ffn_bf16_mid(const emoe_layer_desc& d, const void* x_perm, Row
     const bf16_t* xp = static_cast<const bf16_t*>(x_perm);
     const long long A = (long long)d.T * d.k;
     hipError_t e = hipSuccess;
-    if (!(passes & 1)) {
-    } else if (d.act == EMOE_ACT_SWIGLU)
-        e = launch_one<kSwiglu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), static_cast<const bf16_t*>(w3), h,
-                                partials, A, d.S, d.d_ff, d.d_model, st);
-    else
-        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), nullptr, h, partials, A, d.S, d.d_ff,
-                              d.d_model, st);
+    auto first = [&](auto rows) {
+        const bf16_t* w1p = static_cast<const bf16_t*>(w1);
+        if (d.act == EMOE_ACT_SWIGLU)
+            return launch_one<kSwiglu>(xp, rows, offsets, w1p, static_cast<const bf16_t*>(w3), h, partials, A, d.S, d.d_ff, d.d_model, st);
+        return launch_one<kRelu>(xp, rows, offsets, w1p, nullptr, h, partials, A, d.S, d.d_ff, d.d_model, st);
+    };
+    if (passes & 1) e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
     if (e != hipSuccess || !(passes & 2)) return e;
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const bf16_t*>(w2), nullptr,
                               static_cast<bf16_t*>(y_perm), partials, A, d.S, d.d_model, d.d_ff, st);

@@ -18,7 +18,7 @@
 // K-steps of a tile; their partial sums meet in LDS at the end, added in wavefront order, so the
 // result is reproducible.  A slot with no rows exits before it touches its weights; a slot with more
 // than 32 rows is processed 32 rows at a time (the repeated weight reads come from cache).
-#include "common.h"
+#include "block_sort.h"
 
 namespace emoe {
 namespace {
@@ -73,8 +73,9 @@ __device__ __forceinline__ void barrier_keep_loads() {
 }
 
 // grid.x = S * ceil(N / BNO) workgroups, BNO = output columns per workgroup (32 SwiGLU, else 64).
-template <int EPI, int WR, int TAIL>
-__global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restrict__ a, RowGather gather,
+// Gather: SortingGather if the launch makes the permutation, else RowGather.
+template <int EPI, int WR, int TAIL, class Gather>
+__global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restrict__ a, Gather gather,
                                                            const int32_t* __restrict__ offsets,
                                                            const bf16_t* __restrict__ b0,
                                                            const bf16_t* __restrict__ b1, bf16_t* __restrict__ c,
@@ -91,9 +92,20 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
     __shared__ __align__(16) char lds[STAGES * STAGE_BYTES];
     const int slot = blockIdx.x / n_units;
     const int n0 = (blockIdx.x % n_units) * BNO;
-    const int row0 = offsets[slot], row_end = offsets[slot + 1];
+    BlockSort<4> sorted;
+    constexpr bool sorts = Gather::kSorts;
+    int row0, row_end;
+    if constexpr (sorts) {
+        sorted.run(gather.sort, S, reinterpret_cast<int*>(lds));
+        if (blockIdx.x == 0) sorted.store_slots(gather.sort, S);
+        row0 = __builtin_amdgcn_readlane(sorted.begin, slot);
+        row_end = __builtin_amdgcn_readlane(sorted.end, slot);
+    } else {
+        row0 = offsets[slot];
+        row_end = offsets[slot + 1];
+    }
     if (row_end <= row0) return;  // empty slot: its weights are never touched
-    const int rows_total = offsets[S];
+    const int rows_total = sorts ? row_end : offsets[S];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -135,6 +147,12 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
     for (int tok0 = row0; tok0 < row_end; tok0 += TOK) {  // 32 tokens per pass over the weights
         uint32_t x_voff[LX];
         int x_chunk[LX];
+        int* list = reinterpret_cast<int*>(lds + kSortLdsBytes);
+        if constexpr (sorts) {
+            sorted.list_rows(slot, tok0, TOK, list);
+            if (n0 == 0) sorted.store_rows(gather.sort, slot, tok0, TOK);
+            __syncthreads();
+        }
 #pragma unroll
         for (int i = 0; i < LX; ++i) {
             const int tr = (LX * wave + i) * RPI + l_rin;  // row of the token tile
@@ -142,9 +160,11 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
             int r = tok0 + tr;
             const bool past = r >= row_end;  // rows past the slot's end: out of range, zeros without memory traffic
             r = past ? row_end - 1 : r;
-            if (gather.perm != nullptr) r = gather.perm[r] / gather.k;  // the token's row of x, not a copy of it
+            // the token's row of x, not a copy of it
+            if (gather.perm != nullptr) r = (sorts ? list[r - tok0] : gather.perm[r]) / gather.k;
             x_voff[i] = past ? a_bytes : ((uint32_t)r * (uint32_t)K + x_chunk[i] * 8) * 2u;
         }
+        if (sorts) __syncthreads();  // the list is read: the stages may be filled
         auto issue_tile = [&](int stage, int k0) {
             char* base = lds + stage * STAGE_BYTES;
 #pragma unroll
@@ -242,8 +262,8 @@ __global__ __launch_bounds__(256, 2) void stream_gemm_bf16(const bf16_t* __restr
     }
 }
 
-template <int EPI, int WR>
-hipError_t launch_wr(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c, int S,
+template <int EPI, int WR, class Gather>
+hipError_t launch_wr(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c, int S,
                      int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? WR / 2 : WR;
     const int n_units = (N + BNO - 1) / BNO;
@@ -258,8 +278,8 @@ hipError_t launch_wr(const bf16_t* a, RowGather gather, const int32_t* offsets, 
     return hipGetLastError();
 }
 
-template <int EPI>
-hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c, int S,
+template <int EPI, class Gather>
+hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, const bf16_t* b0, const bf16_t* b1, bf16_t* c, int S,
                       int N, int K, hipStream_t st) {
     if constexpr (EPI != kSwiglu) {
         // fewer 64-row units than workgroup slots (2 per CU): halve the unit so the whole chip streams
@@ -273,19 +293,20 @@ hipError_t launch_one(const bf16_t* a, RowGather gather, const int32_t* offsets,
 
 }  // namespace
 
-hipError_t launch_ffn_bf16_stream(const emoe_layer_desc& d, const void* x_perm, RowGather gather,
+hipError_t launch_ffn_bf16_stream(const emoe_layer_desc& d, const void* x_perm, SortingGather gather,
                                   const int32_t* offsets,
                                   const void* w1, const void* w3, const void* w2, void* y_perm, void* ws,
                                   int passes, hipStream_t st) {
     bf16_t* h = reinterpret_cast<bf16_t*>(static_cast<uint8_t*>(ws) + ffn_ws_layout(d).h);
     const bf16_t* xp = static_cast<const bf16_t*>(x_perm);
     hipError_t e = hipSuccess;
-    if (!(passes & 1)) {
-    } else if (d.act == EMOE_ACT_SWIGLU)
-        e = launch_one<kSwiglu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), static_cast<const bf16_t*>(w3), h, d.S,
-                                d.d_ff, d.d_model, st);
-    else
-        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const bf16_t*>(w1), nullptr, h, d.S, d.d_ff, d.d_model, st);
+    auto first = [&](auto rows) {
+        const bf16_t* w1p = static_cast<const bf16_t*>(w1);
+        if (d.act == EMOE_ACT_SWIGLU)
+            return launch_one<kSwiglu>(xp, rows, offsets, w1p, static_cast<const bf16_t*>(w3), h, d.S, d.d_ff, d.d_model, st);
+        return launch_one<kRelu>(xp, rows, offsets, w1p, nullptr, h, d.S, d.d_ff, d.d_model, st);
+    };
+    if (passes & 1) e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
     if (e != hipSuccess || !(passes & 2)) return e;
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const bf16_t*>(w2), nullptr, static_cast<bf16_t*>(y_perm), d.S,
                               d.d_model, d.d_ff, st);

@@ -26,7 +26,7 @@
 #include <atomic>
 #include <type_traits>
 
-#include "common.h"
+#include "block_sort.h"
 
 namespace emoe {
 namespace {
@@ -74,8 +74,9 @@ __device__ __forceinline__ void barrier_keep_loads() {
 // Tiles are numbered slot by slot, the m-tiles of an n-tile consecutively, and dealt to the XCDs in runs of
 // kXcdRun (workgroup ids go round-robin): tiles that share weight rows share an L2, and every XCD has
 // tiles of every slot, full and half empty ones.
-template <int EPI, bool KTAIL>
-__global__ __launch_bounds__(64 * NW, 4) void grouped_gemm_f32(const float* __restrict__ a, RowGather gather,
+// Gather: SortingGather if the launch makes the permutation, else RowGather.
+template <int EPI, bool KTAIL, class Gather>
+__global__ __launch_bounds__(64 * NW, 4) void grouped_gemm_f32(const float* __restrict__ a, Gather gather,
                                                                const int32_t* __restrict__ offsets,
                                                                const float* __restrict__ b0, const float* __restrict__ b1,
                                                                float* __restrict__ c, int S, int N, int K, int n_tiles,
@@ -87,7 +88,14 @@ __global__ __launch_bounds__(64 * NW, 4) void grouped_gemm_f32(const float* __re
     const int kh = wave >> 1, wn = wave & 1;
 
     // ---- this workgroup's tile: lane s holds slot s's rows and the number of its first tile -------------
-    const int s_begin = lane < S ? offsets[lane] : 0, s_end = lane < S ? offsets[lane + 1] : 0;
+    BlockSort<NW> sorted;
+    constexpr bool sorts = Gather::kSorts;
+    if constexpr (sorts) {
+        sorted.run(gather.sort, S, reinterpret_cast<int*>(lds));
+        if (blockIdx.x == 0) sorted.store_slots(gather.sort, S);
+    }
+    const int s_begin = sorts ? sorted.begin : lane < S ? offsets[lane] : 0;
+    const int s_end = sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0;
     const int s_mtiles = (s_end - s_begin + BM - 1) / BM;
     int incl = s_mtiles * n_tiles;
 #pragma unroll
@@ -116,15 +124,23 @@ __global__ __launch_bounds__(64 * NW, 4) void grouped_gemm_f32(const float* __re
     const int l_row = lane >> 3, l_pos = lane & 7;
     const float* src[LPT];
     int chunk[LPT];
+    int* list = reinterpret_cast<int*>(lds + kSortLdsBytes);
+    if constexpr (sorts) {
+        sorted.list_rows(slot, row0, BM, list);
+        if (n0 == 0) sorted.store_rows(gather.sort, slot, row0, BM);
+        __syncthreads();
+    }
 #pragma unroll
     for (int i = 0; i < LX; ++i) {
         const int tr = (LX * wave + i) * 8 + l_row;
         chunk[i] = l_pos ^ ((tr >> 1) & 7);
         int r = row0 + tr;
         r = r < row_end ? r : row_end - 1;
-        if (gather.perm != nullptr) r = gather.perm[r] / gather.k;  // the token's row of x, not a copy of it
+        // the token's row of x, not a copy of it
+        if (gather.perm != nullptr) r = (sorts ? list[r - row0] : gather.perm[r]) / gather.k;
         src[i] = a + (size_t)r * K + chunk[i] * 4;
     }
+    if (sorts) __syncthreads();  // the list is read: the stages may be filled
     const float* wsel = (EPI == kSwiglu && wave >= NW / 2) ? b1 : b0;  // wavefronts 2, 3 load the W3 half
 #pragma unroll
     for (int i = 0; i < LW; ++i) {
@@ -253,12 +269,12 @@ __global__ __launch_bounds__(64 * NW, 4) void grouped_gemm_f32(const float* __re
     }
 }
 
-template <int EPI, bool KTAIL>
-hipError_t launch_cfg(const float* a, RowGather gather, const int32_t* offsets, const float* b0, const float* b1, float* c,
+template <int EPI, bool KTAIL, class Gather>
+hipError_t launch_cfg(const float* a, Gather gather, const int32_t* offsets, const float* b0, const float* b1, float* c,
                       long long A, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int kLds = kStages * STAGE_BYTES;
-    auto kern = grouped_gemm_f32<EPI, KTAIL>;
+    auto kern = grouped_gemm_f32<EPI, KTAIL, Gather>;
     static std::atomic<bool> attr_set{false};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -279,8 +295,8 @@ hipError_t launch_cfg(const float* a, RowGather gather, const int32_t* offsets, 
     return hipGetLastError();
 }
 
-template <int EPI>
-hipError_t launch_one(const float* a, RowGather gather, const int32_t* offsets, const float* b0, const float* b1, float* c,
+template <int EPI, class Gather>
+hipError_t launch_one(const float* a, Gather gather, const int32_t* offsets, const float* b0, const float* b1, float* c,
                       long long A, int S, int N, int K, hipStream_t st) {
     if (K % BK == 0) return launch_cfg<EPI, false>(a, gather, offsets, b0, b1, c, A, S, N, K, st);
     return launch_cfg<EPI, true>(a, gather, offsets, b0, b1, c, A, S, N, K, st);
@@ -288,18 +304,19 @@ hipError_t launch_one(const float* a, RowGather gather, const int32_t* offsets, 
 
 }  // namespace
 
-hipError_t launch_ffn_f32(const emoe_layer_desc& d, const void* x_perm, RowGather gather, const int32_t* offsets, const void* w1,
+hipError_t launch_ffn_f32(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets, const void* w1,
                           const void* w3, const void* w2, void* y_perm, void* ws, int passes, hipStream_t st) {
     const long long A = (long long)d.T * d.k;
     float* h = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + ffn_ws_layout(d).h);
     const float* xp = static_cast<const float*>(x_perm);
     hipError_t e = hipSuccess;
-    if (!(passes & 1)) {
-    } else if (d.act == EMOE_ACT_SWIGLU)
-        e = launch_one<kSwiglu>(xp, gather, offsets, static_cast<const float*>(w1), static_cast<const float*>(w3), h, A, d.S,
-                                d.d_ff, d.d_model, st);
-    else
-        e = launch_one<kRelu>(xp, gather, offsets, static_cast<const float*>(w1), nullptr, h, A, d.S, d.d_ff, d.d_model, st);
+    auto first = [&](auto rows) {
+        const float* w1p = static_cast<const float*>(w1);
+        if (d.act == EMOE_ACT_SWIGLU)
+            return launch_one<kSwiglu>(xp, rows, offsets, w1p, static_cast<const float*>(w3), h, A, d.S, d.d_ff, d.d_model, st);
+        return launch_one<kRelu>(xp, rows, offsets, w1p, nullptr, h, A, d.S, d.d_ff, d.d_model, st);
+    };
+    if (passes & 1) e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
     if (e != hipSuccess || !(passes & 2)) return e;
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const float*>(w2), nullptr,
                               static_cast<float*>(y_perm), A, d.S, d.d_model, d.d_ff, st);

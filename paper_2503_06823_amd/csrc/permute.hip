@@ -14,7 +14,7 @@
 // precondition) is left out: inv_perm = -1, and it appears in no slot.
 #include <mutex>
 
-#include "common.h"
+#include "block_sort.h"
 
 namespace emoe {
 namespace {
@@ -161,20 +161,6 @@ __global__ __launch_bounds__(kThreads) void place_kernel(const int32_t* __restri
         }
         __syncthreads();  // running[] updated before the next pass reads it and rewrites wave_cnt[]
     }
-}
-
-// The assignments of this wavefront with the same key as this lane's: the lanes that hold them.  One ballot per bit of the
-// key, not one per slot.
-static_assert(kMaxExperts == 64, "six bits of key");
-__device__ __forceinline__ unsigned long long same_key(int key) {
-    unsigned long long m = __ballot(key >= 0);
-#pragma unroll
-    for (int b = 0; b < 6; ++b) {
-        const bool bit = (key >> b) & 1;
-        const unsigned long long set = __ballot(bit);
-        m &= bit ? set : ~set;
-    }
-    return m;
 }
 
 // count + scan + place in one workgroup of 16 wavefronts, for A <= PASSES * 1024 assignments (a decode step, a few prompts):
