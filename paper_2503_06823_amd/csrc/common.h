@@ -58,7 +58,7 @@ constexpr int kPermuteChunk = 1024;  // assignments per workgroup in the countin
 PermuteWs permute_ws_layout(const emoe_layer_desc& d);
 FfnWs ffn_ws_layout(const emoe_layer_desc& d);
 
-// Which kernels the bf16 FFN runs: weight streaming (few rows per slot), tiles of 128 token rows
+// Which kernels the bf16 FFN of more than 16 tokens runs: weight streaming (few rows per slot), tiles of 128 token rows
 // (up to a few hundred rows per slot) or tiles of 256 token rows.
 enum FfnPath { kFfnStream = 0, kFfnMid = 1, kFfnTiled = 2 };
 FfnPath ffn_bf16_path(const emoe_layer_desc& d);
