@@ -259,6 +259,7 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
         // 38 / 25.  64 tokens: 64 experts, d 768 14 / 12, d 1536 16.6 / 18.6; 48 experts, d 1536 16 / 15, d 2048 17 / 18.7,
         // d 6144 25 / 46; 32 experts, d 3072 21 / 20, d 4096 21.6 / 24.7, d 6144 23.5 / 35.  300 tokens: 48 experts,
         // d 8192 54 / 60 but d 4096 37 / 32.5; 32 experts, d 4096 25.7 / 24.8, d 6144 29.7 / 35.
+        // (The matrix kernel's times are from before its top-k took a wavefront per token, 1 to 4 us less now; the lines stand.)
         // (A launch of 2^26 tokens would not fit a grid.)
         const int blocks = (d.E + 15) / 16;
         bool matrix = d.E > 8 ? d.T >= 1024 : d.E > 4 && d.T >= 4096;

@@ -3,16 +3,17 @@
 // 16 tokens computed together on the fp32 matrix instructions.
 //
 // A wavefront per token reads the whole gate matrix for every token, from L2: with 64 experts that is what
-// its time goes into (1024 tokens, d_model 768, 64 experts: 66 us; 13 us with this kernel).  Here a workgroup
+// its time goes into (1024 tokens, d_model 768, 64 experts: 66 us; 11 us with this kernel).  Here a workgroup
 // owns 16 tokens and every gate row fetched is used for all of them.  Its wavefronts - eight, or sixteen
 // with more than 32 experts (15.5 -> 14 us) - split d_model into pieces of 32 floats, loaded straight into
 // registers (a lane holds 4 consecutive floats of row lane % 16; a pair of loads covers whole 128-byte
 // lines).  The kernel is bound by the latency of that walk, hence few tokens per workgroup and many
 // wavefronts.  Partial logits meet in LDS: fp32 accumulation, summation order fixed by the code.
 //
-// Top-k: lane t of wavefront 0 scans the logits of token t in ascending expert order, k rounds, strict
-// comparison (the lower index wins a tie).  Weights are the softmax over the k winners.
-#include "common.h"
+// Top-k: a wavefront per token, lane = expert (route_topk.h); before, 16 lanes of one wavefront each scanned their token's
+// logits k times (us a launch, d_model 768, 64 experts, 1024 tokens: k = 1 12.7 -> 11.0, k = 8 26.3 -> 12.3; 300
+// tokens, d_model 512, 40 experts, k = 6 15.4 -> 7.7; 8192 tokens, d_model 2048, 64 experts, k = 6 72.7 -> 52.1).
+#include "route_topk.h"
 
 namespace emoe {
 namespace {
@@ -36,16 +37,12 @@ __global__ __launch_bounds__(64 * NW) void route_f32_kernel(const float* __restr
     constexpr int EX = EB * 16;
     __shared__ float part[SUMS][EX][LDT];
     __shared__ float logit[EX][LDT];
-    __shared__ float prob[kMaxExperts][TOK];  // [j][token]
-    __shared__ int s_hist[kMaxExperts];       // this workgroup's tokens per expert under ordinary routing
-    __shared__ int s_resident[kMaxExperts];
+    __shared__ int s_hist[kMaxExperts];  // this workgroup's tokens per expert under ordinary routing
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int t0 = blockIdx.x * TOK;
-    if (threadIdx.x < kMaxExperts) {
-        s_hist[threadIdx.x] = 0;
-        s_resident[threadIdx.x] = ((int)threadIdx.x < E && slot_of_expert[threadIdx.x] >= 0) ? 1 : 0;
-    }
+    if (threadIdx.x < kMaxExperts) s_hist[threadIdx.x] = 0;
+    const bool resident = lane < E && slot_of_expert[lane] >= 0;  // lane = expert, for the top-k
 
     // tokens past the last and experts past E repeat the last row; those logits are not looked at
     const int row = lane & 15, at = (lane >> 4) * 4;
@@ -125,65 +122,15 @@ __global__ __launch_bounds__(64 * NW) void route_f32_kernel(const float* __restr
         logit[e][t] = s + ((bias != nullptr && e < E) ? bias[e] : 0.0f);
     }
     __syncthreads();
-    if (wave > 0) return;
-
-    const bool live = lane < TOK && t0 + lane < T_;
-    const int my = lane & (TOK - 1);
-    float lg[EX];
-    unsigned long long avail = 0;  // bit e: expert e is resident and not taken yet
-#pragma unroll
-    for (int e = 0; e < EX; ++e) {
-        lg[e] = logit[e][my];
-        if (s_resident[e]) avail |= 1ull << e;
-    }
-    auto best = [&](unsigned long long left, float& bv) {
-        int be = -1;
-        bv = 0.0f;
-#pragma unroll
-        for (int e = 0; e < EX; ++e) {
-            const bool ok = (left >> e) & 1ull;
-            if (ok && (be < 0 || lg[e] > bv)) { bv = lg[e]; be = e; }
-        }
-        return be;
-    };
-    const size_t out0 = (size_t)(t0 + my) * k;
-    float top_v = 0.0f, sum = 0.0f;
-    for (int j = 0; j < k; ++j) {
-        float bv;
-        int be = best(avail, bv);
-        if (be < 0) {  // fewer than k resident experts: precondition broken, stay defined
-            be = 0;
-            bv = 0.0f;
-        } else {
-            avail &= ~(1ull << be);
-        }
-        if (j == 0) top_v = bv;
-        const float p = expf(bv - top_v);
-        sum += p;
-        if (live) {
-            topk_expert[out0 + j] = be;
-            prob[j][my] = p;
-        }
-    }
-    if (live)
-        for (int j = 0; j < k; ++j) topk_weight[out0 + j] = prob[j][my] / sum;
-
-    // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all E experts,
-    // resident or not; integer counts, so the accumulated result does not depend on order.
+#pragma unroll 1
+    for (int t = wave; t < TOK && t0 + t < T_; t += NW)
+        top_k<EX>(logit[lane < EX ? lane : EX - 1][t], resident, E, k, (size_t)(t0 + t) * k, topk_expert, topk_weight,
+                  expert_tokens != nullptr ? s_hist : nullptr);
     if (expert_tokens == nullptr) return;
-    unsigned long long left = E >= 64 ? ~0ull : (1ull << E) - 1ull;
-    for (int j = 0; j < k; ++j) {
-        float bv;
-        const int be = best(left, bv);
-        if (be >= 0) left &= ~(1ull << be);
-        if (live && be >= 0) atomicAdd(&s_hist[be], 1);
-    }
-    // one wavefront: its LDS operations complete in program order
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-    __builtin_amdgcn_wave_barrier();
-    if (lane < E) {
-        const int n = s_hist[lane];
-        if (n > 0) atomicAdd(&expert_tokens[lane], (unsigned long long)n);
+    __syncthreads();
+    if ((int)threadIdx.x < E) {
+        const int n = s_hist[threadIdx.x];
+        if (n > 0) atomicAdd(&expert_tokens[threadIdx.x], (unsigned long long)n);
     }
 }
 

@@ -20,14 +20,10 @@
 // The partial sums of a logit meet in LDS and are added as a tree: fp32 accumulation, summation
 // order fixed by the code.
 //
-// Top-k: a wavefront per token, lane = expert: k rounds of a maximum over the lanes (DPP), the lowest lane
-// that holds it wins.  The logits are compared as integers of the same order, so that every round has
-// one winner whatever they are; a NaN comes after all numbers.  (With 64 experts and k = 6 the scan of 32 logits per lane
-// that this replaces took some 9 us of a launch.)  Weights are the softmax over the k winners.
+// Top-k: a wavefront per token, lane = expert (route_topk.h).
 #include <atomic>
-#include <type_traits>
 
-#include "common.h"
+#include "route_topk.h"
 
 namespace emoe {
 namespace {
@@ -66,22 +62,6 @@ struct Shape {
     static_assert(SUM_BYTES + kMaxExperts * (int)sizeof(int) <= LDS && LDS <= kLdsBytes, "LDS of one CU");
     static_assert((DEPTH - 1) * LOADS < 64, "vmcnt counts at most 63 loads");
 };
-
-// The largest of the values that lanes 0 .. EX-1 hold, in all lanes; 0 where a lane takes no part.
-template <int EX>
-__device__ __forceinline__ uint32_t max_over_experts(uint32_t v) {
-    auto with = [&](auto ctrl) {
-        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
-        v = v > o ? v : o;
-    };
-    with(std::integral_constant<int, 0x111>{});  // row_shr:1, 2, 4, 8: lane 15 of every 16 holds their largest
-    with(std::integral_constant<int, 0x112>{});
-    with(std::integral_constant<int, 0x114>{});
-    with(std::integral_constant<int, 0x118>{});
-    if (EX > 16) with(std::integral_constant<int, 0x142>{});  // row_bcast:15
-    if (EX > 32) with(std::integral_constant<int, 0x143>{});  // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, EX > 32 ? 63 : EX - 1);
-}
 
 // EB: blocks of 16 experts.  TB: blocks of 16 tokens.
 template <int EB, int TB>
@@ -207,41 +187,7 @@ __global__ __launch_bounds__(64 * NW) void route_mfma_kernel(const bf16_t* __res
 #pragma unroll
             for (int w = 0; w < n; ++w) s[w] += s[w + n];
         const float logit = s[0] + lane_bias;
-        // the logit as an integer of the same order, 1 for a NaN; -0 and +0 are equal
-        const int bits = __float_as_int(logit + 0.0f);
-        const uint32_t order = logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
-        const int t = t0 + tt;
-        uint32_t left = resident ? order : 0u;
-        int top_v = 0, sel_v = 0, sel_e = 0;  // lane j: the j-th winner
-        for (int j = 0; j < k; ++j) {
-            const uint32_t best = max_over_experts<EX>(left);
-            // fewer than k resident experts: precondition broken, stay defined
-            const int je = best ? __builtin_ctzll(__ballot(left == best)) : 0;
-            const int jv = best ? __builtin_amdgcn_readlane(__float_as_int(logit), je) : 0;
-            left = lane == je ? 0u : left;
-            if (j == 0) top_v = jv;
-            if (lane == j) { sel_v = jv; sel_e = je; }
-        }
-        const float prob = expf(__int_as_float(sel_v) - __int_as_float(top_v));
-        float sum = 0.0f;
-        for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(prob), j));
-        if (lane < k) {
-            topk_expert[(size_t)t * k + lane] = sel_e;
-            topk_weight[(size_t)t * k + lane] = prob / sum;
-        }
-        // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all E
-        // experts, resident or not; integer counts, so the accumulated result does not depend on order.
-        if (expert_tokens != nullptr) {
-            left = lane < E ? order : 0u;
-            bool mine = false;
-            for (int j = 0; j < k; ++j) {
-                const uint32_t best = max_over_experts<EX>(left);
-                const bool wins = lane == __builtin_ctzll(__ballot(left == best));  // k <= E: best > 0
-                left = wins ? 0u : left;
-                mine |= wins;
-            }
-            if (mine) atomicAdd(&s_hist[lane], 1);
-        }
+        top_k<EX>(logit, resident, E, k, (size_t)(t0 + tt) * k, topk_expert, topk_weight, expert_tokens != nullptr ? s_hist : nullptr);
     }
     if (expert_tokens == nullptr) return;
     __syncthreads();

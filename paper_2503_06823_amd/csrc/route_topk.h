@@ -1,0 +1,72 @@
+// Resident-restricted top-k of one token by one wavefront, lane = expert (eMoE Section 3.2.2), shared by the matrix-instruction
+// gates: k rounds of a maximum over the lanes (DPP), the lowest lane that holds it wins.  The logits are compared as integers
+// of the same order, so that every round has one winner whatever they are; a NaN comes after all numbers.  (With 64 experts
+// and k = 6 a scan of 32 logits per lane, k times, took some 9 us of a bf16 gate's launch.)  Weights are the softmax
+// over the k winners.
+#pragma once
+#include <type_traits>
+
+#include "common.h"
+
+namespace emoe {
+namespace {
+
+// The largest of the values that lanes 0 .. EX-1 hold, in all lanes; 0 where a lane takes no part.
+template <int EX>
+__device__ __forceinline__ uint32_t max_over_experts(uint32_t v) {
+    auto with = [&](auto ctrl) {
+        const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
+        v = v > o ? v : o;
+    };
+    with(std::integral_constant<int, 0x111>{});  // row_shr:1, 2, 4, 8: lane 15 of every 16 holds their largest
+    with(std::integral_constant<int, 0x112>{});
+    with(std::integral_constant<int, 0x114>{});
+    with(std::integral_constant<int, 0x118>{});
+    if (EX > 16) with(std::integral_constant<int, 0x142>{});  // row_bcast:15
+    if (EX > 32) with(std::integral_constant<int, 0x143>{});  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, EX > 32 ? 63 : EX - 1);
+}
+
+// out0: the token's place in the outputs.  hist: the workgroup's tokens per expert (LDS), or nullptr.
+template <int EX>
+__device__ __forceinline__ void top_k(float logit, bool resident, int E, int k, size_t out0, int32_t* __restrict__ topk_expert,
+                                      float* __restrict__ topk_weight, int* hist) {
+    const int lane = threadIdx.x & 63;
+    // the logit as an integer of the same order, 1 for a NaN; -0 and +0 are equal
+    const int bits = __float_as_int(logit + 0.0f);
+    const uint32_t order = logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
+    uint32_t left = resident ? order : 0u;
+    int top_v = 0, sel_v = 0, sel_e = 0;  // lane j: the j-th winner
+    for (int j = 0; j < k; ++j) {
+        const uint32_t best = max_over_experts<EX>(left);
+        // fewer than k resident experts: precondition broken, stay defined
+        const int je = best ? __builtin_ctzll(__ballot(left == best)) : 0;
+        const int jv = best ? __builtin_amdgcn_readlane(__float_as_int(logit), je) : 0;
+        left = lane == je ? 0u : left;
+        if (j == 0) top_v = jv;
+        if (lane == j) { sel_v = jv; sel_e = je; }
+    }
+    const float prob = expf(__int_as_float(sel_v) - __int_as_float(top_v));
+    float sum = 0.0f;
+    for (int j = 0; j < k; ++j) sum += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(prob), j));
+    if (lane < k) {
+        topk_expert[out0 + lane] = sel_e;
+        topk_weight[out0 + lane] = prob / sum;
+    }
+    // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all E
+    // experts, resident or not; integer counts, so the accumulated result does not depend on order.
+    if (hist != nullptr) {
+        left = lane < E ? order : 0u;
+        bool mine = false;
+        for (int j = 0; j < k; ++j) {
+            const uint32_t best = max_over_experts<EX>(left);
+            const bool wins = lane == __builtin_ctzll(__ballot(left == best));  // k <= E: best > 0
+            left = wins ? 0u : left;
+            mine |= wins;
+        }
+        if (mine) atomicAdd(&hist[lane], 1);
+    }
+}
+
+}  // namespace
+}  // namespace emoe
