@@ -34,9 +34,10 @@ constexpr int kSortLdsBytes = kSortShares * kMaxExperts * (int)sizeof(int);     
 template <int WAVES>
 struct BlockSort {
     static constexpr int PASSES = kSortShares / WAVES;
-    int begin, end;    // lane s: rows of slot s
-    int key[PASSES];   // slot of assignment assignment(p), -1: none
-    int row[PASSES];   // its row
+    int begin, end;     // lane s: rows of slot s
+    // slot << 16 | row of assignment assignment(p), -1: none.  One register an assignment: they live until the rows are listed,
+    // and slot and row apart spilled the fp32 SwiGLU product, which holds 128 registers.
+    int place[PASSES];
 
     __device__ static int assignment(int p) { return p * WAVES * 64 + (int)threadIdx.x; }
 
@@ -45,7 +46,7 @@ struct BlockSort {
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
         const unsigned long long below = (1ull << lane) - 1ull;
         const int slot_of_lane = lane < t.E ? t.slot_of_expert[lane] : -1;
-        int e[PASSES], rank[PASSES];
+        int e[PASSES], key[PASSES], rank[PASSES];
 #pragma unroll
         for (int p = 0; p < PASSES; ++p) e[p] = assignment(p) < t.A ? t.topk_expert[assignment(p)] : -1;
 #pragma unroll
@@ -84,7 +85,10 @@ struct BlockSort {
         begin = incl - total;
         end = incl;
 #pragma unroll
-        for (int p = 0; p < PASSES; ++p) row[p] = __shfl(begin + before[p], key[p] & 63) + rank[p];
+        for (int p = 0; p < PASSES; ++p) {
+            const int row = __shfl(begin + before[p], key[p] & 63) + rank[p];
+            place[p] = key[p] >= 0 ? key[p] << 16 | row : -1;
+        }
     }
 
     // By one workgroup of the launch: the slots' sizes and offsets, and the assignments without a resident expert (only
@@ -100,16 +104,17 @@ struct BlockSort {
         }
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            if (key[p] < 0 && assignment(p) < t.A) t.inv_perm[assignment(p)] = -1;
+            if (place[p] < 0 && assignment(p) < t.A) t.inv_perm[assignment(p)] = -1;
     }
 
     // By one workgroup per tile of rows: the entries of rows row0 .. row0 + n - 1 of `slot`.
     __device__ __forceinline__ void store_rows(const SortTables& t, int slot, int row0, int n) const {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            if (key[p] == slot && row[p] >= row0 && row[p] < row0 + n) {
-                t.perm[row[p]] = assignment(p);
-                t.inv_perm[assignment(p)] = row[p];
+            if (at(p, slot, row0) < (unsigned)n) {
+                const int row = place[p] & 0xffff;
+                t.perm[row] = assignment(p);
+                t.inv_perm[assignment(p)] = row;
             }
     }
 
@@ -117,8 +122,11 @@ struct BlockSort {
     __device__ __forceinline__ void list_rows(int slot, int row0, int n, int* list) const {
 #pragma unroll
         for (int p = 0; p < PASSES; ++p)
-            if (key[p] == slot && row[p] >= row0 && row[p] < row0 + n) list[row[p] - row0] = assignment(p);
+            if (at(p, slot, row0) < (unsigned)n) list[at(p, slot, row0)] = assignment(p);
     }
+
+    // Where assignment(p) is among the rows of `slot` from row0 on; past all of them if it is none of these.
+    __device__ __forceinline__ unsigned at(int p, int slot, int row0) const { return (unsigned)(place[p] - (slot << 16 | row0)); }
 };
 
 }  // namespace
