@@ -86,7 +86,8 @@ int emoe_workspace_bytes(const emoe_layer_desc *desc, size_t *permute_ws_bytes, 
  * result of a token is a list of k expert indices).
  *   logit[t,e] = sum_i x[t,i] * w_gate[e,i] (+ gate_bias[e]), fp32 accumulation.
  *   Among experts with slot_of_expert[e] >= 0, the k largest logits in descending
- *   order (ties: lower expert index) -> topk_expert[t,0..k-1] (expert ids).
+ *   order (ties: lower expert index; a NaN comes after all numbers, -inf included)
+ *   -> topk_expert[t,0..k-1] (expert ids).
  *   topk_weight[t,j] = softmax over those k logits (fp32; sums to 1).
  * x [T,d] dev, w_gate [E,d] dev, gate_bias [E] fp32 dev or NULL,
  * slot_of_expert [E] int32 dev (-1 = not resident),

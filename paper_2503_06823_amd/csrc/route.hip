@@ -16,7 +16,7 @@
 // The summation order is fixed by the code, so results are reproducible run to run.
 #include <type_traits>
 
-#include "common.h"
+#include "route_topk.h"
 
 namespace emoe {
 namespace {
@@ -146,13 +146,24 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
         logit += my_bias;
 
         // Every lane of a group holds its expert's logit.  One lane per expert is read into scalar
-        // registers, so that the k rounds of "largest logit among the resident experts not taken yet,
+        // registers, as an integer of the same order (a NaN comes after all numbers, as in the matrix kernels),
+        // so that the k rounds of "largest logit among the resident experts not taken yet,
         // lower index on a tie" are plain compares on values every lane already has - no exchange
         // between lanes, whose latency would otherwise be paid 18 times per round.
-        float lg[EP];
+        const uint32_t my_order = logit_order(logit);
+        uint32_t order[EP];
 #pragma unroll
-        for (int e = 0; e < EP; ++e)
-            lg[e] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(logit), e * (64 / EP)));
+        for (int e = 0; e < EP; ++e) order[e] = (uint32_t)__builtin_amdgcn_readlane((int)my_order, e * (64 / EP));
+        auto best_of = [&](unsigned long long left) {  // -1: none left
+            uint32_t best = 0;
+            int be = -1;
+#pragma unroll
+            for (int e = 0; e < EP; ++e) {
+                const bool ok = (left >> e) & 1ull;
+                if (ok && order[e] > best) { best = order[e]; be = e; }
+            }
+            return be;
+        };
         const unsigned long long res_lanes = __ballot(resident);
         unsigned long long avail = 0;  // bit e: expert e is resident and not taken yet
 #pragma unroll
@@ -160,13 +171,8 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
         float sel_v = 0.0f, top_v = 0.0f, sum = 0.0f;
         int sel_e = 0;
         for (int j = 0; j < k; ++j) {
-            float bv = 0.0f;
-            int be = -1;
-#pragma unroll
-            for (int e = 0; e < EP; ++e) {
-                const bool ok = (avail >> e) & 1ull;
-                if (ok && (be < 0 || lg[e] > bv)) { bv = lg[e]; be = e; }
-            }
+            int be = best_of(avail);
+            float bv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(logit), (be < 0 ? 0 : be) * (64 / EP)));
             if (be < 0) {  // fewer than k resident experts: precondition broken, stay defined
                 be = 0;
                 bv = 0.0f;
@@ -187,13 +193,7 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
             unsigned long long left = E >= 64 ? ~0ull : (1ull << E) - 1ull;
             int obs_e = -1;
             for (int j = 0; j < k; ++j) {
-                float bv = 0.0f;
-                int be = -1;
-#pragma unroll
-                for (int e = 0; e < EP; ++e) {
-                    const bool ok = (left >> e) & 1ull;
-                    if (ok && (be < 0 || lg[e] > bv)) { bv = lg[e]; be = e; }
-                }
+                const int be = best_of(left);
                 if (be >= 0) left &= ~(1ull << be);
                 if (lane == j) obs_e = be;
             }

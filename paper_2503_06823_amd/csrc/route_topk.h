@@ -1,8 +1,8 @@
 // Resident-restricted top-k of one token by one wavefront, lane = expert (eMoE Section 3.2.2), shared by the matrix-instruction
 // gates: k rounds of a maximum over the lanes (DPP), the lowest lane that holds it wins.  The logits are compared as integers
-// of the same order, so that every round has one winner whatever they are; a NaN comes after all numbers.  (With 64 experts
-// and k = 6 a scan of 32 logits per lane, k times, took some 9 us of a bf16 gate's launch.)  Weights are the softmax
-// over the k winners.
+// of the same order (in the wavefront kernel's rounds too), so that every round has one winner whatever they are; a NaN comes
+// after all numbers.  (With 64 experts and k = 6 a scan of 32 logits per lane, k times, took some 9 us of a bf16 gate's
+// launch.)  Weights are the softmax over the k winners.
 #pragma once
 #include <type_traits>
 
@@ -10,6 +10,12 @@
 
 namespace emoe {
 namespace {
+
+// The logit as an integer of the same order, above 0: 1 for a NaN; -0 and +0 are equal.
+__device__ __forceinline__ uint32_t logit_order(float logit) {
+    const int bits = __float_as_int(logit + 0.0f);
+    return logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
+}
 
 // The largest of the values that lanes 0 .. EX-1 hold, in all lanes; 0 where a lane takes no part.
 template <int EX>
@@ -32,9 +38,7 @@ template <int EX>
 __device__ __forceinline__ void top_k(float logit, bool resident, int E, int k, size_t out0, int32_t* __restrict__ topk_expert,
                                       float* __restrict__ topk_weight, int* hist) {
     const int lane = threadIdx.x & 63;
-    // the logit as an integer of the same order, 1 for a NaN; -0 and +0 are equal
-    const int bits = __float_as_int(logit + 0.0f);
-    const uint32_t order = logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
+    const uint32_t order = logit_order(logit);
     uint32_t left = resident ? order : 0u;
     int top_v = 0, sel_v = 0, sel_e = 0;  // lane j: the j-th winner
     for (int j = 0; j < k; ++j) {
