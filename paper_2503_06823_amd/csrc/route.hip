@@ -10,9 +10,8 @@
 // split the d_model axis (16 bytes per lane per step, so a step reads 1 KiB of the token row
 // contiguously); every lane keeps one
 // partial sum per expert.  A butterfly reduce-scatter then leaves expert e's complete logit in
-// lanes e*(64/EP) .. +64/EP-1: 63 shuffles for 64 experts instead of 64 full reductions.  The logits
-// are then read into scalar registers and top-k is k rounds of compares that every lane performs
-// on the same values (lower index wins a tie); softmax over the k winners.
+// lanes e*(64/EP) .. +64/EP-1: 63 shuffles for 64 experts instead of 64 full reductions.  Top-k: route_topk.h, a group of
+// lanes = expert.
 // The summation order is fixed by the code, so results are reproducible run to run.
 #include <type_traits>
 
@@ -145,60 +144,7 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
         if (!live) continue;
         logit += my_bias;
 
-        // Every lane of a group holds its expert's logit.  One lane per expert is read into scalar
-        // registers, as an integer of the same order (a NaN comes after all numbers, as in the matrix kernels),
-        // so that the k rounds of "largest logit among the resident experts not taken yet,
-        // lower index on a tie" are plain compares on values every lane already has - no exchange
-        // between lanes, whose latency would otherwise be paid 18 times per round.
-        const uint32_t my_order = logit_order(logit);
-        uint32_t order[EP];
-#pragma unroll
-        for (int e = 0; e < EP; ++e) order[e] = (uint32_t)__builtin_amdgcn_readlane((int)my_order, e * (64 / EP));
-        auto best_of = [&](unsigned long long left) {  // -1: none left
-            uint32_t best = 0;
-            int be = -1;
-#pragma unroll
-            for (int e = 0; e < EP; ++e) {
-                const bool ok = (left >> e) & 1ull;
-                if (ok && order[e] > best) { best = order[e]; be = e; }
-            }
-            return be;
-        };
-        const unsigned long long res_lanes = __ballot(resident);
-        unsigned long long avail = 0;  // bit e: expert e is resident and not taken yet
-#pragma unroll
-        for (int e = 0; e < EP; ++e) avail |= ((res_lanes >> (e * (64 / EP))) & 1ull) << e;
-        float sel_v = 0.0f, top_v = 0.0f, sum = 0.0f;
-        int sel_e = 0;
-        for (int j = 0; j < k; ++j) {
-            int be = best_of(avail);
-            float bv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(logit), (be < 0 ? 0 : be) * (64 / EP)));
-            if (be < 0) {  // fewer than k resident experts: precondition broken, stay defined
-                be = 0;
-                bv = 0.0f;
-            } else {
-                avail &= ~(1ull << be);
-            }
-            if (j == 0) top_v = bv;
-            sum += expf(bv - top_v);
-            if (lane == j) { sel_v = bv; sel_e = be; }
-        }
-        if (lane < k) {
-            topk_expert[(size_t)t * k + lane] = sel_e;
-            topk_weight[(size_t)t * k + lane] = expf(sel_v - top_v) / sum;
-        }
-        // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over
-        // all E experts, resident or not.  Integer counts: the accumulated result has no order.
-        if (expert_tokens != nullptr) {
-            unsigned long long left = E >= 64 ? ~0ull : (1ull << E) - 1ull;
-            int obs_e = -1;
-            for (int j = 0; j < k; ++j) {
-                const int be = best_of(left);
-                if (be >= 0) left &= ~(1ull << be);
-                if (lane == j) obs_e = be;
-            }
-            if (lane < k && obs_e >= 0) atomicAdd(&expert_tokens[obs_e], 1ull);
-        }
+        top_k<EP, 64 / EP>(logit, resident, E, k, (size_t)t * k, topk_expert, topk_weight, expert_tokens);
     }
 }
 

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * NW) void route_f32_kernel(const float* __restr
     __syncthreads();
 #pragma unroll 1
     for (int t = wave; t < TOK && t0 + t < T_; t += NW)
-        top_k<EX>(logit[lane < EX ? lane : EX - 1][t], resident, E, k, (size_t)(t0 + t) * k, topk_expert, topk_weight,
+        top_k<EX, 1>(logit[lane < EX ? lane : EX - 1][t], resident, E, k, (size_t)(t0 + t) * k, topk_expert, topk_weight,
                   expert_tokens != nullptr ? s_hist : nullptr);
     if (expert_tokens == nullptr) return;
     __syncthreads();

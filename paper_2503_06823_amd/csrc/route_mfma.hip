@@ -187,7 +187,7 @@ __global__ __launch_bounds__(64 * NW) void route_mfma_kernel(const bf16_t* __res
 #pragma unroll
             for (int w = 0; w < n; ++w) s[w] += s[w + n];
         const float logit = s[0] + lane_bias;
-        top_k<EX>(logit, resident, E, k, (size_t)(t0 + tt) * k, topk_expert, topk_weight, expert_tokens != nullptr ? s_hist : nullptr);
+        top_k<EX, 1>(logit, resident, E, k, (size_t)(t0 + tt) * k, topk_expert, topk_weight, expert_tokens != nullptr ? s_hist : nullptr);
     }
     if (expert_tokens == nullptr) return;
     __syncthreads();

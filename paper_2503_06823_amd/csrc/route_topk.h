@@ -1,8 +1,8 @@
-// Resident-restricted top-k of one token by one wavefront, lane = expert (eMoE Section 3.2.2), shared by the matrix-instruction
-// gates: k rounds of a maximum over the lanes (DPP), the lowest lane that holds it wins.  The logits are compared as integers
-// of the same order (in the wavefront kernel's rounds too), so that every round has one winner whatever they are; a NaN comes
-// after all numbers.  (With 64 experts and k = 6 a scan of 32 logits per lane, k times, took some 9 us of a bf16 gate's
-// launch.)  Weights are the softmax over the k winners.
+// Resident-restricted top-k of one token by one wavefront, a lane or a group of lanes = expert (eMoE Section 3.2.2), shared by
+// all gates: k rounds of a maximum over the lanes (DPP), the lowest lane that holds it wins.  The logits are compared as
+// integers of the same order, so that every round has one winner whatever they are; a NaN comes after all numbers.  (With 64
+// experts and k = 6 a scan of 32 logits per lane, k times, took some 9 us of a bf16 gate's launch.)  Weights are the softmax
+// over the k winners.
 #pragma once
 #include <type_traits>
 
@@ -17,38 +17,41 @@ __device__ __forceinline__ uint32_t logit_order(float logit) {
     return logit != logit ? 1u : bits < 0 ? ~(uint32_t)bits : (uint32_t)bits | 0x80000000u;
 }
 
-// The largest of the values that lanes 0 .. EX-1 hold, in all lanes; 0 where a lane takes no part.
-template <int EX>
-__device__ __forceinline__ uint32_t max_over_experts(uint32_t v) {
+// The largest of the values that lanes 0 .. LANES-1 hold, GROUP neighbours the same one, in all lanes; 0 where a lane takes no
+// part.
+template <int LANES, int GROUP>
+__device__ __forceinline__ uint32_t max_over_lanes(uint32_t v) {
     auto with = [&](auto ctrl) {
         const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, 0xf, 0xf, true);
         v = v > o ? v : o;
     };
-    with(std::integral_constant<int, 0x111>{});  // row_shr:1, 2, 4, 8: lane 15 of every 16 holds their largest
-    with(std::integral_constant<int, 0x112>{});
-    with(std::integral_constant<int, 0x114>{});
-    with(std::integral_constant<int, 0x118>{});
-    if (EX > 16) with(std::integral_constant<int, 0x142>{});  // row_bcast:15
-    if (EX > 32) with(std::integral_constant<int, 0x143>{});  // row_bcast:31
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, EX > 32 ? 63 : EX - 1);
+    // row_shr:1, 2, 4, 8: lane 15 of every 16 holds their largest
+    if (GROUP < 2) with(std::integral_constant<int, 0x111>{});
+    if (GROUP < 4) with(std::integral_constant<int, 0x112>{});
+    if (GROUP < 8) with(std::integral_constant<int, 0x114>{});
+    if (GROUP < 16) with(std::integral_constant<int, 0x118>{});
+    if (LANES > 16 && GROUP < 32) with(std::integral_constant<int, 0x142>{});  // row_bcast:15
+    if (LANES > 32 && GROUP < 64) with(std::integral_constant<int, 0x143>{});  // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, LANES > 32 ? 63 : LANES - 1);
 }
 
-// out0: the token's place in the outputs.  hist: the workgroup's tokens per expert (LDS), or nullptr.
-template <int EX>
+// Lanes e * GROUP .. e * GROUP + GROUP - 1 hold expert e's logit and whether it is resident.  out0: the token's place in the
+// outputs.  workload: tokens per expert (the workgroup's in LDS, or the layer's in memory), or nullptr.
+template <int EX, int GROUP, class Count>
 __device__ __forceinline__ void top_k(float logit, bool resident, int E, int k, size_t out0, int32_t* __restrict__ topk_expert,
-                                      float* __restrict__ topk_weight, int* hist) {
+                                      float* __restrict__ topk_weight, Count* workload) {
     const int lane = threadIdx.x & 63;
     const uint32_t order = logit_order(logit);
     uint32_t left = resident ? order : 0u;
     int top_v = 0, sel_v = 0, sel_e = 0;  // lane j: the j-th winner
     for (int j = 0; j < k; ++j) {
-        const uint32_t best = max_over_experts<EX>(left);
+        const uint32_t best = max_over_lanes<EX * GROUP, GROUP>(left);
         // fewer than k resident experts: precondition broken, stay defined
-        const int je = best ? __builtin_ctzll(__ballot(left == best)) : 0;
-        const int jv = best ? __builtin_amdgcn_readlane(__float_as_int(logit), je) : 0;
-        left = lane == je ? 0u : left;
+        const int jl = best ? __builtin_ctzll(__ballot(left == best)) : 0;  // a group's first lane
+        const int jv = best ? __builtin_amdgcn_readlane(__float_as_int(logit), jl) : 0;
+        left = lane / GROUP == jl / GROUP ? 0u : left;
         if (j == 0) top_v = jv;
-        if (lane == j) { sel_v = jv; sel_e = je; }
+        if (lane == j) { sel_v = jv; sel_e = jl / GROUP; }
     }
     const float prob = expf(__int_as_float(sel_v) - __int_as_float(top_v));
     float sum = 0.0f;
@@ -59,16 +62,16 @@ __device__ __forceinline__ void top_k(float logit, bool resident, int E, int k, 
     }
     // Workload (Section 3.2.2: the number of tokens an expert receives): the same k rounds over all E
     // experts, resident or not; integer counts, so the accumulated result does not depend on order.
-    if (hist != nullptr) {
-        left = lane < E ? order : 0u;
+    if (workload != nullptr) {
+        left = lane / GROUP < E ? order : 0u;
         bool mine = false;
         for (int j = 0; j < k; ++j) {
-            const uint32_t best = max_over_experts<EX>(left);
-            const bool wins = lane == __builtin_ctzll(__ballot(left == best));  // k <= E: best > 0
-            left = wins ? 0u : left;
-            mine |= wins;
+            const uint32_t best = max_over_lanes<EX * GROUP, GROUP>(left);
+            const int jl = __builtin_ctzll(__ballot(left == best));  // k <= E: best > 0
+            left = lane / GROUP == jl / GROUP ? 0u : left;
+            mine |= lane == jl;
         }
-        if (mine) atomicAdd(&hist[lane], 1);
+        if (mine) atomicAdd(&workload[lane / GROUP], (Count)1);
     }
 }
 
