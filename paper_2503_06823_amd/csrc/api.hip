@@ -83,7 +83,7 @@ PermuteWs permute_ws_layout(const emoe_layer_desc& d) {
 namespace {
 constexpr long long kStreamRowsPerSlot = 22;
 constexpr int kSortRounds = 4;  // see first_product_sorts()
-constexpr int kFewTokens = 16;  // one tile of tokens of the few-token kernel; such a layer has at most 16 rows per slot
+constexpr int kFewTokens = 16;  // one tile of tokens of the few-token kernel
 constexpr long long kMidRowsPerSlot = 100;
 // A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
 // fill the chip, not by the weight stream, and around 256 rows per slot the 128-row tiles fill it
@@ -135,7 +135,14 @@ FfnPath ffn_bf16_path(const emoe_layer_desc& d) {
     return kFfnTiled;
 }
 
-// The size goes by the rows per slot and the weights, not by the kernel that ffn_bf16_path() picks among those that fit
+// Up to 16 tokens one tile of tokens holds every slot's rows (emoe_route gives a token k different experts; a caller's own
+// assignments may leave more in a slot, which costs it another pass over its weights).
+FfnPath ffn_path(const emoe_layer_desc& d) {
+    if (d.dtype == EMOE_F32) return kFfnF32;
+    return d.T <= kFewTokens ? kFfnFew : ffn_bf16_path(d);
+}
+
+// The size goes by the rows per slot and the weights, not by the kernel that ffn_path() picks among those that fit
 // it: callers keep it.
 FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
     FfnWs w;
@@ -233,17 +240,17 @@ static int expert_ffn_passes(const emoe_layer_desc* desc, int passes, const void
     if (desc->T == 0) return EMOE_OK;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const SortingGather gather{{perm, desc->k, desc->T, out_perm}, sort};  // perm == nullptr: x_perm holds the grouped rows themselves
-    hipError_t e;
-    if (desc->dtype == EMOE_F32)
-        e = launch_ffn_f32(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
-    else if (desc->T <= kFewTokens)
-        e = launch_ffn_bf16_few(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
-    else if (ffn_bf16_path(*desc) == kFfnStream)
-        e = launch_ffn_bf16_stream(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
-    else if (ffn_bf16_path(*desc) == kFfnMid)
-        e = launch_ffn_bf16_mid(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
-    else
-        e = launch_ffn_bf16_tiled(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
+    hipError_t e = hipErrorInvalidValue;
+    switch (ffn_path(*desc)) {
+        case kFfnF32: e = launch_ffn_f32(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st); break;
+        case kFfnFew: e = launch_ffn_bf16_few(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st); break;
+        case kFfnStream: e = launch_ffn_bf16_stream(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st); break;
+        case kFfnMid: e = launch_ffn_bf16_mid(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st); break;
+        case kFfnTiled:
+            if (sort.A > 0) return EMOE_ERR_DEVICE;  // this kernel does not sort: first_product_sorts() never asks for it
+            e = launch_ffn_bf16_tiled(*desc, x_perm, gather, slot_offsets, w1_slots, w3_slots, w2_slots, y_perm, ws, passes, st);
+            break;
+    }
     return e == hipSuccess ? EMOE_OK : EMOE_ERR_DEVICE;
 }
 
@@ -330,20 +337,24 @@ static bool first_product_sorts(const emoe_layer_desc& d) {
     const long long slots = A < d.S ? A : d.S;
     auto column_tiles = [&](int rows) { return (d.d_ff + (swiglu ? rows / 2 : rows) - 1) / (swiglu ? rows / 2 : rows); };
     long long workgroups, at_once;
-    if (d.dtype == EMOE_F32) {
-        workgroups = (A / 32 + slots) * column_tiles(64);
-        at_once = 4 * shape.cus;
-    } else if (d.T <= kFewTokens) {
-        workgroups = slots * column_tiles(32);
-        at_once = 2 * shape.cus;
-    } else if (ffn_bf16_path(d) == kFfnStream) {
-        workgroups = d.S * (long long)column_tiles(64);
-        at_once = 2 * shape.cus;
-    } else if (ffn_bf16_path(d) == kFfnMid) {
-        workgroups = (A / 128 + slots) * column_tiles(256);
-        at_once = shape.cus;
-    } else {
-        return false;
+    switch (ffn_path(d)) {
+        case kFfnF32:
+            workgroups = (A / 32 + slots) * column_tiles(64);
+            at_once = 4 * shape.cus;
+            break;
+        case kFfnFew:
+            workgroups = slots * column_tiles(32);
+            at_once = 2 * shape.cus;
+            break;
+        case kFfnStream:
+            workgroups = d.S * (long long)column_tiles(64);
+            at_once = 2 * shape.cus;
+            break;
+        case kFfnMid:
+            workgroups = (A / 128 + slots) * column_tiles(256);
+            at_once = shape.cus;
+            break;
+        default: return false;
     }
     const long long passes = (A + 255) / 256;
     return passes * workgroups <= kSortRounds * at_once;

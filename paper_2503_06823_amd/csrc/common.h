@@ -58,9 +58,11 @@ constexpr int kPermuteChunk = 1024;  // assignments per workgroup in the countin
 PermuteWs permute_ws_layout(const emoe_layer_desc& d);
 FfnWs ffn_ws_layout(const emoe_layer_desc& d);
 
-// Which kernels the bf16 FFN of more than 16 tokens runs: weight streaming (few rows per slot), tiles of 128 token rows
-// (up to a few hundred rows per slot) or tiles of 256 token rows.
-enum FfnPath { kFfnStream = 0, kFfnMid = 1, kFfnTiled = 2 };
+// Which kernels a layer's FFN runs: fp32, or for bf16 those of up to 16 tokens, weight streaming (few rows per slot), tiles of
+// 128 token rows (up to a few hundred rows per slot) or tiles of 256 token rows.  The last three by the rows per slot alone:
+// ffn_bf16_path().
+enum FfnPath { kFfnStream = 0, kFfnMid = 1, kFfnTiled = 2, kFfnFew = 3, kFfnF32 = 4 };
+FfnPath ffn_path(const emoe_layer_desc& d);
 FfnPath ffn_bf16_path(const emoe_layer_desc& d);
 
 // Host-side checks common to the entry points; returns EMOE_OK or an error.

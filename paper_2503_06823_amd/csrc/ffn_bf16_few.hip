@@ -1,6 +1,7 @@
 // Expert FFN for bf16 layers of at most 16 tokens (a decode step of a few users; eMoE Section 5.1: fewer experts means
-// fewer global-memory reads): no more slots than assignments receive rows, each at most 16, and the cost is reading those slots'
-// weights from HBM once, or, for small layers, the latency of one walk along K.
+// fewer global-memory reads): no more slots than assignments receive rows, each at most 16 (a token's k experts are
+// different; a caller's own assignments may put more into a slot, 16 per pass over its weights), and the cost is reading those
+// slots' weights from HBM once, or, for small layers, the latency of one walk along K.
 //
 // A workgroup owns 32 weight rows of one slot (SwiGLU: 16 rows of W1 and the same 16 of W3), 16 where 32 would leave
 // half the CUs without any, or 64 where the walks are short and the workgroups many.  Its wavefronts share K in pieces

@@ -45,13 +45,18 @@ def desc_of(cfg: gen.LayerConfig):
     return P.make_desc(cfg.T, cfg.d_model, cfg.d_ff, cfg.E, cfg.k, cfg.slots, cfg.dtype, cfg.act)
 
 
-STREAM, MID, TILED = 0, 1, 2
+STREAM, MID, TILED, FEW, F32 = 0, 1, 2, 3, 4
 
 
 def ffn_path(desc) -> int:
-    """Which kernels a bf16 FFN takes (decided on the host): STREAM, MID (tiles of 128 token rows or fewer) or TILED
-    (256).  An internal symbol of the library: no result tells."""
+    """Which kernels the rows per slot of a bf16 FFN ask for (decided on the host): STREAM, MID (tiles of 128 token rows or
+    fewer) or TILED (256); with more than 16 tokens those that it takes.  An internal symbol of the library: no result tells."""
     return getattr(P.lib(), "_ZN4emoe13ffn_bf16_pathERK15emoe_layer_desc")(ctypes.byref(desc))
+
+
+def ffn_kernels(desc) -> int:
+    """Which kernels a layer's FFN takes: as ffn_path(), FEW with up to 16 tokens, or F32."""
+    return getattr(P.lib(), "_ZN4emoe8ffn_pathERK15emoe_layer_desc")(ctypes.byref(desc))
 
 
 class DeviceLayer:

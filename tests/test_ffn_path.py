@@ -3,7 +3,7 @@ and on both sides of the rows per slot at which the choice may change."""
 import pytest
 
 import paper_2503_06823_amd as P
-from gpu_util import MID, STREAM, TILED, ffn_path
+from gpu_util import F32, FEW, MID, STREAM, TILED, ffn_kernels, ffn_path
 
 
 @pytest.mark.parametrize("rows,small,large", [(1, STREAM, STREAM), (22, STREAM, STREAM), (23, MID, MID), (100, MID, MID),
@@ -40,3 +40,14 @@ FASTER = [
 @pytest.mark.parametrize("d,f,S,rows,act,path", FASTER)
 def test_faster_tiles_are_chosen(d, f, S, rows, act, path):
     assert ffn_path(P.make_desc(rows * S, d, f, S, 1, S, "bf16", act)) == path
+
+
+def test_the_kernels_of_a_layer():
+    for S, k in ((1, 1), (8, 2), (64, 64)):
+        assert ffn_kernels(P.make_desc(1, 256, 512, S, k, S, "f32", "swiglu")) == F32
+        for T in (1, 16):
+            assert ffn_kernels(P.make_desc(T, 4096, 14336, S, k, S, "bf16", "swiglu")) == FEW
+        for T in (17, 22, 200, 5000):
+            desc = P.make_desc(T, 1024, 2048, S, k, S, "bf16", "relu")
+            assert ffn_kernels(desc) == ffn_path(desc)
+            assert ffn_kernels(P.make_desc(T, 1024, 2048, S, k, S, "f32", "relu")) == F32

@@ -8,7 +8,7 @@ import torch
 import emoe_inputs as gen
 import oracle
 import paper_2503_06823_amd as P
-from gpu_util import STREAM, DeviceLayer, check_ffn_rows, check_outputs, check_routing_and_permutation, desc_of, ffn_path
+from gpu_util import FEW, STREAM, DeviceLayer, check_ffn_rows, check_outputs, check_routing_and_permutation, desc_of, ffn_kernels
 
 pytestmark = pytest.mark.gpu
 
@@ -31,7 +31,7 @@ def test_layer_matches_oracle(gpu_device, c):
     inp = gen.make_layer_inputs(c)
     ref = oracle.layer_forward(inp)
     dl = DeviceLayer(inp)
-    assert ffn_path(desc_of(c)) == STREAM
+    assert ffn_kernels(desc_of(c)) == (FEW if c.T <= 16 else STREAM)
     dl.forward()
     torch.cuda.synchronize()
     check_routing_and_permutation(dl, ref)
