@@ -82,7 +82,7 @@ PermuteWs permute_ws_layout(const emoe_layer_desc& d) {
 // 723 against 563 us).
 namespace {
 constexpr long long kStreamRowsPerSlot = 22;
-constexpr int kSortRounds = 4;  // see first_product_sorts()
+constexpr int kSortShortWalk = 1536;  // see first_product_sorts()
 constexpr int kFewTokens = 16;  // one tile of tokens of the few-token kernel
 constexpr long long kMidRowsPerSlot = 100;
 // A small layer (all resident slots' weights stream in some 60 us) is bound by how well its tiles
@@ -155,6 +155,50 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
     const bool mid_only = (long long)A <= kMidRowsPerSlot * d.S || back_on_mid(d);
     w.total += mid_only ? kMidPartialBytes : kTiledPartialBytes;
     return w;
+}
+
+// Whether a layer called as a whole leaves the sort to its first product (block_sort.h), which spares a launch and costs
+// every workgroup its time before the walk: with as many workgroups as the chip holds at once that is less than the
+// launch, with many times as many it is not.  Counted here, by how many the chip holds and times the passes of 256 assignments:
+// units of 32 weight rows (few), of 64 (streaming), tiles of 32 x 64 (fp32), of 128 x 256 (128-row tiles).  The kernels also
+// cut their work smaller, which the lines take into account: they were drawn by layers with the sort and without it, 5000 random
+// ones with weights from HBM, time with / without: fp32 0.97 at a count of 2, 0.99 at 4, 1.00 at 5; few 0.96 at 1, 0.99 at 4, in 64-row
+// units 1.01 at 7; 128-row tiles 0.97 at 2 and 0.98 at 4, where 64-row tiles and tiles of 128 weight rows, up to 9.6 times the
+// places, gain 0.9 us in the mean as well (600 layers, worst 1.03).  Streaming: 0.98 at 2 and 0.99 at 4, but a sort of one pass is
+// little work for the launch, and where walks are short its time before them is much: d_model up to 1536 0.99 at 2, 1.00 at
+// 2.5, 1.01 to 1.03 at 3, 1.01 to 1.05 at 4 (29 tokens, k 3, d 64, f 1344, 41 slots 26.0 / 29.0 us).
+// us, launch / in the product: 64 tokens, d 128, f 256, fp32 24.9 / 23.1 (count 0.06); 300 tokens, k 3, d 1024, f 1024, 8 slots 45.7 / 43.9
+// (1.9); 1 token, k 2, d 4096, f 14336 122.8 / 121.1 (3.5); 30 tokens, k 6, d 2048, f 1408, 64 slots 183 / 183 (5.5); 120 tokens, k 8,
+// d 768, f 3072, 64 slots 178 / 195 (48).
+bool first_product_sorts(const emoe_layer_desc& d, const DeviceShape& shape) {
+    const long long A = (long long)d.T * d.k;
+    if (A <= 0 || A > kBlockSortMax) return false;
+    const bool swiglu = d.act == EMOE_ACT_SWIGLU;
+    const long long slots = A < d.S ? A : d.S, passes = (A + 255) / 256;
+    auto column_tiles = [&](int rows) { return (d.d_ff + (swiglu ? rows / 2 : rows) - 1) / (swiglu ? rows / 2 : rows); };
+    long long workgroups, at_once;
+    double most = 4.0;
+    switch (ffn_path(d)) {
+        case kFfnF32:
+            workgroups = (A / 32 + slots) * column_tiles(64);
+            at_once = 4 * shape.cus;
+            break;
+        case kFfnFew:
+            workgroups = slots * column_tiles(32);
+            at_once = 2 * shape.cus;
+            break;
+        case kFfnStream:
+            workgroups = d.S * (long long)column_tiles(64);
+            at_once = 2 * shape.cus;
+            if (passes == 1 && d.d_model <= kSortShortWalk) most = 2.5;
+            break;
+        case kFfnMid:
+            workgroups = (A / 128 + slots) * column_tiles(256);
+            at_once = shape.cus;
+            break;
+        default: return false;
+    }
+    return (double)(passes * workgroups) <= most * at_once;
 }
 
 }  // namespace emoe
@@ -321,45 +365,6 @@ int emoe_combine(const emoe_layer_desc* desc, const void* y_perm, const int32_t*
     return e == hipSuccess ? EMOE_OK : EMOE_ERR_DEVICE;
 }
 
-// Whether a layer called as a whole leaves the sort to its first product (block_sort.h), which spares a launch and costs
-// every workgroup about 1 us per 256 assignments: with as many workgroups as the chip holds at once that is less than the
-// launch, with many times as many it is not.  Counted here: the workgroups that the kernel launches (few: in units of 32 rows), the
-// surplus ones included, by how many the chip holds.  Layer, us, sort launch / sort in the product, passes x rounds in
-// brackets: 64 tokens, d 128, f 256, fp32 21.3 / 18.8 (1), 1 token, d 4096, f 14336 116.6 / 115.6 (3.5), 300 tokens, k 3, d 1024, f 1024
-// 37.4 / 36.3 (1.9); but 30 tokens, k 6, 64 slots, f 1408 181 / 183 (5.5), 256 tokens, d 4096, f 14336 427 / 429 (8.8), 120 tokens,
-// k 8, 64 slots, f 3072 125 / 133 (24).
-static bool first_product_sorts(const emoe_layer_desc& d) {
-    const long long A = (long long)d.T * d.k;
-    if (A <= 0 || A > kBlockSortMax) return false;
-    DeviceShape shape;
-    if (device_shape(&shape) != hipSuccess) return false;
-    const bool swiglu = d.act == EMOE_ACT_SWIGLU;
-    const long long slots = A < d.S ? A : d.S;
-    auto column_tiles = [&](int rows) { return (d.d_ff + (swiglu ? rows / 2 : rows) - 1) / (swiglu ? rows / 2 : rows); };
-    long long workgroups, at_once;
-    switch (ffn_path(d)) {
-        case kFfnF32:
-            workgroups = (A / 32 + slots) * column_tiles(64);
-            at_once = 4 * shape.cus;
-            break;
-        case kFfnFew:
-            workgroups = slots * column_tiles(32);
-            at_once = 2 * shape.cus;
-            break;
-        case kFfnStream:
-            workgroups = d.S * (long long)column_tiles(64);
-            at_once = 2 * shape.cus;
-            break;
-        case kFfnMid:
-            workgroups = (A / 128 + slots) * column_tiles(256);
-            at_once = shape.cus;
-            break;
-        default: return false;
-    }
-    const long long passes = (A + 255) / 256;
-    return passes * workgroups <= kSortRounds * at_once;
-}
-
 int emoe_layer_forward(const emoe_layer_desc* desc, const void* x, const void* w_gate, const float* gate_bias,
                        const int32_t* slot_of_expert, const void* w1_slots, const void* w3_slots,
                        const void* w2_slots, int32_t* topk_expert, float* topk_weight, int32_t* slot_counts,
@@ -377,7 +382,8 @@ int emoe_layer_forward(const emoe_layer_desc* desc, const void* x, const void* w
     if (!ffn_ws || ffn_ws_bytes < ffn_ws_layout(*desc).total) return EMOE_ERR_WORKSPACE;
     rc = emoe_route(desc, x, w_gate, gate_bias, slot_of_expert, topk_expert, topk_weight, stream);
     if (rc != EMOE_OK) return rc;
-    if (first_product_sorts(*desc)) {
+    DeviceShape shape;
+    if (device_shape(&shape) == hipSuccess && first_product_sorts(*desc, shape)) {
         const SortTables sort{topk_expert, slot_of_expert, slot_counts, slot_offsets, perm, inv_perm, desc->T * desc->k, desc->E};
         return ffn_and_combine(desc, x, perm, inv_perm, slot_offsets, w1_slots, w3_slots, w2_slots, topk_weight, y_perm, out,
                                ffn_ws, ffn_ws_bytes, stream, sort);

@@ -64,6 +64,8 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d);
 enum FfnPath { kFfnStream = 0, kFfnMid = 1, kFfnTiled = 2, kFfnFew = 3, kFfnF32 = 4 };
 FfnPath ffn_path(const emoe_layer_desc& d);
 FfnPath ffn_bf16_path(const emoe_layer_desc& d);
+// Whether emoe_layer_forward leaves the sort of the assignments to the first product.
+bool first_product_sorts(const emoe_layer_desc& d, const DeviceShape& shape);
 
 // Host-side checks common to the entry points; returns EMOE_OK or an error.
 int validate_desc(const emoe_layer_desc* d);

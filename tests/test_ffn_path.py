@@ -1,5 +1,8 @@
 """Which kernels the bf16 FFN of a layer takes, at layers where the times of the two tile sizes were measured to be apart
-and on both sides of the rows per slot at which the choice may change."""
+and on both sides of the rows per slot at which the choice may change; and which layers leave the sort to their first
+product, where that was measured to be faster, or slower."""
+import ctypes
+
 import pytest
 
 import paper_2503_06823_amd as P
@@ -51,3 +54,33 @@ def test_the_kernels_of_a_layer():
             desc = P.make_desc(T, 1024, 2048, S, k, S, "bf16", "relu")
             assert ffn_kernels(desc) == ffn_path(desc)
             assert ffn_kernels(P.make_desc(T, 1024, 2048, S, k, S, "f32", "relu")) == F32
+
+
+class DeviceShape(ctypes.Structure):
+    _fields_ = [("cus", ctypes.c_int), ("xcds", ctypes.c_int), ("groups", ctypes.c_int)]
+
+
+def sorts(*args):
+    fn = getattr(P.lib(), "_ZN4emoe19first_product_sortsERK15emoe_layer_descRKNS_11DeviceShapeE")
+    fn.restype = ctypes.c_bool
+    return fn(ctypes.byref(P.make_desc(*args)), ctypes.byref(DeviceShape(256, 8, 256)))
+
+
+# T, d_model, d_ff, E, k, S, dtype, activation
+SLOWER = [
+    # streaming, one pass, short walks
+    (29, 64, 1344, 42, 3, 41, "bf16", "swiglu"), (30, 384, 1664, 37, 1, 35, "bf16", "swiglu"), (29, 128, 2560, 30, 2, 25, "bf16", "swiglu"),
+    (34, 192, 1920, 58, 7, 33, "bf16", "swiglu"), (25, 128, 7040, 23, 1, 18, "bf16", "relu"), (94, 72, 6784, 53, 1, 16, "bf16", "relu"),
+    (120, 768, 3072, 64, 8, 64, "bf16", "swiglu"), (256, 4096, 14336, 8, 2, 8, "bf16", "swiglu"),
+    (342, 1024, 2048, 8, 3, 8, "bf16", "swiglu"), (1025, 64, 64, 1, 1, 1, "f32", "relu"),  # more than 1024 assignments
+    (1024, 4096, 4096, 2, 1, 2, "bf16", "swiglu"),                                          # the 256-row tiles do not sort
+]
+FASTER_SORTING = [
+    (64, 128, 256, 8, 2, 4, "f32", "swiglu"), (1, 4096, 14336, 8, 2, 6, "bf16", "swiglu"), (300, 1024, 1024, 8, 3, 8, "bf16", "swiglu"),
+    (95, 544, 472, 57, 4, 55, "bf16", "swiglu"), (100, 864, 1176, 24, 3, 21, "bf16", "swiglu"), (90, 400, 864, 35, 4, 29, "bf16", "swiglu"),
+]
+
+
+@pytest.mark.parametrize("layer,where", [(l, False) for l in SLOWER] + [(l, True) for l in FASTER_SORTING], ids=str)
+def test_the_sort_goes_where_it_is_faster(layer, where):
+    assert sorts(*layer) == where
