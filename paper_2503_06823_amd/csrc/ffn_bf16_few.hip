@@ -38,7 +38,6 @@ constexpr int ROW_BYTES = PIECE * 2;  // 128
 constexpr unsigned kRotation = 21;    // rotation of the walk per workgroup
 constexpr int kLongK = 2048;
 constexpr int kStreamOnce = 2;        // non-temporal hint of the weight loads
-constexpr long long kCachedFrom = 128ll << 20;  // bytes of weights of a first product, see launch_shape()
 
 constexpr int wait_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0x0 << 8); }
 // At most N of this wavefront's global->LDS loads pending (they retire in order), its LDS reads done.
@@ -213,9 +212,11 @@ hipError_t launch_shape(const bf16_t* a, Gather gather, const int32_t* offsets, 
                         int slots, int S, int N, int K, hipStream_t st) {
     constexpr int BNO = EPI == kSwiglu ? WR / 2 : WR;
     constexpr int kLds = Shape<WR, WAVES>::LDS;
-    // Where rows are not whole 128-byte lines two pieces share the lines between them: no non-temporal hint there, but for a
-    // small first product (the rule of the streaming kernels).
-    const bool once = K % 64 == 0 || (EPI != kPlain && (long long)S * N * K * (EPI == kSwiglu ? 4 : 2) < kCachedFrom);
+    // Where rows are not whole 128-byte lines every piece shares its lines with its neighbours, which other wavefronts load: no
+    // non-temporal hint there (900 layers whose rows are none, weights from HBM, with the hint against without, by MiB of a
+    // product's weights: 1 to 4 1.01, 8 to 64 1.02 to 1.03, 128 and more 1.03 to 1.05 of the time; one token, d 1992, f 13144, five
+    // slots 175 / 201 us).
+    const bool once = K % 64 == 0;
     auto kern = once ? few_gemm_bf16<EPI, WR, WAVES, true, Gather> : few_gemm_bf16<EPI, WR, WAVES, false, Gather>;
     static std::atomic<bool> attr_set[2] = {};  // set once per kernel; setting it twice from two threads is harmless
     if (!attr_set[once].load(std::memory_order_acquire)) {

@@ -1,5 +1,5 @@
 """bf16 layers of few rows per slot whose weight rows are not whole 128-byte lines, with less and with more than 128 MiB of
-weights in the first product: its loads carry the non-temporal hint below and not above, in the streaming kernels and in
+weights in the first product: its loads carry the non-temporal hint below and not above in the streaming kernels, and never in
 those of up to 16 tokens."""
 import numpy as np
 import pytest
