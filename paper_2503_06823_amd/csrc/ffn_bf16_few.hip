@@ -36,7 +36,7 @@ constexpr int TOK = 16;               // token rows per pass
 constexpr int PIECE = 64;             // elements of a row per wavefront and step
 constexpr int ROW_BYTES = PIECE * 2;  // 128
 constexpr unsigned kRotation = 21;    // rotation of the walk per workgroup
-constexpr int kLongK = 2048;
+constexpr int kLongK = 2048, kShortK = 512;  // see launch_one()
 constexpr int kStreamOnce = 2;        // non-temporal hint of the weight loads
 
 constexpr int wait_imm(int n) { return (n & 0xf) | ((n >> 4) << 14) | (0x7 << 4) | (0x0 << 8); }
@@ -245,8 +245,11 @@ hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, co
     if (units <= shape.cus && long_k) return launch_shape<EPI, 32, 8>(a, gather, offsets, b0, b1, c, slots, S, N, K, st);
     // Short walks in many workgroups: what a workgroup waits for before its walk and after it counts, and 64 rows halve
     // their number (16 tokens, K 768, 1536 units of 32 rows 13.5 -> 11.5 us, K 1000, 6016 units 62.6 -> 56.6); with a long K 32
-    // rows keep more weights in flight (K 4096, 1792 units of 16 + 16 rows: 71.5 against 73.7 us).
-    if (units >= 4 * shape.cus && K <= kLongK) return launch_shape<EPI, 64, 4>(a, gather, offsets, b0, b1, c, slots, S, N, K, st);
+    // rows keep more weights in flight (K 4096, 1792 units of 16 + 16 rows: 71.5 against 73.7 us).  Up to K 512 that holds as
+    // soon as 32 rows take more workgroups than the chip holds (513 to 1023 units, 64 against 32 rows: 0.87 of the time, and 0.96
+    // with K 512 to 1024, slots without rows making it up to 1.17; 1.03 with K 1024 to 2048).
+    if ((units > 2 * shape.cus && K <= kShortK) || (units >= 4 * shape.cus && K <= kLongK))
+        return launch_shape<EPI, 64, 4>(a, gather, offsets, b0, b1, c, slots, S, N, K, st);
     return launch_shape<EPI, 32, 4>(a, gather, offsets, b0, b1, c, slots, S, N, K, st);
 }
 
