@@ -131,6 +131,8 @@ hipError_t launch_ffn_bf16_stream(const emoe_layer_desc& d, const void* x_perm, 
 hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st);
+// Whether launch_ffn_bf16_few() gives a product of A rows, N outputs and K inputs to the streaming kernels.
+bool few_product_streams(bool swiglu, long long A, int slots, int N, int K, int cus);
 hipError_t launch_fill_i32(int32_t* p, int n, int32_t value, hipStream_t st);
 hipError_t launch_write_maps(const int32_t* slot_of_expert_new, int E, const int32_t* expert_of_slot_new, int S,
                              int32_t* slot_of_expert_dev, int32_t* expert_of_slot_dev, hipStream_t st);

@@ -255,21 +255,45 @@ hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, co
 
 }  // namespace
 
+// Whether a product of few tokens is faster in the streaming kernels: where weight rows are not whole 128-byte lines and the
+// walk is long.  A load instruction takes time per line that it touches: 128 bytes of a row are two lines here, the
+// streaming kernels' 256 bytes three, of token rows too, so it hangs on the rows per slot.  Measured at 1100 layers of K from 2048
+// on, time here / streaming at 1 to 2, 3 to 4, 6, 8, 12 to 16 rows per slot: one matrix, 129 to 256 units 1.02, 1.08, 1.11, 1.11,
+// 1.10; 257 to 512 0.96, 1.01, 1.00, 1.04, 1.06; 513 to 1024 0.95, 1.02, 1.05, 1.03, 1.07; above 0.90, 0.94, 0.94, 0.96, 1.04.
+// SwiGLU, up to 256 units 0.72, 0.73, 0.73, 0.73, 0.74; 257 to 512 0.90, 0.94, 1.00, 1.02, 1.06; 513 to 768, where the streaming
+// kernels' units of 32 + 32 rows make a round and a bit, 0.77, 0.82, 0.87, 0.88, 0.91; 769 to 1024 0.94, 1.04, 1.03, 1.04, 1.06; above
+// 0.93, 0.95, 0.99, 1.01, 1.05.  (K 1024 to 2048: 0.94 to 0.97.)  Slots that stay empty, which the host does not know, cost the
+// streaming kernels more.
+bool few_product_streams(bool swiglu, long long A, int slots, int N, int K, int cus) {
+    if (K % 64 == 0 || K < kLongK) return false;
+    const long long units = (long long)slots * ((N + (swiglu ? 15 : 31)) / (swiglu ? 16 : 32));
+    if (swiglu) return A > 6ll * slots && units > cus && (units <= 2 * cus || units > 3 * cus);
+    if (units <= cus) return A > slots && 2 * units > cus;
+    return A > (units <= 2 * cus ? 6ll : units <= 4 * cus ? 3ll : 8ll) * slots;
+}
+
 hipError_t launch_ffn_bf16_few(const emoe_layer_desc& d, const void* x_perm, SortingGather gather, const int32_t* offsets,
                                const void* w1, const void* w3, const void* w2, void* y_perm, void* ws, int passes,
                                hipStream_t st) {
     bf16_t* h = reinterpret_cast<bf16_t*>(static_cast<uint8_t*>(ws) + ffn_ws_layout(d).h);
     const bf16_t* xp = static_cast<const bf16_t*>(x_perm);
     const int A = d.T * d.k, slots = A < d.S ? A : d.S;
-    hipError_t e = hipSuccess;
+    DeviceShape shape;
+    hipError_t e = device_shape(&shape);
+    if (e != hipSuccess) return e;
     auto first = [&](auto rows) {
         const bf16_t* w1p = static_cast<const bf16_t*>(w1);
         if (d.act == EMOE_ACT_SWIGLU)
             return launch_one<kSwiglu>(xp, rows, offsets, w1p, static_cast<const bf16_t*>(w3), h, slots, d.S, d.d_ff, d.d_model, st);
         return launch_one<kRelu>(xp, rows, offsets, w1p, nullptr, h, slots, d.S, d.d_ff, d.d_model, st);
     };
-    if (passes & 1) e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
+    auto streamed = [&](int pass) { return launch_ffn_bf16_stream(d, x_perm, gather, offsets, w1, w3, w2, y_perm, ws, pass, st); };
+    if (passes & 1) {
+        if (few_product_streams(d.act == EMOE_ACT_SWIGLU, A, slots, d.d_ff, d.d_model, shape.cus)) e = streamed(1);
+        else e = gather.sort.A > 0 ? first(gather) : first(RowGather(gather));
+    }
     if (e != hipSuccess || !(passes & 2)) return e;
+    if (few_product_streams(false, A, slots, d.d_model, d.d_ff, shape.cus)) return streamed(2);
     return launch_one<kPlain>(h, RowGather{nullptr, 1, 0, gather.out_perm}, offsets, static_cast<const bf16_t*>(w2), nullptr,
                               static_cast<bf16_t*>(y_perm), slots, d.S, d.d_model, d.d_ff, st);
 }

@@ -1,6 +1,6 @@
 """Which kernels the bf16 FFN of a layer takes, at layers where the times of the two tile sizes were measured to be apart
-and on both sides of the rows per slot at which the choice may change; and which layers leave the sort to their first
-product, where that was measured to be faster, or slower."""
+and on both sides of the rows per slot at which the choice may change; which layers leave the sort to their first
+product, where that was measured to be faster, or slower; and which products of up to 16 tokens the streaming kernels take."""
 import ctypes
 
 import pytest
@@ -84,3 +84,21 @@ FASTER_SORTING = [
 @pytest.mark.parametrize("layer,where", [(l, False) for l in SLOWER] + [(l, True) for l in FASTER_SORTING], ids=str)
 def test_the_sort_goes_where_it_is_faster(layer, where):
     assert sorts(*layer) == where
+
+
+# SwiGLU, rows, slots, outputs, inputs, streaming.  Where weight rows are whole lines, walks short, units few or the rows per slot
+# few, the few-token kernel was the faster one.
+PRODUCTS = [
+    (True, 28, 2, 15816, 3208, True), (True, 39, 3, 10744, 4816, True), (True, 32, 3, 14544, 4568, True), (True, 15, 1, 5200, 5608, True),
+    (True, 28, 2, 5376, 3208, False), (True, 28, 2, 15816, 3200, False), (True, 6, 2, 15816, 3208, False), (True, 28, 2, 2048, 3208, False),
+    (False, 28, 2, 3208, 15816, True), (False, 7, 7, 1752, 16120, False), (False, 16, 8, 552, 13304, True), (False, 10, 10, 552, 13304, False),
+    (False, 28, 2, 3208, 15808, False), (False, 28, 2, 2040, 15816, False), (False, 28, 2, 3208, 2040, False), (False, 7, 1, 16384, 4104, True),
+    (False, 16, 8, 5216, 11208, False), (False, 36, 6, 5216, 11208, True), (False, 6, 6, 5216, 11208, False), (False, 48, 6, 8000, 11208, False),
+]
+
+
+@pytest.mark.parametrize("product", PRODUCTS, ids=str)
+def test_few_token_products_that_stream(product):
+    fn = getattr(P.lib(), "_ZN4emoe19few_product_streamsEbxiiii")
+    fn.restype, fn.argtypes = ctypes.c_bool, [ctypes.c_bool, ctypes.c_longlong] + [ctypes.c_int] * 4
+    assert fn(*product[:5], 256) == product[5]

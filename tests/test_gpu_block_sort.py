@@ -17,6 +17,7 @@ CASES = [
     ("f32", 1, 64, 96, 1, 1, 1, 1, "relu", 0.0), ("f32", 64, 136, 264, 8, 2, 4, 6, "swiglu", 0.0), ("f32", 255, 72, 64, 64, 4, 60, 64, "swiglu", 1.1),
     ("f32", 1024, 64, 128, 64, 1, 20, 24, "relu", 1.2), ("f32", 1025, 64, 128, 64, 1, 20, 24, "relu", 1.2),
     ("bf16", 1, 264, 2056, 8, 2, 6, 6, "swiglu", 0.0), ("bf16", 16, 2056, 264, 64, 8, 60, 64, "relu", 0.0), ("bf16", 13, 2200, 520, 8, 3, 5, 7, "swiglu", 0.0),
+    ("bf16", 16, 2056, 2568, 8, 3, 3, 3, "relu", 0.0), ("bf16", 16, 2056, 2064, 2, 1, 2, 2, "swiglu", 0.0),
     ("bf16", 17, 264, 328, 8, 2, 6, 8, "swiglu", 0.0), ("bf16", 60, 328, 264, 24, 3, 11, 20, "swiglu", 1.2), ("bf16", 128, 264, 328, 64, 8, 60, 64, "relu", 1.1),
     ("bf16", 86, 264, 328, 8, 3, 6, 8, "swiglu", 1.1), ("bf16", 171, 520, 328, 16, 3, 12, 12, "relu", 1.2), ("bf16", 1024, 136, 264, 64, 1, 16, 20, "relu", 1.1),
     ("bf16", 341, 4104, 264, 4, 3, 4, 4, "relu", 0.0), ("bf16", 100, 4104, 200, 2, 1, 2, 2, "relu", 0.0), ("bf16", 200, 1032, 2808, 24, 5, 20, 24, "swiglu", 1.1),

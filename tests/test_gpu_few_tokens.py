@@ -1,6 +1,7 @@
 """bf16 layers of at most 16 tokens at the edges of their kernel: units of 16, 32 and 64 weight rows by four and eight
 wavefronts, rows and K that are not multiples of them, walks shorter than the number of wavefronts, empty slots, one token and
-16; the streaming kernels at 17 tokens; and a slot that receives more than 16 rows of 16 tokens."""
+16; the streaming kernels at 17 tokens and for products of up to 16 whose long rows are not whole lines, the first, the second or
+both; and a slot that receives more than 16 rows of 16 tokens."""
 import numpy as np
 import pytest
 import torch
@@ -23,6 +24,7 @@ CASES = [cfg(i, *a) for i, a in enumerate([
     (16, 2056, 520, 64, 3, 48, 50, "relu"), (9, 72, 8, 8, 8, 8), (5, 2048, 4104, 2, 1, 2, 2, "relu"), (2, 2056, 2568, 2, 1, 2, 2, "relu"),
     (1, 8, 16, 1, 1, 1), (15, 136, 264, 64, 8, 64), (2, 4096, 1024, 8, 2, 6, 8), (1, 1088, 2880, 24, 3, 11),
     (17, 520, 2568, 16, 2, 16), (20, 4104, 4104, 2, 1, 2, 2, "relu"), (20, 4104, 8200, 2, 1, 2, 2, "relu"),
+    (16, 2056, 2568, 8, 3, 3, 3, "relu"), (16, 2056, 2064, 2, 1, 2), (15, 2112, 2056, 4, 1, 2), (15, 2056, 2112, 4, 1, 2, 2, "relu"),
 ])]
 
 
