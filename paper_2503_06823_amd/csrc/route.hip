@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
     }
 }
 
-constexpr int kWaveRouteTokens = 256;
+constexpr int kWaveRouteTokens = 256, kWaveRouteExperts = 8;  // bf16, see launch_route()
 
 template <typename T, int EP>
 hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
@@ -156,7 +156,8 @@ hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate
                      unsigned long long* expert_tokens, hipStream_t st) {
     const T* xp = static_cast<const T*>(x);
     const T* wg = static_cast<const T*>(w_gate);
-    if (d.T <= 2048) {  // fewer than two wavefronts per SIMD otherwise: share each token among four
+    constexpr bool kF32 = std::is_same<T, float>::value;  // bf16: up to kWaveRouteTokens tokens; fp32, EP = 32: up to 2048
+    if (!kF32 || d.T <= 2048) {  // fewer than two wavefronts per SIMD otherwise: share each token among four
         int blocks = d.T < 256 * 16 ? d.T : 256 * 16;
         // All experts (16) at a time takes up to 220 registers, which leaves a CU two workgroups.  With more tokens than
         // CUs fp32 rows take four at a time in 128 registers (9 to 16 experts, d_model 2048, 513 to 1023 tokens: 10.6 to 12.8 us
@@ -165,11 +166,11 @@ hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate
         // tokens: 30, against 35).
         constexpr int kAll = EP < 16 ? EP : 16;
         auto kern = route_kernel<T, EP, 4, EP == 32 ? 4 : kAll, EP == 32 ? 2 : 1>;
-        if constexpr ((EP == 8 || EP == 16) && std::is_same<T, float>::value)
+        if constexpr ((EP == 8 || EP == 16) && kF32)
             if (d.T > 256) kern = route_kernel<T, EP, 4, 4, 4>;
         kern<<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
                                                        expert_tokens, d.T, d.d_model, d.E, d.k);
-    } else {
+    } else if constexpr (kF32 && EP != 32) {
         int blocks = (d.T + 3) / 4;
         if (blocks > 256 * 16) blocks = 256 * 16;
         route_kernel<T, EP, 1, EP < 16 ? EP : 16, 1><<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
@@ -184,12 +185,12 @@ hipError_t launch_t(const emoe_layer_desc& d, const void* x, const void* w_gate,
     if (d.E <= 1) return launch_ep<T, 1>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 2) return launch_ep<T, 2>(d, x, w_gate, bias, soe, te, tw, et, st);
     if (d.E <= 4) return launch_ep<T, 4>(d, x, w_gate, bias, soe, te, tw, et, st);
-    if (d.E <= 8) return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
     if constexpr (std::is_same<T, float>::value) {
         if (d.E > 16 && d.E <= 32 && d.T <= 2048) return launch_ep<T, 32>(d, x, w_gate, bias, soe, te, tw, et, st);
         if (d.E > 16) return launch_ep<T, 64>(d, x, w_gate, bias, soe, te, tw, et, st);
+        if (d.E > 8) return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
     }
-    return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
+    return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
 }
 
 }  // namespace
@@ -219,7 +220,7 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
     // level or better (us, wavefront / matrix: 8 experts, d_model 4096, 1 token 4.4 / 4.8, 128 tokens 4.9 / 5.3, 256 tokens
     // 5.1 / 5.7; d_model 8192, 64 tokens 5.8 / 7.3); with 16 experts it is not (d_model 2048, 1 token 7.3 / 3.9; d_model
     // 4096, 64 tokens 8.8 / 5.3)
-    if (d.T <= kWaveRouteTokens && d.E <= 8 && d.d_model >= 2048)
+    if (d.T <= kWaveRouteTokens && d.E <= kWaveRouteExperts && d.d_model >= 2048)
         return launch_t<bf16_t>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     return launch_route_bf16(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
 }
