@@ -1,5 +1,5 @@
 """The bf16 gate where its matrix-core kernel cuts: 16 or 32 tokens per workgroup (32 from more than 16 per CU on),
-blocks of 16 experts, pieces of 64 elements of d_model dealt to eight or four wavefronts with a ring of two to four
+blocks of 16 experts, pieces of 64 elements of d_model dealt to sixteen, eight or four wavefronts with a ring of two to four
 pieces each, and top-k over up to 64 lanes.  Inputs are small integers with repeated gate rows, as in test_gpu_ties:
 every logit is exact in fp32 in any order, so the routing and the observed workload must equal the oracle's."""
 import numpy as np

@@ -1,10 +1,10 @@
 """GPU routing on inputs with exact ties (Section 3.2.2: the k best resident experts; the rule for equal
-logits, lower expert index first, is this build's reading).  No margin filter here: token rows and
+logits, lower expert index first, is this library's reading).  No margin filter here: token rows and
 gate rows hold small integers, so every logit is an integer that fp32 accumulates exactly in any
 order, and gate rows are repeated, so every token has experts with exactly equal logits: pairs of
-two resident experts, of a resident and an absent one, inside and across the groups of experts that
-one lane of the matrix-core kernel holds.  topk_expert and the observed workload must equal the
-oracle's bit for bit, through both route kernels."""
+two resident experts, of a resident and an absent one, inside and across the blocks of 16 experts
+of the matrix kernels.  topk_expert and the observed workload must equal the
+oracle's bit for bit, through all route kernels."""
 import zlib
 
 import numpy as np
@@ -22,8 +22,13 @@ pytestmark = pytest.mark.gpu
 CASES = [
     ("f32_wave_per_token", "f32", 150, 96, 8, 2, 5, 3, False),
     ("f32_top1_bias", "f32", 90, 64, 16, 1, 6, 5, True),
-    ("bf16_decode_wave_per_token", "bf16", 64, 2048, 12, 2, 7, 5, False),       # T <= 256, E <= 16, d >= 2048
-    ("bf16_decode_wave_per_token_bias", "bf16", 200, 2048, 16, 3, 9, 6, True),
+    ("f32_wave_E64", "f32", 100, 2048, 64, 6, 40, 11, True),
+    ("f32_mfma_E24", "f32", 100, 264, 24, 3, 13, 7, False),
+    ("bf16_decode_wave_per_token_E8", "bf16", 64, 2048, 8, 2, 7, 3, False),      # T <= 256, E <= 8, d >= 2048
+    ("bf16_decode_wave_per_token_E7_bias", "bf16", 200, 2056, 7, 3, 6, 4, True),
+    ("bf16_decode_wave_per_token_E3", "bf16", 30, 4096, 3, 1, 3, 2, False),
+    ("bf16_mfma_E12_long_rows", "bf16", 64, 2048, 12, 2, 7, 5, False),
+    ("bf16_mfma_E16_long_rows_bias", "bf16", 200, 2048, 16, 3, 9, 6, True),
     ("bf16_mfma_E8", "bf16", 300, 256, 8, 2, 4, 3, False),
     ("bf16_mfma_E16_halves", "bf16", 700, 128, 16, 2, 9, 5, False),
     ("bf16_mfma_E32_all_lanes", "bf16", 1000, 192, 32, 4, 13, 7, True),
