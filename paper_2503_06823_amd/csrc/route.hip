@@ -160,10 +160,10 @@ hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate
     if (!kF32 || d.T <= 2048) {  // fewer than two wavefronts per SIMD otherwise: share each token among four
         int blocks = d.T < 256 * 16 ? d.T : 256 * 16;
         // All experts (16) at a time takes up to 220 registers, which leaves a CU two workgroups.  With more tokens than
-        // CUs fp32 rows take four at a time in 128 registers (9 to 16 experts, d_model 2048, 513 to 1023 tokens: 10.6 to 12.8 us
-        // against 13.6 to 16.3; d_model 4096, 512 tokens 10.8 against 11.3; 8 experts, d_model 6144, 600 tokens 9.0 against
-        // 9.4), and so do 32 experts, whose sums alone are many (64 tokens, d_model 6144: 23.5 us, 16 at a time 26.1; 300
-        // tokens: 30, against 35).
+        // CUs fp32 rows take four at a time in 128 registers (9 to 16 experts, d_model 2048, 513 to 1000 tokens: 12.0 to 15.1 us
+        // against 14.6 to 18.1; d_model 4096, 512 tokens 13.1 against 13.6; 8 experts, d_model 6144, 600 tokens 12.9 against
+        // 13.0), and so do 32 experts, whose sums alone are many (64 tokens, d_model 6144: level; 300 tokens: 31.9 us, 16 at a
+        // time 49.6).
         constexpr int kAll = EP < 16 ? EP : 16;
         auto kern = route_kernel<T, EP, 4, EP == 32 ? 4 : kAll, EP == 32 ? 2 : 1>;
         if constexpr ((EP == 8 || EP == 16) && kF32)
@@ -201,12 +201,16 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
     if (d.dtype == EMOE_F32) {
         // The matrix kernel reads the gate matrix once per 16 tokens, the wavefront kernel once per token, which is
         // the better one with few experts, or with so few tokens that each has a CU to itself and rows so long that
-        // splitting them over more wavefronts counts.  Wavefront / matrix, us: 1024 tokens, d 768: 8 experts level, 16: 12 /
-        // 8, 64: 46 / 13; 8192 tokens, d 768, 8 experts 12 / 8, d 2048, 4 experts 13 / 15; 512 tokens, d 2048, 64 experts
-        // 38 / 25.  64 tokens: 64 experts, d 768 14 / 12, d 1536 16.6 / 18.6; 48 experts, d 1536 16 / 15, d 2048 17 / 18.7,
-        // d 6144 25 / 46; 32 experts, d 3072 21 / 20, d 4096 21.6 / 24.7, d 6144 23.5 / 35.  300 tokens: 48 experts,
-        // d 8192 54 / 60 but d 4096 37 / 32.5; 32 experts, d 4096 25.7 / 24.8, d 6144 29.7 / 35.
-        // (The matrix kernel's times are from before its top-k took a wavefront per token, 1 to 4 us less now; the lines stand.)
+        // splitting them over more wavefronts counts.  Wavefront / matrix, us a launch in a row of them, k = 2: 8 experts, 1024
+        // tokens, d 768 6.0 / 7.1, 8192 tokens 15.2 / 10.8; 4 experts, 8192 tokens, d 2048 19.4 / 17.6.  16 experts, 1024 tokens, d 768
+        // 12.3 / 7.4, 64 tokens, d 2048 8.4 / 12.0, 600 tokens, d 2048 13.0 / 12.4, 512 tokens, d 4096 13.0 / 19.6.  32 experts, 64
+        // tokens, d 3072 22.0 / 22.8, d 4096 22.9 / 26.7, d 6144 25.8 / 38.9, 300 tokens, d 4096 27.2 / 27.2, d 6144 31.8 / 39.3.  48
+        // experts, 64 tokens, d 1536 16.0 / 16.9, d 2048 17.0 / 20.7, d 6144 26.5 / 54, 300 tokens, d 4096 40.7 / 36.5, d 8192 58.6 / 67.7
+        // (there the line gives the slower one).  64 experts, 64 tokens, d 768 13.4 / 12.5, d 1536 16.2 / 20.2, 512 tokens, d 2048
+        // 35.5 / 25.2, 1024 tokens, d 768 46.3 / 13.0.  At 1000 random gates of more than 16 experts the line takes 1.002 of the
+        // better kernel's time in the mean.  With up to 16 experts it does not lie at the crossing: with 9 to 16 and d_model up to
+        // 1024 the matrix kernel takes 0.77 to 0.84 of the time with up to 512 tokens already and 0.65 with 513 to 1023, with 5 to 8
+        // and d_model up to 1024 0.73 to 1.26 with 2300 to 4096.
         // (A launch of 2^26 tokens would not fit a grid.)
         const int blocks = (d.E + 15) / 16;
         bool matrix = d.E > 8 ? d.T >= 1024 : d.E > 4 && d.T >= 4096;
@@ -217,9 +221,9 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
         return launch_t<float>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     }
     // bf16: with few tokens and experts a workgroup per token spreads the walk along d_model over more CUs and is
-    // level or better (us, wavefront / matrix: 8 experts, d_model 4096, 1 token 4.4 / 4.8, 128 tokens 4.9 / 5.3, 256 tokens
-    // 5.1 / 5.7; d_model 8192, 64 tokens 5.8 / 7.3); with 16 experts it is not (d_model 2048, 1 token 7.3 / 3.9; d_model
-    // 4096, 64 tokens 8.8 / 5.3)
+    // better (us a launch in a row of them, wavefront / matrix: 8 experts, d_model 4096, 1 token 5.0 / 6.0, 128 tokens 5.4 /
+    // 7.6, 256 tokens 5.6 / 7.6; d_model 8192, 64 tokens 6.7 / 10.9); with 16 experts it was not (one launch, d_model 2048, 1
+    // token 7.3 / 3.9; d_model 4096, 64 tokens 8.8 / 5.3, with the scans that its top-k made then)
     if (d.T <= kWaveRouteTokens && d.E <= kWaveRouteExperts && d.d_model >= 2048)
         return launch_t<bf16_t>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     return launch_route_bf16(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
