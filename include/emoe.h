@@ -211,10 +211,12 @@ int emoe_expert_ffn_gather_combine(const emoe_layer_desc *desc, const void *x, c
 
 /*
  * The whole layer (Section 1: gate plus experts, here over the resident
- * experts only, Section 3.2.2): emoe_route, emoe_permute (indices only) and
- * emoe_expert_ffn_gather_combine enqueued in this order on `stream`, with the same arguments,
- * results and errors as the single calls; nothing else is done and nothing is allocated (with
- * k = 1 y_perm stays unwritten, see emoe_expert_ffn_gather_combine).  All the intermediate
+ * experts only, Section 3.2.2): the results of emoe_route, emoe_permute (indices only) and
+ * emoe_expert_ffn_gather_combine, enqueued on `stream`, with the same arguments and errors as the
+ * single calls, bit for bit; nothing is allocated (with k = 1 y_perm stays unwritten, see
+ * emoe_expert_ffn_gather_combine).  In layers of up to 1024 assignments the first product may make
+ * the permutation itself instead of a launch before it: slot_counts, slot_offsets, perm and inv_perm
+ * are written all the same, permute_ws then is not.  All the intermediate
  * results are caller buffers as in the single calls (x_perm is not needed: the FFN reads the
  * token rows through perm).  Validation of all arguments happens before the first launch, so an
  * error leaves every output untouched.

@@ -161,10 +161,10 @@ FfnWs ffn_ws_layout(const emoe_layer_desc& d) {
 // every workgroup its time before the walk: with as many workgroups as the chip holds at once that is less than the
 // launch, with many times as many it is not.  Counted here, by how many the chip holds and times the passes of 256 assignments:
 // units of 32 weight rows (few), of 64 (streaming), tiles of 32 x 64 (fp32), of 128 x 256 (128-row tiles).  The kernels also
-// cut their work smaller, which the lines take into account: they were drawn by layers with the sort and without it, 5000 random
-// ones with weights from HBM, time with / without: fp32 0.97 at a count of 2, 0.99 at 4, 1.00 at 5; few 0.96 at 1, 0.99 at 4, in 64-row
-// units 1.01 at 7; 128-row tiles 0.97 at 2 and 0.98 at 4, where 64-row tiles and tiles of 128 weight rows, up to 9.6 times the
-// places, gain 0.9 us in the mean as well (600 layers, worst 1.03).  Streaming: 0.98 at 2 and 0.99 at 4, but a sort of one pass is
+// cut their work smaller, which the lines take into account: they were drawn by layers with the sort and without it, 6000 random
+// ones with weights from HBM, time with / without: fp32 0.97 at a count of 2, 0.99 to 1.00 at 4, 1.00 to 1.02 at 5; few 0.96 at 1, 0.99
+// at 4, in 64-row units 1.01 at 7; 128-row tiles 0.97 at 2 and 0.98 at 4, where 64-row tiles and tiles of 128 weight rows, up to 9.6 times
+// the places, gain 0.9 us in the mean as well (600 layers, worst 1.03).  Streaming: 0.98 at 2 and 0.99 at 4, but a sort of one pass is
 // little work for the launch, and where walks are short its time before them is much: d_model up to 1536 0.99 at 2, 1.00 at
 // 2.5, 1.01 to 1.03 at 3, 1.01 to 1.05 at 4 (29 tokens, k 3, d 64, f 1344, 41 slots 26.0 / 29.0 us).
 // us, launch / in the product: 64 tokens, d 128, f 256, fp32 24.9 / 23.1 (count 0.06); 300 tokens, k 3, d 1024, f 1024, 8 slots 45.7 / 43.9
