@@ -1,8 +1,8 @@
 // Gate logits and resident-restricted top-k (eMoE Section 1: the gate; Section 3.2.2, last
 // paragraph: a token whose expert is not on the GPU goes to its next-best expert that is):
 // fp32 inputs with few experts, or with few tokens and long rows, and bf16 inputs when there are few tokens, few
-// experts and long rows (a decode step of a Mixtral-shaped layer).  Other fp32 batches take route_f32.hip, other bf16
-// batches the matrix-core kernel of route_mfma.hip,
+// experts and long rows (a decode step of a Mixtral-shaped layer; up to 16 experts where rows are longer still).  Other fp32
+// batches take route_f32.hip, other bf16 batches the matrix-core kernel of route_mfma.hip,
 // which puts 16 tokens on a workgroup: with 64 tokens it runs on four CUs, bound by the latency of
 // their walk along d_model.
 //
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, PER_CU) void route_kernel(const T* __restrict_
     }
 }
 
-constexpr int kWaveRouteTokens = 256, kWaveRouteExperts = 8;  // bf16, see launch_route()
+constexpr int kWaveRouteTokens = 256;  // bf16, see launch_route()
 
 template <typename T, int EP>
 hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate, const float* bias,
@@ -188,9 +188,9 @@ hipError_t launch_t(const emoe_layer_desc& d, const void* x, const void* w_gate,
     if constexpr (std::is_same<T, float>::value) {
         if (d.E > 16 && d.E <= 32 && d.T <= 2048) return launch_ep<T, 32>(d, x, w_gate, bias, soe, te, tw, et, st);
         if (d.E > 16) return launch_ep<T, 64>(d, x, w_gate, bias, soe, te, tw, et, st);
-        if (d.E > 8) return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
     }
-    return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
+    if (d.E <= 8) return launch_ep<T, 8>(d, x, w_gate, bias, soe, te, tw, et, st);
+    return launch_ep<T, 16>(d, x, w_gate, bias, soe, te, tw, et, st);
 }
 
 }  // namespace
@@ -222,9 +222,13 @@ hipError_t launch_route(const emoe_layer_desc& d, const void* x, const void* w_g
     }
     // bf16: with few tokens and experts a workgroup per token spreads the walk along d_model over more CUs and is
     // better (us a launch in a row of them, wavefront / matrix: 8 experts, d_model 4096, 1 token 5.0 / 6.0, 128 tokens 5.4 /
-    // 7.6, 256 tokens 5.6 / 7.6; d_model 8192, 64 tokens 6.7 / 10.9); with 16 experts it was not (one launch, d_model 2048, 1
-    // token 7.3 / 3.9; d_model 4096, 64 tokens 8.8 / 5.3, with the scans that its top-k made then)
-    if (d.T <= kWaveRouteTokens && d.E <= kWaveRouteExperts && d.d_model >= 2048)
+    // 7.6, 256 tokens 5.6 / 7.6; d_model 8192, 64 tokens 6.7 / 10.9).  With 9 to 16 experts only where rows are long and
+    // the tokens not so few (600 gates, matrix / wavefront by d_model up to 4096, 5120, 6144, 7168, 8192, 12000: up to 8 tokens
+    // 0.62, 0.71, 0.75, 0.74, 0.79, 0.84; 9 to 16 0.75, 0.91, 0.95, 1.01, 1.00, 1.12; 17 to 64 0.79, 0.97, 1.05, 1.06, 1.11, 1.27; 65 to
+    // 256 0.81, 0.97, 1.07, 1.10, 1.19, 1.30).
+    const bool few_experts = d.E <= 8 && d.d_model >= 2048;
+    const bool long_rows = d.E <= 16 && (d.T > 16 ? d.d_model >= 6144 : d.T > 8 && d.d_model >= 8192);
+    if (d.T <= kWaveRouteTokens && (few_experts || long_rows))
         return launch_t<bf16_t>(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
     return launch_route_bf16(d, x, w_gate, bias, slot_of_expert, topk_expert, topk_weight, expert_tokens, st);
 }

@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 # gate kernel, dtype, T, d_model, E, k, R
 CASES = [
     ("wavefront", "bf16", 21, 2048, 8, 3, 6), ("wavefront", "bf16", 256, 2056, 4, 3, 3), ("wavefront", "bf16", 5, 4096, 2, 2, 2),
+    ("wavefront", "bf16", 17, 6152, 16, 10, 10), ("matrix", "bf16", 16, 6152, 16, 10, 10), ("wavefront", "bf16", 9, 8192, 11, 5, 5),
     ("matrix", "bf16", 257, 2048, 8, 3, 6), ("matrix", "bf16", 21, 72, 20, 12, 12), ("matrix", "bf16", 5000, 64, 64, 3, 40),
     ("wavefront", "f32", 21, 64, 8, 6, 6), ("wavefront", "f32", 300, 128, 12, 3, 9), ("wavefront", "f32", 21, 4096, 20, 3, 12),
     ("wavefront", "f32", 33, 2048, 64, 40, 40), ("wavefront", "f32", 2100, 64, 4, 3, 3),

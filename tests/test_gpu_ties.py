@@ -27,6 +27,7 @@ CASES = [
     ("bf16_decode_wave_per_token_E8", "bf16", 64, 2048, 8, 2, 7, 3, False),      # T <= 256, E <= 8, d >= 2048
     ("bf16_decode_wave_per_token_E7_bias", "bf16", 200, 2056, 7, 3, 6, 4, True),
     ("bf16_decode_wave_per_token_E3", "bf16", 30, 4096, 3, 1, 3, 2, False),
+    ("bf16_decode_wave_per_token_E12", "bf16", 40, 6144, 12, 2, 7, 5, False),    # 16 < T <= 256, E <= 16, d >= 6144
     ("bf16_mfma_E12_long_rows", "bf16", 64, 2048, 12, 2, 7, 5, False),
     ("bf16_mfma_E16_long_rows_bias", "bf16", 200, 2048, 16, 3, 9, 6, True),
     ("bf16_mfma_E8", "bf16", 300, 256, 8, 2, 4, 3, False),
