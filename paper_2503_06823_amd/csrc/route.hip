@@ -163,9 +163,11 @@ hipError_t launch_ep(const emoe_layer_desc& d, const void* x, const void* w_gate
         // CUs fp32 rows take four at a time in 128 registers (9 to 16 experts, d_model 2048, 513 to 1000 tokens: 12.0 to 15.1 us
         // against 14.6 to 18.1; d_model 4096, 512 tokens 13.1 against 13.6; 8 experts, d_model 6144, 600 tokens 12.9 against
         // 13.0), and so do 32 experts, whose sums alone are many (64 tokens, d_model 6144: level; 300 tokens: 31.9 us, 16 at a
-        // time 49.6).
+        // time 49.6).  Four fp32 experts: 72 registers, so that a CU holds seven workgroups (74 made 1537 to 1792 tokens, six to
+        // seven workgroups per CU, 1.05 to 1.18 times as slow).
         constexpr int kAll = EP < 16 ? EP : 16;
-        auto kern = route_kernel<T, EP, 4, EP == 32 ? 4 : kAll, EP == 32 ? 2 : 1>;
+        constexpr int kPerCu = EP == 32 ? 2 : EP == 4 && kF32 ? 7 : 1;
+        auto kern = route_kernel<T, EP, 4, EP == 32 ? 4 : kAll, kPerCu>;
         if constexpr ((EP == 8 || EP == 16) && kF32)
             if (d.T > 256) kern = route_kernel<T, EP, 4, 4, 4>;
         kern<<<blocks, 256, 0, st>>>(xp, wg, bias, slot_of_expert, topk_expert, topk_weight,
