@@ -24,8 +24,8 @@
 // consecutive K tiles; halving the requests to L2 was worth 8-15 % here, where the kernel runs at
 // the chip's power limit).  An operand tile (256 rows x 128 bytes = 32 KiB) goes from global memory
 // straight into LDS with buffer_load_dwordx4 ... lds (no staging registers, no LDS store
-// instructions).  LDS is a ring of five operand tiles - token rows of K tile t in slot 2t mod 5,
-// weight rows in slot 2t+1 mod 5 - so one and a half K tiles are in flight while one is multiplied.
+// instructions).  LDS is a ring of five operand tiles - weight rows of K tile t in slot 2t mod 5,
+// token rows in slot 2t+1 mod 5 - so one and a half K tiles are in flight while one is multiplied.
 // Each load instruction fills 1 KiB of LDS contiguously (8 rows x 128 bytes); the 16-byte chunk c
 // of row r is stored at chunk position c ^ ((r >> 1) & 7), chosen by which global chunk a lane
 // fetches, which makes the MFMA fragment reads (16 rows x four chunks per ds_read_b128) bank-conflict
@@ -33,9 +33,13 @@
 // offset, so the loop has no address arithmetic; in the K tail, chunks past K are fetched out of
 // range and arrive as zeros.
 //
-// Schedule per K tile (two MFMA K-steps of 32 each): fragment reads for the next step and the loads
-// of tile t+2 are slotted one by one between the MFMAs, so no memory instruction waits in a full
-// queue while the matrix pipe idles.  One barrier per tile, between its steps.
+// Schedule per K tile (two MFMA K-steps of 32 each): fragment reads for the next step, the loads
+// of tile t+2 and the scalar arithmetic are slotted between the MFMAs, so no memory instruction waits in a full
+// queue while the matrix pipe idles.  One barrier per tile, between its steps.  The places between two MFMAs are counted:
+// an MFMA takes 16 cycles, every other instruction 4 or more, and with one wavefront per SIMD nobody else fills a gap.
+// Fragment read, load and a piece of scalar arithmetic therefore each have a place of their own (the arithmetic in one lump of
+// ten instructions and loads beside reads: fine-grained layer's products 430 + 260 us against 420 + 251; prefill 1297 + 634
+// against 1276 + 626; 4096 tokens in four even slots).
 //
 // The stream of operand tiles does not stop between output tiles: an output tile's last two K tiles
 // request the first two of the next one, and the epilogue stores from registers, without LDS and
@@ -45,8 +49,8 @@
 // 788 -> 763 us, Mixtral prefill layer 2153 -> 2095, two prompts at that shape 816 -> 802.
 //
 // Slots that do not fill their tiles: a slot's rows are spread evenly over its m-tiles in whole
-// 32-row MFMA blocks (257 rows: tiles of 160 and 97 rows, not 256 and 1), a tile's blocks alternate
-// between the two rows of wavefronts, and the K loop is compiled for 0 .. 4 blocks per wavefront, so
+// 16-row MFMA blocks (257 rows: tiles of 144 and 113 rows, not 256 and 1), a tile's blocks alternate
+// between the two rows of wavefronts, and the K loop is compiled for 0 .. 8 blocks per wavefront, so
 // that matrix work is done for blocks with rows only and both wavefront rows finish together.  A
 // tile still costs a pass over its weight panel whatever it holds (8 slots of 257 rows at the Mixtral
 // shape: 0.96 -> 0.88 ms; of 513 rows: 1.51 -> 1.41 ms; full tiles unchanged).
@@ -77,7 +81,7 @@ constexpr int BR = 256;                     // weight rows per tile (SwiGLU: 128
 constexpr int BK = 64;                      // K elements per tile
 constexpr int ROW_BYTES = BK * 2;           // 128: a tile row is one whole cache line
 constexpr int TILE_BYTES = BM * ROW_BYTES;  // 32 KiB per operand
-constexpr int SLOTS = 5;                    // LDS ring of operand tiles: x(t), w(t), x(t+1), w(t+1), x(t+2), ...
+constexpr int SLOTS = 5;                    // LDS ring of operand tiles: w(t), x(t), w(t+1), x(t+1), w(t+2), ...
 constexpr size_t LDS_BYTES = SLOTS * TILE_BYTES;  // 160 KiB, all of a CU's LDS
 constexpr int KSTEP = 32;                   // K elements of one matrix instruction (16 x 16 x 32)
 static_assert(BK / KSTEP == 2, "the K loop is written out for two MFMA K-steps per tile");
@@ -85,10 +89,10 @@ constexpr int kMaxSplits = 8;           // K pieces per leftover tile, at most
 constexpr int kFixupGroups = (kMaxGroups - 1) * 16;  // workgroups of the fix-up launch: the most units there can be
 constexpr int kPlanFloats = kTiledPlanBytes / 4;  // the plan sits ahead of the partial sums
 constexpr unsigned kRotation = 21;  // K-tile rotation per slot
+constexpr int kScalarPieces = 5;    // pieces of a step's address arithmetic
 constexpr int NW = 4;            // wavefronts per workgroup, arranged 2 (tokens) x NW/2 (weight rows)
 constexpr int WN = NW / 2;
-constexpr int TB = 4;            // 32-token blocks per wavefront (128 tokens): the grain in which blocks without rows are skipped
-constexpr int TS = 2 * TB;       // 16-token blocks per wavefront
+constexpr int TS = 8;            // 16-token blocks per wavefront (128 tokens): the grain in which blocks without rows are skipped
 constexpr int WB = BR / WN / 16; // 16-row weight blocks per wavefront
 constexpr int RPI = 1024 / ROW_BYTES;      // tile rows filled by one load instruction (8)
 constexpr int LPW = BM / RPI / NW;         // load instructions per wavefront, per tile and operand (8)
@@ -172,22 +176,20 @@ __device__ __forceinline__ void tile_in_slot(int rem, int m_tiles, int n_tiles, 
 }
 
 // Rows per m-tile of a slot of `rows` rows cut into `tiles` tiles: the rows are spread evenly (in
-// whole 32-row MFMA blocks), so that a slot of 257 rows becomes tiles of 160 and 97 rows instead of
+// whole 16-row MFMA blocks), so that a slot of 257 rows becomes tiles of 144 and 113 rows instead of
 // 256 and 1.  A tile costs a pass over its weight panel whatever it holds; what is saved is the
 // matrix work of the blocks without rows, which both tiles then skip.
 __device__ __forceinline__ int rows_per_tile(int rows, int tiles) {
     const int even = (rows + tiles - 1) / (tiles > 0 ? tiles : 1);
-    return (even + 31) & ~31;  // <= BM, so tile number `tiles - 1` still starts inside the slot
+    return (even + 15) & ~15;  // <= BM, so tile number `tiles - 1` still starts inside the slot
 }
 
-// Which wavefronts multiply which of a tile's 32-row token blocks: the blocks alternate between
+// Which wavefronts multiply which of a tile's 16-row token blocks: the blocks alternate between
 // the two wavefront rows, so that both finish together whatever the number of blocks that hold rows.
-// -> tile block of block i of wavefront row wm, and the number of its blocks that hold rows.
-__device__ __forceinline__ int tile_block(int wm, int i) { return 2 * i + wm; }
-// first tile row of 16-token block j (0 .. TS-1) of wavefront row wm
-__device__ __forceinline__ int token_row(int wm, int j) { return tile_block(wm, j >> 1) * 32 + (j & 1) * 16; }
+// -> first tile row of block j of wavefront row wm, and the number of its blocks that hold rows.
+__device__ __forceinline__ int token_row(int wm, int j) { return (2 * j + wm) * 16; }
 __device__ __forceinline__ int blocks_of_wavefront(int row0, int row_end, int wm) {
-    return ((row_end - row0 + 31) / 32 - wm + 1) / 2;
+    return ((row_end - row0 + 15) / 16 - wm + 1) / 2;
 }
 
 // Four 16 x 16 output blocks of a wavefront side by side: 16-token block ts, weight blocks 4 wg .. 4 wg + 3.  `gate`
@@ -272,7 +274,7 @@ __device__ __forceinline__ int opaque(int v) {
 // their way into the ring meanwhile.  The MFMA layout gives a lane four consecutive columns of one token in every block;
 // two exchanges between odd and even rows of 16 lanes turn those of two neighbouring blocks into eight consecutive columns
 // of one block, and a store instruction then writes 64 contiguous bytes of each of 16 token rows.
-// TBLOCKS: the wavefront's 32-row token blocks that hold rows.
+// TBLOCKS: the wavefront's 16-row token blocks that hold rows.
 // Every wavefront issues kEpilogueStores<EPI> stores, whatever the tile holds (rows and columns that do not exist are
 // addressed out of range, which writes nothing): the K loop counts on it, see there.  "Out of range" is the first byte
 // past the output, c_bytes: all 16 bytes of such a store then lie past it (the host checks leave room for a row
@@ -295,7 +297,7 @@ __device__ __forceinline__ void epilogue(floatx4 (&acc)[WB][TS], __amdgpu_buffer
 #pragma unroll
         for (int np = 0; np < NB; np += 2) {
             uintx4 val = {0u, 0u, 0u, 0u};
-            if (ts < 2 * TBLOCKS) {
+            if (ts < TBLOCKS) {
                 uint32_t two[2][2];  // block, its four columns as two packed pairs
 #pragma unroll
                 for (int b = 0; b < 2; ++b) {
@@ -441,17 +443,19 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         u.at += ROW_BYTES;
         u.at = u.at == u.end ? u.begin : u.at;
     };
-    // one load instruction of the token tile or the weight tile at row byte k, into the ring slot at LDS byte rs
+    // one load instruction of the token tile or the weight tile at row byte k; rs: the LDS byte of the ring slot, and of this
+    // wavefront's part of it
+    const int wave_rs = LPW * 1024 * wave;
     const uint32_t k_bytes = (uint32_t)K * 2u;
     auto issue_x = [&](const uint32_t (&voff)[LPW], int i, int rs, int k) {
         uint32_t v = voff[i];
         if (KTAIL && (uint32_t)(k + chunk2[i & 1] * 16) >= k_bytes) v = a_bytes;  // past K: zeros
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(lds + rs + (LPW * wave + i) * 1024), 16, (int)v, k, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(a_rsrc, (lds_void*)(lds + rs + i * 1024), 16, (int)v, k, 0, 0);
     };
     auto issue_w = [&](const uint32_t (&voff)[LPW], const bf16_t* base, int i, int rs, int k, bool once) {
         uint32_t v = voff[i];
         if (KTAIL && (uint32_t)(k + chunk2[i & 1] * 16) >= k_bytes) v = b_bytes;
-        lds_void* dst = (lds_void*)(lds + rs + (LPW * wave + i) * 1024);
+        lds_void* dst = (lds_void*)(lds + rs + i * 1024);
         if (once) __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 2);  // non-temporal hint
         else __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(base, b_bytes), dst, 16, (int)v, k, 0, 0);
     };
@@ -465,12 +469,12 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     // of the two K-steps differ in bit 6 only.
     const int f_row = lane & 15;
     const int f_sw = ((lane >> 4) ^ ((f_row >> 1) & 7)) * 16;
-    const int x_off = (tile_block(wm, 0) * 32 + f_row) * ROW_BYTES + f_sw;  // token block 0 of this wavefront
+    const int x_off = (token_row(wm, 0) + f_row) * ROW_BYTES + f_sw;  // token block 0 of this wavefront
     // SwiGLU: weight blocks 0..WB/2-1 are gate rows, WB/2..WB-1 the matching up rows
     const int w_off = (wn * ((EPI == kSwiglu ? BR / 2 : BR) / WN) + f_row) * ROW_BYTES + f_sw;
 
     // ---- prologue: K tiles 0 and 1 of the first item on their way, the first landed -------------------
-    // Ring slots: the operand tiles follow each other round the ring, x(0), w(0), x(1), w(1), x(2), ...
+    // Ring slots: the operand tiles follow each other round the ring, w(0), x(0), w(1), x(1), w(2), ...
     Item cur, nxt;
     if (!item_at(0, cur)) return;
     uint32_t a_voff[LPW], b_voff[LPW];
@@ -478,21 +482,19 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     weight_addr(cur, b_voff);
     const bf16_t* w_base = wsel + (size_t)cur.slot * N * K;
     Cursor cursor = cursor_of(cur);
-    int sx = 0;  // ring slot (LDS byte) of the token rows of the K tile being multiplied
+    int sw = 0;  // ring slot (LDS byte) of the weight rows of the K tile being multiplied
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, TILE_BYTES, cursor.at, false);
+    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, wave_rs, cursor.at, false);
     token_addr(cur, perm_entry, a_voff);
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, 0, cursor.at);
+    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, wave_rs + TILE_BYTES, cursor.at);
     advance(cursor);
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, 2 * TILE_BYTES, cursor.at);
+    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, wave_rs + 2 * TILE_BYTES, cursor.at, false);
 #pragma unroll
-    for (int i = 0; i < LPW; ++i) issue_w(b_voff, w_base, i, 3 * TILE_BYTES, cursor.at, false);
+    for (int i = 0; i < LPW; ++i) issue_x(a_voff, i, wave_rs + 3 * TILE_BYTES, cursor.at);
     advance(cursor);
     barrier_keep_loads<2 * LPW>();
-    bf16x8 zero;
-    __builtin_memset(&zero, 0, sizeof(zero));
     bool stores_pending = false;  // the item before this one ended with kEpilogueStores<EPI> stores
 
     for (int idx = 0;; ++idx) {
@@ -509,29 +511,24 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
             }
         }
 
-        // Everything that touches the matrix cores is compiled for NB = 0 .. TB token blocks: the number
-        // of this wavefront's 32-row blocks that hold rows of the tile (a ragged or evenly cut tile holds
-        // fewer than 256 rows).  NB = TB is the full tile, NB = 0 a wavefront that only takes part in the
+        // Everything that touches the matrix cores is compiled for NB = 0 .. TS token blocks: the number
+        // of this wavefront's 16-row blocks that hold rows of the tile (a ragged or evenly cut tile holds
+        // fewer than 256 rows).  NB = TS is the full tile, NB = 0 a wavefront that only takes part in the
         // loads and barriers.  The accumulators live and die inside one instance: where instances met, the compiler
         // would permute all 256 of them.
         auto do_item = [&](auto nb_c, auto once_c) {
             constexpr int NB = decltype(nb_c)::value;
-            floatx4 acc[WB][TS];  // [weight block][token block]
+            floatx4 acc[WB][TS];  // [weight block][token block]; an item's first MFMA step adds to nothing and need not clear them
             mfma_settle();  // the last of the item before have been read
-#pragma unroll
-            for (int i = 0; i < WB; ++i)
-#pragma unroll
-                for (int j = 0; j < 2 * NB; ++j) mfma_zero(acc[i][j], zero);
 
             bf16x8 xf[2][TS], wf[2][WB];
-            // fragment f of MFMA K-step kk: token blocks 0 .. 2 NB - 1, then the weight blocks.  xp, wp: this lane's place (LDS
+            // fragment f of MFMA K-step kk: token blocks 0 .. NB - 1, then the weight blocks.  xp, wp: this lane's place (LDS
             // byte) in the operand tiles for that step
             auto load_frag = [&](int kk, int f, int xp, int wp) {
-                constexpr int NT = 2 * NB;
-                if (f < NT) {
+                if (f < NB) {
                     xf[kk][f] = *reinterpret_cast<const bf16x8*>(lds + xp + token_row(0, f) * ROW_BYTES);
                 } else {
-                    const int i = f - NT;
+                    const int i = f - NB;
                     const int rr = (EPI == kSwiglu && i >= WB / 2) ? BR / 2 + (i - WB / 2) * 16 : i * 16;
                     wf[kk][i] = *reinterpret_cast<const bf16x8*>(lds + wp + rr * ROW_BYTES);
                 }
@@ -539,57 +536,76 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
             // One MFMA K-step: multiplies the fragments of step kk and, slotted in between so that no memory
             // instruction waits in a full queue while the matrix pipe idles, reads the fragments of the step after it
             // (from xp, wp; in the first three quarters of the step, so that they are there at its end), issues LPW
-            // global->LDS loads and runs `scalar`, the next step's address arithmetic.
-            auto step = [&](int kk, int xp, int wp, auto issue, auto scalar) {
-                constexpr int NT = 2 * NB, MF = WB * NT, FR = WB + NT;
+            // global->LDS loads and runs `scalar`, the next step's address arithmetic, in kScalarPieces pieces.
+            // A full tile reads a fragment after every third MFMA, and the others have places between those.  A tile with
+            // fewer blocks is bound by when its operands arrive, not by the matrix pipe: up to six blocks, step 1's
+            // loads go out in its first half (8 slots of 160 rows at the Mixtral shape: 371 + 186 -> 345 + 171 us with the
+            // order of the operands in the ring; on full tiles 1 % slower).
+            auto step = [&](auto first_c, int kk, int xp, int wp, auto issue, auto scalar) {
+                constexpr int MF = WB * NB, FR = WB + NB;
                 if constexpr (NB == 0) {
     #pragma unroll
                     for (int i = 0; i < LPW; ++i) issue(i);
-                    scalar();
+    #pragma unroll
+                    for (int p = 0; p < kScalarPieces; ++p) scalar(p);
                 } else {
-                    constexpr int FR_EVERY = MF * 3 / 4 / FR, LD_EVERY = MF / LPW;
-                    static_assert(FR_EVERY >= 1 && FR_EVERY * FR <= MF && LD_EVERY * LPW <= MF, "everything finds its place");
+                    constexpr auto frags_by = [](int m) { return m * FR / (MF * 3 / 4) < FR ? m * FR / (MF * 3 / 4) : FR; };
+                    constexpr auto load_after = [](int i, int kk) {  // the MFMA behind which load i goes out
+                        const int every = NB <= 6 && NB > 1 && kk == 1 ? MF / LPW / 2 : MF / LPW;
+                        return NB == TS ? 7 + 6 * i : every * i + every / 2;
+                    };
+                    constexpr auto piece_after = [](int p) { return NB == TS ? 16 + 6 * p : MF / 8 + p * (MF * 3 / 4) / kScalarPieces; };
+                    static_assert(frags_by(MF) == FR && load_after(LPW - 1, 0) < MF && piece_after(kScalarPieces - 1) < MF, "everything finds its place");
     #pragma unroll
                     for (int m = 0; m < MF; ++m) {
-                        const int ni = m / NT;
-                        const int mi = (ni & 1) ? NT - 1 - m % NT : m % NT;  // back and forth: only one operand changes between two MFMAs
-                        mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
-                        if (m % FR_EVERY == FR_EVERY - 1 && m / FR_EVERY < FR) load_frag(kk ^ 1, m / FR_EVERY, xp, wp);
-                        if (m % LD_EVERY == LD_EVERY / 2) issue(m / LD_EVERY);
-                        if (m == MF / 2) {
-                            __builtin_amdgcn_sched_barrier(0);
-                            scalar();
-                            __builtin_amdgcn_sched_barrier(0);
-                        }
+                        const int ni = m / NB;
+                        const int mi = (ni & 1) ? NB - 1 - m % NB : m % NB;  // back and forth: only one operand changes between two MFMAs
+                        if (decltype(first_c)::value) mfma_16x16x32_first(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
+                        else mfma_16x16x32(acc[ni][mi], wf[kk][ni], xf[kk][mi]);
+    #pragma unroll
+                        for (int f = frags_by(m); f < frags_by(m + 1); ++f) load_frag(kk ^ 1, f, xp, wp);
+    #pragma unroll
+                        for (int i = 0; i < LPW; ++i)
+                            if (m == load_after(i, kk)) issue(i);
+    #pragma unroll
+                        for (int p = 0; p < kScalarPieces; ++p)
+                            if (m == piece_after(p)) {
+                                __builtin_amdgcn_sched_barrier(0);
+                                scalar(p);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
                     }
                 }
             };
 
             // ---- main loop -----------------------------------------------------------------------------
-            // Per K tile: two MFMA steps of 32.  Token rows of tile t+2 are requested during step 0 (into the slot
-            // that held the weight rows of tile t-1), weight rows of tile t+2 during step 1 (into the slot of this
-            // tile's token rows, dead after the barrier).  One barrier per tile, between the steps: by then every
+            // Per K tile: two MFMA steps of 32.  Weight rows of tile t+2 are requested during step 0 (into the slot
+            // that held the token rows of tile t-1), token rows of tile t+2 during step 1 (into the slot of this
+            // tile's weight rows, dead after the barrier): the weights, which come from HBM, have half a K tile longer to
+            // arrive in than the token rows, which mostly come from nearer.  One barrier per tile, between the steps: by then every
             // wavefront has read its last fragments of tile t, and tile t+1 has landed once only the LPW newest
-            // loads (token rows of t+2) are pending - and, in an item's first K tile, the stores of the item before,
+            // loads (weight rows of t+2) are pending - and, in an item's first K tile, the stores of the item before,
             // which are newer than the loads of this item's first two K tiles.
             // The stream of operand tiles does not end with the item: its last two K tiles request the first two of
             // the next one, which have the epilogue's time to arrive in.
             // A wavefront skips the fragment reads and MFMAs of its token blocks without rows: the kernel
             // runs at the chip's power limit, so work not done is speed for the others.
-            int xp0 = sx + x_off, wp0 = ring(sx, 1) + w_off;
+            int xp0 = ring(sw, 1) + x_off, wp0 = sw + w_off;
     #pragma unroll
-            for (int f = 0; NB > 0 && f < 2 * NB + WB; ++f) load_frag(0, f, xp0, wp0);
+            for (int f = 0; NB > 0 && f < NB + WB; ++f) load_frag(0, f, xp0, wp0);
             int xp1 = xp0 ^ 64, wp1 = wp0 ^ 64;
+            int rs0 = ring(sw, 4) + wave_rs;
             __builtin_amdgcn_sched_barrier(0);
-            auto k_tile = [&] {
+            auto k_tile = [&](auto first_c) {
                 const int k = __builtin_amdgcn_readfirstlane(cursor.at);  // (uniform, which the compiler does not see)
-                const int sx2 = ring(sx, 4);
-                int sx1 = 0;
-                step(0, xp1, wp1, [&](int i) { issue_x(a_voff, i, sx2, k); },
-                     [&] {
-                         sx1 = ring(sx, 2);
-                         xp0 = sx1 + x_off;
-                         wp0 = ring(sx, 3) + w_off;
+                int sw1 = 0, sx1 = 0, rs1 = 0;
+                step(first_c, 0, xp1, wp1, [&](int i) { issue_w(b_voff, w_base, i, rs0, k, decltype(once_c)::value); },
+                     [&](int p) {
+                         if (p == 0) sw1 = ring(sw, 2);
+                         if (p == 1) wp0 = sw1 + w_off;
+                         if (p == 2) sx1 = ring(sw, 3);
+                         if (p == 3) xp0 = sx1 + x_off;
+                         if (p == 4) rs1 = sw + wave_rs;
                      });
                 __builtin_amdgcn_sched_barrier(0);
                 if (stores_pending) {
@@ -599,36 +615,41 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
                     barrier_keep_loads<LPW>();
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                step(1, xp0, wp0, [&](int i) { issue_w(b_voff, w_base, i, sx, k, decltype(once_c)::value); },
-                     [&] {
-                         xp1 = xp0 ^ 64;
-                         wp1 = wp0 ^ 64;
+                step(std::false_type{}, 1, xp0, wp0, [&](int i) { issue_x(a_voff, i, rs1, k); },
+                     [&](int p) {
+                         if (p == 0) xp1 = xp0 ^ 64;
+                         if (p == 1) wp1 = wp0 ^ 64;
+                         if (p == 2) rs0 = ring(sw, 1);
+                         if (p == 3) rs0 += wave_rs;
+                         if (p == 4) advance(cursor);
                      });
                 __builtin_amdgcn_sched_barrier(0);
-                advance(cursor);
-                sx = sx1;
+                sw = sw1;
             };
-            int t = cur.kt - 2;
-            if (t > 0) {
-                do k_tile();
-                while (--t > 0);
-            } else {  // nothing has waited for the next item's perm entries yet
-                __builtin_amdgcn_s_waitcnt(wait_imm(0));
-            }
-            // from here on the loads are the next item's
-            cursor = Cursor{0, 0, 2 * ROW_BYTES};
-            if (have_nxt) {
-                token_addr(nxt, perm_entry, a_voff);
-                weight_addr(nxt, b_voff);
-                w_base = wsel + (size_t)nxt.slot * N * K;
-                cursor = cursor_of(nxt);
-            } else {  // none: they go on, out of range: zeros land in ring slots that nobody reads any more
+            // the last two K tiles request the next item's first two
+            auto turn_to_next = [&] {
+                cursor = Cursor{0, 0, 2 * ROW_BYTES};
+                if (have_nxt) {
+                    token_addr(nxt, perm_entry, a_voff);
+                    weight_addr(nxt, b_voff);
+                    w_base = wsel + (size_t)nxt.slot * N * K;
+                    cursor = cursor_of(nxt);
+                } else {  // none: they go on, out of range: zeros land in ring slots that nobody reads any more
     #pragma unroll
-                for (int i = 0; i < LPW; ++i) { a_voff[i] = a_bytes; b_voff[i] = b_bytes; }
+                    for (int i = 0; i < LPW; ++i) { a_voff[i] = a_bytes; b_voff[i] = b_bytes; }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if (cur.kt == 2) {
+                __builtin_amdgcn_s_waitcnt(wait_imm(0));  // nothing has waited for the next item's perm entries yet
+                turn_to_next();
             }
-            __builtin_amdgcn_sched_barrier(0);
+            k_tile(std::true_type{});
     #pragma unroll 1
-            for (int t = 0; t < 2; ++t) k_tile();
+            for (int left = cur.kt - 1; left > 0; --left) {
+                if (left == 2) turn_to_next();
+                k_tile(std::false_type{});
+            }
             mfma_settle();
 
             if (cur.piece < 0) {
@@ -638,7 +659,7 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
     #pragma unroll
                 for (int i = 0; i < WB; ++i)
     #pragma unroll
-                    for (int j = 0; j < 2 * NB; ++j) {  // (the fix-up skips blocks without rows)
+                    for (int j = 0; j < NB; ++j) {  // (the fix-up skips blocks without rows)
     #pragma unroll
                         for (int v = 0; v < 4; ++v) dst[((i * TS + j) * 4 + v) * (64 * NW)] = acc_read(acc[i][j][v]);
                     }
@@ -652,19 +673,27 @@ __global__ __launch_bounds__(64 * NW) void grouped_gemm_bf16(const bf16_t* __res
         // shape: 10.5 instead of 6.6 GB) and gains nothing: with the three policies (limit 4, 8, none) run
         // in turns inside one process, layer times differ by less than 1 % on every workload (prefill
         // 2.298 / 2.288 / 2.307 ms, fine-grained layer 0.845 / 0.842 / 0.836 ms).
-        const int my_blocks = cur.slot_tiles > kSkipBlocksUpToTiles ? TB : blocks_of_wavefront(cur.row0, cur.row_end, wm);
-        static_assert(TB == 4, "written out for four token blocks per wavefront");
+        const int my_blocks = cur.slot_tiles > kSkipBlocksUpToTiles ? TS : blocks_of_wavefront(cur.row0, cur.row_end, wm);
+        static_assert(TS == 8, "written out for eight token blocks per wavefront");
         // A slot of one m-tile: nobody else reads its weight panel, which is then loaded with the
         // non-temporal hint, so that the stream does not push the token rows out of the caches (but not with a K tail: rows are
         // not whole lines then, and a line between two K tiles would come from HBM twice).
         if (!KTAIL && cur.slot_tiles == 1) {
-            if (my_blocks >= 4) do_item(std::integral_constant<int, 4>{}, std::true_type{});
+            if (my_blocks >= 8) do_item(std::integral_constant<int, 8>{}, std::true_type{});
+            else if (my_blocks == 7) do_item(std::integral_constant<int, 7>{}, std::true_type{});
+            else if (my_blocks == 6) do_item(std::integral_constant<int, 6>{}, std::true_type{});
+            else if (my_blocks == 5) do_item(std::integral_constant<int, 5>{}, std::true_type{});
+            else if (my_blocks == 4) do_item(std::integral_constant<int, 4>{}, std::true_type{});
             else if (my_blocks == 3) do_item(std::integral_constant<int, 3>{}, std::true_type{});
             else if (my_blocks == 2) do_item(std::integral_constant<int, 2>{}, std::true_type{});
             else if (my_blocks == 1) do_item(std::integral_constant<int, 1>{}, std::true_type{});
             else do_item(std::integral_constant<int, 0>{}, std::true_type{});
         } else {
-            if (my_blocks >= 4) do_item(std::integral_constant<int, 4>{}, std::false_type{});
+            if (my_blocks >= 8) do_item(std::integral_constant<int, 8>{}, std::false_type{});
+            else if (my_blocks == 7) do_item(std::integral_constant<int, 7>{}, std::false_type{});
+            else if (my_blocks == 6) do_item(std::integral_constant<int, 6>{}, std::false_type{});
+            else if (my_blocks == 5) do_item(std::integral_constant<int, 5>{}, std::false_type{});
+            else if (my_blocks == 4) do_item(std::integral_constant<int, 4>{}, std::false_type{});
             else if (my_blocks == 3) do_item(std::integral_constant<int, 3>{}, std::false_type{});
             else if (my_blocks == 2) do_item(std::integral_constant<int, 2>{}, std::false_type{});
             else if (my_blocks == 1) do_item(std::integral_constant<int, 1>{}, std::false_type{});
