@@ -31,6 +31,8 @@
 // are addressed out of range of their buffer: zeros arrive and no memory is touched.
 //
 // Work distribution.  Group sizes live on the device; everything is derived from slot_offsets there.
+// An output's columns are cut into tiles as wide as a tile can hold, or narrower ones where those leave CUs idle or a last round
+// nearly empty (narrower_tiles(); the rows that a tile then lacks are addressed out of range as well).
 // Tiles are numbered slot by slot, and inside a slot all m-tiles of an n-tile are consecutive;
 // workgroup ids go round-robin over the 8 XCDs and are remapped so that an XCD works on consecutive
 // tiles: the m-tiles that share a weight panel run at the same time behind the same L2, and the
@@ -88,6 +90,7 @@ constexpr int kGroups = kMaxGroups;  // the persistent launch has one workgroup 
 constexpr int kMinShare = 8;     // K tiles per workgroup, at least, when tiles are cut
 constexpr int kMinSpared = 48;   // tiles are cut only if that shortens every workgroup's K walk by this many K tiles
 constexpr long long kRowsPerSlot64 = 48;  // up to that many rows per slot on average: token tiles of 64 rows
+constexpr int kNarrowFromK = 17; // K tiles from which on column tiles may be narrower than a tile can hold
 constexpr int kMinPersistK = 64; // K tiles from which on the persistent launch (which may cut) is used at all
 
 // The tiles of a launch and how a persistent launch shares them out, derived from slot_offsets by
@@ -99,20 +102,60 @@ struct Work {
     long long units;                      // tiles * kt: the sequence that is cut into shares
     int sharers;                          // > 0: tiles are cut, that many workgroups take equal shares; 0: whole tiles
 };
-__device__ __forceinline__ Work make_work(int s_begin, int s_end, int n_tiles, int K, int lane, int G, int bm) {
+// How an output's N columns are cut into tiles: n tiles of `columns` (a multiple of 8 unless it is all that a tile can hold).
+struct ColumnTiles {
+    int n, columns;
+};
+// Narrower column tiles than a tile can hold, where those leave CUs idle or a last round nearly empty.  Lane l weighs up l tiles
+// more than the fewest.  A CU is bound by the number of lines that it requests, weight rows and token rows of a K tile (it has
+// some 110 outstanding), and a round of the chip's CUs by HBM, which delivers the weight rows of a tile in 1.7 times the time
+// that its CU needs for as many lines; a slot's m-tiles share theirs.  What is not 4 % better than the fewest stays with those.
+// (d 1032, f 2808, 11 slots of 36 to 279 rows: 308 and 126 tiles of 128 columns become 504 of 80 and 252 of 64, products
+// 57.6 + 36.1 -> 51.2 + 28.0 us.)
+__device__ __forceinline__ ColumnTiles narrower_tiles(ColumnTiles fewest, int m_tiles, int slots, int rows, int max_tiles, int rows_per_column,
+                                                      int N, int k_tiles, bool whole_lines, int lane, int cus) {
+    const int full = m_tiles * fewest.n;
+    // the rounds are full as it is (or there are no rows); of one round less is expected, since finding out costs 0.3 us, and a
+    // longer walk: a tile's start weighs as much as some ten K tiles (3 slots of 76 rows, d 1184, f 464: 14.3 -> 15.2 us)
+    if (full * 16 >= (full + cus - 1) / cus * cus * (full <= cus ? 14 : 15)) return fewest;
+    if (k_tiles < (full <= cus ? 32 : whole_lines ? 24 : kNarrowFromK)) return fewest;
+    const int want = fewest.n + lane;
+    const int columns = lane == 0 ? fewest.columns : ((N + want - 1) / want + 7) & ~7;
+    const int n = (N + columns - 1) / columns;
+    const int tiles = m_tiles * n;
+    const float per_cu = (float)rows_per_column * columns + (float)rows / m_tiles;              // lines per K tile and CU
+    const float from_hbm = 1.7f * rows_per_column * columns * slots / m_tiles;                  // a full round's, as long as
+    const int rounds = tiles / cus;
+    const float last = (float)(tiles - rounds * cus) / cus;                                     // share of the CUs in the last round
+    float cost = rounds * fmaxf(per_cu, from_hbm) + (last > 0.0f ? fmaxf(per_cu, from_hbm * last) : 0.0f);
+    if (lane == 0) cost *= 0.96f;
+    else if (tiles > max_tiles) cost = 3.0e38f;
+    float least = cost;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) least = fminf(least, __shfl_xor(least, off));
+    const int best = __ffsll(__ballot(cost == least)) - 1;
+    return ColumnTiles{__builtin_amdgcn_readlane(n, best), __builtin_amdgcn_readlane(columns, best)};
+}
+// The m-tiles per slot of `bm` rows: per lane (= slot), with the number of tiles before it and of all of them.
+__device__ __forceinline__ Work make_work(int s_begin, int s_end, int lane, int bm, int* m_tiles) {
     Work w;
     w.s_begin = s_begin;
     w.s_end = s_end;
     w.s_mtiles = (w.s_end - w.s_begin + bm - 1) / bm;
-    const int span = w.s_mtiles * n_tiles;
-    int incl = span;
+    int incl = w.s_mtiles;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const int up = __shfl_up(incl, off);
         if (lane >= off) incl += up;
     }
-    w.first = incl - span;
-    w.tiles = __builtin_amdgcn_readlane(incl, 63);
+    w.first = incl - w.s_mtiles;
+    *m_tiles = __builtin_amdgcn_readlane(incl, 63);
+    return w;
+}
+// ... and the tiles of the launch, m_tiles for each of n_tiles column tiles.
+__device__ __forceinline__ void finish_work(Work& w, int m_tiles, int n_tiles, int K, int G) {
+    w.first *= n_tiles;
+    w.tiles = m_tiles * n_tiles;
     w.kt = (K + BK - 1) / BK;
     w.units = (long long)w.tiles * w.kt;
     // Cutting pays when it spares every workgroup a K walk of some length: the pieces are extra traffic
@@ -122,7 +165,6 @@ __device__ __forceinline__ Work make_work(int s_begin, int s_end, int n_tiles, i
     p = p < G ? p : G;
     const long long share = p > 0 ? (w.units + p - 1) / p : 0;
     w.sharers = (p > w.tiles && w.kt - share >= kMinSpared) ? (int)p : 0;
-    return w;
 }
 // first unit of share g (g = 0 .. sharers; share g is [share_begin(g), share_begin(g + 1)); from sharers on: empty)
 __device__ __forceinline__ long long share_begin(const Work& w, int g) {
@@ -158,7 +200,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
                                                      const int32_t* __restrict__ offsets,
                                                      const bf16_t* __restrict__ b0, const bf16_t* __restrict__ b1,
                                                      bf16_t* __restrict__ c, float* __restrict__ partials, int S, int N,
-                                                     int K, int n_tiles, int XCDS) {
+                                                     int K, int n_tiles, int max_tiles, int cus, int XCDS) {
     constexpr int W_TILE = BR * ROW_BYTES;             // 32 or 16 KiB
     constexpr int X_TILE = BM * ROW_BYTES;             // 16 or 8 KiB
     constexpr int STAGE_BYTES = X_TILE + W_TILE;
@@ -193,8 +235,22 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         sorted.run(gather.sort, S, reinterpret_cast<int*>(lds));
         if (blockIdx.x == 0) sorted.store_slots(gather.sort, S);
     }
-    const Work work = make_work(sorts ? sorted.begin : lane < S ? offsets[lane] : 0,
-                                sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0, n_tiles, K, lane, G, BM);
+    int m_tiles;
+    Work work = make_work(sorts ? sorted.begin : lane < S ? offsets[lane] : 0, sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0, lane,
+                          BM, &m_tiles);
+    const int rows_total = sorts ? __builtin_amdgcn_readlane(work.s_end, S - 1) : offsets[S];
+    ColumnTiles ct{n_tiles, BNO};
+    const int first_m_tile = work.first;
+    if (PERSIST) finish_work(work, m_tiles, ct.n, K, G);
+    if (PERSIST ? work.sharers == 0 : max_tiles > 0) {
+        ct = narrower_tiles(ct, m_tiles, __popcll(__ballot(work.s_mtiles > 0)), rows_total, max_tiles, EPI == kSwiglu ? 2 : 1, N, (K + BK - 1) / BK,
+                            !KTAIL, lane, cus);
+        work.first = first_m_tile;
+        finish_work(work, m_tiles, ct.n, K, G);
+        work.sharers = 0;
+    } else if (!PERSIST) {
+        finish_work(work, m_tiles, ct.n, K, G);
+    }
     // workgroup ids go round-robin over the XCDs: g numbers them XCD by XCD
     const int xcd = blockIdx.x % XCDS, idx = blockIdx.x / XCDS;
     const int g = xcd * (G / XCDS) + idx;
@@ -217,7 +273,6 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         u = share_begin(work, g);
         u_end = share_begin(work, g + 1);
     }
-    const int rows_total = sorts ? __builtin_amdgcn_readlane(work.s_end, S - 1) : offsets[S];
 
     // ---- lane-constant parts of the addressing -------------------------------------------------------
     // Load instruction (w, i) of an operand fills tile rows (L? * w + i) * 8 .. +7; lane l lands in row
@@ -264,7 +319,8 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         }
         int slot, row0, row_end, nt, slot_mtiles;
         decode_tile(work, S, lane, tile, BM, slot, row0, row_end, nt, slot_mtiles);
-        const int n0 = nt * BNO;
+        const int n0 = nt * ct.columns;
+        const int n_end = n0 + ct.columns < N ? n0 + ct.columns : N;
 
         uint32_t x_voff[LX], w_voff[LW];
         int* list = reinterpret_cast<int*>(lds + kSortLdsBytes);
@@ -288,7 +344,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         for (int i = 0; i < LW; ++i) {
             const int tr = (LW * wave + i) * 8 + l_row;
             const int n = n0 + (EPI == kSwiglu ? tr % (BR / 2) : tr);  // SwiGLU: the second half = the same rows of W3
-            w_voff[i] = n >= N ? b_bytes : ((uint32_t)n * (uint32_t)K + w_chunk[i] * 8) * 2u;
+            w_voff[i] = n >= n_end ? b_bytes : ((uint32_t)n * (uint32_t)K + w_chunk[i] * 8) * 2u;
         }
         const __amdgpu_buffer_rsrc_t b_rsrc = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<bf16_t*>(wsel + (size_t)slot * N * K), 0, (int)b_bytes, 0x00020000);
@@ -477,7 +533,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         for (int it = 0; it < BM / NW / RPS; ++it) {
             const int r = wave * (BM / NW) + it * RPS + lane / CPR;
             const uint4 val = *reinterpret_cast<const uint4*>(lds + r * ROWB + ((jc ^ (r & SWM)) * 16));
-            if (row0 + r < row_end && n < N) {
+            if (row0 + r < row_end && n < n_end) {
                 // combine folded in (second product, one expert per token): the row goes to its token's row of the output
                 const int dr = (EPI == kPlain && gather.out_perm != nullptr) ? gather.out_perm[row0 + r] : row0 + r;
                 *reinterpret_cast<uint4*>(c + (size_t)dr * N + n) = val;
@@ -505,7 +561,9 @@ __global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int b = blockIdx.x + 1;
-    const Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, n_tiles, K, lane, G, BM);
+    int m_tiles;
+    Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, lane, BM, &m_tiles);
+    finish_work(work, m_tiles, n_tiles, K, G);
     if (b >= work.sharers) return;              // nothing was cut, or no share starts here
     const long long ub = share_begin(work, b);  // first unit of share b
     if (ub % work.kt == 0) return;              // the boundary falls between two tiles
@@ -580,14 +638,18 @@ hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, co
     hipError_t es = device_shape(&shape);
     if (es != hipSuccess) return es;
     if (PERSIST) {
-        kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, shape.xcds);
+        kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, shape.cus, shape.xcds);
         if (shape.groups > 1)
             mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
                                                                         shape.groups);
     } else {
-        const long long tiles = m_tiles * n_tiles;
+        // The kernel, which knows how many m-tiles there are, may cut the columns finer; not with a short K, where a tile's start
+        // weighs as much as its walk and finding out costs more than it gives (12 K tiles: 19.0 -> 19.5 us).
+        const bool may_narrow = (K + BK - 1) / BK >= kNarrowFromK;
+        long long tiles = m_tiles * n_tiles;
+        if (may_narrow && tiles < shape.cus) tiles = shape.cus;
         const unsigned blocks = (unsigned)((tiles + shape.xcds - 1) / shape.xcds * shape.xcds);
-        kern<<<blocks, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, shape.xcds);
+        kern<<<blocks, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, may_narrow ? (int)tiles : 0, shape.cus, shape.xcds);
     }
     return hipGetLastError();
 }
