@@ -88,6 +88,7 @@ __device__ __forceinline__ void barrier_keep_loads() {
 
 constexpr int kGroups = kMaxGroups;  // the persistent launch has one workgroup per CU, at most this many
 constexpr int kMinShare = 8;     // K tiles per workgroup, at least, when tiles are cut
+constexpr int kMaxCutK = 1 << 14; // K tiles up to which tiles are cut: (kGroups + 1) * kGroups * kMaxCutK units fit 32 bits
 constexpr int kMinSpared = 48;   // tiles are cut only if that shortens every workgroup's K walk by this many K tiles
 constexpr long long kRowsPerSlot64 = 48;  // up to that many rows per slot on average: token tiles of 64 rows
 constexpr int kNarrowFromK = 17; // K tiles from which on column tiles may be narrower than a tile can hold
@@ -99,7 +100,7 @@ struct Work {
     int s_begin, s_end, s_mtiles, first;  // per lane (= slot)
     int tiles;                            // all output tiles
     int kt;                               // K tiles per output tile
-    long long units;                      // tiles * kt: the sequence that is cut into shares
+    unsigned units;                       // if tiles are cut, tiles * kt: the sequence that is cut into shares
     int sharers;                          // > 0: tiles are cut, that many workgroups take equal shares; 0: whole tiles
 };
 // How an output's N columns are cut into tiles: n tiles of `columns` (a multiple of 8 unless it is all that a tile can hold).
@@ -157,22 +158,26 @@ __device__ __forceinline__ void finish_work(Work& w, int m_tiles, int n_tiles, i
     w.first *= n_tiles;
     w.tiles = m_tiles * n_tiles;
     w.kt = (K + BK - 1) / BK;
-    w.units = (long long)w.tiles * w.kt;
+    w.units = 0;
+    w.sharers = 0;
     // Cutting pays when it spares every workgroup a K walk of some length: the pieces are extra traffic
     // and the second kernel has work to do (a fine-grained layer with K = 2048, 176 tiles: 57 -> 72 us
-    // when cut regardless).
-    long long p = w.units / kMinShare;
-    p = p < G ? p : G;
-    const long long share = p > 0 ? (w.units + p - 1) / p : 0;
-    w.sharers = (p > w.tiles && w.kt - share >= kMinSpared) ? (int)p : 0;
+    // when cut regardless).  (In 32 bits, which a sequence of fewer tiles than workgroups fits: the 64-bit divisions were
+    // 2 us of either kernel's start.)
+    if (w.tiles >= G || w.tiles == 0 || w.kt > kMaxCutK) return;
+    w.units = (unsigned)w.tiles * (unsigned)w.kt;
+    unsigned p = w.units / kMinShare;
+    p = p < (unsigned)G ? p : (unsigned)G;
+    const int share = p > 0 ? (int)((w.units + p - 1) / p) : 0;
+    w.sharers = ((int)p > w.tiles && w.kt - share >= kMinSpared) ? (int)p : 0;
 }
 // first unit of share g (g = 0 .. sharers; share g is [share_begin(g), share_begin(g + 1)); from sharers on: empty)
-__device__ __forceinline__ long long share_begin(const Work& w, int g) {
-    return g >= w.sharers ? w.units : w.units * g / w.sharers;
+__device__ __forceinline__ unsigned share_begin(const Work& w, int g) {
+    return g >= w.sharers ? w.units : w.units * (unsigned)g / (unsigned)w.sharers;
 }
 // the share that holds unit u: the largest g with share_begin(g) <= u
-__device__ __forceinline__ int share_of(const Work& w, long long u) {
-    return (int)(((u + 1) * w.sharers + w.units - 1) / w.units) - 1;
+__device__ __forceinline__ int share_of(const Work& w, unsigned u) {
+    return (int)(((u + 1) * (unsigned)w.sharers + w.units - 1) / w.units) - 1;
 }
 // tile number -> slot, first row, end of the slot's rows, n-tile
 __device__ __forceinline__ void decode_tile(const Work& w, int S, int lane, int L, int bm, int& slot, int& row0,
@@ -258,7 +263,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     // K-tile units [u, u_end) of the tile sequence (a share).
     const bool cut = PERSIST && work.sharers > 0;
     int L, L_end, L_step;
-    long long u = 0, u_end = 0;
+    unsigned u = 0, u_end = 0;
     if (!PERSIST) {  // one tile: XCD x holds tiles x * per_xcd .. in the order they are dispatched
         const int per_xcd = (work.tiles + XCDS - 1) / XCDS;
         L = xcd * per_xcd + idx;
@@ -312,10 +317,10 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
             L += L_step;
         } else {
             if (u >= u_end) break;
-            tile = (int)(u / work.kt);
-            kb = (int)(u - (long long)tile * work.kt);
-            cnt = (long long)(work.kt - kb) < u_end - u ? work.kt - kb : (int)(u_end - u);
-            u += cnt;
+            tile = (int)(u / (unsigned)work.kt);
+            kb = (int)(u - (unsigned)(tile * work.kt));
+            cnt = work.kt - kb < (int)(u_end - u) ? work.kt - kb : (int)(u_end - u);
+            u += (unsigned)cnt;
         }
         int slot, row0, row_end, nt, slot_mtiles;
         decode_tile(work, S, lane, tile, BM, slot, row0, row_end, nt, slot_mtiles);
@@ -545,11 +550,14 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
 
 // Adds the pieces of each tile that the shares cut, in K order, and applies the epilogue.  A cut
 // tile is found at a boundary between two shares; a launch covers every boundary, one workgroup each,
-// which walks the 32 x 32 block positions of a wavefront's accumulators.
+// with four wavefronts for each of the kFixupUnits 32 x 32 block positions of a wavefront's accumulators: they are independent,
+// and one after the other they are a chain of memory latencies.
 // Workgroup b - 1: boundary b = 1 .. G-1 lies between shares b-1 and b.  When the main kernel
 // took whole tiles, which the host cannot know, every workgroup exits after reading slot_offsets.
 template <int EPI, int BM, int BR>
-__global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__ offsets, bf16_t* __restrict__ c,
+constexpr int kFixupUnits = TB * (BR / (NW / (BM / 64)) / 32) / (EPI == kSwiglu ? 2 : 1);
+template <int EPI, int BM, int BR>
+__global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixup(const int32_t* __restrict__ offsets, bf16_t* __restrict__ c,
                                                  const int32_t* __restrict__ out_perm,
                                                  const float* __restrict__ partials, int S, int N, int K,
                                                  int n_tiles, int G) {
@@ -557,63 +565,62 @@ __global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__
     constexpr int WB = BR / WN / 32;
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
-    constexpr int UNITS = TB * NB;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    static_assert(kFixupUnits<EPI, BM, BR> == TB * NB, "every block position");
+    const int tid = threadIdx.x % (64 * NW), lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int b = blockIdx.x + 1;
     int m_tiles;
     Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, lane, BM, &m_tiles);
     finish_work(work, m_tiles, n_tiles, K, G);
     if (b >= work.sharers) return;              // nothing was cut, or no share starts here
-    const long long ub = share_begin(work, b);  // first unit of share b
-    if (ub % work.kt == 0) return;              // the boundary falls between two tiles
-    const int tile = (int)(ub / work.kt);
-    const long long t_begin = (long long)tile * work.kt, t_end = t_begin + work.kt;
+    const unsigned ub = share_begin(work, b);   // first unit of share b
+    const int tile = (int)(ub / (unsigned)work.kt);
+    const unsigned t_begin = (unsigned)(tile * work.kt), t_end = t_begin + (unsigned)work.kt;
+    if (ub == t_begin) return;                  // the boundary falls between two tiles
     const int g_first = share_of(work, t_begin), g_last = share_of(work, t_end - 1);
     if (g_first != b - 1) return;  // several boundaries inside one tile: the first of them does the work
     int slot, row0, row_end, nt, slot_mtiles;
     decode_tile(work, S, lane, tile, BM, slot, row0, row_end, nt, slot_mtiles);
-    for (int unit = 0; unit < UNITS; ++unit) {
-        const int mi = unit / NB, ni = unit % NB;
-        if (row0 + wm * 64 + mi * 32 >= row_end) continue;  // this wavefront's block holds no rows: nothing was written
-        floatx16 gate, up;
+    const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
+    const int mi = unit / NB, ni = unit % NB;
+    if (row0 + wm * 64 + mi * 32 >= row_end) return;  // this wavefront's block holds no rows: nothing was written
+    floatx16 gate, up;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) { gate[v] = 0.0f; up[v] = 0.0f; }
-        for (int gg = g_first; gg <= g_last; ++gg) {
-            // share g_first holds the start of the tile (its piece starts at K tile 0), the others start inside it
-            const float* src = partials + (size_t)piece_slot(gg, gg != g_first) * (BM * BR) + tid;
-            float ga[16], ua[16];  // all loads of a piece in flight together, then the adds
+    for (int v = 0; v < 16; ++v) { gate[v] = 0.0f; up[v] = 0.0f; }
+    for (int gg = g_first; gg <= g_last; ++gg) {
+        // share g_first holds the start of the tile (its piece starts at K tile 0), the others start inside it
+        const float* src = partials + (size_t)piece_slot(gg, gg != g_first) * (BM * BR) + tid;
+        float ga[16], ua[16];  // all loads of a piece in flight together, then the adds
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                ga[v] = src[((ni * TB + mi) * 16 + v) * (64 * NW)];
-                ua[v] = EPI == kSwiglu ? src[(((ni + NB) * TB + mi) * 16 + v) * (64 * NW)] : 0.0f;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                gate[v] += ga[v];
-                up[v] += ua[v];
-            }
+        for (int v = 0; v < 16; ++v) {
+            ga[v] = src[((ni * TB + mi) * 16 + v) * (64 * NW)];
+            ua[v] = EPI == kSwiglu ? src[(((ni + NB) * TB + mi) * 16 + v) * (64 * NW)] : 0.0f;
         }
-        // a lane holds token lane % 32 of its block and weight rows 8 gq + 4 (lane / 32) + 0..3
-        const int r = row0 + wm * 64 + mi * 32 + (lane & 31);
-        if (r >= row_end) continue;
-        bf16_t* crow = c + (size_t)((EPI == kPlain && out_perm != nullptr) ? out_perm[r] : r) * N;
-        const int col0 = nt * BNO + wn * (BNO / WN) + ni * 32 + (lane >> 5) * 4;
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            const int n = col0 + 8 * gq;
-            if (n >= N) continue;
-            floatx4 v;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                float t = gate[4 * gq + q];
-                if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * up[4 * gq + q];
-                if (EPI == kRelu) t = fmaxf(t, 0.0f);
-                v[q] = t;
-            }
-            *reinterpret_cast<bf16x4*>(crow + n) = __builtin_convertvector(v, bf16x4);
+        for (int v = 0; v < 16; ++v) {
+            gate[v] += ga[v];
+            up[v] += ua[v];
         }
+    }
+    // a lane holds token lane % 32 of its block and weight rows 8 gq + 4 (lane / 32) + 0..3
+    const int r = row0 + wm * 64 + mi * 32 + (lane & 31);
+    if (r >= row_end) return;
+    bf16_t* crow = c + (size_t)((EPI == kPlain && out_perm != nullptr) ? out_perm[r] : r) * N;
+    const int col0 = nt * BNO + wn * (BNO / WN) + ni * 32 + (lane >> 5) * 4;
+#pragma unroll
+    for (int gq = 0; gq < 4; ++gq) {
+        const int n = col0 + 8 * gq;
+        if (n >= N) continue;
+        floatx4 v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            float t = gate[4 * gq + q];
+            if (EPI == kSwiglu) t = t * __builtin_amdgcn_rcpf(1.0f + __expf(-t)) * up[4 * gq + q];
+            if (EPI == kRelu) t = fmaxf(t, 0.0f);
+            v[q] = t;
+        }
+        *reinterpret_cast<bf16x4*>(crow + n) = __builtin_convertvector(v, bf16x4);
     }
 }
 
@@ -640,7 +647,7 @@ hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, co
     if (PERSIST) {
         kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, shape.cus, shape.xcds);
         if (shape.groups > 1)
-            mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
+            mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW * kFixupUnits<EPI, BM, BR>, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
                                                                         shape.groups);
     } else {
         // The kernel, which knows how many m-tiles there are, may cut the columns finer; not with a short K, where a tile's start
