@@ -566,6 +566,7 @@ __global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixu
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
     static_assert(kFixupUnits<EPI, BM, BR> == TB * NB, "every block position");
+    static_assert(64 * NW * kFixupUnits<EPI, BM, BR> <= 1024, "threads of one workgroup");
     const int tid = threadIdx.x % (64 * NW), lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
     const int b = blockIdx.x + 1;
@@ -644,7 +645,7 @@ hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, co
     DeviceShape shape;
     hipError_t es = device_shape(&shape);
     if (es != hipSuccess) return es;
-    if (PERSIST) {
+    if constexpr (PERSIST) {
         kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, shape.cus, shape.xcds);
         if (shape.groups > 1)
             mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW * kFixupUnits<EPI, BM, BR>, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
