@@ -54,6 +54,7 @@
 #include <type_traits>
 
 #include "block_sort.h"
+#include "mid_work.h"
 
 namespace emoe {
 namespace {
@@ -87,9 +88,7 @@ __device__ __forceinline__ void barrier_keep_loads() {
 }
 
 constexpr int kGroups = kMaxGroups;  // the persistent launch has one workgroup per CU, at most this many
-constexpr int kMinShare = 8;     // K tiles per workgroup, at least, when tiles are cut
-constexpr int kMaxCutK = 1 << 14; // K tiles up to which tiles are cut: (kGroups + 1) * kGroups * kMaxCutK units fit 32 bits
-constexpr int kMinSpared = 48;   // tiles are cut only if that shortens every workgroup's K walk by this many K tiles
+static_assert((kGroups - 1ull) << 22 < 1ull << 31, "units of tiles that are cut (make_cut()) fit 32 bits");
 constexpr long long kRowsPerSlot64 = 48;  // up to that many rows per slot on average: token tiles of 64 rows
 constexpr int kNarrowFromK = 17; // K tiles from which on column tiles may be narrower than a tile can hold
 constexpr int kMinPersistK = 64; // K tiles from which on the persistent launch (which may cut) is used at all
@@ -100,8 +99,7 @@ struct Work {
     int s_begin, s_end, s_mtiles, first;  // per lane (= slot)
     int tiles;                            // all output tiles
     int kt;                               // K tiles per output tile
-    unsigned units;                       // if tiles are cut, tiles * kt: the sequence that is cut into shares
-    int sharers;                          // > 0: tiles are cut, that many workgroups take equal shares; 0: whole tiles
+    mid::Cut cut;                         // the shares, if tiles are cut along K
 };
 // How an output's N columns are cut into tiles: n tiles of `columns` (a multiple of 8 unless it is all that a tile can hold).
 struct ColumnTiles {
@@ -158,26 +156,7 @@ __device__ __forceinline__ void finish_work(Work& w, int m_tiles, int n_tiles, i
     w.first *= n_tiles;
     w.tiles = m_tiles * n_tiles;
     w.kt = (K + BK - 1) / BK;
-    w.units = 0;
-    w.sharers = 0;
-    // Cutting pays when it spares every workgroup a K walk of some length: the pieces are extra traffic
-    // and the second kernel has work to do (a fine-grained layer with K = 2048, 176 tiles: 57 -> 72 us
-    // when cut regardless).  (In 32 bits, which a sequence of fewer tiles than workgroups fits: the 64-bit divisions were
-    // 2 us of either kernel's start.)
-    if (w.tiles >= G || w.tiles == 0 || w.kt > kMaxCutK) return;
-    w.units = (unsigned)w.tiles * (unsigned)w.kt;
-    unsigned p = w.units / kMinShare;
-    p = p < (unsigned)G ? p : (unsigned)G;
-    const int share = p > 0 ? (int)((w.units + p - 1) / p) : 0;
-    w.sharers = ((int)p > w.tiles && w.kt - share >= kMinSpared) ? (int)p : 0;
-}
-// first unit of share g (g = 0 .. sharers; share g is [share_begin(g), share_begin(g + 1)); from sharers on: empty)
-__device__ __forceinline__ unsigned share_begin(const Work& w, int g) {
-    return g >= w.sharers ? w.units : w.units * (unsigned)g / (unsigned)w.sharers;
-}
-// the share that holds unit u: the largest g with share_begin(g) <= u
-__device__ __forceinline__ int share_of(const Work& w, unsigned u) {
-    return (int)(((u + 1) * (unsigned)w.sharers + w.units - 1) / w.units) - 1;
+    w.cut = mid::make_cut(w.tiles, w.kt, G);
 }
 // tile number -> slot, first row, end of the slot's rows, n-tile
 __device__ __forceinline__ void decode_tile(const Work& w, int S, int lane, int L, int bm, int& slot, int& row0,
@@ -247,12 +226,12 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     ColumnTiles ct{n_tiles, BNO};
     const int first_m_tile = work.first;
     if (PERSIST) finish_work(work, m_tiles, ct.n, K, G);
-    if (PERSIST ? work.sharers == 0 : max_tiles > 0) {
+    if (PERSIST ? work.cut.sharers == 0 : max_tiles > 0) {
         ct = narrower_tiles(ct, m_tiles, __popcll(__ballot(work.s_mtiles > 0)), rows_total, max_tiles, EPI == kSwiglu ? 2 : 1, N, (K + BK - 1) / BK,
                             !KTAIL, lane, cus);
         work.first = first_m_tile;
         finish_work(work, m_tiles, ct.n, K, G);
-        work.sharers = 0;
+        work.cut.sharers = 0;
     } else if (!PERSIST) {
         finish_work(work, m_tiles, ct.n, K, G);
     }
@@ -261,7 +240,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     const int g = xcd * (G / XCDS) + idx;
     // What this workgroup does, as a walk over tiles [L, L_end) in steps of L_step (whole tiles), or over
     // K-tile units [u, u_end) of the tile sequence (a share).
-    const bool cut = PERSIST && work.sharers > 0;
+    const bool cut = PERSIST && work.cut.sharers > 0;
     int L, L_end, L_step;
     unsigned u = 0, u_end = 0;
     if (!PERSIST) {  // one tile: XCD x holds tiles x * per_xcd .. in the order they are dispatched
@@ -275,8 +254,8 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
         L_step = G / XCDS;
     } else {
         L = L_end = L_step = 0;
-        u = share_begin(work, g);
-        u_end = share_begin(work, g + 1);
+        u = mid::share_begin(work.cut, g);
+        u_end = mid::share_begin(work.cut, g + 1);
     }
 
     // ---- lane-constant parts of the addressing -------------------------------------------------------
@@ -573,13 +552,9 @@ __global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixu
     int m_tiles;
     Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, lane, BM, &m_tiles);
     finish_work(work, m_tiles, n_tiles, K, G);
-    if (b >= work.sharers) return;              // nothing was cut, or no share starts here
-    const unsigned ub = share_begin(work, b);   // first unit of share b
-    const int tile = (int)(ub / (unsigned)work.kt);
-    const unsigned t_begin = (unsigned)(tile * work.kt), t_end = t_begin + (unsigned)work.kt;
-    if (ub == t_begin) return;                  // the boundary falls between two tiles
-    const int g_first = share_of(work, t_begin), g_last = share_of(work, t_end - 1);
-    if (g_first != b - 1) return;  // several boundaries inside one tile: the first of them does the work
+    const int tile = mid::tile_of_boundary(work.cut, work.kt, b);
+    if (tile < 0) return;  // nothing was cut, or this boundary leaves nothing to do
+    const unsigned t_end = (unsigned)(tile + 1) * (unsigned)work.kt;
     int slot, row0, row_end, nt, slot_mtiles;
     decode_tile(work, S, lane, tile, BM, slot, row0, row_end, nt, slot_mtiles);
     const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
@@ -588,9 +563,9 @@ __global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixu
     floatx16 gate, up;
 #pragma unroll
     for (int v = 0; v < 16; ++v) { gate[v] = 0.0f; up[v] = 0.0f; }
-    for (int gg = g_first; gg <= g_last; ++gg) {
-        // share g_first holds the start of the tile (its piece starts at K tile 0), the others start inside it
-        const float* src = partials + (size_t)piece_slot(gg, gg != g_first) * (BM * BR) + tid;
+    for (int gg = b - 1; mid::share_begin(work.cut, gg) < t_end; ++gg) {
+        // share b - 1 holds the start of the tile (its piece starts at K tile 0), the others start inside it
+        const float* src = partials + (size_t)piece_slot(gg, gg >= b) * (BM * BR) + tid;
         float ga[16], ua[16];  // all loads of a piece in flight together, then the adds
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
