@@ -55,7 +55,7 @@ def compile_objects(obj_dir: str, extra_flags=(), jobs: int = 8):
 def build_library(force: bool = True, jobs: int = 8, extra_flags=()) -> str:
     """Compile every HIP source and link libemoe.so; returns its path."""
     os.makedirs(OBJ, exist_ok=True)
-    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "mfma_agpr.h"), os.path.join(CSRC, "block_sort.h"), os.path.join(CSRC, "mid_work.h"), os.path.join(CSRC, "route_topk.h"),
+    headers = [os.path.join(CSRC, "common.h"), os.path.join(CSRC, "mfma_agpr.h"), os.path.join(CSRC, "block_sort.h"), os.path.join(CSRC, "mid_work.h"), os.path.join(CSRC, "route_topk.h"), os.path.join(CSRC, "wave_max.h"),
                os.path.join(ROOT, "include", "emoe.h")]
     newest_hdr = max(os.path.getmtime(h) for h in headers)
 

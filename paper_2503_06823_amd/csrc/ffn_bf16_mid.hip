@@ -32,7 +32,7 @@
 //
 // Work distribution.  Group sizes live on the device; everything is derived from slot_offsets there.
 // An output's columns are cut into tiles as wide as a tile can hold, or narrower ones where those leave CUs idle or a last round
-// nearly empty (narrower_tiles(); the rows that a tile then lacks are addressed out of range as well).
+// nearly empty (choose_columns(); the rows that a tile then lacks are addressed out of range as well).
 // Tiles are numbered slot by slot, and inside a slot all m-tiles of an n-tile are consecutive;
 // workgroup ids go round-robin over the 8 XCDs and are remapped so that an XCD works on consecutive
 // tiles: the m-tiles that share a weight panel run at the same time behind the same L2, and the
@@ -55,6 +55,7 @@
 
 #include "block_sort.h"
 #include "mid_work.h"
+#include "wave_max.h"
 
 namespace emoe {
 namespace {
@@ -65,7 +66,6 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) void lds_void;
 
-constexpr int kTileRows = 128;             // token rows per tile (64 in the variant for slots of few rows)
 constexpr int BK = 64;                     // K elements per tile
 constexpr int ROW_BYTES = BK * 2;          // 128
 constexpr int NW = 4;                      // wavefronts: 2 (tokens) x 2 (weight rows)
@@ -89,9 +89,7 @@ __device__ __forceinline__ void barrier_keep_loads() {
 
 constexpr int kGroups = kMaxGroups;  // the persistent launch has one workgroup per CU, at most this many
 static_assert((kGroups - 1ull) << 22 < 1ull << 31, "units of tiles that are cut (make_cut()) fit 32 bits");
-constexpr long long kRowsPerSlot64 = 48;  // up to that many rows per slot on average: token tiles of 64 rows
-constexpr int kNarrowFromK = 17; // K tiles from which on column tiles may be narrower than a tile can hold
-constexpr int kMinPersistK = 64; // K tiles from which on the persistent launch (which may cut) is used at all
+static_assert(BK == mid::kTileK, "the K tiles that the work is counted in");
 
 // The tiles of a launch and how a persistent launch shares them out, derived from slot_offsets by
 // every wavefront: lane s holds slot s's rows and the number of its first tile.
@@ -101,39 +99,13 @@ struct Work {
     int kt;                               // K tiles per output tile
     mid::Cut cut;                         // the shares, if tiles are cut along K
 };
-// How an output's N columns are cut into tiles: n tiles of `columns` (a multiple of 8 unless it is all that a tile can hold).
-struct ColumnTiles {
-    int n, columns;
-};
-// Narrower column tiles than a tile can hold, where those leave CUs idle or a last round nearly empty.  Lane l weighs up l tiles
-// more than the fewest.  A CU is bound by the number of lines that it requests, weight rows and token rows of a K tile (it has
-// some 110 outstanding), and a round of the chip's CUs by HBM, which delivers the weight rows of a tile in 1.7 times the time
-// that its CU needs for as many lines; a slot's m-tiles share theirs.  What is not 4 % better than the fewest stays with those.
-// (d 1032, f 2808, 11 slots of 36 to 279 rows: 308 and 126 tiles of 128 columns become 504 of 80 and 252 of 64, products
-// 57.6 + 36.1 -> 51.2 + 28.0 us.)
-__device__ __forceinline__ ColumnTiles narrower_tiles(ColumnTiles fewest, int m_tiles, int slots, int rows, int max_tiles, int rows_per_column,
-                                                      int N, int k_tiles, bool whole_lines, int lane, int cus) {
-    const int full = m_tiles * fewest.n;
-    // the rounds are full as it is (or there are no rows); of one round less is expected, since finding out costs 0.3 us, and a
-    // longer walk: a tile's start weighs as much as some ten K tiles (3 slots of 76 rows, d 1184, f 464: 14.3 -> 15.2 us)
-    if (full * 16 >= (full + cus - 1) / cus * cus * (full <= cus ? 14 : 15)) return fewest;
-    if (k_tiles < (full <= cus ? 32 : whole_lines ? 24 : kNarrowFromK)) return fewest;
-    const int want = fewest.n + lane;
-    const int columns = lane == 0 ? fewest.columns : ((N + want - 1) / want + 7) & ~7;
-    const int n = (N + columns - 1) / columns;
-    const int tiles = m_tiles * n;
-    const float per_cu = (float)rows_per_column * columns + (float)rows / m_tiles;              // lines per K tile and CU
-    const float from_hbm = 1.7f * rows_per_column * columns * slots / m_tiles;                  // a full round's, as long as
-    const int rounds = tiles / cus;
-    const float last = (float)(tiles - rounds * cus) / cus;                                     // share of the CUs in the last round
-    float cost = rounds * fmaxf(per_cu, from_hbm) + (last > 0.0f ? fmaxf(per_cu, from_hbm * last) : 0.0f);
-    if (lane == 0) cost *= 0.96f;
-    else if (tiles > max_tiles) cost = 3.0e38f;
-    float least = cost;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) least = fminf(least, __shfl_xor(least, off));
-    const int best = __ffsll(__ballot(cost == least)) - 1;
-    return ColumnTiles{__builtin_amdgcn_readlane(n, best), __builtin_amdgcn_readlane(columns, best)};
+// The column tiles of a product: lane l weighs up l tiles more than the fewest.
+__device__ __forceinline__ mid::ColumnTiles choose_columns(const mid::Product& p, int lane) {
+    if (mid::fewest_stay(p)) return p.fewest;
+    const mid::ColumnChoice mine = mid::weigh_columns(p, lane, [](float v) { return __builtin_amdgcn_rcpf(v); });
+    const uint32_t least = ~max_over_lanes<64, 1>(~__float_as_uint(mine.cost));  // costs are above 0: their bits are in their order
+    const int best = __ffsll(__ballot(__float_as_uint(mine.cost) == least)) - 1;
+    return mid::column_tiles(p, __builtin_amdgcn_readlane((int)mine.eighths, best), __builtin_amdgcn_readlane((int)mine.n, best));
 }
 // The m-tiles per slot of `bm` rows: per lane (= slot), with the number of tiles before it and of all of them.
 __device__ __forceinline__ Work make_work(int s_begin, int s_end, int lane, int bm, int* m_tiles) {
@@ -155,7 +127,7 @@ __device__ __forceinline__ Work make_work(int s_begin, int s_end, int lane, int 
 __device__ __forceinline__ void finish_work(Work& w, int m_tiles, int n_tiles, int K, int G) {
     w.first *= n_tiles;
     w.tiles = m_tiles * n_tiles;
-    w.kt = (K + BK - 1) / BK;
+    w.kt = mid::k_tiles_of(K);
     w.cut = mid::make_cut(w.tiles, w.kt, G);
 }
 // tile number -> slot, first row, end of the slot's rows, n-tile
@@ -184,7 +156,7 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
                                                      const int32_t* __restrict__ offsets,
                                                      const bf16_t* __restrict__ b0, const bf16_t* __restrict__ b1,
                                                      bf16_t* __restrict__ c, float* __restrict__ partials, int S, int N,
-                                                     int K, int n_tiles, int max_tiles, int cus, int XCDS) {
+                                                     int K, int n_tiles, int max_tiles, float per_cus, int XCDS) {
     constexpr int W_TILE = BR * ROW_BYTES;             // 32 or 16 KiB
     constexpr int X_TILE = BM * ROW_BYTES;             // 16 or 8 KiB
     constexpr int STAGE_BYTES = X_TILE + W_TILE;
@@ -223,12 +195,12 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     Work work = make_work(sorts ? sorted.begin : lane < S ? offsets[lane] : 0, sorts ? sorted.end : lane < S ? offsets[lane + 1] : 0, lane,
                           BM, &m_tiles);
     const int rows_total = sorts ? __builtin_amdgcn_readlane(work.s_end, S - 1) : offsets[S];
-    ColumnTiles ct{n_tiles, BNO};
+    mid::ColumnTiles ct{n_tiles, BNO};
     const int first_m_tile = work.first;
     if (PERSIST) finish_work(work, m_tiles, ct.n, K, G);
     if (PERSIST ? work.cut.sharers == 0 : max_tiles > 0) {
-        ct = narrower_tiles(ct, m_tiles, __popcll(__ballot(work.s_mtiles > 0)), rows_total, max_tiles, EPI == kSwiglu ? 2 : 1, N, (K + BK - 1) / BK,
-                            !KTAIL, lane, cus);
+        ct = choose_columns(mid::Product{m_tiles, (int)__popcll(__ballot(work.s_mtiles > 0)), rows_total, EPI == kSwiglu ? 2 : 1, N, mid::k_tiles_of(K), !KTAIL,
+                                         max_tiles, per_cus, ct}, lane);
         work.first = first_m_tile;
         finish_work(work, m_tiles, ct.n, K, G);
         work.cut.sharers = 0;
@@ -621,18 +593,14 @@ hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, co
     hipError_t es = device_shape(&shape);
     if (es != hipSuccess) return es;
     if constexpr (PERSIST) {
-        kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, shape.cus, shape.xcds);
+        kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, 1.0f / shape.cus, shape.xcds);
         if (shape.groups > 1)
             mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW * kFixupUnits<EPI, BM, BR>, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
                                                                         shape.groups);
     } else {
-        // The kernel, which knows how many m-tiles there are, may cut the columns finer; not with a short K, where a tile's start
-        // weighs as much as its walk and finding out costs more than it gives (12 K tiles: 19.0 -> 19.5 us).
-        const bool may_narrow = (K + BK - 1) / BK >= kNarrowFromK;
-        long long tiles = m_tiles * n_tiles;
-        if (may_narrow && tiles < shape.cus) tiles = shape.cus;
+        const long long tiles = mid::most_tiles(m_tiles, n_tiles, K, shape.cus);
         const unsigned blocks = (unsigned)((tiles + shape.xcds - 1) / shape.xcds * shape.xcds);
-        kern<<<blocks, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, may_narrow ? (int)tiles : 0, shape.cus, shape.xcds);
+        kern<<<blocks, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, mid::may_narrow(K) ? (int)tiles : 0, 1.0f / shape.cus, shape.xcds);
     }
     return hipGetLastError();
 }
@@ -651,38 +619,26 @@ hipError_t launch_one(const bf16_t* a, Gather gather, const int32_t* offsets, co
     DeviceShape shape;
     hipError_t es = device_shape(&shape);
     if (es != hipSuccess) return es;
-    const int kCUs = shape.cus;
-    // every slot adds at most one partial m-tile to the A / 128 whole ones
-    const long long m_tiles = A / kTileRows + (S < A ? S : A);
-    // Tiles of 256 weight rows, unless they would leave CUs without a tile (the second product of a
-    // layer with a small d_model): then 128 weight rows and five stages, so that twice as many CUs
-    // stream weights, each with as many bytes in flight; and if K is long, in a persistent launch
-    // that cuts the tiles along K when even they are clearly fewer than the CUs (with a short K that
-    // never pays, and the second kernel's launch is saved).
-    constexpr int BNO = EPI == kSwiglu ? 128 : 256;
-    // Few rows per slot: token tiles of 64 rows leave LDS for more stages, 96 (80 with 128 weight rows) KiB
-    // of weights in flight per CU instead of 64.  (With SwiGLU and 128 weight rows a wavefront of the
-    // 64-row arrangement would hold half a block of gate rows: that combination keeps 128 token rows.)
-    const bool few_rows = A <= kRowsPerSlot64 * S;
-    const long long m_tiles64 = A / 64 + (S < A ? S : A);
-    const bool persist = (K + BK - 1) / BK >= kMinPersistK;
-    if (m_tiles * ((N + BNO - 1) / BNO) <= kCUs) {
-        if constexpr (EPI != kSwiglu) {
-            if (few_rows && persist)
-                return launch_ktail<EPI, 64, 128, 6, true>(a, gather, offsets, b0, b1, c, partials, m_tiles64, S, N, K, st);
-            // a short K (no cutting) and so few 128-row tiles that they leave a quarter of the CUs idle even
-            // if every slot has a partial tile: 64-row tiles, about twice as many
-            const bool underfilled = !persist && m_tiles * ((N + 127) / 128) <= kCUs * 3 / 4;
-            if (few_rows || underfilled)
-                return launch_ktail<EPI, 64, 128, 6, false>(a, gather, offsets, b0, b1, c, partials, m_tiles64, S, N, K, st);
-        }
-        if (persist)
-            return launch_ktail<EPI, 128, 128, 5, true>(a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
-        return launch_ktail<EPI, 128, 128, 5, false>(a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
+    const mid::Arrangement tile = mid::arrangement(EPI == kSwiglu, A, S, N, K, shape.cus);
+    const long long m_tiles = mid::most_m_tiles(A, S, tile.rows);
+    auto launch = [&](auto rows, auto weight_rows, auto stages, auto persist) {
+        return launch_ktail<EPI, decltype(rows)::value, decltype(weight_rows)::value, decltype(stages)::value, decltype(persist)::value>(
+            a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
+    };
+    constexpr std::integral_constant<int, 64> k64;
+    constexpr std::integral_constant<int, 128> k128;
+    constexpr std::integral_constant<int, 256> k256;
+    if constexpr (EPI != kSwiglu) {
+        constexpr std::integral_constant<int, 6> stages;
+        if (tile.rows == 64 && tile.weight_rows == 128)
+            return tile.persist ? launch(k64, k128, stages, std::true_type{}) : launch(k64, k128, stages, std::false_type{});
     }
-    if (few_rows)
-        return launch_ktail<EPI, 64, 256, 4, false>(a, gather, offsets, b0, b1, c, partials, m_tiles64, S, N, K, st);
-    return launch_ktail<EPI, 128, 256, 3, false>(a, gather, offsets, b0, b1, c, partials, m_tiles, S, N, K, st);
+    if (tile.weight_rows == 128) {
+        constexpr std::integral_constant<int, 5> stages;
+        return tile.persist ? launch(k128, k128, stages, std::true_type{}) : launch(k128, k128, stages, std::false_type{});
+    }
+    if (tile.rows == 64) return launch(k64, k256, std::integral_constant<int, 4>{}, std::false_type{});
+    return launch(k128, k256, std::integral_constant<int, 3>{}, std::false_type{});
 }
 
 }  // namespace

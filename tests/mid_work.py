@@ -4,6 +4,7 @@ import ctypes
 import os
 import subprocess
 import tempfile
+from typing import NamedTuple
 
 from paper_2503_06823_amd import build as B
 
@@ -21,3 +22,23 @@ def lib():
             _lib = ctypes.CDLL(out)
         _lib.cut_share_begin.restype = ctypes.c_uint
     return _lib
+
+
+class Tiles(NamedTuple):
+    fewest: int          # column tiles as wide as a tile can hold
+    widest: int
+    n: int               # the chosen ones
+    columns: int
+    cut: bool            # along K
+    rows: int            # token rows and weight rows of a tile
+    weight_rows: int
+    persist: bool
+    m_tiles: int
+
+
+def product_tiles(swiglu, counts, N, K, cus=256, ulps=0) -> Tiles:
+    """The tiles of a product of N columns and K inputs over slots of `counts` rows."""
+    out = (ctypes.c_int * 9)()
+    lib().product_tiles(ctypes.c_bool(swiglu), (ctypes.c_int * len(counts))(*map(int, counts)), len(counts), N, K, cus, ulps, out)
+    v = list(out)
+    return Tiles(*v[:4], bool(v[4]), v[5], v[6], bool(v[7]), v[8])
