@@ -499,45 +499,47 @@ __global__ __launch_bounds__(64 * NW) void mid_gemm_bf16(const bf16_t* __restric
     }
 }
 
-// Adds the pieces of each tile that the shares cut, in K order, and applies the epilogue.  A cut
-// tile is found at a boundary between two shares; a launch covers every boundary, one workgroup each,
-// with four wavefronts for each of the kFixupUnits 32 x 32 block positions of a wavefront's accumulators: they are independent,
-// and one after the other they are a chain of memory latencies.
-// Workgroup b - 1: boundary b = 1 .. G-1 lies between shares b-1 and b.  When the main kernel
-// took whole tiles, which the host cannot know, every workgroup exits after reading slot_offsets.
+// Adds the pieces of each tile that the shares cut, in K order, and applies the epilogue.  A workgroup for each of the kFixupUnits
+// 32 x 32 block positions of a wavefront's accumulators, of each tile that there can be: they are independent, and one after the other
+// they are a chain of memory latencies, as the pieces of a tile are.  A tile's workgroups run on the XCD that wrote its first
+// piece, behind the same L2.  (A workgroup per boundary between two shares, with all positions: 916 cut products, weights from HBM,
+// 1.103 times the time in the mean, at least 0.984.  One slot of 25 rows, N 256, K 8384: 15.8 us, 14.9 now, 17.9 with tiles dealt
+// to XCDs regardless; 2 slots of 58 rows, SwiGLU, N 1024, K 5616: 28.9, 25.1, 24.4.)  When the main kernel took whole tiles, which
+// the host cannot know, every workgroup exits after reading slot_offsets.
 template <int EPI, int BM, int BR>
 constexpr int kFixupUnits = TB * (BR / (NW / (BM / 64)) / 32) / (EPI == kSwiglu ? 2 : 1);
 template <int EPI, int BM, int BR>
-__global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixup(const int32_t* __restrict__ offsets, bf16_t* __restrict__ c,
+__global__ __launch_bounds__(64 * NW) void mid_fixup(const int32_t* __restrict__ offsets, bf16_t* __restrict__ c,
                                                  const int32_t* __restrict__ out_perm,
                                                  const float* __restrict__ partials, int S, int N, int K,
-                                                 int n_tiles, int G) {
+                                                 int n_tiles, int G, int XCDS) {
     constexpr int WM = BM / 64, WN = NW / WM;  // as in the main kernel
     constexpr int WB = BR / WN / 32;
     constexpr int BNO = EPI == kSwiglu ? BR / 2 : BR;
     constexpr int NB = EPI == kSwiglu ? WB / 2 : WB;
     static_assert(kFixupUnits<EPI, BM, BR> == TB * NB, "every block position");
-    static_assert(64 * NW * kFixupUnits<EPI, BM, BR> <= 1024, "threads of one workgroup");
-    const int tid = threadIdx.x % (64 * NW), lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
-    const int b = blockIdx.x + 1;
+    constexpr int UNITS = kFixupUnits<EPI, BM, BR>;
+    const int xcd = blockIdx.x % XCDS, idx = blockIdx.x / XCDS, unit = idx % UNITS;
     int m_tiles;
     Work work = make_work(lane < S ? offsets[lane] : 0, lane < S ? offsets[lane + 1] : 0, lane, BM, &m_tiles);
     finish_work(work, m_tiles, n_tiles, K, G);
-    const int tile = mid::tile_of_boundary(work.cut, work.kt, b);
-    if (tile < 0) return;  // nothing was cut, or this boundary leaves nothing to do
-    const unsigned t_end = (unsigned)(tile + 1) * (unsigned)work.kt;
+    if (work.cut.sharers == 0) return;
+    const int tile = mid::first_tile(work.cut, work.kt, xcd * (G / XCDS)) + idx / UNITS;
+    if (tile >= mid::first_tile(work.cut, work.kt, (xcd + 1) * (G / XCDS))) return;
+    const mid::Pieces pieces = mid::pieces_of(work.cut, work.tiles, work.kt, tile);
+    if (pieces.end - pieces.first < 2) return;  // not cut
     int slot, row0, row_end, nt, slot_mtiles;
     decode_tile(work, S, lane, tile, BM, slot, row0, row_end, nt, slot_mtiles);
-    const int unit = __builtin_amdgcn_readfirstlane(threadIdx.x / (64 * NW));
     const int mi = unit / NB, ni = unit % NB;
     if (row0 + wm * 64 + mi * 32 >= row_end) return;  // this wavefront's block holds no rows: nothing was written
     floatx16 gate, up;
 #pragma unroll
     for (int v = 0; v < 16; ++v) { gate[v] = 0.0f; up[v] = 0.0f; }
-    for (int gg = b - 1; mid::share_begin(work.cut, gg) < t_end; ++gg) {
-        // share b - 1 holds the start of the tile (its piece starts at K tile 0), the others start inside it
-        const float* src = partials + (size_t)piece_slot(gg, gg >= b) * (BM * BR) + tid;
+    for (int g = pieces.first; g < pieces.end; ++g) {
+        // the first piece holds the start of the tile (K tile 0), the others start inside it
+        const float* src = partials + (size_t)piece_slot(g, g != pieces.first) * (BM * BR) + tid;
         float ga[16], ua[16];  // all loads of a piece in flight together, then the adds
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -548,7 +550,7 @@ __global__ __launch_bounds__((64 * NW * kFixupUnits<EPI, BM, BR>)) void mid_fixu
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             gate[v] += ga[v];
-            up[v] += ua[v];
+            if (EPI == kSwiglu) up[v] += ua[v];
         }
     }
     // a lane holds token lane % 32 of its block and weight rows 8 gq + 4 (lane / 32) + 0..3
@@ -594,9 +596,11 @@ hipError_t launch_cfg(const bf16_t* a, Gather gather, const int32_t* offsets, co
     if (es != hipSuccess) return es;
     if constexpr (PERSIST) {
         kern<<<shape.groups, 64 * NW, kLds, st>>>(a, gather, offsets, b0, b1, c, partials, S, N, K, n_tiles, INT32_MAX, 1.0f / shape.cus, shape.xcds);
-        if (shape.groups > 1)
-            mid_fixup<EPI, BM, BR><<<shape.groups - 1, 64 * NW * kFixupUnits<EPI, BM, BR>, 0, st>>>(offsets, c, gather.out_perm, partials, S, N, K, n_tiles,
-                                                                        shape.groups);
+        // the tiles that begin in an XCD's shares: one per share at most
+        const long long tiles = m_tiles * n_tiles, per_xcd = tiles < shape.groups / shape.xcds ? tiles : shape.groups / shape.xcds;
+        if (per_xcd > 0)
+            mid_fixup<EPI, BM, BR><<<(unsigned)(shape.xcds * per_xcd) * kFixupUnits<EPI, BM, BR>, 64 * NW, 0, st>>>(
+                offsets, c, gather.out_perm, partials, S, N, K, n_tiles, shape.groups, shape.xcds);
     } else {
         const long long tiles = mid::most_tiles(m_tiles, n_tiles, K, shape.cus);
         const unsigned blocks = (unsigned)((tiles + shape.xcds - 1) / shape.xcds * shape.xcds);

@@ -33,15 +33,20 @@ constexpr unsigned share_begin(Cut cut, int g) {
     const unsigned p = (unsigned)cut.sharers, whole = cut.units / p, rest = cut.units - whole * p;
     return whole * (unsigned)g + rest * (unsigned)g / p;
 }
-// The tile that boundary b between shares b - 1 and b cuts, if this is the first boundary inside it (the one that sees to the
-// adding of its pieces), else -1.  The pieces: shares b - 1, b, ... as long as they begin before the tile's end.
-constexpr int tile_of_boundary(Cut cut, int kt, int b) {
-    if (b >= cut.sharers) return -1;  // nothing was cut, or no share begins here
-    const unsigned at = share_begin(cut, b);
-    const int tile = (int)(at / (unsigned)kt);
-    const unsigned tile_begin = (unsigned)tile * (unsigned)kt;
-    return at != tile_begin && share_begin(cut, b - 1) <= tile_begin ? tile : -1;
+// The shares that hold a part of a tile: first .. end - 1, in K order.  More than one: the tile is cut.
+struct Pieces {
+    int first, end;
+};
+constexpr Pieces pieces_of(Cut cut, int tiles, int kt, int tile) {
+    const unsigned begin = (unsigned)tile * (unsigned)kt;
+    int first = tile * cut.sharers / tiles, end = (tile + 1) * cut.sharers / tiles;  // begin at or before the tile, and at or before its end
+    if (share_begin(cut, first + 1) <= begin) ++first;
+    if (share_begin(cut, end) < begin + (unsigned)kt) ++end;
+    return Pieces{first, end};
 }
+
+// The first tile that begins in share g or after it.  No share holds the beginnings of two.
+constexpr int first_tile(Cut cut, int kt, int g) { return (int)((share_begin(cut, g) + (unsigned)kt - 1) / (unsigned)kt); }
 
 // ---- which tiles a product takes ---------------------------------------------------------------------
 constexpr int kTileK = 64;                // K elements per K tile

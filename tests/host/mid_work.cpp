@@ -43,5 +43,10 @@ void product_tiles(bool swiglu, const int* counts, int S, int N, int K, int cus,
     const int all[9] = {fewest.n, fewest.columns, chosen.n, chosen.columns, cut, tile.rows, tile.weight_rows, tile.persist, m_tiles};
     for (int i = 0; i < 9; ++i) out[i] = all[i];
 }
-int cut_tile_of_boundary(int tiles, int kt, int G, int b) { return tile_of_boundary(make_cut(tiles, kt, G), kt, b); }
+int cut_first_tile(int tiles, int kt, int G, int g) { return first_tile(make_cut(tiles, kt, G), kt, g); }
+void cut_pieces(int tiles, int kt, int G, int tile, int* out) {
+    const Pieces p = pieces_of(make_cut(tiles, kt, G), tiles, kt, tile);
+    out[0] = p.first;
+    out[1] = p.end;
+}
 }

@@ -1,6 +1,5 @@
 """The kernel that adds the pieces of tiles cut along K is built for the arrangements that can be cut, those with 128 weight rows, and
-for no other: with 256 weight rows it would ask for 2048 threads per workgroup, twice what there can be (read from the
-assembly of the kernels' own build)."""
+for no other, which nothing would launch (read from the assembly of the kernels' own build)."""
 import os
 import re
 import subprocess

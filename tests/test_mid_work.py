@@ -1,6 +1,7 @@
 """How products on tiles of 64 and 128 token rows are divided.  Tiles cut along K, against whole-number arithmetic of any length: which
 products are cut, where the shares begin, and which pieces the second kernel adds; K from one K tile to the longest that an
 accepted layer can have.  Column tiles: whatever is chosen covers the columns and fits the tile and the launch."""
+import ctypes
 import random
 
 import numpy as np
@@ -44,17 +45,14 @@ def test_cut_is_exact(long_k):
         sharers, begins = reference(tiles, kt, G)
         assert lib().cut_sharers(tiles, kt, G) == sharers, (tiles, kt, G)
         assert [lib().cut_share_begin(tiles, kt, G, g) for g in range(sharers + 1 if sharers else 0)] == begins, (tiles, kt, G)
-        # every tile that a boundary falls into has exactly one boundary that sees to it: the first, whose left share holds its start
-        owner = {}
-        for b in range(1, G):
-            tile = lib().cut_tile_of_boundary(tiles, kt, G, b)
-            if tile >= 0:
-                assert tile not in owner
-                owner[tile] = b
-        cut_at = [x for x in begins[1:-1] if x % kt]
-        assert set(owner) == {x // kt for x in cut_at}, (tiles, kt, G)
-        for tile, b in owner.items():
-            assert begins[b - 1] <= tile * kt < begins[b] < (tile + 1) * kt
+        for tile in range(tiles if sharers else 0):  # the shares that hold a part of it
+            pieces = (ctypes.c_int * 2)()
+            lib().cut_pieces(tiles, kt, G, tile, pieces)
+            assert list(range(*pieces)) == [g for g in range(sharers) if begins[g] < (tile + 1) * kt and begins[g + 1] > tile * kt], (tiles, kt, G, tile)
+        for first in range(G if sharers else 0):  # a tile begins in one share, and no share holds the beginnings of two
+            tile, after = (lib().cut_first_tile(tiles, kt, G, g) for g in (first, first + 1))
+            assert tile <= after <= tile + 1 and (after == tile or begins[first] <= tile * kt < begins[first + 1])
+        assert not sharers or (lib().cut_first_tile(tiles, kt, G, 0), lib().cut_first_tile(tiles, kt, G, G)) == (0, tiles)
         seen += sharers > 0
     assert seen > 50
 
