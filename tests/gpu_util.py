@@ -187,10 +187,10 @@ def check_elementwise(got: np.ndarray, ref: np.ndarray, rel: float, abs_rms: flo
                                 f"row rms {rms[worst[0], 0]:.4g}")
 
 
-def stratified_rows(slot_offsets: np.ndarray, seed: int, block: int = 32) -> np.ndarray:
+def stratified_rows(slot_offsets: np.ndarray, seed: int, block: int = 16) -> np.ndarray:
     """Grouped rows to compare at full size: of every slot its first and last row and one seeded row
     of every `block`-row block counted from the slot's start.  Every kernel here cuts a slot's rows
-    into tiles at multiples of 32 rows from the slot's start and multiplies them in blocks of 32, so
+    into tiles at multiples of 16 rows from the slot's start and multiplies them in blocks of 16 (256-row tiles) or 32, so
     this puts a row into every block of every m-tile; a row is compared over all its columns, which
     covers every n-tile, whole or cut along K."""
     rng = np.random.default_rng(seed)
@@ -231,3 +231,44 @@ def check_ffn_rows(dl: DeviceLayer, pm: oracle.Permutation, rows: np.ndarray):
     check_elementwise(h_got, h_ref, *el["h"], "h")
     check_within(y_got, y_ref, y_bound(dl, row_slot, h_ref, y_ref), "y_perm")
     return h_err, y_err
+
+
+# fp32 sums of up to 8400 terms with partial sums up to 5 are off by some 2^-24 * sqrt(8400) * 5 = 3e-5, and a gate's error meets an up
+# value of up to 5 (a K tile left out moves an element by 0.1)
+FFN_SUMS = 2e-4
+
+
+def check_grouped_ffn(desc, act: str, rows, seed: int, device):
+    """The FFN of a bf16 layer of one expert per token whose slots hold `rows` rows, tokens in a random order: every element of h against
+    an fp32 product, and every element of y against one of the h that the first product left.  Each is rounded once (2^-9, or to the
+    neighbour where the sums differ)."""
+    d, f, S, T = desc.d_model, desc.d_ff, len(rows), sum(rows)
+    g = torch.Generator(device=device)
+    g.manual_seed(seed)
+
+    def normal(shape, std):
+        return torch.empty(shape, dtype=torch.bfloat16, device=device).normal_(0.0, std, generator=g)
+
+    x, w1, w2 = normal((T, d), 1.0), normal((S, f, d), d ** -0.5), normal((S, d, f), f ** -0.5)
+    w3 = normal((S, f, d), d ** -0.5) if act == "swiglu" else None
+    perm = torch.randperm(T, generator=g, device=device).to(torch.int32)
+    starts = [sum(rows[:s]) for s in range(S + 1)]
+    offsets = torch.tensor(starts, dtype=torch.int32, device=device)
+    b = P.LayerBuffers.allocate(desc, device)
+    b.y_perm.fill_(float("nan"))
+    b.ffn_ws.fill_(255)  # NaN, also in every partial sum that nobody writes
+    P.emoe_expert_ffn_gather(desc, x, perm, offsets, w1, w3, w2, b.y_perm, b.ffn_ws, b.ffn_ws.numel())
+    torch.cuda.synchronize()
+    h_all = b.ffn_ws[:T * f * 2].view(torch.bfloat16).view(T, f)
+    for s in range(S):
+        mine = slice(starts[s], starts[s + 1])
+        if not rows[s]:
+            continue
+        xs = x[perm[mine].long()].float()
+        h = xs @ w1[s].float().t()
+        h = torch.nn.functional.silu(h) * (xs @ w3[s].float().t()) if act == "swiglu" else torch.relu(h)
+        h_got = h_all[mine].float()
+        y = h_got @ w2[s].float().t()
+        for name, got, ref in (("h", h_got, h), ("y", b.y_perm[mine].float(), y)):
+            worst = float(((got - ref).abs() - 2.0 ** -8 * ref.abs() - FFN_SUMS).max())
+            assert worst <= 0, f"{name} of slot {s} with {rows[s]} rows: {worst} past the bound"

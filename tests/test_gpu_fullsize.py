@@ -1,7 +1,7 @@
 """GPU parity at the full sizes of the five workloads, in the launch configuration bench.py times.
 Routing and the permutation are compared in full (bit-exact).  The expert FFN is compared on a
 stratified sample of grouped rows that the oracle computes one by one: of every slot the first and the
-last row and a seeded row of every 32-row block, so that every output tile of every round of the
+last row and a seeded row of every 16-row block, so that every output tile of every round of the
 persistent launch, every tile cut along K and every ragged last tile holds compared rows; both the
 intermediate h and y_perm, by relative L2 and element by element.  The combine is compared on a seeded
 sample of tokens."""

@@ -1,7 +1,7 @@
 """Layers of so many 256-row tiles that every workgroup of the persistent launch walks several: the operand stream that runs
-on from one output tile to the next, its stores that are still on their way, tiles of 0 to 4 row blocks per wavefront
+on from one output tile to the next, its stores that are still on their way, tiles of 0 to 8 row blocks per wavefront
 one after the other, and the tiles at the end that are cut along K; SwiGLU and ReLU, K with and without a tail, slots of one
-and of many tiles, and (k = 1) rows stored through the permutation.  Compared with the oracle on a row of every 32-row
+and of many tiles, and (k = 1) rows stored through the permutation.  Compared with the oracle on a row of every 16-row
 block of every slot, over all columns.  And layers of few such tiles, most of them cut along K."""
 import numpy as np
 import pytest
