@@ -7,6 +7,7 @@
             [--kernels substring,substring]
     rocprofv3 --kernel-trace --output-format csv -d <dir> -- python3 -m paper_2503_06823_amd.profile_tools run-layers
     python -m paper_2503_06823_amd.profile_tools layers <dir> --command "<cmd>" --out profiles/x.md
+    python -m paper_2503_06823_amd.profile_tools rates --out profiles/x.md      (on the GPU, no profiler)
 
 <dir> is what `rocprofv3 -d <dir>` wrote (searched recursively for *_kernel_stats.csv or
 *_counter_collection.csv).  `traffic` expects the profiled command to have run bench.py with
@@ -24,6 +25,7 @@ import json
 import os
 import re
 import sys
+import time
 
 csv.field_size_limit(1 << 30)
 CALIBRATION_BYTES = 1 << 30       # bench.py --copy-calibration copies 1 GiB device to device
@@ -212,7 +214,7 @@ def cmd_layers(a):
     if len(marks) != 2 * len(names):
         raise SystemExit(f"{len(marks)} marker kernels, expected {2 * len(names)}")
     with open(a.out, "w") as f:
-        f.write(f"# {a.title}\n\nCommand (run on the MI355X box from the repository root):\n\n```\n{a.command.strip()}\n```\n\n")
+        f.write(f"# {a.title or 'Kernel times of the layers of perf/cases.py (rocprofv3 --kernel-trace)'}\n\nCommand (run on the MI355X box from the repository root):\n\n```\n{a.command.strip()}\n```\n\n")
         f.write(f"Each layer {LAYER_PASSES} times, each time on another of several states (weights from HBM):\n\n")
         f.write("| layer | kernel | median us | min us |\n|---|---|---|---|\n")
         for n, name in enumerate(names):
@@ -223,6 +225,50 @@ def cmd_layers(a):
                 f.write(f"| {name if i == 0 else ''} | `{short_name(part[i]['Kernel_Name'])}` | {us[len(us) // 2]:.1f} | {us[0]:.1f} |\n")
         if a.note:
             f.write("\n" + a.note + "\n")
+    print(a.out)
+
+
+def cmd_rates(a):
+    """What this card reaches on a large copy, a large read, loops of matrix instructions and large matrix products of the library."""
+    import torch
+    from . import binding as B
+
+    def seconds(fn, n=20):
+        start = time.perf_counter()
+        while time.perf_counter() - start < 0.5:  # clocks under load, at the card's power
+            for _ in range(10):
+                fn()
+            torch.cuda.synchronize()
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(n + 1)]
+        ev[0].record()
+        for i in range(n):
+            fn()
+            ev[i + 1].record()
+        torch.cuda.synchronize()
+        return sorted(ev[i].elapsed_time(ev[i + 1]) for i in range(n))[n // 2] * 1e-3
+
+    def normal(*shape, dtype=torch.bfloat16):
+        return torch.empty(shape, dtype=dtype, device="cuda:0").normal_()
+
+    gib = 1 << 30
+    src, dst = (torch.empty(gib, dtype=torch.uint8, device="cuda:0").zero_() for _ in range(2))
+    sink, sink16 = (torch.empty(256 * 256, dtype=torch.float32, device="cuda:0"), torch.empty(4, dtype=torch.int32, device="cuda:0"))
+    rows = [("copy of 1 GiB, read + written", 2 * gib / seconds(lambda: dst.copy_(src)) / 1e12, "TB/s"),
+            ("`emoe_measure_read_stream`, 1 GiB", gib / seconds(lambda: B.emoe_measure_read_stream(src, gib, 8192, sink16)) / 1e12, "TB/s")]
+    x, w = normal(4096, 4096), normal(14336, 4096).mul_(1 / 64)
+    for lds in (False, True):
+        flop = B.emoe_measure_mfma_loop(x, w, lds, 256, 896, sink)
+        rows.append((f"`emoe_measure_mfma_loop`, {'fragments from LDS' if lds else 'registers only'}",
+                     flop / seconds(lambda: B.emoe_measure_mfma_loop(x, w, lds, 256, 896, sink)) / 1e15, "PFLOP/s"))
+    for dtype, name in ((torch.bfloat16, "bf16"), (torch.float32, "fp32")):
+        for M, N, K in ((8192, 28672, 4096), (8192, 4096, 14336), (8192, 8192, 8192)):
+            p, q = normal(M, K, dtype=dtype), normal(N, K, dtype=dtype).mul_(K ** -0.5)
+            rows.append((f"torch `x @ w.t()`, {name}, {M} x {N} x {K}", 2.0 * M * N * K / seconds(lambda: p @ q.t()) / 1e15, "PFLOP/s"))
+    with open(a.out, "w") as f:
+        f.write("# Rates that a card reaches\n\nCommand (run on the MI355X box from the repository root; medians of 20 after half a second of the same load, N(0,1) values, weights "
+                "scaled by 1/sqrt(K)):\n\n```\npython3 -m paper_2503_06823_amd.profile_tools rates --out <file>\n```\n\n| what | rate |\n|---|---|\n")
+        for what, rate, unit in rows:
+            f.write(f"| {what} | {rate:.3f} {unit} |\n")
     print(a.out)
 
 
@@ -245,6 +291,7 @@ def main(argv=None):
     p.set_defaults(fn=cmd_counters)
     p = sub.add_parser("run-layers"); p.set_defaults(fn=cmd_run_layers)
     p = sub.add_parser("layers"); p.add_argument("dir"); common(p); p.set_defaults(fn=cmd_layers)
+    p = sub.add_parser("rates"); p.add_argument("--out", required=True); p.set_defaults(fn=cmd_rates)
     a = ap.parse_args(argv)
     a.fn(a)
 
