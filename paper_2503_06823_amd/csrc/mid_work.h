@@ -84,8 +84,7 @@ constexpr Arrangement arrangement(bool swiglu, long long A, int S, int N, int K,
 }
 
 // The workgroups of a launch that is not a persistent one, for at most m_tiles m-tiles of n column tiles each.  The kernel, which knows how
-// many m-tiles there are, may cut the columns finer; not with a short K, where a tile's start weighs as much as its walk and finding
-// out costs more than it gives (12 K tiles: 19.0 -> 19.5 us).
+// many m-tiles there are, may cut the columns finer; not with a short K, where a tile's start weighs as much as its walk.
 constexpr bool may_narrow(int K) { return k_tiles_of(K) >= kNarrowFromK; }
 constexpr long long most_tiles(long long m_tiles, int n, int K, int cus) {
     const long long tiles = m_tiles * n;
@@ -109,8 +108,10 @@ struct Product {
 constexpr float down(float v) { return (float)(int)v; }
 constexpr float up(float v) { return down(v) + (down(v) < v ? 1.0f : 0.0f); }
 // Narrower column tiles than a tile can hold, where those leave CUs idle or a last round nearly empty.
-// Whether the fewest are kept without weighing up others: the rounds are full as it is (or there are no rows); of one round less
-// is expected, and a longer walk: a tile's start weighs as much as some ten K tiles.
+// Whether the fewest are kept without weighing up others: the rounds are full as it is (or there are no rows), of one round less is
+// expected; or K is short.  (12 K tiles: 19.0 -> 19.5 us.  The limits of 24 and 32 are older than the price of a tile's start in
+// weigh_columns() and no longer needed for its sake: without them products of 17 to 31 K tiles are 1.06 to 1.36 times as fast in the mean,
+// weights from HBM, and 0.97 to 1.12 from the Infinity Cache.)
 constexpr bool fewest_stay(const Product& p) {
     const float rounds = p.m_tiles * p.fewest.n * p.per_cus;
     if (rounds * 16.0f >= up(rounds) * (rounds <= 1.0f ? 14.0f : 15.0f)) return true;
